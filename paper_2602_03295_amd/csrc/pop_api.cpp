@@ -186,15 +186,10 @@ namespace {
 
 constexpr int kKvChunk = 8;  // pruned layers projected per batched GEMM
 
-// Parts into which the down projection (K = d_ffn) of T prompt rows splits its K range.  With 256 x 256 tiles
-// the projection has ceil(T / 256) * ceil(d / 256) tiles; when that is half the chip or less, and K is long, as
-// many work-groups again per part run the tiles' K ranges side by side (measured at 2048 rows of the Llama-3.1-8B
-// shape: 128 tiles, 2 parts).  The parts are added in index order by the kernel that normalises the result for the
-// next layer, or by the split's own second kernel.  1 = no split (few rows use the automatic rule of the GEMM).
+// Parts of the K range of the down projection (K = d_ffn) that the workspace of T > 512 prompt rows has room for:
+// as many as its 256 x 256 tiles leave work-groups idle.  How many are used is the GEMM's choice; they are added in
+// index order by the kernel that normalises the result for the next layer, or by the split's own second kernel.
 int down_split_parts(int T, int d, int f) {
-#ifdef POP_NO_DOWN_SPLIT      // (experiments only: a build without it, for A/B timing)
-  return 1;
-#endif
   if (T <= 512 || f < 8192) return 1;
   const long long tiles = (long long)((T + 255) / 256) * ((d + 255) / 256);
   int S = 1;
@@ -213,6 +208,9 @@ struct Workspace {
   size_t o_dcs_g, o_dcs_l;   // (cos, sin) of the decode-style rows' positions, [B][hd/2] per RoPE base
   size_t o_xb, o_ab, o_qkvb, o_qb, o_attnb, o_ub, o_part, o_splitk;
   size_t splitk_bytes;
+  // scratch for the K parts of a kept layer's projections: the split scratch, or the buffers of the K/V-only path
+  // (not in use while a kept layer runs) where they are larger
+  size_t o_kept_split, kept_split_bytes;
   size_t total;
   int Tp_max, nt64_max, nta_max, n_splits_max;
 };
@@ -289,6 +287,9 @@ Workspace carve(const pop_config& c, int T, int B, int maxp) {
   if (const int S = down_split_parts(T, (int)d, (int)f); S > 1)
     w.splitk_bytes = std::max(w.splitk_bytes, 4 * (size_t)S * (size_t)T * d);
   w.o_splitk = take(w.splitk_bytes);
+  const bool kv_larger = w.o_xb - w.o_a_multi > w.splitk_bytes;
+  w.o_kept_split = kv_larger ? w.o_a_multi : w.o_splitk;
+  w.kept_split_bytes = kv_larger ? w.o_xb - w.o_a_multi : w.splitk_bytes;
   w.total = o;
   return w;
 }
@@ -1255,7 +1256,6 @@ pop_status pop_prefill(pop_model* m, pop_cache* c, const pop_prefill_args* a, fl
   // abuf_gamma: the norm scale with which abuf already holds RMSNorm(h) (left there by the previous layer's down
   // projection when its K range was split: the kernel that adds the parts to h normalises the sum on the way).
   const float* abuf_gamma = nullptr;
-  const int down_parts = down_split_parts(T, d, f);
   auto kept_layer = [&](int l) -> pop_status {
     const pop_layer_weights& lw = m->layers[l - 1];
     const bool glob = layer_is_global(cfg, l);
@@ -1270,8 +1270,8 @@ pop_status pop_prefill(pop_model* m, pop_cache* c, const pop_prefill_args* a, fl
     // q, k, v leave the GEMM as fp16: they only feed the RoPE/append and attention kernels, and fp16
     // keeps three more mantissa bits than bf16 for the score contraction (the cache itself is bf16)
     g.M = T; g.N = Dqkv; g.K = d; g.epilogue = pop::EPI_STORE_F16;
-    g.splitk_ws = w.splitk_bytes ? at<float>(ws, w.o_splitk) : nullptr;
-    g.splitk_ws_bytes = w.splitk_bytes;
+    g.splitk_ws = w.kept_split_bytes ? at<float>(ws, w.o_kept_split) : nullptr;
+    g.splitk_ws_bytes = w.kept_split_bytes;
     {
       StepTimer tm(m, st, POP_STEP_QKV_GEMM);
       if (pop_status s = gemm_or_fail(g, st, "QKV")) return s;
@@ -1302,14 +1302,24 @@ pop_status pop_prefill(pop_model* m, pop_cache* c, const pop_prefill_args* a, fl
     g.A = attn; g.lda = Dq; g.W = (const bf16_t*)lw.wo; g.ldw = Dq; g.out = h; g.ldc = d;
     g.M = T; g.N = d; g.K = Dq; g.epilogue = pop::EPI_ADD_F32;
     g.scaled = a->gates != nullptr; g.scale = a->gates ? a->gates[l - 1] : 1.f;   // virtual gate of the layer
+    // If its K range is split, the kernel that adds the parts to h also writes the normalised input of the FFN block.
+    int o_parts = 1;
+    g.partials_only = d % 4 == 0;
+    g.split_used = &o_parts;
     {
       StepTimer tm(m, st, POP_STEP_O_GEMM);
       if (pop_status s = gemm_or_fail(g, st, "O")) return s;
     }
     {
       StepTimer tm(m, st, POP_STEP_NORM);
-      pop::launch_rmsnorm(h, nullptr, nullptr, (const float*)lw.norm_post, abuf, nullptr, T, d, cfg.rms_eps, st);
+      if (o_parts > 1)
+        pop::launch_add_parts_rmsnorm(h, g.splitk_ws, o_parts, (size_t)T * d, (const float*)lw.norm_post, abuf, T, d,
+                                      cfg.rms_eps, st, pop::residual_scale(g));
+      else
+        pop::launch_rmsnorm(h, nullptr, nullptr, (const float*)lw.norm_post, abuf, nullptr, T, d, cfg.rms_eps, st);
     }
+    g.partials_only = false;
+    g.split_used = nullptr;
     g.A = abuf; g.lda = d; g.W = (const bf16_t*)lw.w_gate_up; g.ldw = d; g.out = u; g.ldc = f;
     g.M = T; g.N = f; g.K = d; g.epilogue = pop::EPI_GLU_BF16; g.act = cfg.act;
     {
@@ -1323,8 +1333,7 @@ pop_status pop_prefill(pop_model* m, pop_cache* c, const pop_prefill_args* a, fl
     // writes that layer's normalised input (one pass over h instead of two).
     const float* next_gamma = l < cfg.n_layers && !plan.pruned[l + 1] ? (const float*)m->layers[l].norm_in : nullptr;
     int parts = 1;
-    g.force_split = down_parts;
-    g.partials_only = down_parts > 1 && next_gamma != nullptr && d % 4 == 0;
+    g.partials_only = next_gamma != nullptr && d % 4 == 0;
     g.split_used = &parts;
     {
       StepTimer tm(m, st, POP_STEP_DOWN_GEMM);
@@ -1370,6 +1379,12 @@ pop_status pop_prefill(pop_model* m, pop_cache* c, const pop_prefill_args* a, fl
       g.M = rows; g.N = 2 * Dkv; g.K = d; g.epilogue = pop::EPI_STORE_BF16;
       g.batch = n; g.strideA = (long long)rows * d; g.strideC = (long long)rows * 2 * Dkv;
       g.W_list = d_wlist + c0;
+      if (n == 1) {   // a single layer is a plain GEMM, whose K range may be split
+        g.W_list = nullptr;
+        g.W = (const bf16_t*)m->layers[layers[c0] - 1].wqkv + (size_t)Dq * d;
+        g.splitk_ws = w.splitk_bytes ? at<float>(ws, w.o_splitk) : nullptr;
+        g.splitk_ws_bytes = w.splitk_bytes;
+      }
       // Straight into the paged cache (RoPE and the page scatter in the GEMM's epilogue) when the layers of the
       // chunk have no per-head key norm (that needs a head's sum of squares first) and the 256 x 256 tiles of that
       // epilogue fill at least three quarters of the chip (one pruned layer of a 2048-token prompt is 64 tiles: the

@@ -25,13 +25,17 @@
 //   * The main loop is software pipelined by one 32-wide sub-step and rotated so that MFMAs with
 //     operands already in registers follow the barrier; when K is a multiple of 64 it contains no
 //     vector-ALU instruction besides the MFMAs (they share an issue port).
-//   * Tile shape is chosen per problem so that the number of tiles fills 256 CUs evenly; a partly
-//     filled last round of 256x256 tiles is computed by a second launch with 128x256 tiles.
+//   * Tile shape and the number of K parts are chosen per problem by a measured cost model, from sixteen
+//     shapes between 64x64 and 256x256, so that the work-groups fill 256 CUs evenly.
+//   * With few rows the column tiles start their K loops at different K offsets (`stagger`): the rows of W
+//     lie a power of two apart, and work-groups that read the same 128 bytes of thousands of such rows at
+//     the same time meet on a few memory channels.
 //   * The MFMA is issued with W as the first operand, so a lane ends up with 4 consecutive output
 //     columns of one row: epilogues use 8/16-byte accesses.
 //   * Work-group ids are remapped so that the 32 groups that run together on one XCD (ids equal mod
 //     8) work on 8 row tiles x 4 column tiles and share them through that XCD's L2.
 #include <algorithm>
+#include <cmath>
 #include <cstdlib>
 #include <type_traits>
 #include <utility>
@@ -54,7 +58,7 @@ struct GemmParams {
   int lda, ldw, ldc;     // elements
   int act;
   int tiles_m, tiles_n;  // per batch, of this launch
-  int n_tile0;           // first column tile of this launch (a GEMM may be split into two launches)
+  int stagger;           // 1: column tile tn starts its K loop at K-step tn * nk / tiles_n and wraps around
   long long strideA, strideC, strideW;
   const bf16_t* const* W_list;
   float scale;           // EPI_ADD_F32: out += scale * C
@@ -120,7 +124,7 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_kernel(GemmParams p) {
   }
   const int m0 = tm * BM;
   constexpr int BN_OUT = EPI == EPI_GLU_BF16 ? BN / 2 : BN;
-  const int n0 = (p.n_tile0 + tn) * BN_OUT;  // first output column of the tile
+  const int n0 = tn * BN_OUT;  // first output column of the tile
 
   const int z = blockIdx.z;
   const bf16_t* A = p.A + (long long)z * p.strideA;
@@ -176,11 +180,24 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_kernel(GemmParams p) {
   constexpr int LOADS = LA + LB;
   constexpr int LPS = (LOADS + STEPS - 1) / STEPS;  // loads per slice
   const int nk = (p.K + BK - 1) / BK;
-  // KFULL: a K-step beyond the last one re-stages the last one (into a stage nobody reads any more),
-  // which keeps the number of loads per iteration uniform without a per-lane mask.
+  // First K-step of this column tile (the sum over K wraps around), the same for all its row tiles, so that they
+  // still share W in L2.  gate|up at 8 / 64 / 256 rows, K = 4096 (rows 8 KB apart): 51.9 / 52.7 / 71.2 us without,
+  // 41.0 / 43.9 / 66.9 us with (3.3 to 4.5 -> 3.5 to 5.7 TB/s of weights); nothing with rows 7680 bytes apart.
+  // The larger tiles are not built with it: they serve problems that the matrix pipe bounds, where the scalar
+  // instructions of the wrap-around cost 0.6 % (gate|up at 32768 rows).
+  constexpr bool STAGGER = KFULL && BM * BN <= 32768;
+  const int k_start = STAGGER && p.stagger ? (int)((long long)tn * nk / p.tiles_n) : 0;
+  // K-step kt of the loop is K-step k_step(kt) of the operands.  KFULL: a K-step beyond the last one re-stages
+  // the last one (into a stage nobody reads any more), which keeps the number of loads per iteration uniform
+  // without a per-lane mask.
+  auto k_step = [&](int kt) {
+    if (!KFULL) return kt;
+    const int k = min(kt, nk - 1) + k_start;
+    return STAGGER && k >= nk ? k - nk : k;
+  };
   auto issue_one = [&](int q, int kt, unsigned char* stage_base, uint32_t tail_mask) {
     if (q >= LOADS) return;
-    const int k0 = (KFULL ? min(kt, nk - 1) : kt) * BK;
+    const int k0 = k_step(kt) * BK;
     unsigned char* sa = stage_base;
     unsigned char* sb = sa + A_BYTES;
     if (q < LA)
@@ -232,7 +249,7 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_kernel(GemmParams p) {
   }
   auto prefetch = [&](int kt) {   // one DMA load per wave; lanes beyond K or beyond the tile are masked
     const uint32_t off = KFULL ? pf_off : ((kt * BK < p.K) ? pf_off : kOOB);
-    const int kk = KFULL ? min(kt, nk - 1) : kt;
+    const int kk = k_step(kt);
     if (wave == 0) __builtin_amdgcn_raw_ptr_buffer_load_lds(rW, (lds_ptr_t)pf_scratch, 4, off, kk * BK * 2, 0, 0);
     else __builtin_amdgcn_raw_ptr_buffer_load_lds(rA, (lds_ptr_t)(pf_scratch + 256), 4, off, kk * BK * 2, 0, 0);
   };
@@ -567,8 +584,17 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_kernel(GemmParams p) {
 #endif
 }
 
-template <int BM, int BN, int WGM, int WGN, int STAGES, int EPI>
-hipError_t launch_cfg(const GemmArgs& g, hipStream_t st, int n_tile0 = 0, int n_tiles = -1) {
+// Whether the column tiles start at different K offsets: the rows of W lie a multiple of 4 KB apart, and the
+// activations fit the 4 MB L2 of an XCD (its tiles no longer walk the same K window of them together; with more
+// rows they would come from further away: the down projection of 2048 rows took 269 instead of 190 us).  The parts
+// of a split K already start at different offsets (staggered as well, the O projection lost 3 %).
+inline bool stagger_k(const GemmArgs& g) {
+  return g.batch <= 1 && (g.ldw * 2) % 4096 == 0 && (long long)g.M * g.K * 2 <= (4LL << 20);
+}
+
+// MASKED: also built for K that is not a multiple of BK.
+template <int BM, int BN, int WGM, int WGN, int STAGES, int EPI, bool MASKED = false>
+hipError_t launch_cfg(const GemmArgs& g, hipStream_t st) {
   constexpr int BN_OUT = EPI == EPI_GLU_BF16 ? BN / 2 : BN;
   constexpr int smem = STAGES * (BM + BN) * BK * 2 + 1024;  // stages + prefetch scratch
   static_assert(smem <= 160 * 1024, "LDS budget of a gfx950 CU");
@@ -582,108 +608,122 @@ hipError_t launch_cfg(const GemmArgs& g, hipStream_t st, int n_tile0 = 0, int n_
   p.kv_pool_stride = g.kv_pool_stride;
   p.kvq = g.kvq;
   p.tiles_m = (g.M + BM - 1) / BM;
-  p.tiles_n = n_tiles >= 0 ? n_tiles : (g.N + BN_OUT - 1) / BN_OUT;
-  p.n_tile0 = n_tile0;
-  if (p.tiles_n <= 0) return hipSuccess;
+  p.tiles_n = (g.N + BN_OUT - 1) / BN_OUT;
+  p.stagger = stagger_k(g) ? 1 : 0;
   p.strideA = g.strideA; p.strideC = g.strideC; p.strideW = g.W_list ? 0 : g.strideW;
   p.W_list = g.batch > 1 || g.W_list ? g.W_list : nullptr;
   // once per instantiation; the initialisation of a function-local static is thread-safe
   static const hipError_t attr_err = [] {
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_kernel<BM, BN, WGM, WGN, STAGES, EPI, true>),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, smem);
-    if (e != hipSuccess) return e;
-    return hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_kernel<BM, BN, WGM, WGN, STAGES, EPI, false>),
-                               hipFuncAttributeMaxDynamicSharedMemorySize, smem);
+    if constexpr (MASKED) {
+      if (e != hipSuccess) return e;
+      e = hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_kernel<BM, BN, WGM, WGN, STAGES, EPI, false>),
+                              hipFuncAttributeMaxDynamicSharedMemorySize, smem);
+    }
+    return e;
   }();
   if (attr_err != hipSuccess) return attr_err;
   const int total = p.tiles_m * p.tiles_n;
   const int grid = ((total + 7) / 8) * 8;
   const dim3 grid3(grid, 1, g.batch > 0 ? g.batch : 1), block3(64 * WGM * WGN);
-  if (g.K % BK == 0)
+  if (g.K % BK == 0) {
     hipLaunchKernelGGL((gemm_kernel<BM, BN, WGM, WGN, STAGES, EPI, true>), grid3, block3, smem, st, p);
-  else
-    hipLaunchKernelGGL((gemm_kernel<BM, BN, WGM, WGN, STAGES, EPI, false>), grid3, block3, smem, st, p);
+  } else {
+    if constexpr (MASKED)
+      hipLaunchKernelGGL((gemm_kernel<BM, BN, WGM, WGN, STAGES, EPI, false>), grid3, block3, smem, st, p);
+    else
+      return hipErrorInvalidValue;
+  }
   return hipGetLastError();
 }
 
-// Tile choice: minimise the estimated time on the critical path,
-//     rounds * K-steps * max(latency floor of a K-step, work-groups per CU * compute time of a K-step),
-//     rounds = ceil(tiles / (256 CUs * work-groups per CU)).
-// The compute time of a K-step is tile area * a relative cost per flop measured on MI355X at the
-// Llama-3.1-8B projection shapes (256x256 tiles move the fewest operand bytes per flop and are the
-// fastest per flop; smaller tiles only win when they fill the chip better).  The floor is what a
-// K-step takes when the work-group only waits for its loads (0.55 us with 2 stages, about half with
-// 3): with few rows (short prompts) a projection is weight streaming, every configuration runs at
-// its floor, and the small tiles win because more work-groups, several per CU, have loads in flight.
-struct TileCfg { int id, bm, bn; double rel; int occ; double floor_us; };
+// Tile shape and K parts: the pair with the least estimated time
+//     launch + (rounds of work-groups and weight bytes / HBM rate, 4-norm) + cost of adding the parts,
+//     a round = K-steps * max(latency of a K-step, work-groups per CU * compute time of a K-step)
+//               + work-groups per CU * prologue and epilogue,     256 CUs * work-groups per CU in a round.
+// The three numbers of a shape and the four common ones are a least-squares fit to 19000 timings (MI355X; 10
+// projection shapes of K 3840 to 15360, 8 to 4096 rows, 1 to 8 K parts, weights from HBM): 4 % rms; over those
+// problems the choice is on average 1.6 % slower than the best measured pair.  What the shapes between the powers
+// of two are for is the rows in between: 528 rows are 3 tiles of 256 (69 % of their work useful) or of 192 (92 %).
+struct TileCfg { int id, bm, bn, occ; double floor_us, step_us, end_us; };
 constexpr TileCfg kTileCfgs[] = {
-    {1, 256, 256, 1.00, 1, 0.55}, {5, 256, 192, 1.08, 1, 0.55}, {3, 256, 128, 1.25, 1, 0.30},
-    {4, 128, 128, 1.40, 2, 0.55}, {7, 128, 64, 1.75, 2, 0.30},  {8, 64, 128, 1.67, 2, 0.30},
-    {6, 64, 64, 2.09, 3, 0.27},   {9, 64, 64, 2.09, 1, 0.22},   // 9: six stages, one work-group per CU
+    // id, rows, columns, work-groups per CU, latency of a K-step, its compute time, prologue + epilogue (us)
+    {1, 256, 256, 1, 0.310, 1.432, 5.35}, {2, 256, 192, 1, 0.245, 1.188, 5.86}, {3, 192, 256, 1, 0.392, 1.162, 5.58},
+    {4, 160, 256, 1, 0.028, 1.059, 5.25}, {5, 192, 192, 1, 0.338, 0.831, 4.31}, {6, 256, 128, 1, 0.362, 0.812, 3.33},
+    {7, 128, 256, 1, 0.190, 0.817, 4.24}, {8, 192, 128, 1, 0.475, 0.662, 3.18}, {9, 128, 192, 1, 0.336, 0.655, 4.18},
+    {10, 96, 256, 1, 0.156, 0.692, 4.38}, {11, 160, 128, 1, 0.111, 0.607, 2.96}, {12, 128, 128, 1, 0.075, 0.514, 3.35},
+    {13, 96, 128, 1, 0.120, 0.464, 2.58}, {14, 64, 128, 2, 0.425, 0.383, 1.69}, {15, 96, 64, 1, 0.291, 0.186, 2.22},
+    {16, 64, 64, 1, 0.246, 0.158, 2.12},
 };
+constexpr bool masked_cfg(int id) { return id == 1 || id == 6 || id == 12 || id == 14 || id == 16; }
+constexpr double kLaunchUs = 2.49, kUsPerWeightMB = 0.187, kReduceUs = 2.37, kReduceUsPerMB = 0.30, kContention = 0.10;
 
-// Estimated time (us) of configuration c for M rows, `cols` W rows, K, `batch` problems.
+// Rounds of `tiles` work-groups of nk K-steps each.  In the last round, work-groups that leave CUs idle compute up
+// to kContention faster (bandwidth and power are shared by fewer).
+inline double rounds_us(const TileCfg& c, long long tiles, double nk) {
+  const long long slots = 256LL * c.occ, full = (tiles - 1) / slots, last = tiles - full * slots;
+  const long long share = std::min<long long>(c.occ, (last + 255) / 256);
+  auto round = [&](long long n, double fill) {
+    return nk * std::max(c.floor_us, n * c.step_us * (1 - kContention * (1 - fill))) + n * c.end_us;
+  };
+  return full * round(c.occ, 1.0) + round(share, last / (256.0 * share));
+}
+inline long long tiles_of(const TileCfg& c, long long M, long long cols) {
+  return ((M + c.bm - 1) / c.bm) * ((cols + c.bn - 1) / c.bn);
+}
+// Estimated time (us) of the GEMM launch alone: `batch` problems of M rows, `cols` W rows, K.
 inline double tile_cost_us(const TileCfg& c, long long M, long long cols, long long K, long long batch) {
-  const long long tiles = ((M + c.bm - 1) / c.bm) * ((cols + c.bn - 1) / c.bn) * batch;
-  const double kstep_us = (double)c.bm * c.bn * c.rel * (1.54 / 65536.0);   // 256x256: 1.54 us
-  const long long rounds = (tiles + 256LL * c.occ - 1) / (256LL * c.occ);
-  const long long share = std::min<long long>(c.occ, (tiles + 255) / 256);
-  return (double)rounds * (double)((K + BK - 1) / BK) * std::max(c.floor_us, (double)share * kstep_us);
+  const double weights = (double)cols * K * 2 * batch / 1e6 * kUsPerWeightMB;
+  const long long tiles = tiles_of(c, M, cols) * batch;
+  double work = rounds_us(c, tiles, (double)((K + BK - 1) / BK));
+  // (over several rounds the smaller tiles lose a little more than the fit says)
+  if (c.id != 1 && tiles > 512LL * c.occ) work *= 1.02;
+  auto sq = [](double v) { return v * v; };
+  return kLaunchUs + std::sqrt(std::sqrt(sq(sq(work)) + sq(sq(weights))));
+}
+
+struct TileChoice { int id; double us; };
+// The fastest shape for `batch` problems of M rows, `cols` W rows, K.
+inline TileChoice choose_tile(long long M, long long cols, long long K, long long batch) {
+  TileChoice best{1, 1e300};
+  for (const TileCfg& c : kTileCfgs) {      // ordered by area: ties go to the larger tile
+    if (K % BK && !masked_cfg(c.id)) continue;
+    const double t = tile_cost_us(c, M, cols, K, batch);
+    if (t < best.us) best = {c.id, t};
+  }
+  return best;
 }
 
 template <int EPI>
 hipError_t launch_epi(const GemmArgs& g, hipStream_t st) {
   const long long batch = g.batch > 0 ? g.batch : 1;
   const long long cols = EPI == EPI_GLU_BF16 ? 2LL * g.N : g.N;  // W rows consumed
-  auto cost = [&](const TileCfg& c) { return tile_cost_us(c, g.M, cols, g.K, batch); };
-  // Building with -DPOP_FORCE_GEMM_TILE=1..9 forces one configuration (tile-shape experiments, never the
-  // product build): the choice is a compile-time constant and nothing in the environment can change it.
+  // Building with -DPOP_FORCE_GEMM_TILE=1..16 forces one shape (tile-shape experiments, never the product
+  // build): the choice is a compile-time constant and nothing in the environment can change it.
 #ifdef POP_FORCE_GEMM_TILE
-  constexpr int forced = POP_FORCE_GEMM_TILE;
+  const int pick = g.K % BK && !masked_cfg(POP_FORCE_GEMM_TILE) ? 16 : POP_FORCE_GEMM_TILE;
 #else
-  constexpr int forced = 0;
+  const int pick = choose_tile(g.M, cols, g.K, batch).id;
 #endif
-  int pick = forced;
-  if (pick < 1 || pick > 9 || (pick == 5 && EPI == EPI_GLU_BF16)) {
-    double best = 1e300;
-    for (const TileCfg& c : kTileCfgs) {      // ordered by area: ties go to the larger tile
-      if (c.id == 5 && EPI == EPI_GLU_BF16) continue;
-      const double t = cost(c);
-      if (t < best) { best = t; pick = c.id; }
-    }
-  }
   switch (pick) {
-    case 2: return launch_cfg<256, 256, 2, 4, 2, EPI>(g, st);
-    case 3: return launch_cfg<256, 128, 2, 2, 3, EPI>(g, st);
-    case 4: return launch_cfg<128, 128, 2, 2, 2, EPI>(g, st);
-    case 6: return launch_cfg<64, 64, 2, 2, 3, EPI>(g, st);
-    case 7: return launch_cfg<128, 64, 2, 2, 3, EPI>(g, st);
-    case 8: return launch_cfg<64, 128, 2, 2, 3, EPI>(g, st);
-    case 9: return launch_cfg<64, 64, 2, 2, 6, EPI>(g, st);
-    case 5:
-      if constexpr (EPI != EPI_GLU_BF16) return launch_cfg<256, 192, 2, 2, 2, EPI>(g, st);
-      [[fallthrough]];
-    default: break;
+    case 2: return launch_cfg<256, 192, 2, 2, 2, EPI>(g, st);
+    case 3: return launch_cfg<192, 256, 2, 2, 2, EPI>(g, st);
+    case 4: return launch_cfg<160, 256, 2, 2, 2, EPI>(g, st);
+    case 5: return launch_cfg<192, 192, 2, 2, 3, EPI>(g, st);
+    case 6: return launch_cfg<256, 128, 2, 2, 3, EPI, true>(g, st);
+    case 7: return launch_cfg<128, 256, 2, 2, 3, EPI>(g, st);
+    case 8: return launch_cfg<192, 128, 2, 2, 3, EPI>(g, st);
+    case 9: return launch_cfg<128, 192, 2, 2, 3, EPI>(g, st);
+    case 10: return launch_cfg<96, 256, 2, 2, 3, EPI>(g, st);
+    case 11: return launch_cfg<160, 128, 2, 2, 3, EPI>(g, st);
+    case 12: return launch_cfg<128, 128, 2, 2, 4, EPI, true>(g, st);
+    case 13: return launch_cfg<96, 128, 2, 2, 4, EPI>(g, st);
+    case 14: return launch_cfg<64, 128, 2, 2, 3, EPI, true>(g, st);
+    case 15: return launch_cfg<96, 64, 2, 2, 4, EPI>(g, st);
+    case 16: return launch_cfg<64, 64, 2, 2, 6, EPI, true>(g, st);
+    default: return launch_cfg<256, 256, 2, 2, 2, EPI, true>(g, st);
   }
-  // 256x256 tiles.  If they leave the last round of 256 work-groups partly empty, the column tiles
-  // of that last round are computed by a second launch with 128x256 tiles (twice as many, half as
-  // long): at M = 2048 the gate|up projection has 896 tiles = 3.5 rounds, i.e. 3 rounds of 256x256
-  // plus one round of 128x256 instead of four rounds.
-  const int tiles_m = (g.M + 255) / 256;
-  const int tiles_n = (int)((cols + 255) / 256);
-  const long long total = (long long)tiles_m * tiles_n * batch;
-  const long long rem = total % 256;
-  if (forced == 0 && batch == 1 && total > 256 && rem > 0 && rem <= 128 && g.M > 128) {
-    const int tail_cols = (int)((rem + tiles_m - 1) / tiles_m);   // column tiles moved to the second launch
-    const int head_cols = tiles_n - tail_cols;
-    // only worth it when the second launch fills the chip better than the partial round did
-    if (head_cols > 0 && (long long)tail_cols * ((g.M + 127) / 128) <= 256) {
-      hipError_t e = launch_cfg<256, 256, 2, 2, 2, EPI>(g, st, 0, head_cols);
-      if (e != hipSuccess) return e;
-      return launch_cfg<128, 256, 2, 2, 2, EPI>(g, st, head_cols, tail_cols);
-    }
-  }
-  return launch_cfg<256, 256, 2, 2, 2, EPI>(g, st);
 }
 
 }  // namespace gemm_impl
@@ -723,43 +763,29 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(const float* __restr
   }
 }
 
-// Number of K parts for this problem (1 = do not split).  Measured inside the model, where every layer's
-// weights come from HBM for the first time: with 256 rows the down projection (K = 14336, 256 work-groups
-// of 224 K-steps each) takes 75 us unsplit and 51 us in 8 parts; at K = 4096 (QKV, O) a split gains
-// nothing (the second kernel costs what the shorter loop saves), and from 1024 rows on the projections
-// are compute bound.  Hence: split only long K with few rows, as far as the scratch allows, and any K when
-// the rows fit one 64-row tile and the launch would leave CUs idle.
+// Number of K parts for this problem (1 = do not split): the cost model's best over 1, 2, 4 and 8 parts, as far as
+// the scratch allows.  Parts of at least 8 K-steps.  A caller that adds the parts itself (partials_only) does so in
+// the kernel that normalises the result, which it launches in any case and which reads the rows once.
 inline int choose_split(const GemmArgs& g) {
   if (!g.splitk_ws || g.batch > 1 || g.W_list || g.epilogue == EPI_GLU_BF16 || g.epilogue == EPI_KV_CACHE) return 1;
   if (g.N % 4 || g.K % BK || (reinterpret_cast<uintptr_t>(g.splitk_ws) & 15)) return 1;
-  if (g.M > 512 && g.force_split <= 1) return 1;
-  // Building with -DPOP_FORCE_SPLITK=S forces S parts where the problem allows it (experiments only).
-#ifdef POP_FORCE_SPLITK
-  constexpr int forced = POP_FORCE_SPLITK;
-#else
-  constexpr int forced = 0;
-#endif
   auto fits = [&](int S) {
     return g.K % (S * BK) == 0 && g.K / (S * BK) >= 8 && (size_t)S * g.M * g.N * 4 <= g.splitk_ws_bytes;
   };
-  if (forced == 1) return 1;
-  if (forced > 1) return fits(forced) ? forced : 1;
-  if (g.force_split > 1 && g.force_split <= 8 && fits(g.force_split)) return g.force_split;
-  if (g.M > 256) return 1;
-  if (g.K >= 8192) {
-    for (int S = 8; S >= 2; S /= 2)
-      if (fits(S)) return S;
-    return 1;
+  // Building with -DPOP_FORCE_SPLITK=S forces S parts where the problem allows it (experiments only).
+#ifdef POP_FORCE_SPLITK
+  return POP_FORCE_SPLITK > 1 && fits(POP_FORCE_SPLITK) ? POP_FORCE_SPLITK : 1;
+#endif
+  const double mb = (double)g.M * g.N / 1e6;
+  int best = 1;
+  // unsplit, a caller that would have merged the two launches the norm kernel by itself (6 bytes an element)
+  double best_us = choose_tile(g.M, g.N, g.K, 1).us + (g.partials_only ? kReduceUs + 6 * mb / 4.0 : 0.0);
+  for (int S = 2; S <= 8; S *= 2) {
+    if (!fits(S)) continue;
+    const double us = choose_tile(g.M, g.N, g.K / S, S).us + kReduceUs + 4 * mb * S * kReduceUsPerMB;
+    if (us < best_us) { best_us = us; best = S; }
   }
-  // A handful of rows (decode steps, boundary rows) and a short K: the unsplit launch has one row of 64-wide
-  // tiles, fewer work-groups than CUs (96 for the Llama QKV projection); split until there are about 256.
-  // Measured on batch-8 decode steps at the Llama-3.1-8B shape: 5.29 -> 4.93 ms per step.
-  if (g.M > 64) return 1;
-  const long long tiles = (g.N + 63) / 64;
-  if (tiles >= 256) return 1;
-  for (int S = 2; S <= 8; S *= 2)
-    if (tiles * S >= 256 || S == 8) return fits(S) ? S : (S > 2 && fits(S / 2) ? S / 2 : 1);
-  return 1;
+  return best;
 }
 }  // namespace gemm_impl
 
@@ -819,9 +845,9 @@ hipError_t launch_gemm(const GemmArgs& g, hipStream_t st) {
       if (!gemm_kv_cache_supported(g.kv_heads, g.kv_hd) || g.N != 2 * g.kv_heads * g.kv_hd || !g.kv_dest ||
           !g.kv_slot || g.kv_page_size < 1)
         return hipErrorInvalidValue;
-      if (g.kv_hd == 64) return launch_cfg<256, 256, 2, 2, 2, EPI_KV64>(g, st);
-      if (g.kv_hd == 128) return launch_cfg<256, 256, 2, 2, 2, EPI_KV128>(g, st);
-      return launch_cfg<256, 256, 4, 1, 2, EPI_KV256>(g, st);
+      if (g.kv_hd == 64) return launch_cfg<256, 256, 2, 2, 2, EPI_KV64, true>(g, st);
+      if (g.kv_hd == 128) return launch_cfg<256, 256, 2, 2, 2, EPI_KV128, true>(g, st);
+      return launch_cfg<256, 256, 4, 1, 2, EPI_KV256, true>(g, st);
   }
   return hipErrorInvalidValue;
 }
