@@ -669,7 +669,7 @@ struct WorkspaceF32 {
   size_t meta_bytes;
   size_t o_tokens, o_row_src, o_pos, o_slot, o_row_seq, o_bnd_row, o_bnd_pos, o_bnd_slot, o_bnd_seq, o_bt, o_kv_first, o_tr_row, o_tr_pos,
       o_tr_slot;
-  size_t o_h, o_a, o_qkv, o_attn, o_u, o_xb, o_ab, o_qkvb, o_attnb, o_ub;
+  size_t o_h, o_qkv, o_attn, o_u, o_xb, o_qkvb, o_attnb, o_ub;
   size_t total;
 };
 
@@ -699,12 +699,10 @@ WorkspaceF32 carve_f32(const pop_config& c, int T, int B, int maxp) {
   w.o_tr_slot = take(4 * (size_t)T);
   w.meta_bytes = o;
   w.o_h = take(4 * (size_t)T * d);
-  w.o_a = take(4 * (size_t)T * d);
   w.o_qkv = take(4 * (size_t)T * Dqkv);
   w.o_attn = take(4 * (size_t)T * Dq);
   w.o_u = take(4 * (size_t)T * f);
   w.o_xb = take(4 * (size_t)B * d);
-  w.o_ab = take(4 * (size_t)B * d);
   w.o_qkvb = take(4 * (size_t)B * Dqkv);
   w.o_attnb = take(4 * (size_t)B * Dq);
   w.o_ub = take(4 * (size_t)B * f);
@@ -724,17 +722,18 @@ struct CtxF32 {
   float gate(int l /*1-based*/) const { return gates ? gates[l - 1] : 1.f; }
 };
 
-// One layer of Sec. 2.1 for `rows` rows of x (fp32 [rows, d], updated in place); a / qkv / attn / u are
-// scratch of matching height.  row_seq / pos / slot are device arrays [rows].
-pop_status layer_f32(const CtxF32& x, int l /*1-based*/, int rows, float* xh, float* a, float* qkv, float* attn, float* u,
-                     const int32_t* row_seq, const int32_t* pos, const int32_t* slot, int max_len) {
+// One layer of Sec. 2.1 for `rows` rows of x (fp32 [rows, d], updated in place); qkv / attn / u are
+// scratch of matching height.  row_seq / pos / slot are device arrays [rows].  packed: prompt rows, sequence by
+// sequence (otherwise one row per sequence).
+pop_status layer_f32(const CtxF32& x, int l /*1-based*/, int rows, float* xh, float* qkv, float* attn, float* u,
+                     const int32_t* row_seq, const int32_t* pos, const int32_t* slot, int max_len, bool packed) {
   const pop_config& c = x.m->cfg;
   const pop_layer_weights& lw = x.m->layers[l - 1];
   const int d = c.d_model, f = c.d_ffn, hd = c.head_dim, Dq = x.m->Dq, Dkv = x.m->Dkv, Dqkv = x.m->Dqkv;
   const bool glob = layer_is_global(c, l);
   namespace F = pop::f32;
-  F::launch_rmsnorm(xh, (const float*)lw.norm_in, a, nullptr, rows, d, c.rms_eps, x.st);
-  F::launch_gemm(a, d, (const float*)lw.wqkv, d, qkv, Dqkv, rows, Dqkv, d, F::EPI_STORE, 0, x.st);
+  F::launch_norm_gemm(xh, nullptr, (const float*)lw.norm_in, c.rms_eps, (const float*)lw.wqkv, qkv, Dqkv, rows, Dqkv, d,
+                      F::EPI_STORE, 0, x.st);
   F::launch_rope_write(qkv, Dqkv, 0, Dq, Dq + Dkv, c.n_q_heads, c.n_kv_heads, hd, pos, slot,
                        glob ? (double)c.rope_theta : (double)c.rope_theta_local, x.c->k_pool_f32(l - 1),
                        x.c->v_pool_f32(l - 1), c.page_size, rows, x.st, (const float*)lw.q_norm, (const float*)lw.k_norm,
@@ -743,11 +742,11 @@ pop_status layer_f32(const CtxF32& x, int l /*1-based*/, int rows, float* xh, fl
                                      at<int32_t>(x.ws, x.w->o_bt), x.c->max_pages, c.page_size,
                                      glob ? 0 : c.sliding_window,
                                      x.kv_first ? x.kv_first + (size_t)(l - 1) * x.B : nullptr, rows, c.n_q_heads,
-                                     c.n_kv_heads, hd, max_len, x.st);
+                                     c.n_kv_heads, hd, max_len, packed, x.st);
   if (e != hipSuccess) return fail(POP_EHIP, "fp32 attention launch failed: %s", hipGetErrorString(e));
   F::launch_gemm(attn, Dq, (const float*)lw.wo, Dq, xh, d, rows, d, Dq, F::EPI_ADD, 0, x.st, x.gate(l));
-  F::launch_rmsnorm(xh, (const float*)lw.norm_post, a, nullptr, rows, d, c.rms_eps, x.st);
-  F::launch_gemm(a, d, (const float*)lw.w_gate_up, d, u, f, rows, f, d, F::EPI_GLU, c.act, x.st);
+  F::launch_norm_gemm(xh, nullptr, (const float*)lw.norm_post, c.rms_eps, (const float*)lw.w_gate_up, u, f, rows, f, d,
+                      F::EPI_GLU, c.act, x.st);
   F::launch_gemm(u, f, (const float*)lw.w_down, f, xh, d, rows, d, f, F::EPI_ADD, 0, x.st, x.gate(l));
   POP_HIP(hipGetLastError());
   return POP_OK;
@@ -756,11 +755,8 @@ pop_status layer_f32(const CtxF32& x, int l /*1-based*/, int rows, float* xh, fl
 pop_status lm_head_f32(const CtxF32& x, int B, float* dev_logits) {
   const pop_config& c = x.m->cfg;
   namespace F = pop::f32;
-  float* xb = at<float>(x.ws, x.w->o_xb);
-  float* ab = at<float>(x.ws, x.w->o_ab);
-  F::launch_rmsnorm(xb, (const float*)x.m->w.final_norm, ab, nullptr, B, c.d_model, c.rms_eps, x.st);
-  F::launch_gemm(ab, c.d_model, (const float*)x.m->w.lm_head, c.d_model, dev_logits, c.vocab, B, c.vocab, c.d_model,
-                 F::EPI_STORE, 0, x.st);
+  F::launch_norm_gemm(at<float>(x.ws, x.w->o_xb), nullptr, (const float*)x.m->w.final_norm, c.rms_eps,
+                      (const float*)x.m->w.lm_head, dev_logits, c.vocab, B, c.vocab, c.d_model, F::EPI_STORE, 0, x.st);
   POP_HIP(hipGetLastError());
   return POP_OK;
 }
@@ -817,7 +813,6 @@ pop_status prefill_f32(pop_model* m, pop_cache* c, const pop_prefill_args* a, co
   namespace F = pop::f32;
   const int d = cfg.d_model, hd = cfg.head_dim, Dq = m->Dq, Dkv = m->Dkv;
   float* h = at<float>(ws, w.o_h);
-  float* abuf = at<float>(ws, w.o_a);
   float* qkv = at<float>(ws, w.o_qkv);
   float* attn = at<float>(ws, w.o_attn);
   float* u = at<float>(ws, w.o_u);
@@ -838,7 +833,7 @@ pop_status prefill_f32(pop_model* m, pop_cache* c, const pop_prefill_args* a, co
   const bool boundary = a->mode == POP_MODE_POP;
   for (int l = 1; l <= cfg.n_layers;) {
     if (!plan.pruned[l]) {
-      if (pop_status s = layer_f32(x, l, T, h, abuf, qkv, attn, u, at<int32_t>(ws, w.o_row_seq), d_pos, d_slot, max_len))
+      if (pop_status s = layer_f32(x, l, T, h, qkv, attn, u, at<int32_t>(ws, w.o_row_seq), d_pos, d_slot, max_len, true))
         return s;
       ++l;
       continue;
@@ -851,10 +846,8 @@ pop_status prefill_f32(pop_model* m, pop_cache* c, const pop_prefill_args* a, co
         // a sliding-window layer may store only the tail rows a later token can see (window_kv_writes)
         const bool tail = plan.window_writes && !layer_is_global(cfg, j);
         const int rows = tail ? tr.n : T;
-        F::launch_rmsnorm(h, (const float*)lw.norm_in, abuf, tail ? at<int32_t>(ws, w.o_tr_row) : nullptr, rows, d,
-                          cfg.rms_eps, st);
-        F::launch_gemm(abuf, d, (const float*)lw.wqkv + (size_t)Dq * d, d, qkv, 2 * Dkv, rows, 2 * Dkv, d, F::EPI_STORE, 0,
-                       st);
+        F::launch_norm_gemm(h, tail ? at<int32_t>(ws, w.o_tr_row) : nullptr, (const float*)lw.norm_in, cfg.rms_eps,
+                            (const float*)lw.wqkv + (size_t)Dq * d, qkv, 2 * Dkv, rows, 2 * Dkv, d, F::EPI_STORE, 0, st);
         F::launch_rope_write(qkv, 2 * Dkv, -1, 0, Dkv, cfg.n_q_heads, cfg.n_kv_heads, hd,
                              tail ? at<int32_t>(ws, w.o_tr_pos) : d_pos, tail ? at<int32_t>(ws, w.o_tr_slot) : d_slot,
                              layer_is_global(cfg, j) ? (double)cfg.rope_theta : (double)cfg.rope_theta_local,
@@ -865,9 +858,9 @@ pop_status prefill_f32(pop_model* m, pop_cache* c, const pop_prefill_args* a, co
     if (boundary) {
       pop::launch_gather_rows(h, bnd_row, xb, B, d, st);
       for (int j = l; j <= r; ++j)
-        if (pop_status s = layer_f32(x, j, B, xb, at<float>(ws, w.o_ab), at<float>(ws, w.o_qkvb), at<float>(ws, w.o_attnb),
+        if (pop_status s = layer_f32(x, j, B, xb, at<float>(ws, w.o_qkvb), at<float>(ws, w.o_attnb),
                                      at<float>(ws, w.o_ub), at<int32_t>(ws, w.o_bnd_seq), at<int32_t>(ws, w.o_bnd_pos),
-                                     at<int32_t>(ws, w.o_bnd_slot), max_len))
+                                     at<int32_t>(ws, w.o_bnd_slot), max_len, false))
           return s;
       pop::launch_scatter_rows(xb, bnd_row, h, B, d, st);
     }
@@ -915,9 +908,9 @@ pop_status decode_step_f32(pop_model* m, pop_cache* c, const int32_t* host_token
   float* xb = at<float>(ws, w.o_xb);
   pop::f32::launch_embed((const float*)m->w.embed, at<int32_t>(ws, w.o_tokens), nullptr, nullptr, xb, B, cfg.d_model, st);
   for (int l = 1; l <= cfg.n_layers; ++l)
-    if (pop_status s = layer_f32(x, l, B, xb, at<float>(ws, w.o_ab), at<float>(ws, w.o_qkvb), at<float>(ws, w.o_attnb),
+    if (pop_status s = layer_f32(x, l, B, xb, at<float>(ws, w.o_qkvb), at<float>(ws, w.o_attnb),
                                  at<float>(ws, w.o_ub), at<int32_t>(ws, w.o_bnd_seq), at<int32_t>(ws, w.o_bnd_pos),
-                                 at<int32_t>(ws, w.o_bnd_slot), max_len))
+                                 at<int32_t>(ws, w.o_bnd_slot), max_len, false))
       return s;
   return lm_head_f32(x, B, dev_logits);
 }
@@ -1630,9 +1623,9 @@ pop_status pop_generate(pop_model* m, pop_cache* c, const pop_prefill_args* a, i
     for (int s = 1; s < n_new; ++s) {
       pop::f32::launch_embed((const float*)m->w.embed, d_tok, nullptr, nullptr, xb, B, cfg.d_model, st);
       for (int l = 1; l <= cfg.n_layers; ++l)
-        if (pop_status e = layer_f32(x, l, B, xb, at<float>(ws, w.o_ab), at<float>(ws, w.o_qkvb), at<float>(ws, w.o_attnb),
+        if (pop_status e = layer_f32(x, l, B, xb, at<float>(ws, w.o_qkvb), at<float>(ws, w.o_attnb),
                                      at<float>(ws, w.o_ub), at<int32_t>(ws, w.o_bnd_seq), d_gpos + (size_t)(s - 1) * B,
-                                     d_gslot + (size_t)(s - 1) * B, max_len + s))
+                                     d_gslot + (size_t)(s - 1) * B, max_len + s, false))
           return e;
       if (pop_status e = lm_head_f32(x, B, dev_logits)) return e;
       pop::launch_argmax(dev_logits, cfg.vocab, d_tok, dev_tokens_out, n_new, s, eos_token, B, st);

@@ -1,8 +1,12 @@
 // fp32 instantiation of the POP prefill path: every step of Sec. 2.1 / Sec. 3.3 with fp32 weights,
 // activations and cache entries and fp32 accumulation.  It exists for tight numerical checks on small
-// models (max relative error 1e-4 against an fp64 reference instead of the 2e-2 of the bf16 path):
-// plain, LDS-tiled FMA kernels, no MFMA, not tuned for speed.
+// models (max relative error 1e-4 against an fp64 reference instead of the 2e-2 of the bf16 path).  Such models are
+// small: a call is a chain of short launches whose latency counts, so the kernels cut every step into many waves and
+// keep the chain short (the norms run inside the projections that read them).  All products on the fp32 MFMA
+// (v_mfma_f32_16x16x4_f32, fp32 inputs and accumulation).
 #include <math.h>
+
+#include <algorithm>
 
 #include "pop_device.h"
 #include "pop_kernels.h"
@@ -22,86 +26,176 @@ __global__ void embed_kernel(const float* __restrict__ table, const int32_t* __r
   for (int i = threadIdx.x; i < d; i += blockDim.x) h[(size_t)t * d + i] = src[i];
 }
 
-// out[t,:] = x[r,:] * rsqrt(mean(x[r,:]^2) + eps) * gamma, r = row_idx ? row_idx[t] : t     (LN of Sec. 2.1)
-__global__ __launch_bounds__(256) void rmsnorm_kernel(const float* __restrict__ x, const float* __restrict__ gamma,
-                                                      float* __restrict__ out, const int32_t* __restrict__ row_idx,
-                                                      int d, float eps) {
-  __shared__ float red[4];
-  const int t = blockIdx.x;
-  const float* xr = x + (size_t)(row_idx ? row_idx[t] : t) * d;
-  float ss = 0.f;
-  for (int i = threadIdx.x; i < d; i += 256) ss += xr[i] * xr[i];
-  ss = wave_sum(ss);
-  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = ss;
-  __syncthreads();
-  const float tot = (red[0] + red[1]) + (red[2] + red[3]);
-  const float rstd = 1.0f / sqrtf(tot / (float)d + eps);
-  for (int i = threadIdx.x; i < d; i += 256) out[(size_t)t * d + i] = xr[i] * rstd * gamma[i];
-}
-
 __device__ __forceinline__ float glu_act(float g, int act) {
   if (act == 0) return g / (1.f + expf(-g));
   const float u = 0.7978845608028654f * (g + 0.044715f * g * g * g);
   return 0.5f * g * (1.f + tanhf(u));
 }
 
-// C = A[M,K] W[N,K]^T, 64x64 output tile per work-group, 16-wide K steps through LDS, 4x4 outputs per
-// thread.  EPI: 0 store, 1 out += C, 2 out = act(A Wg^T) * (A Wu^T) with Wg = W rows 0..N-1, Wu = rows N..2N-1.
-template <int EPI>
-__global__ __launch_bounds__(256) void gemm_kernel(const float* __restrict__ A, int lda, const float* __restrict__ W,
-                                                   int ldw, float* __restrict__ out, int ldc, int M, int N, int K,
-                                                   int act, float scale /* EPI 1: out += scale * C */) {
-  constexpr int BT = 64, BKK = 16;
-  __shared__ float sa[BKK][BT + 1], sw[BKK][BT + 1], su[EPI == 2 ? BKK : 1][BT + 1];
-  const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
-  const int m0 = blockIdx.y * BT, n0 = blockIdx.x * BT;
-  float acc[4][4], acu[4][4];
+// C = A[M,K] W[N,K]^T.  A wave computes TM x TN blocks of 16 x 16 (GLU: of the gate and of the up columns); the
+// work-group is KW waves that share a tile and split K between them (their sums meet in LDS, in wave order), or
+// KW = 1 and 2 x 2 waves with a tile each.  Operands come straight from global memory: lane l of a load holds 4
+// consecutive k of row l % 16, at 4 (l / 16) of a 16-wide k chunk, so one 16-byte load per operand block feeds four
+// MFMAs (MFMA j contracts k = 4 g + j of the chunk, g = 0..3, the same on both sides).
+// Bound by latency at the sizes this path is for, hence the split of K inside the work-group: 128 rows, N = 512,
+// K = 256: 256 work-groups of 8 waves with 2 chunks each (64 x 64 tiles with one wave's worth of parallelism per SIMD
+// took 47 us, this 5 us; N = 256, K = 688: 160 and 6 us).
+// NORM: the rows of A are RMS-normalised on the way (the LN of Sec. 2.1): C = rstd (A * gamma) W^T, with the sum of
+// squares taken from the same loads.  row_idx: row m of A is A[row_idx[m]].
+// EPI: 0 store, 1 out += scale C, 2 out = act(A Wg^T) * (A Wu^T) with Wg = W rows 0..N-1, Wu = rows N..2N-1.
+struct GemmF32 {
+  const float* A;
+  const float* W;
+  float* out;
+  const int32_t* row_idx;
+  const float* gamma;
+  int lda, ldw, ldc, M, N, K, act;
+  float eps, scale;
+};
+
+template <int TM, int TN, int KW, int EPI, bool NORM>
+__global__ __launch_bounds__(KW == 1 ? 256 : 64 * KW) void gemm_kernel(GemmF32 p) {
+  constexpr int NB = EPI == EPI_GLU ? 2 * TN : TN;     // W blocks of a wave
+  constexpr int U = TM * NB >= 8 ? 2 : 4;              // chunks of 16 k requested together
+  __shared__ float4 red[KW > 1 ? KW : 1][KW > 1 ? TM * NB : 1][64];
+  __shared__ float red_ss[KW][TM][16];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int r16 = lane & 15, g = lane >> 4;
+  const int kw = KW > 1 ? wave : 0;
+  const int m0 = (KW > 1 ? blockIdx.y : blockIdx.y * 2 + (wave >> 1)) * TM * 16;
+  const int n0 = (KW > 1 ? blockIdx.x : blockIdx.x * 2 + (wave & 1)) * TN * 16;
+  // rows and columns beyond the matrix repeat its last one (never stored)
+  const float* ar[TM];
+  const float* wr[NB];
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
-#pragma unroll
-    for (int j = 0; j < 4; ++j) acc[i][j] = acu[i][j] = 0.f;
-  for (int k0 = 0; k0 < K; k0 += BKK) {
-    // 64 rows x 16 k per tile = 1024 values, 4 per thread: thread -> (row = id / 4 + 0.., k = (id % 4) * 4 ..)
-    for (int e = threadIdx.x; e < BT * BKK; e += 256) {
-      const int r = e / BKK, kk = e % BKK;
-      const int k = k0 + kk;
-      sa[kk][r] = (m0 + r < M && k < K) ? A[(size_t)(m0 + r) * lda + k] : 0.f;
-      sw[kk][r] = (n0 + r < N && k < K) ? W[(size_t)(n0 + r) * ldw + k] : 0.f;
-      if (EPI == 2) su[kk][r] = (n0 + r < N && k < K) ? W[(size_t)(N + n0 + r) * ldw + k] : 0.f;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int kk = 0; kk < BKK; ++kk) {
-      float av[4], wv[4], uv[4];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) av[i] = sa[kk][ty * 4 + i];
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        wv[j] = sw[kk][tx * 4 + j];
-        uv[j] = EPI == 2 ? su[kk][tx * 4 + j] : 0.f;
-      }
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          acc[i][j] += av[i] * wv[j];
-          if (EPI == 2) acu[i][j] += av[i] * uv[j];
-        }
-    }
-    __syncthreads();
+  for (int i = 0; i < TM; ++i) {
+    const int m = min(m0 + i * 16 + r16, p.M - 1);
+    ar[i] = p.A + (size_t)(p.row_idx ? p.row_idx[m] : m) * p.lda + 4 * g;
   }
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int m = m0 + ty * 4 + i;
-    if (m >= M) continue;
+  for (int j = 0; j < NB; ++j) {
+    const int n = min(n0 + (j % TN) * 16 + r16, p.N - 1);
+    wr[j] = p.W + (size_t)(j < TN ? n : p.N + n) * p.ldw + 4 * g;
+  }
+  floatx4_t acc[TM][NB];
+  float ss[TM];
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int n = n0 + tx * 4 + j;
-      if (n >= N) continue;
-      float* o = out + (size_t)m * ldc + n;
-      if (EPI == 0) *o = acc[i][j];
-      else if (EPI == 1) *o += acc[i][j] * scale;
-      else *o = glu_act(acc[i][j], act) * acu[i][j];
+  for (int i = 0; i < TM; ++i) {
+    ss[i] = 0.f;
+#pragma unroll
+    for (int j = 0; j < NB; ++j) acc[i][j] = floatx4_t{0.f, 0.f, 0.f, 0.f};
+  }
+  const int chunks = (p.K + 15) >> 4, per = (chunks + KW - 1) / KW;
+  const int c_end = min(chunks, (kw + 1) * per);
+  for (int c0 = kw * per; c0 < c_end; c0 += U) {
+    // Loads without branches, so that all of a step are in flight together: a lane beyond K, or of a chunk beyond
+    // this wave's, reads the row's start and its activations are replaced by zeros.
+    float4 a[U][TM], w[U][NB], gm[U];
+    bool in[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      in[u] = c0 + u < c_end && (c0 + u) * 16 + 4 * g < p.K;      // (K is a multiple of 4)
+      const int k = in[u] ? (c0 + u) * 16 : -4 * g;
+#pragma unroll
+      for (int i = 0; i < TM; ++i) a[u][i] = *reinterpret_cast<const float4*>(ar[i] + k);
+#pragma unroll
+      for (int j = 0; j < NB; ++j) w[u][j] = *reinterpret_cast<const float4*>(wr[j] + k);
+      if (NORM) gm[u] = *reinterpret_cast<const float4*>(p.gamma + k + 4 * g);
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+#pragma unroll
+      for (int i = 0; i < TM; ++i) {
+        float4& v = a[u][i];
+        v.x = in[u] ? v.x : 0.f; v.y = in[u] ? v.y : 0.f; v.z = in[u] ? v.z : 0.f; v.w = in[u] ? v.w : 0.f;
+      }
+      if (NORM) {
+#pragma unroll
+        for (int i = 0; i < TM; ++i) {
+          float4& v = a[u][i];
+          ss[i] += v.x * v.x + v.y * v.y + v.z * v.z + v.w * v.w;
+          v.x *= gm[u].x; v.y *= gm[u].y; v.z *= gm[u].z; v.w *= gm[u].w;
+        }
+      }
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+#pragma unroll
+        for (int j = 0; j < NB; ++j)
+#pragma unroll
+          for (int i = 0; i < TM; ++i)
+            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32((&w[u][j].x)[e], (&a[u][i].x)[e], acc[i][j], 0, 0, 0);
+    }
+  }
+  // acc[i][j][v]: row m0 + 16 i + lane % 16, column n0 + 16 j + 4 (lane / 16) + v
+  if (NORM) {
+#pragma unroll
+    for (int i = 0; i < TM; ++i) {
+      ss[i] += __shfl_xor(ss[i], 16, 64);
+      ss[i] += __shfl_xor(ss[i], 32, 64);
+      if (KW > 1 && g == 0) red_ss[kw][i][r16] = ss[i];
+    }
+  }
+  if (KW > 1) {
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int j = 0; j < NB; ++j)
+        red[kw][i * NB + j][lane] = make_float4(acc[i][j][0], acc[i][j][1], acc[i][j][2], acc[i][j][3]);
+    __syncthreads();
+  }
+  // wave w of a split finishes blocks w, w + KW, ...; without a split every wave its own
+  for (int blk = KW > 1 ? wave : 0; blk < TM * TN; blk += KW) {
+    const int i = blk / TN, j = blk % TN;
+    float4 c, up;
+    float sq = 0.f;
+    if (KW > 1) {
+      c = red[0][i * NB + j][lane];
+      up = red[0][i * NB + (EPI == EPI_GLU ? TN + j : j)][lane];
+      if (NORM) sq = red_ss[0][i][r16];
+      for (int k = 1; k < KW; ++k) {
+        const float4 x = red[k][i * NB + j][lane];
+        c.x += x.x; c.y += x.y; c.z += x.z; c.w += x.w;
+        if (EPI == EPI_GLU) {
+          const float4 y = red[k][i * NB + TN + j][lane];
+          up.x += y.x; up.y += y.y; up.z += y.z; up.w += y.w;
+        }
+        if (NORM) sq += red_ss[k][i][r16];
+      }
+    } else {
+      // (constant indices: the loop is unrolled over the blocks)
+#pragma unroll
+      for (int q = 0; q < TM * TN; ++q)
+        if (q == blk) {
+          const floatx4_t x = acc[q / TN][q % TN], y = acc[q / TN][EPI == EPI_GLU ? TN + q % TN : q % TN];
+          c = make_float4(x[0], x[1], x[2], x[3]);
+          up = make_float4(y[0], y[1], y[2], y[3]);
+          sq = ss[q / TN];
+        }
+    }
+    const float rstd = NORM ? 1.0f / sqrtf(sq / (float)p.K + p.eps) : 1.f;
+    const int m = m0 + i * 16 + r16, n = n0 + j * 16 + 4 * g;
+    if (m >= p.M) continue;
+    float* o = p.out + (size_t)m * p.ldc + n;
+    if (n + 3 < p.N && (p.ldc & 3) == 0) {     // four columns at once
+      float4 r = make_float4(c.x * rstd, c.y * rstd, c.z * rstd, c.w * rstd);
+      if (EPI == EPI_ADD) {
+        const float4 old = *reinterpret_cast<const float4*>(o);
+        r = make_float4(old.x + r.x * p.scale, old.y + r.y * p.scale, old.z + r.z * p.scale, old.w + r.w * p.scale);
+      } else if (EPI == EPI_GLU) {
+        r = make_float4(glu_act(r.x, p.act) * (up.x * rstd), glu_act(r.y, p.act) * (up.y * rstd),
+                        glu_act(r.z, p.act) * (up.z * rstd), glu_act(r.w, p.act) * (up.w * rstd));
+      }
+      *reinterpret_cast<float4*>(o) = r;
+      continue;
+    }
+    const float cv[4] = {c.x, c.y, c.z, c.w}, uv[4] = {up.x, up.y, up.z, up.w};
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      if (n + v >= p.N) break;
+      const float x = cv[v] * rstd;
+      if (EPI == EPI_STORE) o[v] = x;
+      else if (EPI == EPI_ADD) o[v] += x * p.scale;
+      else o[v] = glu_act(x, p.act) * (uv[v] * rstd);
     }
   }
 }
@@ -163,39 +257,62 @@ __global__ void rope_write_kernel(float* __restrict__ qkv, int ld, int q_col, in
   }
 }
 
-// Attn of Sec. 2.1 for one (row, query head) per work-group against the paged cache of the row's
-// sequence: keys lo..pos with lo = max(0, pos - window + 1) (window > 0) or 0, and not below the
-// first position the layer holds an entry for (kv_first[sequence], if given).  Scores live in LDS.
-__global__ __launch_bounds__(256) void attention_kernel(const float* __restrict__ q, int ldq, int q_col,
-                                                        float* __restrict__ out, const int32_t* __restrict__ row_seq,
-                                                        const int32_t* __restrict__ row_pos,
-                                                        const float* __restrict__ k_pool,
-                                                        const float* __restrict__ v_pool,
-                                                        const int32_t* __restrict__ block_table, int max_pages, int P,
-                                                        int window, const int32_t* __restrict__ kv_first,
-                                                        int n_q_heads, int n_kv_heads, int hd, float scale) {
-  extern __shared__ float smem[];
+// First key a row at position pos of sequence b sees: max(0, pos - window + 1) (window > 0) or 0, and not below the
+// first position the layer holds an entry for (kv_first[b], if given; the row's own entry always exists).
+__device__ __forceinline__ int first_key(int pos, int b, int window, const int32_t* kv_first) {
+  const int lo = window > 0 ? max(0, pos - window + 1) : 0;
+  return kv_first ? max(lo, min(kv_first[b], pos)) : lo;
+}
+
+struct AttnF32 {
+  const float* q;
+  int ldq, q_col;
+  float* out;
+  const int32_t* row_seq;
+  const int32_t* row_pos;
+  const float* k_pool;
+  const float* v_pool;
+  const int32_t* block_table;
+  int max_pages, P, window;
+  const int32_t* kv_first;
+  int rows, n_q_heads, n_kv_heads;
+  float scale;
+};
+
+// Attn of Sec. 2.1 for one (row, query head) per work-group against the paged cache of the row's sequence (rows of
+// different sequences: decode steps, boundary rows).  HD/4 lanes share a key, 16 bytes each; scores live in LDS.
+template <int HD>
+__global__ __launch_bounds__(256) void attention_kernel(AttnF32 a) {
+  constexpr int LPK = HD / 4, KPI = 256 / LPK;     // lanes per key, keys per pass of the work-group
+  extern __shared__ float sc[];                    // [n keys]
   __shared__ float red[4];
-  float* qs = smem;        // [hd]
-  float* sc = smem + hd;   // [n keys]
+  __shared__ float4 red_o[KPI][LPK];
   const int r = blockIdx.x, head = blockIdx.y, tid = threadIdx.x;
-  const int b = row_seq[r], pos = row_pos[r];
-  int lo = window > 0 ? max(0, pos - window + 1) : 0;
-  if (kv_first) lo = max(lo, min(kv_first[b], pos));   // the row's own entry always exists
+  const int b = a.row_seq[r], pos = a.row_pos[r];
+  const int lo = first_key(pos, b, a.window, a.kv_first);
   const int n = pos - lo + 1;
-  const int kvh = head / (n_q_heads / n_kv_heads);
-  const int32_t* bt = block_table + (size_t)b * max_pages;
-  for (int i = tid; i < hd; i += 256) qs[i] = q[(size_t)r * ldq + q_col + head * hd + i];
-  __syncthreads();
+  const int kvh = head / (a.n_q_heads / a.n_kv_heads);
+  const int32_t* bt = a.block_table + (size_t)b * a.max_pages;
+  const int li = tid % LPK, ks = tid / LPK;
+  auto entry = [&](const float* pool, int key) {
+    return *reinterpret_cast<const float4*>(
+        pool + (((size_t)bt[key / a.P] * a.n_kv_heads + kvh) * a.P + (key % a.P)) * HD + li * 4);
+  };
+  const float4 qv = *reinterpret_cast<const float4*>(a.q + (size_t)r * a.ldq + a.q_col + head * HD + li * 4);
   float mx = -INFINITY;
-  for (int j = tid; j < n; j += 256) {
-    const int key = lo + j;
-    const float* kp = k_pool + (((size_t)bt[key / P] * n_kv_heads + kvh) * P + (key % P)) * hd;
-    float s = 0.f;
-    for (int i = 0; i < hd; ++i) s += qs[i] * kp[i];
-    s *= scale;
-    sc[j] = s;
-    mx = fmaxf(mx, s);
+#pragma unroll 4
+  for (int j0 = 0; j0 < n; j0 += KPI) {            // (uniform over the block: the sums below cross lanes)
+    const int j = j0 + ks;
+    const float4 kv = entry(a.k_pool, lo + min(j, n - 1));
+    float s = qv.x * kv.x + qv.y * kv.y + qv.z * kv.z + qv.w * kv.w;
+    s = group_sum<16>(s);
+    if (LPK > 16) s += __shfl_xor(s, 16, 64);
+    if (LPK > 32) s += __shfl_xor(s, 32, 64);
+    s *= a.scale;
+    if (j < n) {
+      if (li == 0) sc[j] = s;
+      mx = fmaxf(mx, s);
+    }
   }
   mx = wave_max(mx);
   if ((tid & 63) == 0) red[tid >> 6] = mx;
@@ -204,21 +321,150 @@ __global__ __launch_bounds__(256) void attention_kernel(const float* __restrict_
   __syncthreads();
   float sum = 0.f;
   for (int j = tid; j < n; j += 256) {
-    const float p = expf(sc[j] - mx);
-    sc[j] = p;
-    sum += p;
+    const float pv = expf(sc[j] - mx);
+    sc[j] = pv;
+    sum += pv;
   }
   sum = wave_sum(sum);
   if ((tid & 63) == 0) red[tid >> 6] = sum;
   __syncthreads();
   const float tot = (red[0] + red[1]) + (red[2] + red[3]);
-  for (int e = tid; e < hd; e += 256) {
-    float acc = 0.f;
-    for (int j = 0; j < n; ++j) {
-      const int key = lo + j;
-      acc += sc[j] * v_pool[(((size_t)bt[key / P] * n_kv_heads + kvh) * P + (key % P)) * hd + e];
+  float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll 4
+  for (int j = ks; j < n; j += KPI) {
+    const float4 v = entry(a.v_pool, lo + j);
+    const float pv = sc[j];
+    acc.x += pv * v.x; acc.y += pv * v.y; acc.z += pv * v.z; acc.w += pv * v.w;
+  }
+  red_o[ks][li] = acc;
+  __syncthreads();
+  if (tid < LPK) {
+    float4 o = red_o[0][tid];
+    for (int k = 1; k < KPI; ++k) {
+      const float4 x = red_o[k][tid];
+      o.x += x.x; o.y += x.y; o.z += x.z; o.w += x.w;
     }
-    out[(size_t)r * n_q_heads * hd + head * hd + e] = acc / tot;
+    *reinterpret_cast<float4*>(a.out + (size_t)r * a.n_q_heads * HD + head * HD + tid * 4) =
+        make_float4(o.x / tot, o.y / tot, o.z / tot, o.w / tot);
+  }
+}
+
+// The same for packed prompt rows: a work-group takes 16 consecutive rows of one query head, its four waves every
+// fourth block of 16 keys.  S^T = K Q^T and O^T += V^T P^T on the MFMA with a running maximum and sum per wave; a
+// lane then holds 4 keys of one row, which are the operand of the second product as they are (MFMA j takes key
+// 4 g + j from lane group g).  The waves' results meet in LDS.  Rows of different sequences in one tile are taken
+// sequence by sequence.  One work-group per row and head re-read every entry 16 times as often and waited for each
+// (30 us for 128 rows of 4 heads, 5 us now).
+template <int HD>
+__global__ __launch_bounds__(256) void attention_tile_kernel(AttnF32 a) {
+  constexpr int C = HD / 16;
+  extern __shared__ float smem[];                  // [4 waves][16 rows][HD + 4]
+  __shared__ float red_m[4][16], red_l[4][16];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int r16 = lane & 15, g = lane >> 4;
+  const int head = blockIdx.y, kvh = head / (a.n_q_heads / a.n_kv_heads);
+  const int t0 = blockIdx.x * 16, tile_end = min(t0 + 16, a.rows);
+  // lane i (and i + 16, ..) looks at row t0 + i; the rows of a sequence are found without further loads
+  const int seq_i = a.row_seq[min(t0 + r16, a.rows - 1)], pos_i = a.row_pos[min(t0 + r16, a.rows - 1)];
+  for (int r0 = t0; r0 < tile_end;) {
+    const int b = __builtin_amdgcn_readlane(seq_i, r0 - t0);
+    const uint32_t others = (uint32_t)__builtin_amdgcn_ballot_w64(seq_i != b) & 0xffffu & (0xffffffffu << (r0 - t0));
+    const int r1 = others ? min(t0 + __ffs(others) - 1, tile_end) : tile_end;   // rows r0 .. r1-1 of sequence b
+    const int row = min(r0 + r16, r1 - 1);
+    const int pos = __shfl(pos_i, row - t0, 64);                                // positions ascending
+    const int lo = first_key(pos, b, a.window, a.kv_first);
+    const int k_lo = __builtin_amdgcn_readfirstlane(lo);                        // lane 0 has row r0
+    const int k_hi = __builtin_amdgcn_readlane(pos_i, r1 - 1 - t0);
+    const int32_t* bt = a.block_table + (size_t)b * a.max_pages;
+    auto entry = [&](const float* pool, int key) {
+      return pool + (((size_t)bt[key / a.P] * a.n_kv_heads + kvh) * a.P + (key % a.P)) * HD;
+    };
+    float4 qf[C];
+#pragma unroll
+    for (int c = 0; c < C; ++c)
+      qf[c] = *reinterpret_cast<const float4*>(a.q + (size_t)row * a.ldq + a.q_col + head * HD + c * 16 + 4 * g);
+    floatx4_t o[C];
+#pragma unroll
+    for (int c = 0; c < C; ++c) o[c] = floatx4_t{0.f, 0.f, 0.f, 0.f};
+    float m_run = -INFINITY, l_run = 0.f;
+    for (int k0 = k_lo + wave * 16; k0 <= k_hi; k0 += 64) {
+      // keys beyond the last one repeat it (masked below)
+      const float* kp = entry(a.k_pool, min(k0 + r16, k_hi)) + 4 * g;
+      const float* vp[4];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) vp[j] = entry(a.v_pool, min(k0 + 4 * g + j, k_hi)) + r16;
+      float4 kf[C];
+      float vf[C][4];
+#pragma unroll
+      for (int c = 0; c < C; ++c) kf[c] = *reinterpret_cast<const float4*>(kp + c * 16);
+      if (HD <= 128) {
+#pragma unroll
+        for (int c = 0; c < C; ++c)
+#pragma unroll
+          for (int j = 0; j < 4; ++j) vf[c][j] = vp[j][c * 16];
+      }
+      floatx4_t s = floatx4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int c = 0; c < C; ++c)
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          s = __builtin_amdgcn_mfma_f32_16x16x4f32((&kf[c].x)[e], (&qf[c].x)[e], s, 0, 0, 0);
+      // s[v]: row r16, key k0 + 4 g + v
+      float mx = -INFINITY;
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const int key = k0 + 4 * g + v;
+        s[v] = key >= lo && key <= pos ? s[v] * a.scale : -INFINITY;
+        mx = fmaxf(mx, s[v]);
+      }
+      mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
+      mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+      const float m_new = fmaxf(m_run, mx);
+      const float m_use = m_new == -INFINITY ? 0.f : m_new;     // (no key of this row yet)
+      const float alpha = expf(m_run - m_use);
+      float p[4], sum = 0.f;
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        p[v] = expf(s[v] - m_use);
+        sum += p[v];
+      }
+      l_run = l_run * alpha + sum;       // this lane group's keys; the groups are added at the end
+      m_run = m_new;
+#pragma unroll
+      for (int c = 0; c < C; ++c) {
+#pragma unroll
+        for (int v = 0; v < 4; ++v) o[c][v] *= alpha;
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+          o[c] = __builtin_amdgcn_mfma_f32_16x16x4f32(HD <= 128 ? vf[c][j] : vp[j][c * 16], p[j], o[c], 0, 0, 0);
+      }
+    }
+    l_run += __shfl_xor(l_run, 16, 64);
+    l_run += __shfl_xor(l_run, 32, 64);
+    // o[c][v]: row r16, head-dim 16 c + 4 g + v
+    if (g == 0) { red_m[wave][r16] = m_run; red_l[wave][r16] = l_run; }
+#pragma unroll
+    for (int c = 0; c < C; ++c)
+      *reinterpret_cast<float4*>(smem + (wave * 16 + r16) * (HD + 4) + c * 16 + 4 * g) =
+          make_float4(o[c][0], o[c][1], o[c][2], o[c][3]);
+    __syncthreads();
+    for (int it = threadIdx.x; it < (r1 - r0) * (HD / 4); it += 256) {
+      const int r = it / (HD / 4), i = it % (HD / 4) * 4;
+      const float m = fmaxf(fmaxf(red_m[0][r], red_m[1][r]), fmaxf(red_m[2][r], red_m[3][r]));
+      float4 num = make_float4(0.f, 0.f, 0.f, 0.f);
+      float den = 0.f;
+#pragma unroll
+      for (int w = 0; w < 4; ++w) {
+        const float f = expf(red_m[w][r] - m);                  // (a wave without keys: exp(-inf) = 0)
+        const float4 x = *reinterpret_cast<const float4*>(smem + (w * 16 + r) * (HD + 4) + i);
+        num.x += f * x.x; num.y += f * x.y; num.z += f * x.z; num.w += f * x.w;
+        den += f * red_l[w][r];
+      }
+      *reinterpret_cast<float4*>(a.out + (size_t)(r0 + r) * a.n_q_heads * HD + head * HD + i) =
+          make_float4(num.x / den, num.y / den, num.z / den, num.w / den);
+    }
+    __syncthreads();                                             // before the next sequence reuses LDS
+    r0 = r1;
   }
 }
 
@@ -230,22 +476,38 @@ void launch_embed(const float* table, const int32_t* tokens, const int32_t* row_
   hipLaunchKernelGGL(impl::embed_kernel, dim3(T), dim3(256), 0, st, table, tokens, row_src, embeds, h, d);
 }
 
-void launch_rmsnorm(const float* x, const float* gamma, float* out, const int32_t* row_idx, int rows, int d, float eps,
-                    hipStream_t st) {
-  if (rows <= 0) return;
-  hipLaunchKernelGGL(impl::rmsnorm_kernel, dim3(rows), dim3(256), 0, st, x, gamma, out, row_idx, d, eps);
+namespace impl {
+template <int EPI, bool NORM>
+void launch_gemm_en(const GemmF32& p, hipStream_t st) {
+  auto up = [](int x, int t) { return (x + t - 1) / t; };
+  // The smallest tiles until every CU has two work-groups, then 32 x 32, from four rounds of those on 64 x 64 per
+  // wave (128 x 128 per work-group; GLU half as wide), which need a quarter of the loads per product.
+  if ((long long)up(p.M, 16) * up(p.N, 16) <= 512) {
+    hipLaunchKernelGGL((gemm_kernel<1, 1, 8, EPI, NORM>), dim3(up(p.N, 16), up(p.M, 16)), dim3(512), 0, st, p);
+  } else if ((long long)up(p.M, 32) * up(p.N, 32) <= 4096) {
+    hipLaunchKernelGGL((gemm_kernel<2, 2, 4, EPI, NORM>), dim3(up(p.N, 32), up(p.M, 32)), dim3(256), 0, st, p);
+  } else {
+    constexpr int TN = EPI == EPI_GLU ? 2 : 4;
+    hipLaunchKernelGGL((gemm_kernel<4, TN, 1, EPI, NORM>), dim3(up(p.N, 32 * TN), up(p.M, 128)), dim3(256), 0, st, p);
+  }
 }
+template <bool NORM>
+void launch_gemm_n(const GemmF32& p, int epi, hipStream_t st) {
+  if (p.M <= 0 || p.N <= 0) return;
+  if (epi == EPI_STORE) launch_gemm_en<EPI_STORE, NORM>(p, st);
+  else if (epi == EPI_ADD) launch_gemm_en<EPI_ADD, NORM>(p, st);
+  else launch_gemm_en<EPI_GLU, NORM>(p, st);
+}
+}  // namespace impl
 
 void launch_gemm(const float* A, int lda, const float* W, int ldw, float* out, int ldc, int M, int N, int K, int epi,
                  int act, hipStream_t st, float scale) {
-  if (M <= 0 || N <= 0) return;
-  const dim3 grid((N + 63) / 64, (M + 63) / 64);
-  if (epi == EPI_STORE)
-    hipLaunchKernelGGL((impl::gemm_kernel<0>), grid, dim3(256), 0, st, A, lda, W, ldw, out, ldc, M, N, K, act, scale);
-  else if (epi == EPI_ADD)
-    hipLaunchKernelGGL((impl::gemm_kernel<1>), grid, dim3(256), 0, st, A, lda, W, ldw, out, ldc, M, N, K, act, scale);
-  else
-    hipLaunchKernelGGL((impl::gemm_kernel<2>), grid, dim3(256), 0, st, A, lda, W, ldw, out, ldc, M, N, K, act, scale);
+  impl::launch_gemm_n<false>(impl::GemmF32{A, W, out, nullptr, nullptr, lda, ldw, ldc, M, N, K, act, 0.f, scale}, epi, st);
+}
+
+void launch_norm_gemm(const float* x, const int32_t* row_idx, const float* gamma, float eps, const float* W, float* out,
+                      int ldc, int M, int N, int K, int epi, int act, hipStream_t st) {
+  impl::launch_gemm_n<true>(impl::GemmF32{x, W, out, row_idx, gamma, K, K, ldc, M, N, K, act, eps, 1.f}, epi, st);
 }
 
 void launch_rope_write(float* qkv, int ld, int q_col, int k_col, int v_col, int n_q_heads, int n_kv_heads, int hd,
@@ -257,17 +519,37 @@ void launch_rope_write(float* qkv, int ld, int q_col, int k_col, int v_col, int 
                      v_pool, P, q_gamma, k_gamma, qk_eps, kvq);
 }
 
+namespace impl {
+template <int HD>
+hipError_t launch_attention_hd(const AttnF32& a, bool packed, int max_len, hipStream_t st) {
+  if (packed) {
+    constexpr size_t smem = (size_t)4 * 16 * (HD + 4) * sizeof(float);
+    // once per head size; the initialisation of a function-local static is thread-safe
+    static const hipError_t attr_err = hipFuncSetAttribute(reinterpret_cast<const void*>(&attention_tile_kernel<HD>),
+                                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
+    if (attr_err != hipSuccess) return attr_err;
+    hipLaunchKernelGGL(attention_tile_kernel<HD>, dim3((a.rows + 15) / 16, a.n_q_heads), dim3(256), smem, st, a);
+  } else {
+    hipLaunchKernelGGL(attention_kernel<HD>, dim3(a.rows, a.n_q_heads), dim3(256), (size_t)max_len * sizeof(float), st, a);
+  }
+  return hipGetLastError();
+}
+}  // namespace impl
+
 hipError_t launch_attention(const float* q, int ldq, int q_col, float* out, const int32_t* row_seq,
                             const int32_t* row_pos, const float* k_pool, const float* v_pool,
                             const int32_t* block_table, int max_pages, int P, int window, const int32_t* kv_first, int rows, int n_q_heads,
-                            int n_kv_heads, int hd, int max_len, hipStream_t st) {
+                            int n_kv_heads, int hd, int max_len, bool packed, hipStream_t st) {
   if (rows <= 0) return hipSuccess;
-  const size_t smem = ((size_t)hd + (size_t)max_len) * sizeof(float);
   if (max_len > kMaxContext) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(impl::attention_kernel, dim3(rows, n_q_heads), dim3(256), smem, st, q, ldq, q_col, out, row_seq,
-                     row_pos, k_pool, v_pool, block_table, max_pages, P, window, kv_first, n_q_heads, n_kv_heads, hd,
-                     1.f / sqrtf((float)hd));
-  return hipGetLastError();
+  const impl::AttnF32 a{q, ldq, q_col, out, row_seq, row_pos, k_pool, v_pool, block_table, max_pages, P, window, kv_first,
+                        rows, n_q_heads, n_kv_heads, 1.f / sqrtf((float)hd)};
+  switch (hd) {
+    case 64: return impl::launch_attention_hd<64>(a, packed, max_len, st);
+    case 128: return impl::launch_attention_hd<128>(a, packed, max_len, st);
+    case 256: return impl::launch_attention_hd<256>(a, packed, max_len, st);
+  }
+  return hipErrorInvalidValue;
 }
 
 }  // namespace f32

@@ -235,12 +235,12 @@ constexpr int kMaxContext = 15000;  // scores of one query row are held in LDS
 enum { EPI_STORE = 0, EPI_ADD = 1, EPI_GLU = 2 };
 void launch_embed(const float* table, const int32_t* tokens, const int32_t* row_src, const float* embeds, float* h,
                   int T, int d, hipStream_t st);
-// out[t,:] = LN(x[row_idx ? row_idx[t] : t, :])
-void launch_rmsnorm(const float* x, const float* gamma, float* out, const int32_t* row_idx, int rows, int d, float eps,
-                    hipStream_t st);
 // out (op)= A[M,K] W[N,K]^T ; EPI_GLU: W is [2N,K] (gate rows, then up rows)
 void launch_gemm(const float* A, int lda, const float* W, int ldw, float* out, int ldc, int M, int N, int K, int epi,
                  int act, hipStream_t st, float scale = 1.f);   // EPI_ADD: out += scale * C
+// The same with A = LN(x[row_idx ? row_idx[m] : m, :]) (rows of K values, scale gamma), normalised inside the kernel.
+void launch_norm_gemm(const float* x, const int32_t* row_idx, const float* gamma, float eps, const float* W, float* out,
+                      int ldc, int M, int N, int K, int epi, int act, hipStream_t st);
 // rotate q (unless q_col < 0) and k of `rows` rows in place, append k, v at slot[row]
 void launch_rope_write(float* qkv, int ld, int q_col, int k_col, int v_col, int n_q_heads, int n_kv_heads, int hd,
                        const int32_t* pos, const int32_t* slot, double theta, float* k_pool, float* v_pool, int P,
@@ -249,10 +249,11 @@ void launch_rope_write(float* qkv, int ld, int q_col, int k_col, int v_col, int 
 // (kvq.fp8: the fp32 entries stored are the values of the e4m3 codes, i.e. decode(encode(x * inv)) * scale)
 // out[r, :] = Attn of row r (sequence row_seq[r], position row_pos[r]) over its cache entries
 // kv_first: per sequence, first position that has a cache entry in this layer (nullptr = 0)
+// packed: the rows are prompt rows, sequence by sequence with ascending positions (otherwise any rows)
 hipError_t launch_attention(const float* q, int ldq, int q_col, float* out, const int32_t* row_seq,
                             const int32_t* row_pos, const float* k_pool, const float* v_pool,
                             const int32_t* block_table, int max_pages, int P, int window, const int32_t* kv_first,
-                            int rows, int n_q_heads, int n_kv_heads, int hd, int max_len, hipStream_t st);
+                            int rows, int n_q_heads, int n_kv_heads, int hd, int max_len, bool packed, hipStream_t st);
 }  // namespace f32
 
 // Greedy choice of the next token of every sequence from fp32 logits [B, vocab]: tok[b] (device, in/out)

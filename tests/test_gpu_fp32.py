@@ -97,3 +97,23 @@ def test_fp32_visual_rows_override(pop):
     logits = run.prefill(tokens, 2, embeds=emb.to(torch.float32).cuda(), embed_ranges=ranges)
     worst, _ = compare_with_oracle(run, W, tokens, 2, logits, embeds=emb.numpy(), embed_ranges=ranges, tol=TOL32)
     print("fp32 visual", worst)
+
+
+@pytest.mark.parametrize("hd,hq,hkv,window", [(64, 4, 2, 0), (128, 3, 1, 50), (256, 2, 2, 0)])
+@pytest.mark.parametrize("lens,d,f", [([1, 17, 300, 45, 16], 264, 1000), ([9], 72, 40), ([1030, 470], 264, 2824)])
+def test_fp32_kernel_shapes(pop, hd, hq, hkv, window, lens, d, f):
+    """Tiles of 16, 32 and 64 rows, K and N that are no multiples of them, several sequences in one query tile,
+    sliding windows, then a decode step: against the oracle at the bound of the tests above."""
+    cfg = synth.get_config("tiny", n_layers=3, d_model=d, n_q_heads=hq, n_kv_heads=hkv, head_dim=hd, d_ffn=f, vocab=523,
+                           sliding_window=window, global_every=2 if window else 0)
+    W = synth.make_weights(cfg, seed=5)
+    synth.randomize_norms(W, cfg)
+    tokens = synth.make_tokens(cfg["vocab"], sum(lens), seed=6)
+    run = DeviceRun(pop, cfg, W, lens, shuffle_seed=3)
+    logits = run.prefill(tokens, 2)
+    worst, outs = compare_with_oracle(run, W, tokens, 2, logits, tol=1e-5)
+    step = synth.make_tokens(cfg["vocab"], len(lens), seed=8)
+    got = run.decode(step)
+    for b, (Kc, Vc, _) in enumerate(outs):
+        ref, _, _ = O.decode_step(cfg, W, O.embed_rows(W, step[b:b + 1], np.float64)[0], Kc, Vc)
+        assert rel_err(got[b], ref) <= 1e-5
