@@ -502,12 +502,12 @@ void record_kv_first(pop_cache* c, const pop_prefill_args* a, const PrunePlan& p
     }
 }
 
-// Projection of the B rows of a decode-style layer.  The GEMV kernel streams every weight row once per row
-// group and is the fastest form for one or a few rows; from kRowsForGemm rows on the tiled MFMA GEMM with
-// its small tiles (and the split of a long K) reads the weights faster than the GEMV kernel's 8-row form
-// (measured on decode steps of 8 sequences at the Llama-3.1-8B shape: 4.75 ms per step through the tiled GEMM, 7.6 ms
-// through the 8-row GEMV, whose 256 work-groups for 4096 output rows leave a CU with four waves' worth of loads).
-constexpr int kRowsForGemm = 5;
+// Projection of the B rows of a decode-style layer.  The GEMV kernel (every weight row streamed once per group of 1, 2
+// or 4 rows) is the faster form for one and two rows, which it also normalises itself; from kRowsForGemm rows on the
+// tiled MFMA GEMM with its small tiles, the staggered K start and the split of K is: at the Llama-3.1-8B shape, QKV,
+// O, gate|up and down of 2 rows take 12.6 / 9.6 / 45 / 24 us as GEMV and 14.2 / 12.7 / 41 / 26 us tiled, of 3 rows
+// 23 / 17 / 85 / 43 us (two groups) and 14.1 / 12.7 / 41 / 26 us, of 4 rows 18 / 13.6 / 56 / 32 us and the same.
+constexpr int kRowsForGemm = 3;
 constexpr int rows_for_gemm() { return kRowsForGemm; }
 constexpr int kFusedAppendRows = 4;   // decode-style rows up to which the attention kernel does RoPE + append itself
 
@@ -609,12 +609,12 @@ pop_status decode_layer(const LayerCtx& x, int l /*1-based*/, int B, const int32
   const bool fused_append = B <= kFusedAppendRows;
   int qkv_parts = 1;
   if (pop_status s = normed_few_rows_projection(x, xb, (const float*)lw.norm_in, ab, lw.wqkv, qkvb, B, Dqkv, d, Dqkv,
-                                                pop::GEMV_STORE_F32, 0, fused_append ? nullptr : &qkv_parts))
+                                                pop::GEMV_STORE_F32, 0, &qkv_parts))
     return s;
   pop::AttnDecodeArgs ad{};
   if (fused_append) {
-    ad.qkv_raw = qkvb;
-    ad.ld = Dqkv; ad.n_parts = 1; ad.part_stride = 0;
+    ad.qkv_raw = qkv_parts > 1 ? at<float>(x.ws, x.w->o_splitk) : qkvb;
+    ad.ld = Dqkv; ad.n_parts = qkv_parts; ad.part_stride = (size_t)B * Dqkv;
     ad.cs = at<float2>(x.ws, glob ? x.w->o_dcs_g : x.w->o_dcs_l);
     ad.q_gamma = (const float*)lw.q_norm; ad.k_gamma = (const float*)lw.k_norm; ad.qk_eps = c.rms_eps;
   } else {
@@ -638,12 +638,10 @@ pop_status decode_layer(const LayerCtx& x, int l /*1-based*/, int B, const int32
   ad.n_kv_heads = c.n_kv_heads;
   ad.hd = c.head_dim;
   const int span = ad.window > 0 ? std::min(max_len, ad.window) : max_len;
-  ad.n_splits = std::max(1, (span + pop::kDecodeKeysPerSplit - 1) / pop::kDecodeKeysPerSplit);
-  ad.max_len = max_len;
   ad.part = at<float>(x.ws, x.w->o_part);
   ad.out = attnb;
   ad.kvq = kv_quant(c);
-  pop::launch_attention_decode(ad, x.st);
+  pop::launch_attention_decode(ad, span, x.st);
   if (pop_status s = residual_few_rows_projection(x, attnb, lw.wo, B, d, Dq, (const float*)lw.norm_post, x.gate(l))) return s;
   if (pop_status s = normed_few_rows_projection(x, xb, (const float*)lw.norm_post, ab, lw.w_gate_up, ub, B, f, d, f,
                                                 pop::GEMV_GLU_BF16, c.act))

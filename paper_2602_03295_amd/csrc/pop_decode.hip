@@ -3,6 +3,7 @@
 // They carry the boundary token of Sec. 3.3 ("Boundary Handling for the Last Input Token": x_N is
 // the first decode step with the full model) and pop_decode_step (Sec. 3.2, decode operator).
 // With M <= 8 rows every projection streams its weights once: these kernels are HBM-bound.
+#include <algorithm>
 #include <type_traits>
 
 #include "pop_device.h"
@@ -363,247 +364,356 @@ void launch_rope_append(const float* qkv, int ld, bf16_t* q_out, int n_q_heads, 
 // ------------------------------------------------------------------------------------- decode attention
 namespace decode_impl {
 
-constexpr int KCH = kDecodeKeysPerSplit;  // keys per work-group (one split)
 constexpr int GMAX = 8;   // query heads per KV head
 
-// grid (n_splits, Hkv, B), 256 threads.  Split s of sequence b covers keys lo + s*KCH .. +KCH-1,
-// lo = first visible key (window start, or the first position the layer holds an entry for).  Writes the unnormalised partial output, its max and its sum.
+// Reduces values that the lanes li, li + LPK, ... of a wave hold for the same head-dim slice, by a butterfly that
+// halves the number of values a lane carries at every step (a lane sends the half its partner keeps): N values cost
+// N (1 - LPK / 64) exchanges.  Returns the index of this lane's v[0]; the first N * LPK / 64 entries are its results.
+template <int LPK, int N>
+__device__ __forceinline__ int fold_keys(float (&v)[N], int lane) {
+  int first = 0;
+  auto fold = [&](auto n_c, int o) {
+    constexpr int H = decltype(n_c)::value / 2;
+    const bool upper = (lane & o) != 0;
+#pragma unroll
+    for (int i = 0; i < H; ++i) {
+      const float send = upper ? v[i] : v[i + H];
+      const float keep = upper ? v[i + H] : v[i];
+      v[i] = keep + __shfl_xor(send, o, 64);
+    }
+    if (upper) first += H;
+  };
+  constexpr int N2 = LPK <= 32 ? N / 2 : N, N3 = LPK <= 16 ? N2 / 2 : N2;
+  static_assert(N * LPK >= 64, "a lane keeps at least one value");
+  if constexpr (LPK <= 32) fold(std::integral_constant<int, N>{}, 32);
+  if constexpr (LPK <= 16) fold(std::integral_constant<int, N2>{}, 16);
+  if constexpr (LPK <= 8) fold(std::integral_constant<int, N3>{}, 8);
+  return first;
+}
+
+// grid (n_splits, Hkv, B), 256 threads.  Split s of sequence b covers keys lo + s * split_keys .., lo = first visible
+// key (window start, or the first position the layer holds an entry for); wave w of the work-group takes its key
+// blocks (NB groups of 16 keys) w, w + 4, ... with a running maximum and sum of its own.
+//   S = K Q^T on the MFMA (v_mfma_f32_16x16x32_bf16; the G query heads of the KV head are columns, the others zero):
+//   lane l loads 16-byte chunks of key l % 16, which are the operand as they are (8-bit codes become bf16, exactly).
+//   O += P V on the vector ALU in fp32 with P in fp32: V's rows are contiguous in the head-dim, so an MFMA would need
+//   them transposed; LPK = HD / 8 lanes share a V row, P crosses lanes through LDS inside the wave.
+//   The next block's K is requested as soon as S is formed, its V as soon as P V is: a wave has 8 to 16 KB in flight.
+// A work-group per 64 keys with everything on the vector ALU spent its time there and on 130 partial values per head
+// and 64 keys; at 8 sequences: 2048 keys 27 us, 8192 keys of the 8-bit cache 70 + 10 us (with the merge).
 // GT: compile-time bound of the number of query heads per KV head (registers and loops are sized by it).
-// FUSED: RoPE + append inside this kernel (a.qkv_raw given); a template parameter because the preparation's registers
-// would otherwise halve the occupancy of the plain form as well.
-template <int HD, int GT, bool FUSED>
+// FUSED: RoPE + append inside this kernel (a.qkv_raw given).
+template <int HD, int GT, bool FUSED, bool FP8, int NB>
 __global__ __launch_bounds__(256) void attn_decode_split_kernel(AttnDecodeArgs a, float scale) {
-  constexpr int LPK = HD / 8;        // lanes per key (16-byte chunk each)
-  constexpr int KPI = 256 / LPK;     // keys per block iteration
-  __shared__ float sc[GT][KCH];
-  __shared__ float red[4][GT][HD];  // one partial per wave
-  __shared__ float stat[GT][2];
+  constexpr int KS = HD / 32;                       // MFMA steps over the head dim
+  constexpr int LPK = HD / 8, KPL = 64 / LPK;       // lanes per V row, V rows per load
+  constexpr int VL = 16 / KPL;                      // V loads per 16 keys
+  constexpr int HALF = HD / 2;
+  typedef typename std::conditional<FP8, uint2, uint4>::type chunk_t;   // 8 elements
+  __shared__ float ps[4][NB * 16][GT];              // P of a wave's block, then unused
+  __shared__ float al[4][GT];                       // rescaling factors of a wave
+  __shared__ float red[4][GT][HD];
+  __shared__ float stat[4][2][GT];
 
   const int split = blockIdx.x, kvh = blockIdx.y, b = blockIdx.z;
   const int G = a.n_q_heads / a.n_kv_heads;
-  const int P = a.page_size, lgP = __ffs(P) - 1;   // page sizes are powers of two
+  const int P = a.page_size, lgP = __ffs(P) - 1;    // page sizes are powers of two
   const int qpos = a.pos[b];
   int lo = a.window > 0 ? max(0, qpos - a.window + 1) : 0;
   if (a.kv_first) lo = max(lo, min(a.kv_first[b], qpos));   // the query token's own entry always exists
-  const int k_first = lo + split * KCH;
-  const int n_keys = min(KCH, qpos + 1 - k_first);  // <= 0: this split is empty
-  const int tid = threadIdx.x;
-  const bool fp8 = a.kvq.fp8 != 0;      // uniform: the pools hold one-byte e4m3 codes
-  const int li = tid % LPK, kslot = tid / LPK;
+  const int k_first = lo + split * a.split_keys;
+  const int n_keys = min(a.split_keys, qpos + 1 - k_first);  // <= 0: this split is empty
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int r16 = lane & 15, g4 = lane >> 4;        // key (K operand) or query head (Q operand); k chunk
+  const int li = lane % LPK, vs = lane / LPK;       // V: head-dim chunk, row of the load
   const int32_t* bt = a.block_table + (size_t)b * a.max_pages;
   float* part = a.part + (((size_t)b * a.n_q_heads + (size_t)kvh * G) * a.n_splits + split) * (HD + 2);
   const size_t part_head_stride = (size_t)a.n_splits * (HD + 2);
-
-  if (n_keys <= 0) {
-    for (int i = tid; i < G * (HD + 2); i += 256) {
-      const int g = i / (HD + 2), e = i % (HD + 2);
-      part[g * part_head_stride + e] = e == HD ? -INFINITY : 0.f;
-    }
+  if (n_keys <= 0) {                                // the merge skips a split whose maximum is -inf
+    if (tid < G) part[tid * part_head_stride + HD] = -INFINITY;
     return;
   }
-
-  // this thread's K and V chunks of the split are requested up front (one memory round trip), before the query
-  // rows are prepared (in the fused mode the slot of the query position is read too, and replaced further down)
-  constexpr int NIT = KCH / KPI;
-  uint4 kw[NIT], vw[NIT];
-#pragma unroll
-  for (int it = 0; it < NIT; ++it) {
-    const int kk = kslot + it * KPI;
-    kw[it] = make_uint4(0, 0, 0, 0);
-    vw[it] = make_uint4(0, 0, 0, 0);
-    if (kk < n_keys) {
-      const int key = k_first + kk;
-      const int page = bt[key >> lgP];
-      const size_t off = (((size_t)page * a.n_kv_heads + kvh) * P + (key & (P - 1))) * HD + li * 8;
-      if (fp8) {   // 8 one-byte codes per chunk
-        const uint2 k8 = *reinterpret_cast<const uint2*>(reinterpret_cast<const unsigned char*>(a.k_pool) + off);
-        const uint2 v8 = *reinterpret_cast<const uint2*>(reinterpret_cast<const unsigned char*>(a.v_pool) + off);
-        kw[it].x = k8.x; kw[it].y = k8.y;
-        vw[it].x = v8.x; vw[it].y = v8.y;
-      } else {
-        kw[it] = *reinterpret_cast<const uint4*>(a.k_pool + off);
-        vw[it] = *reinterpret_cast<const uint4*>(a.v_pool + off);
-      }
-    }
-  }
-  // ---- RoPE + append inside this kernel: head rows from the projection's fp32 output
-  constexpr bool fused = FUSED;
-  constexpr int HALF = HD / 2;
-  const bool hi_half = li * 8 >= HALF;          // this thread's 8 dims are the second members of their pairs
-  float rc[8], rs[8];                           // (cos, sin) of those pairs
-  if constexpr (fused) {
-    const float4* csp = reinterpret_cast<const float4*>(a.cs + (size_t)b * HALF + (li * 8) % HALF);
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const float4 t = csp[e];
-      rc[2 * e] = t.x; rs[2 * e] = t.y; rc[2 * e + 1] = t.z; rs[2 * e + 1] = t.w;
-    }
-  }
-  // This thread's 8 values of the head that starts at column `col` of the raw row: parts added, optionally
-  // RMS-normalised over the head (its LPK lanes are an aligned group), optionally rotated.  x = own dims, y = the
-  // other members of their pairs; first members become x c - y s, second members x c + y s.
-  auto head8 = [&](int col, const float* gamma, bool rotate, float* out8) {
-    const float* row = a.qkv_raw + (size_t)b * a.ld + col;
-    float x[8], y[8];
-    {
-      const float4 x0 = *reinterpret_cast<const float4*>(row + li * 8), x1 = *reinterpret_cast<const float4*>(row + li * 8 + 4);
-      const float4 y0 = *reinterpret_cast<const float4*>(row + ((li * 8) ^ HALF)), y1 = *reinterpret_cast<const float4*>(row + ((li * 8) ^ HALF) + 4);
-      x[0] = x0.x; x[1] = x0.y; x[2] = x0.z; x[3] = x0.w; x[4] = x1.x; x[5] = x1.y; x[6] = x1.z; x[7] = x1.w;
-      y[0] = y0.x; y[1] = y0.y; y[2] = y0.z; y[3] = y0.w; y[4] = y1.x; y[5] = y1.y; y[6] = y1.z; y[7] = y1.w;
-    }
-    for (int p = 1; p < a.n_parts; ++p) {
-      const float* rp = row + (size_t)p * a.part_stride;
-#pragma unroll
-      for (int e = 0; e < 8; ++e) { x[e] += rp[li * 8 + e]; y[e] += rp[((li * 8) ^ HALF) + e]; }
-    }
-    if (gamma) {
-      float s2 = 0.f;
-#pragma unroll
-      for (int e = 0; e < 8; ++e) s2 += x[e] * x[e];
-      s2 = group_sum<(LPK < 16 ? LPK : 16)>(s2);
-      if (LPK > 16) s2 += __shfl_xor(s2, 16, 64);
-      const float rstd = 1.0f / sqrtf(s2 / (float)HD + a.qk_eps);
-#pragma unroll
-      for (int e = 0; e < 8; ++e) { x[e] *= rstd * gamma[li * 8 + e]; y[e] *= rstd * gamma[((li * 8) ^ HALF) + e]; }
-    }
-#pragma unroll
-    for (int e = 0; e < 8; ++e)
-      out8[e] = !rotate ? x[e] : (hi_half ? x[e] * rc[e] + y[e] * rs[e] : x[e] * rc[e] - y[e] * rs[e]);
+  const chunk_t* k_pool = reinterpret_cast<const chunk_t*>(a.k_pool);
+  const chunk_t* v_pool = reinterpret_cast<const chunk_t*>(a.v_pool);
+  // chunk index of entry `key` (in page `page`)
+  auto entry = [&](int key, int page) {
+    return (((size_t)page * a.n_kv_heads + kvh) * P + (key & (P - 1))) * LPK;
   };
+  // Key kk of the split (kk beyond the last one repeats it, masked below).
+  auto key_of = [&](int kk) { return k_first + min(kk, n_keys - 1); };
+  const int n_blocks = (n_keys + NB * 16 - 1) / (NB * 16);
+  int page_k[NB];                                   // page of this lane's key (r16) in each group of the next block
+  chunk_t kw[NB][KS], vw[NB][VL];
+  auto load_pages = [&](int blk) {
+#pragma unroll
+    for (int n = 0; n < NB; ++n) page_k[n] = bt[key_of((blk * NB + n) * 16 + r16) >> lgP];
+  };
+  auto load_k = [&](int blk) {
+#pragma unroll
+    for (int n = 0; n < NB; ++n) {
+      const chunk_t* p = k_pool + entry(key_of((blk * NB + n) * 16 + r16), page_k[n]) + g4;
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks) kw[n][ks] = p[ks * 4];
+    }
+  };
+  int page_v[NB];                                   // pages of the block whose V is loaded next
+  auto load_v = [&](int blk) {
+#pragma unroll
+    for (int n = 0; n < NB; ++n)
+#pragma unroll
+      for (int i = 0; i < VL; ++i) {
+        const int k16 = i * KPL + vs;
+        vw[n][i] = v_pool[entry(key_of((blk * NB + n) * 16 + k16), __shfl(page_v[n], k16, 64)) + li];
+      }
+  };
+  // the first block's entries travel while the query rows are prepared
+  load_pages(wave);
+#pragma unroll
+  for (int n = 0; n < NB; ++n) page_v[n] = page_k[n];
+  if (wave < n_blocks) {
+    load_k(wave);
+    load_v(wave);
+  }
 
-  // ---- scores
-  float qv[GT][8];
+  // ---- query rows: lane l holds head r16 (zeros beyond G), dims 32 ks + 8 g4 .. + 7, as bf16.  The other member of
+  //      a rotation pair, HALF dims on, is the same lane's chunk ks + KS / 2.
+  bf16x8_t qf[KS];
+  uint4 k_new[KS];                                  // FUSED: the query position's own entry, as loaded from the pools
+  uint4 v_new = make_uint4(0, 0, 0, 0);
+  const bool has_new = FUSED && qpos - k_first < a.split_keys;     // (uniform) its key falls into this split
+  if constexpr (FUSED) {
+    // the 8 * KS values of this lane of the head at column `col`: parts added, optionally RMS-normalised over the
+    // head (its four lanes g4 hold it all), rotated
+    float cc[KS / 2][8], sn[KS / 2][8];
+    const float2* csp = a.cs + (size_t)b * HALF + g4 * 8;
 #pragma unroll
-  for (int g = 0; g < GT; ++g) {
-    if (g < G) {
-      if constexpr (fused) {
-        head8((kvh * G + g) * HD, a.q_gamma, true, qv[g]);
+    for (int ks = 0; ks < KS / 2; ++ks)
 #pragma unroll
-        for (int e = 0; e < 8; ++e) qv[g][e] = bf16_to_f32(f32_to_bf16(qv[g][e]));   // q enters the scores as bf16
-      } else {
-        const uint4 w = *reinterpret_cast<const uint4*>(a.q + ((size_t)b * a.n_q_heads + kvh * G + g) * HD + li * 8);
-        qv[g][0] = bf16lo(w.x); qv[g][1] = bf16hi(w.x); qv[g][2] = bf16lo(w.y); qv[g][3] = bf16hi(w.y);
-        qv[g][4] = bf16lo(w.z); qv[g][5] = bf16hi(w.z); qv[g][6] = bf16lo(w.w); qv[g][7] = bf16hi(w.w);
+      for (int e = 0; e < 4; ++e) {
+        const float4 t = *reinterpret_cast<const float4*>(csp + ks * 32 + 2 * e);
+        cc[ks][2 * e] = t.x; sn[ks][2 * e] = t.y; cc[ks][2 * e + 1] = t.z; sn[ks][2 * e + 1] = t.w;
+      }
+    auto head_row = [&](int col, const float* gamma, float (&x)[KS][8]) {
+      const float* row = a.qkv_raw + (size_t)b * a.ld + col + g4 * 8;
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks) {
+        const float4 u = *reinterpret_cast<const float4*>(row + ks * 32), w = *reinterpret_cast<const float4*>(row + ks * 32 + 4);
+        x[ks][0] = u.x; x[ks][1] = u.y; x[ks][2] = u.z; x[ks][3] = u.w;
+        x[ks][4] = w.x; x[ks][5] = w.y; x[ks][6] = w.z; x[ks][7] = w.w;
+      }
+      for (int p = 1; p < a.n_parts; ++p) {
+        const float* rp = row + (size_t)p * a.part_stride;
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) {
+          const float4 u = *reinterpret_cast<const float4*>(rp + ks * 32), w = *reinterpret_cast<const float4*>(rp + ks * 32 + 4);
+          x[ks][0] += u.x; x[ks][1] += u.y; x[ks][2] += u.z; x[ks][3] += u.w;
+          x[ks][4] += w.x; x[ks][5] += w.y; x[ks][6] += w.z; x[ks][7] += w.w;
+        }
+      }
+      if (gamma) {
+        float s2 = 0.f;
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks)
+#pragma unroll
+          for (int e = 0; e < 8; ++e) s2 += x[ks][e] * x[ks][e];
+        s2 += __shfl_xor(s2, 16, 64);
+        s2 += __shfl_xor(s2, 32, 64);
+        const float rstd = 1.0f / sqrtf(s2 / (float)HD + a.qk_eps);
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks)
+#pragma unroll
+          for (int e = 0; e < 8; ++e) x[ks][e] *= rstd * gamma[ks * 32 + g4 * 8 + e];
+      }
+#pragma unroll
+      for (int ks = 0; ks < KS / 2; ++ks)
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          const float lo8 = x[ks][e], hi8 = x[ks + KS / 2][e];
+          x[ks][e] = lo8 * cc[ks][e] - hi8 * sn[ks][e];
+          x[ks + KS / 2][e] = hi8 * cc[ks][e] + lo8 * sn[ks][e];
+        }
+    };
+    auto pack8 = [&](const float* x, float inv) {   // a cache chunk: bf16 values or e4m3 codes
+      if (FP8)
+        return make_uint4(e4m3_pack4(x[0] * inv, x[1] * inv, x[2] * inv, x[3] * inv),
+                          e4m3_pack4(x[4] * inv, x[5] * inv, x[6] * inv, x[7] * inv), 0u, 0u);
+      return make_uint4(pack_bf16x2(x[0], x[1]), pack_bf16x2(x[2], x[3]), pack_bf16x2(x[4], x[5]), pack_bf16x2(x[6], x[7]));
+    };
+    float x[KS][8];
+    head_row((kvh * G + min(r16, G - 1)) * HD, a.q_gamma, x);
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) {
+      const uint4 w = r16 < G ? make_uint4(pack_bf16x2(x[ks][0], x[ks][1]), pack_bf16x2(x[ks][2], x[ks][3]),
+                                           pack_bf16x2(x[ks][4], x[ks][5]), pack_bf16x2(x[ks][6], x[ks][7]))
+                              : make_uint4(0, 0, 0, 0);
+      qf[ks] = __builtin_bit_cast(bf16x8_t, w);
+    }
+    if (has_new) {
+      head_row((a.n_q_heads + kvh) * HD, a.k_gamma, x);
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks) k_new[ks] = pack8(x[ks], a.kvq.k_inv);
+      float v8[8];
+      const float* row = a.qkv_raw + (size_t)b * a.ld + (a.n_q_heads + a.n_kv_heads + kvh) * HD + li * 8;
+#pragma unroll
+      for (int e = 0; e < 8; ++e) v8[e] = row[e];
+      for (int p = 1; p < a.n_parts; ++p)
+#pragma unroll
+        for (int e = 0; e < 8; ++e) v8[e] += row[(size_t)p * a.part_stride + e];
+      v_new = pack8(v8, a.kvq.v_inv);
+    }
+  } else {
+    const bf16_t* q = a.q + ((size_t)b * a.n_q_heads + kvh * G + min(r16, G - 1)) * HD + g4 * 8;
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) {
+      const uint4 w = *reinterpret_cast<const uint4*>(q + ks * 32);
+      qf[ks] = __builtin_bit_cast(bf16x8_t, r16 < G ? w : make_uint4(0, 0, 0, 0));
+    }
+  }
+  auto as_chunk = [](const uint4& w) {
+    if constexpr (FP8) return make_uint2(w.x, w.y);
+    else return w;
+  };
+  // FUSED, in the block that holds the query position's key (the split's last): the chunks loaded for it, also by
+  // lanes that repeat it, are replaced by the new entry, and the lanes whose key it is store it.
+  auto patch_k = [&](int blk) {
+#pragma unroll
+    for (int n = 0; n < NB; ++n) {
+      const int kk = (blk * NB + n) * 16 + r16, key = key_of(kk);
+      if (key != qpos) continue;
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks) kw[n][ks] = as_chunk(k_new[ks]);
+      if (kk == n_keys - 1) {
+        chunk_t* o = reinterpret_cast<chunk_t*>(const_cast<bf16_t*>(a.k_pool)) + entry(key, bt[key >> lgP]) + g4;
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) o[ks * 4] = as_chunk(k_new[ks]);
       }
     }
-  }
-  // The query position's own entry, if its key falls into this split: formed here (every group of lanes computes
-  // the same values; the group whose key it is stores them and keeps them in place of a load).
-  const int kk_new = qpos - k_first;
-  const bool has_new = fused && kk_new >= 0 && kk_new < n_keys;
-  uint4 k_new = make_uint4(0, 0, 0, 0), v_new = make_uint4(0, 0, 0, 0);
-  if (has_new) {
-    float k8[8], v8[8];
-    head8((a.n_q_heads + kvh) * HD, a.k_gamma, true, k8);
-    head8((a.n_q_heads + a.n_kv_heads + kvh) * HD, nullptr, false, v8);
-    if (fp8) {
-      k_new.x = e4m3_pack4(k8[0] * a.kvq.k_inv, k8[1] * a.kvq.k_inv, k8[2] * a.kvq.k_inv, k8[3] * a.kvq.k_inv);
-      k_new.y = e4m3_pack4(k8[4] * a.kvq.k_inv, k8[5] * a.kvq.k_inv, k8[6] * a.kvq.k_inv, k8[7] * a.kvq.k_inv);
-      v_new.x = e4m3_pack4(v8[0] * a.kvq.v_inv, v8[1] * a.kvq.v_inv, v8[2] * a.kvq.v_inv, v8[3] * a.kvq.v_inv);
-      v_new.y = e4m3_pack4(v8[4] * a.kvq.v_inv, v8[5] * a.kvq.v_inv, v8[6] * a.kvq.v_inv, v8[7] * a.kvq.v_inv);
-    } else {
-      k_new = make_uint4(pack_bf16x2(k8[0], k8[1]), pack_bf16x2(k8[2], k8[3]), pack_bf16x2(k8[4], k8[5]), pack_bf16x2(k8[6], k8[7]));
-      v_new = make_uint4(pack_bf16x2(v8[0], v8[1]), pack_bf16x2(v8[2], v8[3]), pack_bf16x2(v8[4], v8[5]), pack_bf16x2(v8[6], v8[7]));
-    }
-  }
-  if (has_new) {
+  };
+  auto patch_v = [&](int blk) {
 #pragma unroll
-    for (int it = 0; it < NIT; ++it) {
-      if (kslot + it * KPI != kk_new) continue;
-      // the new entry: stored (the pools are written in this mode) and kept in place of what was loaded
-      kw[it] = k_new;
-      vw[it] = v_new;
-      const int page = bt[qpos >> lgP];
-      const size_t off = (((size_t)page * a.n_kv_heads + kvh) * P + (qpos & (P - 1))) * HD + li * 8;
-      if (fp8) {
-        *reinterpret_cast<uint2*>(reinterpret_cast<unsigned char*>(const_cast<bf16_t*>(a.k_pool)) + off) = make_uint2(k_new.x, k_new.y);
-        *reinterpret_cast<uint2*>(reinterpret_cast<unsigned char*>(const_cast<bf16_t*>(a.v_pool)) + off) = make_uint2(v_new.x, v_new.y);
-      } else {
-        *reinterpret_cast<uint4*>(const_cast<bf16_t*>(a.k_pool) + off) = k_new;
-        *reinterpret_cast<uint4*>(const_cast<bf16_t*>(a.v_pool) + off) = v_new;
+    for (int n = 0; n < NB; ++n)
+#pragma unroll
+      for (int i = 0; i < VL; ++i) {
+        const int kk = (blk * NB + n) * 16 + i * KPL + vs, key = key_of(kk);
+        if (key != qpos) continue;
+        vw[n][i] = as_chunk(v_new);
+        if (kk == n_keys - 1)
+          reinterpret_cast<chunk_t*>(const_cast<bf16_t*>(a.v_pool))[entry(key, bt[key >> lgP]) + li] = as_chunk(v_new);
       }
-    }
-  }
-  // the 8 values of a chunk as floats: bf16 entries, or e4m3 codes times the tensor's scale
-  auto unpack8 = [&](const uint4& w, float* f, float scale8) {
-    if (fp8) {
+  };
+  // a chunk of K as the MFMA operand
+  auto k_operand = [&](const chunk_t& w) {
+    if constexpr (FP8) {     // e4m3 values have 4 significant bits: their bf16 is the upper half of their fp32
+      float f[8];
       e4m3_decode4_hw(w.x, f);
       e4m3_decode4_hw(w.y, f + 4);
+      uint32_t u[4];
 #pragma unroll
-      for (int e = 0; e < 8; ++e) f[e] *= scale8;
+      for (int e = 0; e < 4; ++e)
+        u[e] = (__builtin_bit_cast(uint32_t, f[2 * e]) >> 16) | (__builtin_bit_cast(uint32_t, f[2 * e + 1]) & 0xffff0000u);
+      return __builtin_bit_cast(bf16x8_t, make_uint4(u[0], u[1], u[2], u[3]));
     } else {
-      f[0] = bf16lo(w.x); f[1] = bf16hi(w.x); f[2] = bf16lo(w.y); f[3] = bf16hi(w.y);
-      f[4] = bf16lo(w.z); f[5] = bf16hi(w.z); f[6] = bf16lo(w.w); f[7] = bf16hi(w.w);
+      return __builtin_bit_cast(bf16x8_t, w);
     }
   };
-#pragma unroll
-  for (int it = 0; it < NIT; ++it) {
-    const int kk = kslot + it * KPI;
-    float s[GT];
-#pragma unroll
-    for (int g = 0; g < GT; ++g) s[g] = 0.f;
-    {
-      float kf[8];
-      unpack8(kw[it], kf, a.kvq.k_scale);
-#pragma unroll
-      for (int g = 0; g < GT; ++g)
-        if (g < G) {
-#pragma unroll
-          for (int e = 0; e < 8; ++e) s[g] += qv[g][e] * kf[e];
-        }
-    }
-#pragma unroll
-    for (int g = 0; g < GT; ++g)
-      if (g < G) {
-        // the LPK lanes of a key are an aligned group inside a row of 16 lanes (two rows at head_dim 256)
-        s[g] = group_sum<(LPK < 16 ? LPK : 16)>(s[g]);
-        if (LPK > 16) s[g] += __shfl_xor(s[g], 16, 64);
-        if (li == 0) sc[g][kk] = kk < n_keys ? s[g] * scale : -INFINITY;
-      }
-  }
-  __syncthreads();
-  // ---- per-head max and exp-sum (wave w handles heads w, w+4)
-  {
-    const int w = tid >> 6, lane = tid & 63;
-    for (int g = w; g < G; g += 4) {
-      float mx = -INFINITY;
-      for (int i = lane; i < KCH; i += 64) mx = fmaxf(mx, sc[g][i]);
-      mx = wave_max_rows(mx);
-      float sum = 0.f;
-      for (int i = lane; i < KCH; i += 64) {
-        const float pv = __expf(sc[g][i] - mx);
-        sc[g][i] = pv;
-        sum += pv;
-      }
-      sum = wave_sum_rows(sum);
-      if (lane == 0) { stat[g][0] = mx; stat[g][1] = sum; }
-    }
-  }
-  __syncthreads();
-  // ---- partial O = P V : thread owns 8 head-dim values, strides over keys
+  const float s_scale = FP8 ? scale * a.kvq.k_scale : scale;
   float acc[GT][8];
 #pragma unroll
   for (int g = 0; g < GT; ++g)
 #pragma unroll
     for (int e = 0; e < 8; ++e) acc[g][e] = 0.f;
+  float m_run = -INFINITY, l_run = 0.f;             // of query head r16; l_run: this lane's keys
+
+  for (int blk = wave; blk < n_blocks; blk += 4) {
+    const bool last_block = blk == n_blocks - 1;
+    if (FUSED && has_new && last_block) {
+      patch_k(blk);
+      patch_v(blk);
+    }
+    if (blk + 4 < n_blocks) load_pages(blk + 4);
+    floatx4_t s[NB];
 #pragma unroll
-  for (int it = 0; it < NIT; ++it) {
-    const int kk = kslot + it * KPI;
-    if (kk >= n_keys) continue;
-    float vf[8];
-    unpack8(vw[it], vf, a.kvq.v_scale);
+    for (int n = 0; n < NB; ++n) {
+      s[n] = floatx4_t{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int g = 0; g < GT; ++g)
-      if (g < G) {
-        const float pv = sc[g][kk];
+      for (int ks = 0; ks < KS; ++ks)
+        s[n] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(k_operand(kw[n][ks]), qf[ks], s[n], 0, 0, 0);
+    }
+    if (blk + 4 < n_blocks) load_k(blk + 4);
+    // s[n][v]: query head r16, key 16 n + 4 g4 + v of the block
+    float mx = -INFINITY;
 #pragma unroll
-        for (int e = 0; e < 8; ++e) acc[g][e] += pv * vf[e];
+    for (int n = 0; n < NB; ++n)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const bool in = (blk * NB + n) * 16 + 4 * g4 + v < n_keys;
+        s[n][v] = in ? s[n][v] * s_scale : -INFINITY;
+        mx = fmaxf(mx, s[n][v]);
       }
+    mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
+    mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+    const float m_new = fmaxf(m_run, mx);           // every block has a key: finite unless the scores are not
+    const float alpha = __expf(m_run - m_new);
+    float sum = 0.f;
+#pragma unroll
+    for (int n = 0; n < NB; ++n)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const float pv = __expf(s[n][v] - m_new);
+        if (r16 < G) ps[wave][n * 16 + 4 * g4 + v][r16 % GT] = pv;
+        sum += pv;
+      }
+    l_run = l_run * alpha + sum;
+    const bool moved = __builtin_amdgcn_ballot_w64(r16 < G && alpha != 1.f) != 0;
+    if (moved && g4 == 0 && r16 < G) al[wave][r16 % GT] = alpha;
+    m_run = m_new;
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");     // the wave's own LDS writes, read by its other lanes
+    if (moved) {
+#pragma unroll
+      for (int g = 0; g < GT; ++g)
+        if (g < G) {
+          const float f = al[wave][g];
+#pragma unroll
+          for (int e = 0; e < 8; ++e) acc[g][e] *= f;
+        }
+    }
+#pragma unroll
+    for (int n = 0; n < NB; ++n)
+#pragma unroll
+      for (int i = 0; i < VL; ++i) {
+        float vf[8];
+        if constexpr (FP8) {
+          e4m3_decode4_hw(vw[n][i].x, vf);
+          e4m3_decode4_hw(vw[n][i].y, vf + 4);
+        } else {
+          const uint4 w = vw[n][i];
+          vf[0] = bf16lo(w.x); vf[1] = bf16hi(w.x); vf[2] = bf16lo(w.y); vf[3] = bf16hi(w.y);
+          vf[4] = bf16lo(w.z); vf[5] = bf16hi(w.z); vf[6] = bf16lo(w.w); vf[7] = bf16hi(w.w);
+        }
+#pragma unroll
+        for (int g = 0; g < GT; ++g)
+          if (g < G) {
+            const float pv = ps[wave][n * 16 + i * KPL + vs][g];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) acc[g][e] += pv * vf[e];
+          }
+      }
+    if (blk + 4 < n_blocks) {
+#pragma unroll
+      for (int n = 0; n < NB; ++n) page_v[n] = page_k[n];
+      load_v(blk + 4);
+    }
+    asm volatile("" ::: "memory");                  // the next block's P is written after this block's was read
   }
-  // Lanes li, li + LPK, ... of a wave hold partial sums of the same head-dim slice.  They are added by a
-  // butterfly that halves the number of values a lane carries at every step (a lane sends the half its partner
-  // keeps), so the GT * 8 values cost GT * 8 * (1 - LPK / 64) exchanges instead of GT * 8 per step; at the end
-  // the lanes of the different rows hold different values, and all of them write.  Then the 4 waves are added.
+
+  // ---- the wave's key slots, then the four waves, each with its own maximum
+  l_run += __shfl_xor(l_run, 16, 64);
+  l_run += __shfl_xor(l_run, 32, 64);
+  if (g4 == 0 && r16 < G) {
+    stat[wave][0][r16 % GT] = m_run;
+    stat[wave][1][r16 % GT] = l_run;
+  }
   {
     constexpr int NV = GT * 8;
     float v[NV];
@@ -611,38 +721,35 @@ __global__ __launch_bounds__(256) void attn_decode_split_kernel(AttnDecodeArgs a
     for (int g = 0; g < GT; ++g)
 #pragma unroll
       for (int e = 0; e < 8; ++e) v[g * 8 + e] = acc[g][e];
-    const int lane = tid & 63;
-    int first = 0;   // index (g * 8 + e) of this lane's v[0]
-    auto fold = [&](auto n_c, int o) {
-      constexpr int H = decltype(n_c)::value / 2;
-      const bool upper = (lane & o) != 0;
+    const int first = fold_keys<LPK, NV>(v, lane);
 #pragma unroll
-      for (int i = 0; i < H; ++i) {
-        const float send = upper ? v[i] : v[i + H];
-        const float keep = upper ? v[i + H] : v[i];
-        v[i] = keep + __shfl_xor(send, o, 64);
-      }
-      if (upper) first += H;
-    };
-    constexpr int N1 = NV, N2 = LPK <= 32 ? N1 / 2 : N1, N3 = LPK <= 16 ? N2 / 2 : N2, N4 = LPK <= 8 ? N3 / 2 : N3;
-    if constexpr (LPK <= 32) fold(std::integral_constant<int, N1>{}, 32);
-    if constexpr (LPK <= 16) fold(std::integral_constant<int, N2>{}, 16);
-    if constexpr (LPK <= 8) fold(std::integral_constant<int, N3>{}, 8);
-    static_assert(N4 >= 1, "a lane keeps at least one value");
-#pragma unroll
-    for (int i = 0; i < N4; ++i) {
+    for (int i = 0; i < NV * LPK / 64; ++i) {
       const int idx = first + i, g = idx >> 3, e = idx & 7;
-      if (g < G) red[tid >> 6][g][li * 8 + e] = v[i];
+      if (g < G) red[wave][g][li * 8 + e] = v[i];
     }
   }
   __syncthreads();
+  const float v_scale = FP8 ? a.kvq.v_scale : 1.f;
   for (int i = tid; i < G * HD; i += 256) {
     const int g = i / HD, e = i % HD;
-    part[g * part_head_stride + e] = (red[0][g][e] + red[1][g][e]) + (red[2][g][e] + red[3][g][e]);
-  }
-  if (tid < G) {
-    part[tid * part_head_stride + HD] = stat[tid][0];
-    part[tid * part_head_stride + HD + 1] = stat[tid][1];
+    const float m = fmaxf(fmaxf(stat[0][0][g], stat[1][0][g]), fmaxf(stat[2][0][g], stat[3][0][g]));
+    float num = 0.f, den = 0.f;
+#pragma unroll
+    for (int w = 0; w < 4; ++w) {
+      const float f = stat[w][0][g] == -INFINITY ? 0.f : __expf(stat[w][0][g] - m);   // (a wave without keys)
+      num += f * red[w][g][e];
+      den += f * stat[w][1][g];
+    }
+    num *= v_scale;
+    if (a.n_splits == 1) {
+      a.out[((size_t)b * a.n_q_heads + kvh * G + g) * HD + e] = f32_to_bf16(den > 0.f ? num / den : 0.f);
+    } else {
+      part[g * part_head_stride + e] = num;
+      if (e == 0) {
+        part[g * part_head_stride + HD] = m;
+        part[g * part_head_stride + HD + 1] = den;
+      }
+    }
   }
 }
 
@@ -668,9 +775,11 @@ __global__ __launch_bounds__(256) void attn_decode_combine_kernel(const float* _
 #pragma unroll 4
   for (int s = grp; s < n_splits; s += ng) {
     const float m = p[s * stride + hd];
+    // (an empty split holds nothing but its maximum, -inf)
     const float w = m == -INFINITY ? 0.f : __expf(m - mx);
-    num += w * p[s * stride + i];
-    den += w * p[s * stride + hd + 1];
+    const float x = p[s * stride + i], y = p[s * stride + hd + 1];
+    num += m == -INFINITY ? 0.f : w * x;
+    den += m == -INFINITY ? 0.f : w * y;
   }
   red_num[grp][i] = num;
   if (i == 0) red_den[grp] = den;
@@ -682,22 +791,37 @@ __global__ __launch_bounds__(256) void attn_decode_combine_kernel(const float* _
   }
 }
 
-template <int HD>
-void launch_decode_hd(const AttnDecodeArgs& a, hipStream_t st) {
+template <int HD, bool FUSED, bool FP8, int NB>
+void launch_decode_cfg(const AttnDecodeArgs& a, hipStream_t st) {
   const float scale = 1.f / sqrtf((float)HD);
   const dim3 grid(a.n_splits, a.n_kv_heads, a.B);
   const int G = a.n_q_heads / a.n_kv_heads;
-  auto go = [&](auto fused_c) {
-    constexpr bool F = decltype(fused_c)::value;
-    if (G <= 1) hipLaunchKernelGGL((attn_decode_split_kernel<HD, 1, F>), grid, dim3(256), 0, st, a, scale);
-    else if (G <= 2) hipLaunchKernelGGL((attn_decode_split_kernel<HD, 2, F>), grid, dim3(256), 0, st, a, scale);
-    else if (G <= 4) hipLaunchKernelGGL((attn_decode_split_kernel<HD, 4, F>), grid, dim3(256), 0, st, a, scale);
-    else hipLaunchKernelGGL((attn_decode_split_kernel<HD, GMAX, F>), grid, dim3(256), 0, st, a, scale);
+  if (G <= 1) hipLaunchKernelGGL((attn_decode_split_kernel<HD, 1, FUSED, FP8, NB>), grid, dim3(256), 0, st, a, scale);
+  else if (G <= 2) hipLaunchKernelGGL((attn_decode_split_kernel<HD, 2, FUSED, FP8, NB>), grid, dim3(256), 0, st, a, scale);
+  else if (G <= 4) hipLaunchKernelGGL((attn_decode_split_kernel<HD, 4, FUSED, FP8, NB>), grid, dim3(256), 0, st, a, scale);
+  else hipLaunchKernelGGL((attn_decode_split_kernel<HD, GMAX, FUSED, FP8, NB>), grid, dim3(256), 0, st, a, scale);
+}
+
+template <int HD>
+void launch_decode_hd(const AttnDecodeArgs& a, hipStream_t st) {
+  // Two groups of 16 keys per block where a wave has several blocks (half the cross-lane steps per key); head size
+  // 256 has no registers for the second.
+  auto go = [&](auto fused_c, auto fp8_c) {
+    constexpr bool F = decltype(fused_c)::value, Q = decltype(fp8_c)::value;
+    if constexpr (HD <= 128) {
+      if (a.split_keys >= 256) { launch_decode_cfg<HD, F, Q, 2>(a, st); return; }
+    }
+    launch_decode_cfg<HD, F, Q, 1>(a, st);
   };
-  if (a.qkv_raw) go(std::true_type{});
-  else go(std::false_type{});
-  hipLaunchKernelGGL(attn_decode_combine_kernel, dim3(a.B * a.n_q_heads), dim3(256), 0, st, a.part, a.out,
-                     a.n_splits, HD);
+  auto go_q = [&](auto fused_c) {
+    if (a.kvq.fp8) go(fused_c, std::true_type{});
+    else go(fused_c, std::false_type{});
+  };
+  if (a.qkv_raw) go_q(std::true_type{});
+  else go_q(std::false_type{});
+  if (a.n_splits > 1)
+    hipLaunchKernelGGL(attn_decode_combine_kernel, dim3(a.B * a.n_q_heads), dim3(256), 0, st, a.part, a.out,
+                       a.n_splits, HD);
 }
 }  // namespace decode_impl
 using namespace decode_impl;
@@ -769,8 +893,20 @@ void launch_argmax(const float* logits, int vocab, int32_t* tok, int32_t* out, i
                      eos);
 }
 
-void launch_attention_decode(const AttnDecodeArgs& a, hipStream_t st) {
+// Splits of the key range: about three work-groups per CU (what the kernel's registers allow), but no split of fewer
+// than 64 keys (16 per wave); equal shares, in whole rounds of the four waves.
+void choose_decode_splits(AttnDecodeArgs& a, int span) {
+  const long long pairs = (long long)a.B * a.n_kv_heads;
+  const int want = (int)std::max(1LL, std::min<long long>((span + 63) / 64, (768 + pairs - 1) / pairs));
+  const int keys = (span + want - 1) / want;
+  a.split_keys = (keys + 63) / 64 * 64;
+  a.n_splits = (span + a.split_keys - 1) / a.split_keys;
+}
+
+void launch_attention_decode(const AttnDecodeArgs& args, int span, hipStream_t st) {
+  AttnDecodeArgs a = args;
   if (a.B <= 0) return;
+  choose_decode_splits(a, span);
   switch (a.hd) {
     case 64: launch_decode_hd<64>(a, st); break;
     case 128: launch_decode_hd<128>(a, st); break;

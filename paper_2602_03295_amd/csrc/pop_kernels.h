@@ -182,8 +182,8 @@ void launch_gemv_norm(const float* xf, const float* gamma, float eps, const bf16
 // (n_parts > 1: qkv is given as that many fp32 partial products, part_stride elements apart, which are added in
 // index order first: the second kernel of a QKV projection whose K range was split)
 
-// Keys per split of the decode attention: small enough that a 2K-token context already gives every
-// CU a work-group (len / 64 splits x KV heads x sequences).
+// Fewest keys per split of the decode attention: a 2K-token context already gives every CU a work-group
+// (len / 64 splits x KV heads x sequences).
 constexpr int kDecodeKeysPerSplit = 64;
 
 // Attention of one query row per sequence over its paged cache entries 0..len-1 (len = pos + 1),
@@ -207,8 +207,7 @@ struct AttnDecodeArgs {
                             // a layer pruned without KV projections holds nothing for the prompt body
   int window;
   int B, n_q_heads, n_kv_heads, hd;
-  int n_splits;         // splits of kDecodeKeysPerSplit keys that cover the longest visible key range
-  int max_len;          // upper bound of pos+1 over the batch
+  int n_splits, split_keys;   // splits that cover the longest visible key range, and their size (set by the launch)
   float* part;          // [B, Hq, n_splits, hd + 2]
   bf16_t* out;          // [B, Hq*hd]
   KvQuant kvq;          // bf16 entries or e4m3 codes in the pools
@@ -225,7 +224,8 @@ struct AttnDecodeArgs {
   const float* k_gamma;
   float qk_eps;
 };
-void launch_attention_decode(const AttnDecodeArgs& a, hipStream_t st);
+// span: upper bound of the keys a query row sees, over the batch
+void launch_attention_decode(const AttnDecodeArgs& a, int span, hipStream_t st);
 
 // ---------------------------------------------------------------------------------------------
 // fp32 instantiation of every step (pop_f32.hip): fp32 weights, activations and cache entries

@@ -1,0 +1,73 @@
+"""Decode attention over the paged cache at the edges of its key blocks and splits: every bound of query heads per KV
+head, every head size, few rows (RoPE and append inside the kernel) and more, both cache types, a sliding window."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import pop_oracle as O
+from paper_2602_03295_amd import synth
+from tests.gpu_util import DeviceRun, TOL, rel_err
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def pop():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2602_03295_amd import pop as p
+    return p
+
+
+def check(pop, lens, steps, tol=TOL, l_keep=1, **kw):
+    cfg = synth.get_config("tiny", dtype=synth.DTYPE_BF16, n_layers=2, d_ffn=256, vocab=512, **kw)
+    W = synth.make_weights(cfg, seed=21)
+    synth.add_qk_norms(W, cfg)
+    tokens = synth.make_tokens(cfg["vocab"], sum(lens), seed=22)
+    run = DeviceRun(pop, cfg, W, lens, reserve_pages=2, shuffle_seed=23, poison=float("nan"))
+    logits = run.prefill(tokens, l_keep)
+    outs = O.pop_prefill_batch(cfg, W, tokens, run.cu, l_keep)
+    state = []
+    for b, (Kc, Vc, ref) in enumerate(outs):
+        assert rel_err(logits[b], ref) <= tol, ("prefill", b, lens[b])
+        state.append((Kc, Vc))
+    for s in range(steps):
+        tok = synth.make_tokens(cfg["vocab"], len(lens), seed=30 + s)
+        got = run.decode(tok)
+        for b in range(len(lens)):
+            ref, Kc, Vc = O.decode_step(cfg, W, O.embed_rows(W, tok[b:b + 1], np.float64)[0], *state[b])
+            state[b] = (Kc, Vc)
+            assert rel_err(got[b], ref) <= tol, (s, b, lens[b])
+            for l in range(cfg["n_layers"]):       # the new entries, where the step stored them
+                k, v = run.kv(l, b, lens[b] + s + 1)
+                assert rel_err(k[-1], Kc[l][-1]) <= 2 * tol and rel_err(v[-1], Vc[l][-1]) <= 2 * tol
+
+
+EDGES = [1, 15, 16, 17, 31, 63, 64, 65, 129]
+
+
+@pytest.mark.parametrize("hd,hq,hkv", [(64, 2, 2), (64, 6, 3), (128, 3, 1), (128, 8, 1), (256, 4, 2), (256, 5, 1)])
+@pytest.mark.parametrize("rows", [3, 9])
+def test_edges(pop, hd, hq, hkv, rows):
+    for i in range(0, 9, rows):
+        check(pop, EDGES[i:i + rows], 2, head_dim=hd, n_q_heads=hq, n_kv_heads=hkv)
+
+
+@pytest.mark.parametrize("rows", [3, 9])
+@pytest.mark.parametrize("hd", [64, 128, 256])
+def test_window_and_page_sizes(pop, rows, hd):
+    for P in (1, 8, 64):
+        check(pop, [40, 129, 65, 16, 33, 100, 250, 7, 64][:rows], 2, head_dim=hd, n_q_heads=4, n_kv_heads=2,
+              sliding_window=33, global_every=2, page_size=P)
+
+
+@pytest.mark.parametrize("rows", [3, 9])
+@pytest.mark.parametrize("hd", [64, 128, 256])
+def test_8_bit_cache(pop, rows, hd):
+    # code flips put one code step (6 to 12 % of an element) on a few entries: the bound of the 8-bit cache's own tests
+    check(pop, EDGES[:rows], 2, tol=8e-2, head_dim=hd, n_q_heads=4, n_kv_heads=2, kv_dtype=1, k_scale=0.02, v_scale=0.02)
+
+
+def test_two_key_groups_per_block(pop):
+    """Enough sequences and keys that a split has 256 of them or more."""
+    check(pop, [3300, 3137, 3072, 3400, 3329, 3201], 1, l_keep=0, head_dim=64, n_q_heads=16, n_kv_heads=8)
