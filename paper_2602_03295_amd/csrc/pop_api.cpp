@@ -185,6 +185,7 @@ struct pop_cache {
 namespace {
 
 constexpr int kKvChunk = 8;  // pruned layers projected per batched GEMM
+constexpr int kFusedAppendRows = 4;   // decode-style rows up to which the attention kernel does RoPE + append itself
 
 // Parts of the K range of the down projection (K = d_ffn) that the workspace of T > 512 prompt rows has room for:
 // as many as its 256 x 256 tiles leave work-groups idle.  How many are used is the GEMM's choice; they are added in
@@ -362,13 +363,22 @@ pop_status slot_map_impl(const int32_t* cu, int n_seqs, const int32_t* bt, int m
 // Work list of the prefill attention kernel.  A work-group processes one or two query tiles of 128
 // rows of one sequence: the k-th latest tile (most keys) is paired with the k-th earliest (fewest),
 // so every work-group of a sequence sees the same number of key tiles and the causal triangle is
-// balanced.  Longer sequences (more work per pair) come first.  Returns the number of entries.
-int build_attention_work(const int32_t* cu, int B, int32_t* seq_out, int32_t* start_out, int32_t* start2_out) {
+// balanced.  Longer sequences (more work per pair) come first.  Where the tiles of all heads do not fill the chip once,
+// each gets a work-group of its own instead (prompts of 77 + 301 + 150 tokens, 32 heads: the paired work-groups took 26
+// us for 7 key tiles in a row).  Returns the number of entries.
+int build_attention_work(const int32_t* cu, int B, int n_heads, int32_t* seq_out, int32_t* start_out, int32_t* start2_out) {
   struct Item { int work, seq, a, b; };
   std::vector<Item> items;
+  long long tiles = 0;
+  for (int b = 0; b < B; ++b) tiles += (cu[b + 1] - cu[b] + 127) / 128;
+  const bool single = tiles * n_heads <= 256;
   for (int b = 0; b < B; ++b) {
     const int len = cu[b + 1] - cu[b];
     const int nt = (len + 127) / 128;
+    if (single) {
+      for (int k = 0; k < nt; ++k) items.push_back(Item{k + 1, b, k * 128, -1});
+      continue;
+    }
     for (int k = 0; k < (nt + 1) / 2; ++k) {
       const int heavy = nt - 1 - k, light = k;
       items.push_back(Item{heavy == light ? heavy + 1 : nt + 1, b, heavy * 128, heavy == light ? -1 : light * 128});
@@ -399,14 +409,17 @@ struct LayerCtx {
 };
 
 // (cos, sin) tables of the B decode-style rows at positions pos[0..B-1], one per RoPE base in use: what the decode
-// attention kernel rotates the query token's q and k with.  Once per pass over the layers.
-void decode_rope_tables(const LayerCtx& x, const int32_t* pos, int B) {
+// attention kernel rotates the query token's q and k with.  Once per pass over the layers (the separate append kernel
+// of larger batches forms its angles itself).
+pop::RopeTables decode_rope_tables(const LayerCtx& x, const int32_t* pos, int B) {
+  pop::RopeTables tabs;
+  if (B > kFusedAppendRows) return tabs;
   const pop_config& c = x.m->cfg;
-  pop::launch_rope_table(pos, at<float2>(x.ws, x.w->o_dcs_g), B, c.head_dim, (double)c.rope_theta, x.st);
+  tabs.add(pos, at<float2>(x.ws, x.w->o_dcs_g), B, c.head_dim, (double)c.rope_theta);
   bool any_local = false;
   for (int l = 1; l <= c.n_layers; ++l) any_local = any_local || !layer_is_global(c, l);
-  if (any_local)
-    pop::launch_rope_table(pos, at<float2>(x.ws, x.w->o_dcs_l), B, c.head_dim, (double)c.rope_theta_local, x.st);
+  if (any_local) tabs.add(pos, at<float2>(x.ws, x.w->o_dcs_l), B, c.head_dim, (double)c.rope_theta_local);
+  return tabs;
 }
 
 // The prefill's pruning, resolved from the arguments (Sec. 2.2: a skip set; Sec. 3.3: applied to the
@@ -509,7 +522,6 @@ void record_kv_first(pop_cache* c, const pop_prefill_args* a, const PrunePlan& p
 // 23 / 17 / 85 / 43 us (two groups) and 14.1 / 12.7 / 41 / 26 us, of 4 rows 18 / 13.6 / 56 / 32 us and the same.
 constexpr int kRowsForGemm = 3;
 constexpr int rows_for_gemm() { return kRowsForGemm; }
-constexpr int kFusedAppendRows = 4;   // decode-style rows up to which the attention kernel does RoPE + append itself
 
 // parts_out (optional): the caller can add partial products itself.  If the K range was split, *parts_out receives
 // the number of parts (fp32 [parts][B][N] dense at the split scratch of the workspace) and `out` is not written;
@@ -537,7 +549,8 @@ pop_status few_rows_projection(const LayerCtx& x, const bf16_t* in, const void* 
 }
 
 // The same for fp32 rows that are RMS-normalised first (Sec. 2.1): with a few rows the GEMV kernel normalises
-// them itself; otherwise the norm kernel writes bf16 rows to `normed` and the projection reads those.
+// them itself (two rows for thousands of work-groups cost more than the norm's own launch: gate|up 45.4 us against
+// 40.3 + 2.5 us, LM head of 16032 rows 28.6 against 23.6 + 2.5 us; QKV, 6144 rows, 12.6 against 11.1 + 2.5 us); otherwise the norm kernel writes bf16 rows to `normed` and the projection reads those.
 pop_status normed_few_rows_projection(const LayerCtx& x, float* rows, const float* gamma, bf16_t* normed, const void* W,
                                       void* out, int B, int N, int K, int ldo, int gemv_epi, int act,
                                       int* parts_out = nullptr) {
@@ -545,7 +558,7 @@ pop_status normed_few_rows_projection(const LayerCtx& x, float* rows, const floa
   const float eps = x.m->cfg.rms_eps;
   if (x.ab_gamma == gamma && gamma != nullptr)   // the previous projection's second kernel left them in `normed`
     return few_rows_projection(x, normed, W, out, B, N, K, ldo, gemv_epi, act, parts_out);
-  if (B < rows_for_gemm() && pop::gemv_norm_supported(B, K)) {
+  if (B < rows_for_gemm() && pop::gemv_norm_supported(B, K) && (B == 1 || N <= 8192)) {
     pop::launch_gemv_norm(rows, gamma, eps, (const bf16_t*)W, out, B, N, K, ldo, gemv_epi, act, x.st);
     return POP_OK;
   }
@@ -1150,7 +1163,7 @@ pop_status pop_prefill(pop_model* m, pop_cache* c, const pop_prefill_args* a, fl
     mi(w.o_bnd_slot)[b] = slots[s0 + len - 1];
     std::copy(a->block_table + (size_t)b * maxp, a->block_table + (size_t)(b + 1) * maxp, mi(w.o_bt) + (size_t)b * maxp);
   }
-  n_ta = build_attention_work(a->cu_seqlens, B, mi(w.o_ta_seq), mi(w.o_ta_start), mi(w.o_ta_start2));
+  n_ta = build_attention_work(a->cu_seqlens, B, cfg.n_q_heads, mi(w.o_ta_seq), mi(w.o_ta_start), mi(w.o_ta_start2));
   record_kv_first(c, a, plan, mi(w.o_kv_first));
   // Pruned layers in two lists: those that store an entry for every row, and (window_kv_writes) the
   // sliding-window ones that store the tail rows only.  A run of consecutive pruned layers is a range of each.
@@ -1217,15 +1230,15 @@ pop_status pop_prefill(pop_model* m, pop_cache* c, const pop_prefill_args* a, fl
 
   {
     StepTimer tm(m, st, POP_STEP_EMBED);
-    pop::launch_embed((const bf16_t*)m->w.embed, d_tokens, a->n_ranges > 0 ? d_row_src : nullptr,
-                      (const bf16_t*)a->embeds, h, T, d, st);
+    pop::RopeTables tabs;
     bool any_local = false;
     for (int l = 1; l <= cfg.n_layers; ++l) any_local |= !layer_is_global(cfg, l);
-    pop::launch_rope_table(d_pos, cs_g, T, hd, (double)cfg.rope_theta, st);
-    if (any_local) pop::launch_rope_table(d_pos, cs_l, T, hd, (double)cfg.rope_theta_local, st);
+    tabs.add(d_pos, cs_g, T, hd, (double)cfg.rope_theta);
+    if (any_local) tabs.add(d_pos, cs_l, T, hd, (double)cfg.rope_theta_local);
     if (tr.n > 0)
-      pop::launch_rope_table(at<int32_t>(ws, w.o_tr_pos), at<float2>(ws, w.o_cs_tail), tr.n, hd,
-                             (double)cfg.rope_theta_local, st);
+      tabs.add(at<int32_t>(ws, w.o_tr_pos), at<float2>(ws, w.o_cs_tail), tr.n, hd, (double)cfg.rope_theta_local);
+    pop::launch_embed((const bf16_t*)m->w.embed, d_tokens, a->n_ranges > 0 ? d_row_src : nullptr,
+                      (const bf16_t*)a->embeds, h, T, d, st, tabs);
   }
   POP_HIP(hipGetLastError());
 
@@ -1456,13 +1469,11 @@ pop_status pop_prefill(pop_model* m, pop_cache* c, const pop_prefill_args* a, fl
       if (pop_status s = kv_only_run(l, r)) return s;
     if (boundary) {
       StepTimer tm(m, st, POP_STEP_BOUNDARY);
-      pop::launch_gather_rows(h, bnd_row, xb, B, d, st);
+      pop::launch_gather_rows(h, bnd_row, xb, B, d, st,
+                              dec_tables_done ? pop::RopeTables{} : decode_rope_tables(x, at<int32_t>(ws, w.o_bnd_pos), B));
+      dec_tables_done = true;
       x.ab_gamma = nullptr;
       rows_in_xb = true;
-      if (!dec_tables_done) {
-        decode_rope_tables(x, at<int32_t>(ws, w.o_bnd_pos), B);
-        dec_tables_done = true;
-      }
       for (int j = l; j <= r; ++j) {
         // what reads these rows next: the following layer of the run, the LM head, or (a kept layer follows) h
         const float* next = j < r ? (const float*)m->layers[j].norm_in
@@ -1543,8 +1554,7 @@ pop_status pop_decode_step_gated(pop_model* m, pop_cache* c, const int32_t* host
   x.kv_first = c->any_kv_first ? at<int32_t>(ws, w.o_kv_first) : nullptr;
   x.gates = host_gates;
   pop::launch_embed((const bf16_t*)m->w.embed, at<int32_t>(ws, w.o_tokens), nullptr, nullptr, at<float>(ws, w.o_xb),
-                    B, cfg.d_model, st);
-  decode_rope_tables(x, at<int32_t>(ws, w.o_bnd_pos), B);
+                    B, cfg.d_model, st, decode_rope_tables(x, at<int32_t>(ws, w.o_bnd_pos), B));
   for (int l = 1; l <= cfg.n_layers; ++l) {
     const float* next = (const float*)(l < cfg.n_layers ? m->layers[l].norm_in : m->w.final_norm);
     if (pop_status s = decode_layer(x, l, B, at<int32_t>(ws, w.o_bnd_pos), at<int32_t>(ws, w.o_bnd_slot), max_len, next))
@@ -1633,9 +1643,9 @@ pop_status pop_generate(pop_model* m, pop_cache* c, const pop_prefill_args* a, i
     LayerCtx x{m, c, ws, &w, st};
     x.kv_first = c->any_kv_first ? at<int32_t>(ws, w.o_kv_first) : nullptr;   // uploaded by the prefill
     for (int s = 1; s < n_new; ++s) {
-      pop::launch_embed((const bf16_t*)m->w.embed, d_tok, nullptr, nullptr, at<float>(ws, w.o_xb), B, cfg.d_model, st);
+      pop::launch_embed((const bf16_t*)m->w.embed, d_tok, nullptr, nullptr, at<float>(ws, w.o_xb), B, cfg.d_model, st,
+                        decode_rope_tables(x, d_gpos + (size_t)(s - 1) * B, B));
       x.ab_gamma = nullptr;
-      decode_rope_tables(x, d_gpos + (size_t)(s - 1) * B, B);
       for (int l = 1; l <= cfg.n_layers; ++l) {
         const float* next = (const float*)(l < cfg.n_layers ? m->layers[l].norm_in : m->w.final_norm);
         if (pop_status e = decode_layer(x, l, B, d_gpos + (size_t)(s - 1) * B, d_gslot + (size_t)(s - 1) * B, max_len + s,
@@ -1782,14 +1792,16 @@ pop_status pop_op_rope_attention(void* qkv, const int32_t* cu, int32_t B, int32_
     Tp += (int)round_up(len, 64);
     for (int p0 = 0; p0 < len; p0 += 64) { mi(w.o_t64_seq)[n64] = b; mi(w.o_t64_start)[n64++] = p0; }
   }
-  nta = build_attention_work(cu, B, mi(w.o_ta_seq), mi(w.o_ta_start), mi(w.o_ta_start2));
+  nta = build_attention_work(cu, B, Hq, mi(w.o_ta_seq), mi(w.o_ta_start), mi(w.o_ta_start2));
   hipStream_t st = reinterpret_cast<hipStream_t>(stream);
   POP_HIP(hipMemcpyAsync(workspace, meta.data(), w.meta_bytes, hipMemcpyHostToDevice, st));
   POP_HIP(hipStreamSynchronize(st));   // `meta` is pageable memory of this call: wait until it has been read
   const int Dq = Hq * hd, Dkv = Hkv * hd, ld = Dq + 2 * Dkv;
   float2* cs = at<float2>(workspace, w.o_cs);
   bf16_t* vT = at<bf16_t>(workspace, w.o_vT);
-  pop::launch_rope_table(at<int32_t>(workspace, w.o_pos), cs, T, hd, (double)rope_theta, st);
+  pop::RopeTables tabs;
+  tabs.add(at<int32_t>(workspace, w.o_pos), cs, T, hd, (double)rope_theta);
+  pop::launch_embed(nullptr, nullptr, nullptr, nullptr, nullptr, 0, 0, st, tabs);
   pop::RopeWriteArgs rw{};
   rw.qkv = (bf16_t*)qkv; rw.ld = ld; rw.q_col = 0; rw.k_col = Dq; rw.v_col = Dq + Dkv;
   rw.n_q_heads = Hq; rw.n_kv_heads = Hkv; rw.hd = hd; rw.cs = cs; rw.slot = nullptr;

@@ -7,13 +7,39 @@
 
 namespace pop {
 
-// ------------------------------------------------------------------------------------- embed
+// ------------------------------------------------------------------------------------- embed + RoPE tables
+__device__ __forceinline__ void rope_table_entries(const RopeTable& t, int i) {
+  if (i >= t.T * t.half) return;
+  const int r = i / t.half, f = i - r * t.half;
+  const double inv_freq = exp2((double)f * t.neg2_over_hd_log2theta);
+  const double ang = (double)t.pos[r] * inv_freq;
+  double s, c;
+  sincos(ang, &s, &c);
+  t.cs[i] = make_float2((float)c, (float)s);
+}
+
+// One launch for what a call starts with: blocks 0 .. T-1 take an embedding row each, the blocks after them 256 entries
+// of the RoPE tables (a launch of its own costs a decode step of one sequence 4.5 us of 410, whatever its size).
 __global__ __launch_bounds__(256) void embed_kernel(const bf16_t* __restrict__ table,
                                                     const int32_t* __restrict__ tokens,
                                                     const int32_t* __restrict__ row_src,
                                                     const bf16_t* __restrict__ embeds,
-                                                    float* __restrict__ h, int d) {
-  const int t = blockIdx.x;
+                                                    float* __restrict__ h, int T, int d, RopeTables tabs) {
+  int t = blockIdx.x;
+  if (t >= T) {
+    t -= T;
+#pragma unroll
+    for (int j = 0; j < 3; ++j) {
+      if (j >= tabs.n) break;
+      const int blocks = (tabs.t[j].T * tabs.t[j].half + 255) / 256;
+      if (t < blocks) {
+        rope_table_entries(tabs.t[j], t * 256 + threadIdx.x);
+        return;
+      }
+      t -= blocks;
+    }
+    return;
+  }
   const int src = row_src ? row_src[t] : -1;
   const bf16_t* row = src < 0 ? table + (size_t)tokens[t] * d : embeds + (size_t)src * d;
   float* dst = h + (size_t)t * d;
@@ -26,24 +52,48 @@ __global__ __launch_bounds__(256) void embed_kernel(const bf16_t* __restrict__ t
   }
 }
 
-void launch_embed(const bf16_t* table, const int32_t* tokens, const int32_t* row_src,
-                  const bf16_t* embeds, float* h, int T, int d, hipStream_t st) {
-  if (T <= 0) return;
-  hipLaunchKernelGGL(embed_kernel, dim3(T), dim3(256), 0, st, table, tokens, row_src, embeds, h, d);
+void RopeTables::add(const int32_t* pos, float2* cs, int T, int hd, double theta) {
+  if (T > 0 && n < 3) t[n++] = RopeTable{pos, cs, T, hd / 2, -2.0 / (double)hd * log2(theta)};
 }
 
+void launch_embed(const bf16_t* table, const int32_t* tokens, const int32_t* row_src,
+                  const bf16_t* embeds, float* h, int T, int d, hipStream_t st, const RopeTables& tabs) {
+  if (T <= 0 && tabs.n == 0) return;
+  int blocks = std::max(T, 0);
+  for (int j = 0; j < tabs.n; ++j) blocks += (tabs.t[j].T * tabs.t[j].half + 255) / 256;
+  hipLaunchKernelGGL(embed_kernel, dim3(blocks), dim3(256), 0, st, table, tokens, row_src, embeds, h, std::max(T, 0), d, tabs);
+}
+
+// (with the RoPE tables of the gathered rows, as embed_kernel)
 __global__ __launch_bounds__(256) void gather_rows_kernel(const float* __restrict__ src,
                                                           const int32_t* __restrict__ idx,
-                                                          float* __restrict__ dst, int d) {
+                                                          float* __restrict__ dst, int rows, int d, RopeTables tabs) {
+  if ((int)blockIdx.x >= rows) {
+    int t = blockIdx.x - rows;
+#pragma unroll
+    for (int j = 0; j < 3; ++j) {
+      if (j >= tabs.n) break;
+      const int blocks = (tabs.t[j].T * tabs.t[j].half + 255) / 256;
+      if (t < blocks) {
+        rope_table_entries(tabs.t[j], t * 256 + threadIdx.x);
+        return;
+      }
+      t -= blocks;
+    }
+    return;
+  }
   const float* s = src + (size_t)idx[blockIdx.x] * d;
   float* o = dst + (size_t)blockIdx.x * d;
   for (int i = threadIdx.x * 4; i < d; i += 256 * 4)
     *reinterpret_cast<float4*>(o + i) = *reinterpret_cast<const float4*>(s + i);
 }
 
-void launch_gather_rows(const float* src, const int32_t* idx, float* dst, int rows, int d, hipStream_t st) {
+void launch_gather_rows(const float* src, const int32_t* idx, float* dst, int rows, int d, hipStream_t st,
+                        const RopeTables& tabs) {
   if (rows <= 0) return;
-  hipLaunchKernelGGL(gather_rows_kernel, dim3(rows), dim3(256), 0, st, src, idx, dst, d);
+  int blocks = rows;
+  for (int j = 0; j < tabs.n; ++j) blocks += (tabs.t[j].T * tabs.t[j].half + 255) / 256;
+  hipLaunchKernelGGL(gather_rows_kernel, dim3(blocks), dim3(256), 0, st, src, idx, dst, rows, d, tabs);
 }
 
 __global__ __launch_bounds__(256) void scatter_rows_kernel(const float* __restrict__ src,
@@ -129,24 +179,36 @@ void launch_rmsnorm(float* x, const float* add1, const float* add2, const float*
                      row_idx, d, eps);
 }
 
-// Same thread layout, summation order and roundings as rmsnorm_kernel; the parts are added in the order of
-// splitk_reduce_kernel (parts first, then the old value).
-__global__ __launch_bounds__(256) void add_parts_rmsnorm_kernel(float* __restrict__ x, const float* __restrict__ parts,
-                                                                int S, size_t part_stride,
-                                                                const float* __restrict__ gamma,
-                                                                bf16_t* __restrict__ out, int d, float eps,
-                                                                float scale) {
-  __shared__ float red[4];
+// The parts are added in the order of splitk_reduce_kernel (parts first, then the old value).  NT threads per row:
+// 256, in the thread layout and summation order of rmsnorm_kernel, or 1024 for few rows, whose launch takes as long
+// as its longest chain of loads: then every thread has one or two quads, and all parts, the old value and the norm
+// scale are requested at once (8 rows of 4096 in 4 parts: 6.7 us with 256 threads and the scale read after the sum).
+template <int NT>
+__global__ __launch_bounds__(NT) void add_parts_rmsnorm_kernel(float* __restrict__ x, const float* __restrict__ parts,
+                                                               int S, size_t part_stride,
+                                                               const float* __restrict__ gamma,
+                                                               bf16_t* __restrict__ out, int d, float eps,
+                                                               float scale) {
+  constexpr int NV = kNormMaxV * 256 / NT;
+  constexpr bool EARLY = NT > 256;      // (with 256 threads the scales would cost 32 registers and occupancy)
+  __shared__ float red[NT / 64];
   const size_t row = blockIdx.x;
   float* xr = x + row * d;
-  float4 v[kNormMaxV];
+  float4 v[NV], gv[EARLY ? NV : 1];
   float ss = 0.f;
+  if (EARLY) {
 #pragma unroll
-  for (int j = 0; j < kNormMaxV; ++j) {
-    const int i = (j * 256 + threadIdx.x) * 4;
+    for (int j = 0; j < NV; ++j) {
+      const int i = (j * NT + threadIdx.x) * 4;
+      if (i < d) gv[j] = *reinterpret_cast<const float4*>(gamma + i);
+    }
+  }
+#pragma unroll
+  for (int j = 0; j < NV; ++j) {
+    const int i = (j * NT + threadIdx.x) * 4;
     if (i < d) {
       const float* p0 = parts + row * d + i;
-      // all parts are requested before the first addition (S <= 8; few blocks run, so latency is what counts)
+      // all parts are requested before the first addition (S <= 8)
       float4 q[8];
 #pragma unroll
       for (int s = 0; s < 8; ++s)
@@ -163,14 +225,19 @@ __global__ __launch_bounds__(256) void add_parts_rmsnorm_kernel(float* __restric
       ss += acc.x * acc.x + acc.y * acc.y + acc.z * acc.z + acc.w * acc.w;
     }
   }
-  const float total = block_sum_256(ss, red);
+  ss = wave_sum(ss);
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = ss;
+  __syncthreads();
+  float total = red[0];
+#pragma unroll
+  for (int w = 1; w < NT / 64; ++w) total += red[w];
   const float rstd = rsqrtf(total / (float)d + eps);
   bf16_t* orow = out + row * d;
 #pragma unroll
-  for (int j = 0; j < kNormMaxV; ++j) {
-    const int i = (j * 256 + threadIdx.x) * 4;
+  for (int j = 0; j < NV; ++j) {
+    const int i = (j * NT + threadIdx.x) * 4;
     if (i < d) {
-      const float4 gg = *reinterpret_cast<const float4*>(gamma + i);
+      const float4 gg = EARLY ? gv[EARLY ? j : 0] : *reinterpret_cast<const float4*>(gamma + i);
       uint2 p;
       p.x = pack_bf16x2(v[j].x * rstd * gg.x, v[j].y * rstd * gg.y);
       p.y = pack_bf16x2(v[j].z * rstd * gg.z, v[j].w * rstd * gg.w);
@@ -182,8 +249,12 @@ __global__ __launch_bounds__(256) void add_parts_rmsnorm_kernel(float* __restric
 void launch_add_parts_rmsnorm(float* x, const float* parts, int S, size_t part_stride, const float* gamma, bf16_t* out,
                               int rows, int d, float eps, hipStream_t st, float scale) {
   if (rows <= 0 || S < 1 || S > 8) return;
-  hipLaunchKernelGGL(add_parts_rmsnorm_kernel, dim3(rows), dim3(256), 0, st, x, parts, S, part_stride, gamma, out, d,
-                     eps, scale);
+  if (rows <= 512)     // (two 1024-thread rows per CU at a time)
+    hipLaunchKernelGGL(add_parts_rmsnorm_kernel<1024>, dim3(rows), dim3(1024), 0, st, x, parts, S, part_stride, gamma,
+                       out, d, eps, scale);
+  else
+    hipLaunchKernelGGL(add_parts_rmsnorm_kernel<256>, dim3(rows), dim3(256), 0, st, x, parts, S, part_stride, gamma,
+                       out, d, eps, scale);
 }
 
 void launch_rmsnorm_multi(const float* x, GammaList gammas, int n_out, bf16_t* out, size_t out_stride,
@@ -192,28 +263,6 @@ void launch_rmsnorm_multi(const float* x, GammaList gammas, int n_out, bf16_t* o
   hipLaunchKernelGGL(rmsnorm_kernel, dim3(rows), dim3(256), 0, st, const_cast<float*>(x),
                      (const float*)nullptr, (const float*)nullptr, gammas, n_out, out, out_stride,
                      row_idx, d, eps);
-}
-
-// ------------------------------------------------------------------------------------- RoPE table
-__global__ __launch_bounds__(256) void rope_table_kernel(const int32_t* __restrict__ pos,
-                                                         float2* __restrict__ cs, int T, int half,
-                                                         double neg2_over_hd_log2theta) {
-  const int i = blockIdx.x * 256 + threadIdx.x;
-  if (i >= T * half) return;
-  const int t = i / half, f = i - t * half;
-  const double inv_freq = exp2((double)f * neg2_over_hd_log2theta);
-  const double ang = (double)pos[t] * inv_freq;
-  double s, c;
-  sincos(ang, &s, &c);
-  cs[i] = make_float2((float)c, (float)s);
-}
-
-void launch_rope_table(const int32_t* pos, float2* cs, int T, int hd, double theta, hipStream_t st) {
-  if (T <= 0) return;
-  const int half = hd / 2;
-  const int n = T * half;
-  hipLaunchKernelGGL(rope_table_kernel, dim3((n + 255) / 256), dim3(256), 0, st, pos, cs, T, half,
-                     -2.0 / (double)hd * log2(theta));
 }
 
 // ------------------------------------------------------------------------------------- RoPE + cache append

@@ -24,9 +24,22 @@ struct KvQuant {
 // ---------------------------------------------------------------------------------------------
 // Elementwise / bandwidth-bound steps (pop_elementwise.hip)
 // ---------------------------------------------------------------------------------------------
-// h[t,:] = row_src[t] < 0 ? table[tokens[t],:] : embeds[row_src[t],:]      (fp32 residual stream)
+// cs[t, i] = (cos, sin)(pos[t] * theta^(-2 i / hd)), i < hd/2, angle formed in fp64.
+struct RopeTable {
+  const int32_t* pos;
+  float2* cs;
+  int T, half;
+  double neg2_over_hd_log2theta;
+};
+// Up to three tables that a launch computes beside its own work.
+struct RopeTables {
+  int n = 0;
+  RopeTable t[3];
+  void add(const int32_t* pos, float2* cs, int T, int hd, double theta);
+};
+// h[t,:] = row_src[t] < 0 ? table[tokens[t],:] : embeds[row_src[t],:]      (fp32 residual stream), and the tables.
 void launch_embed(const bf16_t* table, const int32_t* tokens, const int32_t* row_src,
-                  const bf16_t* embeds, float* h, int T, int d, hipStream_t st);
+                  const bf16_t* embeds, float* h, int T, int d, hipStream_t st, const RopeTables& tabs = RopeTables{});
 
 // out[t,:] = bf16( x[t,:] * rsqrt(mean(x[t,:]^2) + eps) * gamma )   -- LN(.) of Sec. 2.1
 // If row_idx != nullptr the source row of output row t is row_idx[t] (gather).
@@ -49,9 +62,6 @@ void launch_rmsnorm_multi(const float* x, GammaList gammas, int n_out, bf16_t* o
 void launch_add_parts_rmsnorm(float* x, const float* parts, int S, size_t part_stride, const float* gamma, bf16_t* out,
                               int rows, int d, float eps, hipStream_t st, float scale = 1.f);
 // (scale: the sum of the parts is multiplied by it before it is added to x)
-
-// cs[t, i] = (cos, sin)(pos[t] * theta^(-2 i / hd)), i < hd/2, angle formed in fp64.
-void launch_rope_table(const int32_t* pos, float2* cs, int T, int hd, double theta, hipStream_t st);
 
 // Prefill RoPE + cache append for one layer.  Work is organised in tiles of 64 consecutive
 // positions of one sequence: tile i covers positions tile_start[i] .. +63 of sequence tile_seq[i].
@@ -219,7 +229,7 @@ struct AttnDecodeArgs {
   const float* qkv_raw;     // fp32 [n_parts][B, ld], rows q | k | v; the parts (a split projection) are added
   int ld, n_parts;
   size_t part_stride;       // elements between parts
-  const float2* cs;         // [B, hd/2] (cos, sin) of each sequence's query position (launch_rope_table)
+  const float2* cs;         // [B, hd/2] (cos, sin) of each sequence's query position (RopeTables)
   const float* q_gamma;     // per-head QK-norm scales [hd], or nullptr
   const float* k_gamma;
   float qk_eps;
@@ -262,8 +272,9 @@ hipError_t launch_attention(const float* q, int ldq, int q_col, float* out, cons
 void launch_argmax(const float* logits, int vocab, int32_t* tok, int32_t* out, int out_stride, int step, int eos,
                    int B, hipStream_t st);
 
-// gather fp32 rows: dst[i,:] = src[idx[i],:]
-void launch_gather_rows(const float* src, const int32_t* idx, float* dst, int rows, int d, hipStream_t st);
+// gather fp32 rows: dst[i,:] = src[idx[i],:], and compute the tables
+void launch_gather_rows(const float* src, const int32_t* idx, float* dst, int rows, int d, hipStream_t st,
+                        const RopeTables& tabs = RopeTables{});
 // dst[idx[r], :] = src[r, :] (fp32 rows of width d; idx must not repeat)
 void launch_scatter_rows(const float* src, const int32_t* idx, float* dst, int rows, int d, hipStream_t st);
 
