@@ -58,6 +58,7 @@ struct GemmParams {
   int lda, ldw, ldc;     // elements
   int act;
   int tiles_m, tiles_n;  // per batch, of this launch
+  int n_first;           // first output column of this launch (a GEMM may be split into two launches)
   int stagger;           // 1: column tile tn starts its K loop at K-step tn * nk / tiles_n and wraps around
   long long strideA, strideC, strideW;
   const bf16_t* const* W_list;
@@ -124,7 +125,7 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_kernel(GemmParams p) {
   }
   const int m0 = tm * BM;
   constexpr int BN_OUT = EPI == EPI_GLU_BF16 ? BN / 2 : BN;
-  const int n0 = tn * BN_OUT;  // first output column of the tile
+  const int n0 = p.n_first + tn * BN_OUT;  // first output column of the tile
 
   const int z = blockIdx.z;
   const bf16_t* A = p.A + (long long)z * p.strideA;
@@ -594,7 +595,7 @@ inline bool stagger_k(const GemmArgs& g) {
 
 // MASKED: also built for K that is not a multiple of BK.
 template <int BM, int BN, int WGM, int WGN, int STAGES, int EPI, bool MASKED = false>
-hipError_t launch_cfg(const GemmArgs& g, hipStream_t st) {
+hipError_t launch_cfg(const GemmArgs& g, hipStream_t st, int n_first = 0, int n_cols = -1 /* output columns; -1: to the end */) {
   constexpr int BN_OUT = EPI == EPI_GLU_BF16 ? BN / 2 : BN;
   constexpr int smem = STAGES * (BM + BN) * BK * 2 + 1024;  // stages + prefetch scratch
   static_assert(smem <= 160 * 1024, "LDS budget of a gfx950 CU");
@@ -608,7 +609,8 @@ hipError_t launch_cfg(const GemmArgs& g, hipStream_t st) {
   p.kv_pool_stride = g.kv_pool_stride;
   p.kvq = g.kvq;
   p.tiles_m = (g.M + BM - 1) / BM;
-  p.tiles_n = (g.N + BN_OUT - 1) / BN_OUT;
+  p.n_first = n_first;
+  p.tiles_n = ((n_cols < 0 ? g.N - n_first : n_cols) + BN_OUT - 1) / BN_OUT;
   p.stagger = stagger_k(g) ? 1 : 0;
   p.strideA = g.strideA; p.strideC = g.strideC; p.strideW = g.W_list ? 0 : g.strideW;
   p.W_list = g.batch > 1 || g.W_list ? g.W_list : nullptr;
@@ -643,16 +645,17 @@ hipError_t launch_cfg(const GemmArgs& g, hipStream_t st) {
 //     a round = K-steps * max(latency of a K-step, work-groups per CU * compute time of a K-step)
 //               + work-groups per CU * prologue and epilogue,     256 CUs * work-groups per CU in a round.
 // The three numbers of a shape and the four common ones are a least-squares fit to 19000 timings (MI355X; 10
-// projection shapes of K 3840 to 15360, 8 to 4096 rows, 1 to 8 K parts, weights from HBM): 4 % rms; over those
+// projection shapes of K 3840 to 15360, 8 to 4096 rows, 1 to 8 K parts, weights from HBM; four compute times are
+// lowered by 4 to 5 % to centre the timings near the best from 500 rows on): 4 % rms; over those
 // problems the choice is on average 1.6 % slower than the best measured pair.  What the shapes between the powers
 // of two are for is the rows in between: 528 rows are 3 tiles of 256 (69 % of their work useful) or of 192 (92 %).
 struct TileCfg { int id, bm, bn, occ; double floor_us, step_us, end_us; };
 constexpr TileCfg kTileCfgs[] = {
     // id, rows, columns, work-groups per CU, latency of a K-step, its compute time, prologue + epilogue (us)
-    {1, 256, 256, 1, 0.310, 1.432, 5.35}, {2, 256, 192, 1, 0.245, 1.188, 5.86}, {3, 192, 256, 1, 0.392, 1.162, 5.58},
-    {4, 160, 256, 1, 0.028, 1.059, 5.25}, {5, 192, 192, 1, 0.338, 0.831, 4.31}, {6, 256, 128, 1, 0.362, 0.812, 3.33},
+    {1, 256, 256, 1, 0.310, 1.432, 5.35}, {2, 256, 192, 1, 0.245, 1.140, 5.86}, {3, 192, 256, 1, 0.392, 1.116, 5.58},
+    {4, 160, 256, 1, 0.028, 1.006, 5.25}, {5, 192, 192, 1, 0.338, 0.831, 4.31}, {6, 256, 128, 1, 0.362, 0.812, 3.33},
     {7, 128, 256, 1, 0.190, 0.817, 4.24}, {8, 192, 128, 1, 0.475, 0.662, 3.18}, {9, 128, 192, 1, 0.336, 0.655, 4.18},
-    {10, 96, 256, 1, 0.156, 0.692, 4.38}, {11, 160, 128, 1, 0.111, 0.607, 2.96}, {12, 128, 128, 1, 0.075, 0.514, 3.35},
+    {10, 96, 256, 1, 0.156, 0.692, 4.38}, {11, 160, 128, 1, 0.111, 0.607, 2.96}, {12, 128, 128, 1, 0.075, 0.493, 3.35},
     {13, 96, 128, 1, 0.120, 0.464, 2.58}, {14, 64, 128, 2, 0.425, 0.383, 1.69}, {15, 96, 64, 1, 0.291, 0.186, 2.22},
     {16, 64, 64, 1, 0.246, 0.158, 2.12},
 };
@@ -683,16 +686,56 @@ inline double tile_cost_us(const TileCfg& c, long long M, long long cols, long l
   return kLaunchUs + std::sqrt(std::sqrt(sq(sq(work)) + sq(sq(weights))));
 }
 
-struct TileChoice { int id; double us; };
-// The fastest shape for `batch` problems of M rows, `cols` W rows, K.
-inline TileChoice choose_tile(long long M, long long cols, long long K, long long batch) {
-  TileChoice best{1, 1e300};
+// The fastest way for `batch` problems of M rows, `cols` W rows, K: one launch of a shape (tail_id 0), or its full
+// rounds of work-groups alone (the first head_cols W rows) and a second launch of another shape for the columns of the
+// partly filled last round: at M = 2048 the gate|up projection has 896 tiles of 256 x 256 = 3.5 rounds; 3 rounds and
+// one round of 128 x 256 tiles take 317 + 66 us where four rounds take 413.
+struct TileChoice { int id; double us; int tail_id; long long head_cols; };
+inline TileChoice choose_single(long long M, long long cols, long long K, long long batch) {
+  TileChoice best{1, 1e300, 0, 0};
   for (const TileCfg& c : kTileCfgs) {      // ordered by area: ties go to the larger tile
     if (K % BK && !masked_cfg(c.id)) continue;
     const double t = tile_cost_us(c, M, cols, K, batch);
-    if (t < best.us) best = {c.id, t};
+    if (t < best.us) best = {c.id, t, 0, 0};
   }
   return best;
+}
+inline TileChoice choose_tile(long long M, long long cols, long long K, long long batch) {
+  TileChoice best = choose_single(M, cols, K, batch);
+  if (batch != 1 || K % BK || M <= 128) return best;
+  const double single = best.us;
+  for (const TileCfg& c : kTileCfgs) {
+    const long long tiles_m = (M + c.bm - 1) / c.bm, slots = 256LL * c.occ;
+    const long long rounds = tiles_of(c, M, cols) / slots, head = rounds * slots / tiles_m;   // whole column tiles
+    if (rounds < 1 || head < 1 || head * c.bn >= cols) continue;
+    const TileChoice tail = choose_single(M, cols - head * c.bn, K, 1);
+    const double t = kLaunchUs + rounds_us(c, tiles_m * head, (double)(K / BK)) + tail.us;
+    // (the second launch waits for the last work-group of the first: worth it from 4 % on)
+    if (t < best.us && t < 0.96 * single) best = {c.id, t, tail.id, head * c.bn};
+  }
+  return best;
+}
+
+template <int EPI>
+hipError_t launch_shape(int id, const GemmArgs& g, hipStream_t st, int n0, int nc) {
+  switch (id) {
+    case 2: return launch_cfg<256, 192, 2, 2, 2, EPI>(g, st, n0, nc);
+    case 3: return launch_cfg<192, 256, 2, 2, 2, EPI>(g, st, n0, nc);
+    case 4: return launch_cfg<160, 256, 2, 2, 2, EPI>(g, st, n0, nc);
+    case 5: return launch_cfg<192, 192, 2, 2, 3, EPI>(g, st, n0, nc);
+    case 6: return launch_cfg<256, 128, 2, 2, 3, EPI, true>(g, st, n0, nc);
+    case 7: return launch_cfg<128, 256, 2, 2, 3, EPI>(g, st, n0, nc);
+    case 8: return launch_cfg<192, 128, 2, 2, 3, EPI>(g, st, n0, nc);
+    case 9: return launch_cfg<128, 192, 2, 2, 3, EPI>(g, st, n0, nc);
+    case 10: return launch_cfg<96, 256, 2, 2, 3, EPI>(g, st, n0, nc);
+    case 11: return launch_cfg<160, 128, 2, 2, 3, EPI>(g, st, n0, nc);
+    case 12: return launch_cfg<128, 128, 2, 2, 4, EPI, true>(g, st, n0, nc);
+    case 13: return launch_cfg<96, 128, 2, 2, 4, EPI>(g, st, n0, nc);
+    case 14: return launch_cfg<64, 128, 2, 2, 3, EPI, true>(g, st, n0, nc);
+    case 15: return launch_cfg<96, 64, 2, 2, 4, EPI>(g, st, n0, nc);
+    case 16: return launch_cfg<64, 64, 2, 2, 6, EPI, true>(g, st, n0, nc);
+    default: return launch_cfg<256, 256, 2, 2, 2, EPI, true>(g, st, n0, nc);
+  }
 }
 
 template <int EPI>
@@ -702,28 +745,14 @@ hipError_t launch_epi(const GemmArgs& g, hipStream_t st) {
   // Building with -DPOP_FORCE_GEMM_TILE=1..16 forces one shape (tile-shape experiments, never the product
   // build): the choice is a compile-time constant and nothing in the environment can change it.
 #ifdef POP_FORCE_GEMM_TILE
-  const int pick = g.K % BK && !masked_cfg(POP_FORCE_GEMM_TILE) ? 16 : POP_FORCE_GEMM_TILE;
+  const TileChoice pick{g.K % BK && !masked_cfg(POP_FORCE_GEMM_TILE) ? 16 : POP_FORCE_GEMM_TILE, 0.0, 0, 0};
 #else
-  const int pick = choose_tile(g.M, cols, g.K, batch).id;
+  const TileChoice pick = choose_tile(g.M, cols, g.K, batch);
 #endif
-  switch (pick) {
-    case 2: return launch_cfg<256, 192, 2, 2, 2, EPI>(g, st);
-    case 3: return launch_cfg<192, 256, 2, 2, 2, EPI>(g, st);
-    case 4: return launch_cfg<160, 256, 2, 2, 2, EPI>(g, st);
-    case 5: return launch_cfg<192, 192, 2, 2, 3, EPI>(g, st);
-    case 6: return launch_cfg<256, 128, 2, 2, 3, EPI, true>(g, st);
-    case 7: return launch_cfg<128, 256, 2, 2, 3, EPI>(g, st);
-    case 8: return launch_cfg<192, 128, 2, 2, 3, EPI>(g, st);
-    case 9: return launch_cfg<128, 192, 2, 2, 3, EPI>(g, st);
-    case 10: return launch_cfg<96, 256, 2, 2, 3, EPI>(g, st);
-    case 11: return launch_cfg<160, 128, 2, 2, 3, EPI>(g, st);
-    case 12: return launch_cfg<128, 128, 2, 2, 4, EPI, true>(g, st);
-    case 13: return launch_cfg<96, 128, 2, 2, 4, EPI>(g, st);
-    case 14: return launch_cfg<64, 128, 2, 2, 3, EPI, true>(g, st);
-    case 15: return launch_cfg<96, 64, 2, 2, 4, EPI>(g, st);
-    case 16: return launch_cfg<64, 64, 2, 2, 6, EPI, true>(g, st);
-    default: return launch_cfg<256, 256, 2, 2, 2, EPI, true>(g, st);
-  }
+  if (pick.tail_id == 0) return launch_shape<EPI>(pick.id, g, st, 0, -1);
+  const int head = (int)(EPI == EPI_GLU_BF16 ? pick.head_cols / 2 : pick.head_cols);   // output columns
+  if (hipError_t e = launch_shape<EPI>(pick.id, g, st, 0, head); e != hipSuccess) return e;
+  return launch_shape<EPI>(pick.tail_id, g, st, head, -1);
 }
 
 }  // namespace gemm_impl

@@ -27,7 +27,7 @@ def rel(got, ref):
 
 SIZES = [
     (1281, 8196, 64),     # 256 x 256, a single K-step
-    (3000, 12292, 192),   # 256 x 256
+    (3000, 12292, 192),   # 256 x 256, the last round as 160 x 128 in a second launch
     (2047, 6140, 448),    # 256 x 192
     (1281, 8196, 128),    # 192 x 256
     (257, 28668, 64),     # 160 x 256, a single K-step
@@ -48,7 +48,7 @@ SIZES = [
     (193, 3080, 64),      # 64 x 128, a single K-step
     (65, 8196, 448),      # 96 x 64
     (385, 1000, 448),     # 64 x 64
-    (2047, 28668, 2048),  # 256 x 256, four rounds of work-groups
+    (2047, 28668, 2048),  # 256 x 256, three rounds, the rest as 256 x 128 in a second launch
     (8, 14336, 4096),     # few rows: the column tiles start at different K offsets
     (250, 9000, 4096),    # the same, several row tiles
     (129, 1000, 2112),    # rows that are not a multiple of 4 KB apart: all start at offset 0
