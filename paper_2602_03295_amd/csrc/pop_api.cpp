@@ -185,7 +185,7 @@ struct pop_cache {
 namespace {
 
 constexpr int kKvChunk = 8;  // pruned layers projected per batched GEMM
-constexpr int kFusedAppendRows = 4;   // decode-style rows up to which the attention kernel does RoPE + append itself
+constexpr int kFusedAppendRows = 2;   // decode-style rows up to which the attention kernel does RoPE + append itself
 
 // Parts of the K range of the down projection (K = d_ffn) that the workspace of T > 512 prompt rows has room for:
 // as many as its 256 x 256 tiles leave work-groups idle.  How many are used is the GEMM's choice; they are added in
@@ -615,19 +615,19 @@ pop_status decode_layer(const LayerCtx& x, int l /*1-based*/, int B, const int32
   const bool glob = layer_is_global(c, l);
   // Up to kFusedAppendRows rows: RoPE and the append of the new entries happen inside the attention kernel (one
   // launch less; decode_rope_tables has run for these positions, the slot is implied by the block table).  With more
-  // rows every one of the n_splits x Hkv x B work-groups would repeat the preparation of its query heads, and a
-  // separate kernel that does it once per row and head is faster (measured at 8 sequences of 2048 tokens: attention
-  // 33.7 us + 4.9 us for the projection's own reduction of its K parts, against 24.5 us + 4.8 us for that kernel,
-  // which also adds the parts).
+  // rows the n_splits x Hkv x B work-groups would all repeat the preparation of their query heads, from the parts of a
+  // split projection, and a separate kernel that does it once per row and head, and adds the parts, is faster (a step,
+  // fused and separate: 4 sequences of 850 tokens 503 and 486 us, with heads of 256 910 and 775 us; 8 of 2048 tokens 597
+  // and 547 us; one of 139 tokens 403 and 409 us).
   const bool fused_append = B <= kFusedAppendRows;
   int qkv_parts = 1;
   if (pop_status s = normed_few_rows_projection(x, xb, (const float*)lw.norm_in, ab, lw.wqkv, qkvb, B, Dqkv, d, Dqkv,
-                                                pop::GEMV_STORE_F32, 0, &qkv_parts))
+                                                pop::GEMV_STORE_F32, 0, fused_append ? nullptr : &qkv_parts))
     return s;
   pop::AttnDecodeArgs ad{};
   if (fused_append) {
-    ad.qkv_raw = qkv_parts > 1 ? at<float>(x.ws, x.w->o_splitk) : qkvb;
-    ad.ld = Dqkv; ad.n_parts = qkv_parts; ad.part_stride = (size_t)B * Dqkv;
+    ad.qkv_raw = qkvb;
+    ad.ld = Dqkv;
     ad.cs = at<float2>(x.ws, glob ? x.w->o_dcs_g : x.w->o_dcs_l);
     ad.q_gamma = (const float*)lw.q_norm; ad.k_gamma = (const float*)lw.k_norm; ad.qk_eps = c.rms_eps;
   } else {

@@ -483,8 +483,8 @@ __global__ __launch_bounds__(256) void attn_decode_split_kernel(AttnDecodeArgs a
   uint4 v_new = make_uint4(0, 0, 0, 0);
   const bool has_new = FUSED && qpos - k_first < a.split_keys;     // (uniform) its key falls into this split
   if constexpr (FUSED) {
-    // the 8 * KS values of this lane of the head at column `col`: parts added, optionally RMS-normalised over the
-    // head (its four lanes g4 hold it all), rotated
+    // the 8 * KS values of this lane of the head at column `col`: optionally RMS-normalised over the head (its four
+    // lanes g4 hold it all), rotated
     float cc[KS / 2][8], sn[KS / 2][8];
     const float2* csp = a.cs + (size_t)b * HALF + g4 * 8;
 #pragma unroll
@@ -501,15 +501,6 @@ __global__ __launch_bounds__(256) void attn_decode_split_kernel(AttnDecodeArgs a
         const float4 u = *reinterpret_cast<const float4*>(row + ks * 32), w = *reinterpret_cast<const float4*>(row + ks * 32 + 4);
         x[ks][0] = u.x; x[ks][1] = u.y; x[ks][2] = u.z; x[ks][3] = u.w;
         x[ks][4] = w.x; x[ks][5] = w.y; x[ks][6] = w.z; x[ks][7] = w.w;
-      }
-      for (int p = 1; p < a.n_parts; ++p) {
-        const float* rp = row + (size_t)p * a.part_stride;
-#pragma unroll
-        for (int ks = 0; ks < KS; ++ks) {
-          const float4 u = *reinterpret_cast<const float4*>(rp + ks * 32), w = *reinterpret_cast<const float4*>(rp + ks * 32 + 4);
-          x[ks][0] += u.x; x[ks][1] += u.y; x[ks][2] += u.z; x[ks][3] += u.w;
-          x[ks][4] += w.x; x[ks][5] += w.y; x[ks][6] += w.z; x[ks][7] += w.w;
-        }
       }
       if (gamma) {
         float s2 = 0.f;
@@ -557,9 +548,6 @@ __global__ __launch_bounds__(256) void attn_decode_split_kernel(AttnDecodeArgs a
       const float* row = a.qkv_raw + (size_t)b * a.ld + (a.n_q_heads + a.n_kv_heads + kvh) * HD + li * 8;
 #pragma unroll
       for (int e = 0; e < 8; ++e) v8[e] = row[e];
-      for (int p = 1; p < a.n_parts; ++p)
-#pragma unroll
-        for (int e = 0; e < 8; ++e) v8[e] += row[(size_t)p * a.part_stride + e];
       v_new = pack8(v8, a.kvq.v_inv);
     }
   } else {
@@ -804,11 +792,12 @@ void launch_decode_cfg(const AttnDecodeArgs& a, hipStream_t st) {
 
 template <int HD>
 void launch_decode_hd(const AttnDecodeArgs& a, hipStream_t st) {
-  // Two groups of 16 keys per block where a wave has several blocks (half the cross-lane steps per key); head size
-  // 256 has no registers for the second.
+  // Two groups of 16 keys per block where a wave has several blocks of an 8-bit cache (half the cross-lane steps per key:
+  // 8 sequences of 8192 tokens 604 us a step against 629); bf16 entries, twice the registers, do better with one and
+  // more waves (691 against 706 us), and with three or four neither does.
   auto go = [&](auto fused_c, auto fp8_c) {
     constexpr bool F = decltype(fused_c)::value, Q = decltype(fp8_c)::value;
-    if constexpr (HD <= 128) {
+    if constexpr (Q && HD <= 128) {
       if (a.split_keys >= 256) { launch_decode_cfg<HD, F, Q, 2>(a, st); return; }
     }
     launch_decode_cfg<HD, F, Q, 1>(a, st);

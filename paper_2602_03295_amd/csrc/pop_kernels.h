@@ -226,9 +226,8 @@ struct AttnDecodeArgs {
   // the query position also forms that position's cache entry (per-head key norm, rotation, rounding to the cache's
   // type), stores it and uses it from registers.  One launch less; pays with few sequences (each of the
   // n_splits x Hkv x B work-groups repeats the preparation of its query heads).
-  const float* qkv_raw;     // fp32 [n_parts][B, ld], rows q | k | v; the parts (a split projection) are added
-  int ld, n_parts;
-  size_t part_stride;       // elements between parts
+  const float* qkv_raw;     // fp32 [B, ld], rows q | k | v
+  int ld;
   const float2* cs;         // [B, hd/2] (cos, sin) of each sequence's query position (RopeTables)
   const float* q_gamma;     // per-head QK-norm scales [hd], or nullptr
   const float* k_gamma;
