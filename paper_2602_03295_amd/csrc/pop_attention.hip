@@ -8,8 +8,8 @@
 // Inside this kernel Q, K, V and P are fp16 (the RoPE/append kernel hands over fp16 copies; the cache
 // itself stays bf16): with random-like V the softmax average shrinks signal and rounding noise alike, so
 // the relative error of the output equals that of the individual probabilities, and bf16's 8-bit
-// mantissa in q, k and P was the largest error source of a whole layer.  P <= 1 and saturating
-// conversions keep fp16's range safe.
+// mantissa in q, k and P was the largest error source of a whole layer.  P <= 2^kMaxLag and
+// saturating conversions keep fp16's range safe.
 //
 // MFMA arrangement (v_mfma_f32_32x32x16_f16, D = A * B with A rows / B columns spread over lanes):
 //   S^T = K * Q^T   : A = K tile rows (keys), B = Q rows.  A lane then owns ONE query row (lane & 31)
@@ -19,7 +19,7 @@
 //                     accumulator registers 8G..8G+7 of a block are exactly the B operand of the
 //                     G-th 16-key step, because the keys are fed to the first MFMA in the permuted
 //                     order key(i) below; no cross-lane data movement is needed for P.
-// Softmax is computed in fp32 with exp2 and running max / sum (online softmax); P is rounded to fp16
+// Softmax is computed in fp32 with exp2 and running (lagging) max / sum (online softmax); P is rounded to fp16
 // for the second MFMA, O accumulates in fp32.
 #include <type_traits>
 
@@ -33,6 +33,10 @@ namespace attn_impl {
 typedef __attribute__((address_space(3))) void* lds_ptr_t;
 constexpr int BQ = 128;   // query rows per work-group
 constexpr int BKV = 64;   // keys per LDS stage
+// The running maximum is raised only when a row outgrows it by this much (in powers of two): P <= 2^8 stays far inside
+// fp16, whose relative rounding does not depend on the magnitude, and O is rescaled a few times per row instead of in
+// every tile that moves one of a wave's 32 maxima (prompts of 6144 / 32768 tokens: 7057 -> 6969, 61739 -> 60776 us).
+constexpr float kMaxLag = 8.f;
 
 // MFMA row i (0..31) of the S^T block is fed key row key_of_row(i) of the 32-key block, chosen so
 // that accumulator registers 8G..8G+7 of lane-half h hold keys 16G + 8h + (0..7).
@@ -256,10 +260,10 @@ __global__ __launch_bounds__(256) void attn_prefill_kernel(AttnPrefillArgs a, fl
 #pragma unroll
     for (int n = 0; n < DIST && n < CNT; ++n) frag_read(n);
 
-    const float mx = fmaxf(mx_part, mx_other);
-    const float m_new = fmaxf(m_run, mx * scale_log2);
+    const float mx = fmaxf(mx_part, mx_other) * scale_log2;
+    const bool raise = mx > m_run + kMaxLag;                     // (m_run = -inf: any finite maximum)
+    const float m_new = raise ? mx : m_run;
     const float m_use = m_new == -INFINITY ? 0.f : m_new;
-    const float alpha = __builtin_amdgcn_exp2f(m_run - m_use);  // m_run = -inf -> 0
     float psum = 0.f;
     // the exponentials are skewed over the slots (argument two slots ahead, exp one slot ahead, sum
     // and packing in the slot itself) so that consecutive vector instructions do not wait on each other
@@ -292,7 +296,7 @@ __global__ __launch_bounds__(256) void attn_prefill_kernel(AttnPrefillArgs a, fl
         const int kb = slot >> 4, v = slot & 15;
         psum += ea[slot];
         if (v & 1) {
-          // 0 <= P <= 1: plain round-to-nearest packing, no saturation needed
+          // 0 <= P <= 2^kMaxLag: plain round-to-nearest packing, no saturation needed
           const float2_t pp = {ea[slot - 1], ea[slot]};
           pw[kb][v >> 3][(v & 7) >> 1] = __builtin_bit_cast(uint32_t, __builtin_convertvector(pp, half2_t));
           // keep the softmax arithmetic inside its slot (otherwise it is sunk below the loop's
@@ -322,14 +326,16 @@ __global__ __launch_bounds__(256) void attn_prefill_kernel(AttnPrefillArgs a, fl
       for (int n = lo; n < hi; ++n) do_mfma(n);
       __builtin_amdgcn_sched_barrier(0);
     }
-    l_run = l_run * alpha + psum;
-    m_run = m_new;
-    if (__builtin_amdgcn_ballot_w64(alpha != 1.f)) {  // the running max moved for some row of this wave
+    if (__builtin_amdgcn_ballot_w64(raise)) {  // the running max moves for some row of this wave
+      const float alpha = raise ? __builtin_amdgcn_exp2f(m_run - m_use) : 1.f;   // m_run = -inf -> 0
+      l_run *= alpha;
 #pragma unroll
       for (int i = 0; i < OB; ++i)
 #pragma unroll
         for (int v = 0; v < 16; ++v) o[i][v] *= alpha;
     }
+    l_run += psum;
+    m_run = m_new;
     if (!UNROLL2) {   // single-parity form: move the results to where the next iteration expects them
 #pragma unroll
       for (int kb = 0; kb < 2; ++kb) {

@@ -1,0 +1,44 @@
+"""Prefill attention when the row maxima keep growing along the keys: the running maximum is raised late and many times."""
+import math
+
+import numpy as np
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("hd,hq,hkv", [(64, 4, 2), (128, 4, 1), (256, 2, 1)])
+@pytest.mark.parametrize("growth", [0.0, 0.03, 0.4, -0.4])
+def test_growing_scores(hd, hq, hkv, growth):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2602_03295_amd import pop
+    T = 700
+    g = torch.Generator(device="cuda").manual_seed(hd + int(100 * growth) + 100)
+    qkv = torch.randn(T, (hq + 2 * hkv) * hd, device="cuda", generator=g)
+    # a large RoPE base leaves the last pair of a head unrotated: its product adds growth * position to every score
+    # (in natural units; the maximum is raised by factors of 2^8, i.e. every 5.5 units)
+    pos = torch.arange(T, device="cuda").float()
+    q, k, v = qkv.view(T, hq + 2 * hkv, hd).split([hq, hkv, hkv], dim=1)
+    q[..., hd // 2 - 1], q[..., hd - 1] = 8.0, 0.0
+    k[..., hd // 2 - 1], k[..., hd - 1] = (growth * math.sqrt(hd) / 8.0 * pos)[:, None], 0.0
+    qkv = qkv.to(torch.bfloat16)
+    q, k, v = qkv.double().view(T, hq + 2 * hkv, hd).split([hq, hkv, hkv], dim=1)
+    theta = 1e30
+    ang = pos.double()[:, None] * theta ** (-2.0 * torch.arange(hd // 2, device="cuda", dtype=torch.float64) / hd)
+    c, s = torch.cos(ang)[:, None], torch.sin(ang)[:, None]
+    rot = lambda x: torch.cat([x[..., :hd // 2] * c - x[..., hd // 2:] * s, x[..., hd // 2:] * c + x[..., :hd // 2] * s], -1)
+    qr, kr = rot(q), rot(k)
+    hidden = torch.ones(T, T, device="cuda", dtype=torch.bool).triu(1)
+    ref = torch.empty(T, hq, hd, device="cuda", dtype=torch.float64)
+    scores = []
+    for h in range(hq):
+        sc = (qr[:, h] @ kr[:, h // (hq // hkv)].t().contiguous()) / math.sqrt(hd)
+        sc = sc.masked_fill(hidden, -math.inf)
+        scores.append(float(sc[~hidden].abs().max()))
+        ref[:, h] = torch.softmax(sc, -1) @ v[:, h // (hq // hkv)].contiguous()
+    got = pop.pop_op_rope_attention(qkv, np.array([0, T], dtype=np.int32), hq, hkv, hd, theta).double().view(T, hq, hd)
+    # q and k are fp16 in the contraction: a score of size s carries s 2^-11 of error, a probability as much relatively
+    tol = 2.0 ** -7 + 2.0 ** -10 * max(scores)
+    assert float((got - ref).abs().max() / ref.abs().max()) <= tol
