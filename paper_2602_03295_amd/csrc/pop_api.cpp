@@ -1276,10 +1276,16 @@ pop_status pop_prefill(pop_model* m, pop_cache* c, const pop_prefill_args* a, fl
     g.M = T; g.N = Dqkv; g.K = d; g.epilogue = pop::EPI_STORE_F16;
     g.splitk_ws = w.kept_split_bytes ? at<float>(ws, w.o_kept_split) : nullptr;
     g.splitk_ws_bytes = w.kept_split_bytes;
+    // (if its K range is split, the RoPE + append kernel adds the parts)
+    int parts = 1;
+    g.partials_only = g.parts_free = true;
+    g.split_used = &parts;
     {
       StepTimer tm(m, st, POP_STEP_QKV_GEMM);
       if (pop_status s = gemm_or_fail(g, st, "QKV")) return s;
     }
+    g.parts_free = false;
+    rw.parts = parts > 1 ? g.splitk_ws : nullptr; rw.n_parts = parts; rw.part_stride = (size_t)T * Dqkv;
     rw.qkv = qkv; rw.ld = Dqkv; rw.q_col = 0; rw.k_col = Dq; rw.v_col = Dq + Dkv;
     rw.cs = glob ? cs_g : cs_l;
     rw.q_gamma = (const float*)lw.q_norm; rw.k_gamma = (const float*)lw.k_norm; rw.qk_eps = cfg.rms_eps;
@@ -1336,7 +1342,7 @@ pop_status pop_prefill(pop_model* m, pop_cache* c, const pop_prefill_args* a, fl
     // If the K range is split and another kept layer follows directly, the kernel that adds the parts to h also
     // writes that layer's normalised input (one pass over h instead of two).
     const float* next_gamma = l < cfg.n_layers && !plan.pruned[l + 1] ? (const float*)m->layers[l].norm_in : nullptr;
-    int parts = 1;
+    parts = 1;
     g.partials_only = next_gamma != nullptr && d % 4 == 0;
     g.split_used = &parts;
     {
@@ -1379,6 +1385,7 @@ pop_status pop_prefill(pop_model* m, pop_cache* c, const pop_prefill_args* a, fl
                                   tail ? at<int32_t>(ws, w.o_tr_row) : nullptr);
       }
       pop::GemmArgs g{};
+      int parts = 1;
       g.A = a_multi; g.lda = d; g.W = nullptr; g.ldw = d; g.out = kv_out; g.ldc = 2 * Dkv;
       g.M = rows; g.N = 2 * Dkv; g.K = d; g.epilogue = pop::EPI_STORE_BF16;
       g.batch = n; g.strideA = (long long)rows * d; g.strideC = (long long)rows * 2 * Dkv;
@@ -1388,6 +1395,8 @@ pop_status pop_prefill(pop_model* m, pop_cache* c, const pop_prefill_args* a, fl
         g.W = (const bf16_t*)m->layers[layers[c0] - 1].wqkv + (size_t)Dq * d;
         g.splitk_ws = w.splitk_bytes ? at<float>(ws, w.o_splitk) : nullptr;
         g.splitk_ws_bytes = w.splitk_bytes;
+        g.partials_only = g.parts_free = true;
+        g.split_used = &parts;
       }
       // Straight into the paged cache (RoPE and the page scatter in the GEMM's epilogue) when the layers of the
       // chunk have no per-head key norm (that needs a head's sum of squares first) and the 256 x 256 tiles of that
@@ -1413,6 +1422,7 @@ pop_status pop_prefill(pop_model* m, pop_cache* c, const pop_prefill_args* a, fl
       StepTimer tmw(m, st, POP_STEP_KV_ONLY_WRITE);
       for (int j = 0; j < n; ++j) {
         const int l = layers[c0 + j];
+        rk.parts = parts > 1 ? g.splitk_ws : nullptr; rk.n_parts = parts; rk.part_stride = (size_t)rows * 2 * Dkv;
         rk.qkv = kv_out + (size_t)j * rows * 2 * Dkv; rk.ld = 2 * Dkv; rk.q_col = -1; rk.k_col = 0; rk.v_col = Dkv;
         rk.cs = tail ? at<float2>(ws, w.o_cs_tail) : (layer_is_global(cfg, l) ? cs_g : cs_l);
         rk.q_gamma = nullptr; rk.k_gamma = (const float*)m->layers[l - 1].k_norm; rk.qk_eps = cfg.rms_eps;

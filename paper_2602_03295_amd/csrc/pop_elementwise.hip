@@ -271,6 +271,9 @@ void launch_rmsnorm_multi(const float* x, GammaList gammas, int n_out, bf16_t* o
 //   With q_gamma / k_gamma the head is first RMS-normalised over its hd values (per-head QK-norm); the
 //   threads that share a head row are neighbouring lanes and add their sums of squares by shuffles.
 //   v head: store to the V pool (+ transposed fp16 copy vT[h][i][col], zero beyond the sequence end).
+//   PARTS: q, k and v as the fp32 partial products of a projection whose K range was split (RopeWriteArgs::parts): the
+//     second kernel of the split, merged with this one (a launch of its own took 5 us at any size).
+template <bool PARTS>
 __global__ __launch_bounds__(256) void rope_write_kernel(RopeWriteArgs a, int heads_per_block) {
   __shared__ uint16_t tr[256 * 66];  // [hd][64 + 2] transposed V tile
   const int tile = blockIdx.x;
@@ -283,6 +286,29 @@ __global__ __launch_bounds__(256) void rope_write_kernel(RopeWriteArgs a, int he
   const int P = a.page_size;
   const int n_rot = nq + a.n_kv_heads;                               // heads that are rotated
   const int n_rot_blocks = (n_rot + heads_per_block - 1) / heads_per_block;
+  // 8 consecutive values of packed row t from column c on
+  auto load8 = [&](size_t t, int c, float (&x)[8]) {
+    if constexpr (PARTS) {
+      const float* p = a.parts + t * a.ld + c;
+      float4 u = *reinterpret_cast<const float4*>(p), v = *reinterpret_cast<const float4*>(p + 4);
+#pragma unroll 4
+      for (int s = 1; s < a.n_parts; ++s) {
+        const float4 u2 = *reinterpret_cast<const float4*>(p + s * a.part_stride);
+        const float4 v2 = *reinterpret_cast<const float4*>(p + s * a.part_stride + 4);
+        u.x += u2.x; u.y += u2.y; u.z += u2.z; u.w += u2.w;
+        v.x += v2.x; v.y += v2.y; v.z += v2.z; v.w += v2.w;
+      }
+      x[0] = u.x; x[1] = u.y; x[2] = u.z; x[3] = u.w; x[4] = v.x; x[5] = v.y; x[6] = v.z; x[7] = v.w;
+    } else {
+      const uint4 w4 = *reinterpret_cast<const uint4*>(a.qkv + t * a.ld + c);
+      const uint32_t w[4] = {w4.x, w4.y, w4.z, w4.w};
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        x[2 * e] = a.fp16_input ? f16lo(w[e]) : bf16lo(w[e]);
+        x[2 * e + 1] = a.fp16_input ? f16hi(w[e]) : bf16hi(w[e]);
+      }
+    }
+  };
 
   if ((int)blockIdx.y < n_rot_blocks) {
     // ---- rotate (q or k): a block takes heads_per_block heads of its 64 positions, so that a thread's
@@ -307,17 +333,9 @@ __global__ __launch_bounds__(256) void rope_write_kernel(RopeWriteArgs a, int he
         const int col = (is_k ? a.k_col : a.q_col) + hh * hd;
         const float* gamma = is_k ? a.k_gamma : a.q_gamma;
         bf16_t* row = a.qkv + t * a.ld + col;
-        const uint4 lo = valid ? *reinterpret_cast<const uint4*>(row + g * 8) : make_uint4(0, 0, 0, 0);
-        const uint4 hi = valid ? *reinterpret_cast<const uint4*>(row + half + g * 8) : make_uint4(0, 0, 0, 0);
-        const uint32_t lw[4] = {lo.x, lo.y, lo.z, lo.w}, hw[4] = {hi.x, hi.y, hi.z, hi.w};
-        float xs[8], ys[8];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          xs[2 * e] = a.fp16_input ? f16lo(lw[e]) : bf16lo(lw[e]);
-          xs[2 * e + 1] = a.fp16_input ? f16hi(lw[e]) : bf16hi(lw[e]);
-          ys[2 * e] = a.fp16_input ? f16lo(hw[e]) : bf16lo(hw[e]);
-          ys[2 * e + 1] = a.fp16_input ? f16hi(hw[e]) : bf16hi(hw[e]);
-        }
+        float xs[8], ys[8];       // (a row beyond the sequence reads its first one: in bounds, and not stored)
+        load8(t, col + g * 8, xs);
+        load8(t, col + half + g * 8, ys);
         if (gamma) {   // uniform over the block
           float ss = 0.f;
 #pragma unroll
@@ -391,23 +409,17 @@ __global__ __launch_bounds__(256) void rope_write_kernel(RopeWriteArgs a, int he
   const int groups = hd >> 3;
   for (int it = threadIdx.x; it < 64 * groups; it += 256) {
     const int p = it / groups, g = it - p * groups;
-    uint4 v = make_uint4(0, 0, 0, 0);
-    bool v_is_f16 = a.fp16_input != 0;     // format of the 8 values in v (fp16 or bf16)
+    // the 8 values as the cache stores them and as the transposed fp16 copy takes them (an 8-bit cache: the codes, and
+    // the values they stand for)
+    uint4 vh = make_uint4(0, 0, 0, 0);
     if (p0 + p < len) {
       const size_t t = (size_t)seq0 + p0 + p;
-      v = *reinterpret_cast<const uint4*>(a.qkv + t * a.ld + col + g * 8);
+      float f[8];
+      load8(t, col + g * 8, f);
       if (a.kvq.fp8) {
-        // 8-bit cache: store the codes; what the attention kernel reads (vT) are the values they stand for
-        const uint32_t w[4] = {v.x, v.y, v.z, v.w};
-        float f[8];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          f[2 * e] = (a.fp16_input ? f16lo(w[e]) : bf16lo(w[e])) * a.kvq.v_inv;
-          f[2 * e + 1] = (a.fp16_input ? f16hi(w[e]) : bf16hi(w[e])) * a.kvq.v_inv;
-        }
         uint2 c;
-        c.x = e4m3_pack4(f[0], f[1], f[2], f[3]);
-        c.y = e4m3_pack4(f[4], f[5], f[6], f[7]);
+        c.x = e4m3_pack4(f[0] * a.kvq.v_inv, f[1] * a.kvq.v_inv, f[2] * a.kvq.v_inv, f[3] * a.kvq.v_inv);
+        c.y = e4m3_pack4(f[4] * a.kvq.v_inv, f[5] * a.kvq.v_inv, f[6] * a.kvq.v_inv, f[7] * a.kvq.v_inv);
         if (a.v_pool) {
           const int s = a.slot[t];
           unsigned char* dst = reinterpret_cast<unsigned char*>(a.v_pool) +
@@ -416,26 +428,21 @@ __global__ __launch_bounds__(256) void rope_write_kernel(RopeWriteArgs a, int he
         }
 #pragma unroll
         for (int e = 0; e < 8; ++e) f[e] = e4m3_decode(((e < 4 ? c.x : c.y) >> (8 * (e & 3))) & 0xffu) * a.kvq.v_scale;
-        v = make_uint4(pack_f16x2(f[0], f[1]), pack_f16x2(f[2], f[3]), pack_f16x2(f[4], f[5]), pack_f16x2(f[6], f[7]));
-        v_is_f16 = true;
       } else if (a.v_pool) {
         const int s = a.slot[t];
         bf16_t* dst = a.v_pool + (((size_t)(s / P) * a.n_kv_heads + hh) * P + (s % P)) * hd;
-        uint4 vb = v;   // the cache entry is bf16
-        if (a.fp16_input) {
-          vb.x = pack_bf16x2(f16lo(v.x), f16hi(v.x)); vb.y = pack_bf16x2(f16lo(v.y), f16hi(v.y));
-          vb.z = pack_bf16x2(f16lo(v.z), f16hi(v.z)); vb.w = pack_bf16x2(f16lo(v.w), f16hi(v.w));
-        }
-        *reinterpret_cast<uint4*>(dst + g * 8) = vb;
+        *reinterpret_cast<uint4*>(dst + g * 8) = make_uint4(pack_bf16x2(f[0], f[1]), pack_bf16x2(f[2], f[3]),
+                                                            pack_bf16x2(f[4], f[5]), pack_bf16x2(f[6], f[7]));
       }
+      // (exact from fp16 and, inside fp16's range, from bf16; saturates outside)
+      vh = make_uint4(pack_f16x2(f[0], f[1]), pack_f16x2(f[2], f[3]), pack_f16x2(f[4], f[5]), pack_f16x2(f[6], f[7]));
     }
     if (a.vT) {
-      // the transposed copy is fp16 (bf16 -> fp16 is exact inside fp16's range; saturates outside)
-      const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+      const uint32_t w[4] = {vh.x, vh.y, vh.z, vh.w};
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        tr[(g * 8 + 2 * e) * 66 + p] = v_is_f16 ? (uint16_t)(w[e] & 0xffff) : f32_to_f16_sat(bf16lo(w[e]));
-        tr[(g * 8 + 2 * e + 1) * 66 + p] = v_is_f16 ? (uint16_t)(w[e] >> 16) : f32_to_f16_sat(bf16hi(w[e]));
+        tr[(g * 8 + 2 * e) * 66 + p] = (uint16_t)(w[e] & 0xffff);
+        tr[(g * 8 + 2 * e + 1) * 66 + p] = (uint16_t)(w[e] >> 16);
       }
     }
   }
@@ -462,7 +469,9 @@ void launch_rope_write(const RopeWriteArgs& a, hipStream_t st) {
   const int n_rot = nq + a.n_kv_heads;
   const int hpb = std::max(1, std::min(4, (int)((long long)a.n_tiles * n_rot / 512)));
   const int n_rot_blocks = (n_rot + hpb - 1) / hpb;
-  hipLaunchKernelGGL(rope_write_kernel, dim3(a.n_tiles, n_rot_blocks + a.n_kv_heads), dim3(256), 0, st, a, hpb);
+  const dim3 grid(a.n_tiles, n_rot_blocks + a.n_kv_heads);
+  if (a.parts) hipLaunchKernelGGL(rope_write_kernel<true>, grid, dim3(256), 0, st, a, hpb);
+  else hipLaunchKernelGGL(rope_write_kernel<false>, grid, dim3(256), 0, st, a, hpb);
 }
 
 }  // namespace pop

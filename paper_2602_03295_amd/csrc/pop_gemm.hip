@@ -794,7 +794,8 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(const float* __restr
 
 // Number of K parts for this problem (1 = do not split): the cost model's best over 1, 2, 4 and 8 parts, as far as
 // the scratch allows.  Parts of at least 8 K-steps.  A caller that adds the parts itself (partials_only) does so in
-// the kernel that normalises the result, which it launches in any case and which reads the rows once.
+// the kernel that normalises the result, which it launches in any case and which reads the rows once, or (parts_free) in
+// one that reads the projection's result anyway.
 inline int choose_split(const GemmArgs& g) {
   if (!g.splitk_ws || g.batch > 1 || g.W_list || g.epilogue == EPI_GLU_BF16 || g.epilogue == EPI_KV_CACHE) return 1;
   if (g.N % 4 || g.K % BK || (reinterpret_cast<uintptr_t>(g.splitk_ws) & 15)) return 1;
@@ -808,10 +809,10 @@ inline int choose_split(const GemmArgs& g) {
   const double mb = (double)g.M * g.N / 1e6;
   int best = 1;
   // unsplit, a caller that would have merged the two launches the norm kernel by itself (6 bytes an element)
-  double best_us = choose_tile(g.M, g.N, g.K, 1).us + (g.partials_only ? kReduceUs + 6 * mb / 4.0 : 0.0);
+  double best_us = choose_tile(g.M, g.N, g.K, 1).us + (g.partials_only && !g.parts_free ? kReduceUs + 6 * mb / 4.0 : 0.0);
   for (int S = 2; S <= 8; S *= 2) {
     if (!fits(S)) continue;
-    const double us = choose_tile(g.M, g.N, g.K / S, S).us + kReduceUs + 4 * mb * S * kReduceUsPerMB;
+    const double us = choose_tile(g.M, g.N, g.K / S, S).us + (g.parts_free ? 0.0 : kReduceUs) + 4 * mb * S * kReduceUsPerMB;
     if (us < best_us) { best_us = us; best = S; }
   }
   return best;

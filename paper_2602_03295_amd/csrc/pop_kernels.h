@@ -68,6 +68,11 @@ void launch_add_parts_rmsnorm(float* x, const float* parts, int S, size_t part_s
 struct RopeWriteArgs {
   bf16_t* qkv;            // [T, ld] rows q | k | v ; q and k are rotated in place
   int fp16_input;         // 1: qkv holds fp16 (EPI_STORE_F16 output), 0: bf16
+  // not nullptr: q | k | v come as this many fp32 partial products of the projection (dense [n_parts][T][ld],
+  // part_stride elements apart), which are added in index order; nothing is read from qkv
+  const float* parts;
+  int n_parts;
+  size_t part_stride;
   int ld;                 // row stride in elements
   int q_col, k_col, v_col;  // first column of q / k / v inside a row (q_col < 0: no q heads)
   int n_q_heads, n_kv_heads, hd;
@@ -137,6 +142,9 @@ struct GemmArgs {
   // parts: epilogue applied as usual).
   bool partials_only;
   int* split_used;
+  // partials_only, where the kernel that takes the parts is launched in any case (otherwise it stands in for a norm
+  // launch of its own): what a split costs is then its traffic alone
+  bool parts_free;
   // EPI_ADD_F32 with `scaled`: out += scale * C (the virtual gate of Sec. 3.1 on a residual branch); otherwise
   // out += C.  A caller that adds partial products itself (partials_only) applies the scale there.
   bool scaled;
