@@ -301,8 +301,8 @@ enum {
   POP_STEP_KV_ONLY_GEMM = 9,  /* pruned layers: batched K/V projection            */
   POP_STEP_KV_ONLY_WRITE = 10, /* pruned layers: RoPE + cache append              */
   POP_STEP_BOUNDARY = 11,     /* boundary rows: deep layers + final norm + LM head */
-  POP_STEP_DOWN_ADD_NORM = 12, /* long prompts: adds the K parts of the down projection to the hidden state and
-                                  writes the next layer's normalised input (or only adds, after the last kept layer) */
+  POP_STEP_DOWN_ADD_NORM = 12, /* where the K range of the down projection is split and a kept layer follows: adds the
+                                  parts to the hidden state and writes that layer's normalised input */
   POP_N_STEPS = 13
 };
 pop_status pop_timing_enable(pop_model* m, int32_t enable);

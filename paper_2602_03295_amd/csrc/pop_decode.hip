@@ -1,8 +1,9 @@
 // Decode-step kernels: one row per sequence through a full layer against the paged KV cache (few-row
-// projections, attention over the cache with RoPE and the append of the new entry inside, greedy choice).
+// projections, attention over the cache, for one or two rows with RoPE and the append of the new entry inside, greedy
+// choice).
 // They carry the boundary token of Sec. 3.3 ("Boundary Handling for the Last Input Token": x_N is
 // the first decode step with the full model) and pop_decode_step (Sec. 3.2, decode operator).
-// With M <= 8 rows every projection streams its weights once: these kernels are HBM-bound.
+// Every projection streams its weights once: HBM-bound (three and more rows go through the tiled GEMM).
 #include <algorithm>
 #include <type_traits>
 
