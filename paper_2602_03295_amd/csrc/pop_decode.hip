@@ -884,10 +884,14 @@ void launch_argmax(const float* logits, int vocab, int32_t* tok, int32_t* out, i
 }
 
 // Splits of the key range: about three work-groups per CU (what the kernel's registers allow), but no split of fewer
-// than 64 keys (16 per wave); equal shares, in whole rounds of the four waves.
+// than 64 keys (16 per wave); equal shares, in whole rounds of the four waves.  At most three, so that no few are left
+// for a second round (four layers of a decode step, us, rounded up -> down: 64 sequences of 400 / 700 keys 665 -> 653 /
+// 734 -> 706, 40 of 1000 664 -> 649, 8-bit 637 -> 619, 28 of 700 592 -> 587, 10 of 4000 632 -> 626); head size 256, with
+// twice the bytes per work-group, keeps the finer cut (20 sequences of 700 keys 916, rounded down 922).
 void choose_decode_splits(AttnDecodeArgs& a, int span) {
   const long long pairs = (long long)a.B * a.n_kv_heads;
-  const int want = (int)std::max(1LL, std::min<long long>((span + 63) / 64, (768 + pairs - 1) / pairs));
+  const long long per_pair = a.hd <= 128 ? 768 / pairs : (768 + pairs - 1) / pairs;
+  const int want = (int)std::max(1LL, std::min<long long>((span + 63) / 64, per_pair));
   const int keys = (span + want - 1) / want;
   a.split_keys = (keys + 63) / 64 * 64;
   a.n_splits = (span + a.split_keys - 1) / a.split_keys;

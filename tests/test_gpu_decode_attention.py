@@ -71,3 +71,8 @@ def test_8_bit_cache(pop, rows, hd):
 def test_two_key_groups_per_block(pop):
     """Enough sequences and keys that a split has 256 of them or more."""
     check(pop, [3300, 3137, 3072, 3400, 3329, 3201], 1, l_keep=0, head_dim=64, n_q_heads=16, n_kv_heads=8)
+
+
+def test_one_split_for_many_sequences(pop):
+    """More (sequence, KV head) pairs than half the work-groups that run at once: one split, whatever the length."""
+    check(pop, [EDGES[i % 9] + 40 * (i % 3) for i in range(49)], 1, head_dim=64, n_q_heads=8, n_kv_heads=8)
