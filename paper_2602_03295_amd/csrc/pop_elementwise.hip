@@ -335,9 +335,12 @@ __global__ __launch_bounds__(256) void rope_write_kernel(RopeWriteArgs a, int he
         const int col = (is_k ? a.k_col : a.q_col) + hh * hd;
         const float* gamma = is_k ? a.k_gamma : a.q_gamma;
         bf16_t* row = a.qkv + t * a.ld + col;
-        float xs[8], ys[8];       // (a row beyond the sequence reads its first one: in bounds, and not stored)
-        load8(t, col + g * 8, xs);
-        load8(t, col + half + g * 8, ys);
+        // (zeros beyond the sequence: the tile's first row, which t is there, is being rewritten by other lanes)
+        float xs[8] = {}, ys[8] = {};
+        if (valid) {
+          load8(t, col + g * 8, xs);
+          load8(t, col + half + g * 8, ys);
+        }
         if (gamma) {   // uniform over the block
           float ss = 0.f;
 #pragma unroll

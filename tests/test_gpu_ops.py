@@ -253,3 +253,24 @@ def test_gemm_few_rows_split_k(pop, M, N, K, epi):
     tol = 2.0 ** -8 if epi == 0 else 1e-5
     assert rel(outs[0], ref) <= tol, (rel(outs[0], ref), tol)
     assert np.array_equal(outs[0], outs[1])
+
+
+@pytest.mark.parametrize("hd,hq,hkv", [(64, 4, 2), (128, 8, 1), (256, 2, 1)])
+def test_rotation_in_place_at_sequence_ends(pop, hd, hq, hkv):
+    """Sequences that end anywhere inside a tile of 64 positions: the rotated q and k stand in place as fp16, once per
+    row, and v is left as it was."""
+    lens = [1, 63, 64, 65, 2, 130]
+    cu = np.concatenate([[0], np.cumsum(lens)])
+    rng = np.random.default_rng(hd)
+    qkv = bf16_round(rng.standard_normal((int(cu[-1]), (hq + 2 * hkv) * hd)).astype(np.float32))
+    dev = qkv.cuda()
+    pop.pop_op_rope_attention(dev, cu, hq, hkv, hd, 10000.0)
+    torch.cuda.synchronize()
+    rot = (hq + hkv) * hd
+    got = dev[:, :rot].contiguous().view(torch.float16).double().cpu().numpy()
+    for b, n in enumerate(lens):
+        rows = qkv[cu[b]:cu[b + 1], :rot].double().numpy().reshape(n, hq + hkv, hd)
+        ref = O.rope(rows, np.arange(n), 10000.0).reshape(n, rot)
+        # one rounding to fp16 (2^-11) of fp32 products of values up to 5
+        assert np.all(np.abs(got[cu[b]:cu[b + 1]] - ref) <= np.abs(ref) * 2.0 ** -11 + 2e-6)
+    assert torch.equal(dev[:, rot:].cpu(), qkv[:, rot:])
