@@ -26,6 +26,12 @@ pop_status pop_op_rmsnorm(const float* x, const float* gamma, void* out, int32_t
 pop_status pop_op_gemm(const void* A, int64_t lda, const void* W, int64_t ldw, void* out, int64_t ldc,
                        int32_t M, int32_t N, int32_t K, int32_t epilogue, int32_t act, pop_stream stream);
 
+/* How pop_op_gemm (scratch_bytes 0) or pop_op_gemm_splitk would run a problem with dense operands; nothing is launched and
+ * no device is needed.  plan HOST int32 [6]: rows and columns of a tile, parts of the K range, output columns of the first
+ * launch (N: there is one launch), rows and columns of the second launch's tiles (0, 0: there is none).  A tile's
+ * columns are W rows: with epilogue 2, half of them gate and half up.  Errors: POP_EINVAL, POP_ESHAPE. */
+pop_status pop_op_gemm_plan(int32_t M, int32_t N, int32_t K, int32_t epilogue, size_t scratch_bytes, int32_t* plan);
+
 /* The same projection (Sec. 2.1, Attn / FFN blocks; the short prompts of Sec. 4.3, where a projection is
  * weight streaming) with scratch memory that allows a deterministic split of K (few rows, long K: the
  * projections of short prompts are weight streaming, and more work-groups stream faster).  The library

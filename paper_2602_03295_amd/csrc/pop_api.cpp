@@ -1700,6 +1700,22 @@ pop_status pop_op_gemm(const void* A, int64_t lda, const void* W, int64_t ldw, v
   return POP_OK;
 }
 
+pop_status pop_op_gemm_plan(int32_t M, int32_t N, int32_t K, int32_t epilogue, size_t scratch_bytes, int32_t* plan) {
+  if (!plan) return fail(POP_EINVAL, "NULL pointer");
+  if (M < 1 || N < 1 || K < 1) return fail(POP_EINVAL, "bad sizes");
+  if (epilogue < 0 || epilogue > 3) return fail(POP_EINVAL, "unknown epilogue %d", epilogue);
+  if (K % 8) return fail(POP_ESHAPE, "K must be a multiple of 8");
+  pop::GemmArgs g{};
+  g.lda = g.ldw = K; g.ldc = N;
+  g.M = M; g.N = N; g.K = K; g.epilogue = epilogue; g.batch = 1;
+  if (scratch_bytes > 0) g.splitk_ws = reinterpret_cast<float*>(256);   // an aligned address, never read
+  g.splitk_ws_bytes = scratch_bytes;
+  const pop::GemmPlan p = pop::gemm_plan(g);
+  plan[0] = p.tile_rows; plan[1] = p.tile_cols; plan[2] = p.k_parts;
+  plan[3] = p.head_cols; plan[4] = p.tail_rows; plan[5] = p.tail_cols;
+  return POP_OK;
+}
+
 pop_status pop_op_gemm_splitk(const void* A, int64_t lda, const void* W, int64_t ldw, void* out, int64_t ldc, int32_t M,
                               int32_t N, int32_t K, int32_t epilogue, void* dev_scratch, size_t scratch_bytes,
                               pop_stream stream) {

@@ -37,6 +37,7 @@
 #include <algorithm>
 #include <cmath>
 #include <cstdlib>
+#include <iterator>
 #include <type_traits>
 #include <utility>
 
@@ -593,8 +594,7 @@ inline bool stagger_k(const GemmArgs& g) {
   return g.batch <= 1 && (g.ldw * 2) % 4096 == 0 && (long long)g.M * g.K * 2 <= (4LL << 20);
 }
 
-// MASKED: also built for K that is not a multiple of BK.
-template <int BM, int BN, int WGM, int WGN, int STAGES, int EPI, bool MASKED = false>
+template <int BM, int BN, int WGM, int WGN, int STAGES, int EPI>
 hipError_t launch_cfg(const GemmArgs& g, hipStream_t st, int n_first = 0, int n_cols = -1 /* output columns; -1: to the end */) {
   constexpr int BN_OUT = EPI == EPI_GLU_BF16 ? BN / 2 : BN;
   constexpr int smem = STAGES * (BM + BN) * BK * 2 + 1024;  // stages + prefetch scratch
@@ -618,25 +618,18 @@ hipError_t launch_cfg(const GemmArgs& g, hipStream_t st, int n_first = 0, int n_
   static const hipError_t attr_err = [] {
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_kernel<BM, BN, WGM, WGN, STAGES, EPI, true>),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, smem);
-    if constexpr (MASKED) {
-      if (e != hipSuccess) return e;
-      e = hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_kernel<BM, BN, WGM, WGN, STAGES, EPI, false>),
-                              hipFuncAttributeMaxDynamicSharedMemorySize, smem);
-    }
-    return e;
+    if (e != hipSuccess) return e;
+    return hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_kernel<BM, BN, WGM, WGN, STAGES, EPI, false>),
+                               hipFuncAttributeMaxDynamicSharedMemorySize, smem);
   }();
   if (attr_err != hipSuccess) return attr_err;
   const int total = p.tiles_m * p.tiles_n;
   const int grid = ((total + 7) / 8) * 8;
   const dim3 grid3(grid, 1, g.batch > 0 ? g.batch : 1), block3(64 * WGM * WGN);
-  if (g.K % BK == 0) {
+  if (g.K % BK == 0)
     hipLaunchKernelGGL((gemm_kernel<BM, BN, WGM, WGN, STAGES, EPI, true>), grid3, block3, smem, st, p);
-  } else {
-    if constexpr (MASKED)
-      hipLaunchKernelGGL((gemm_kernel<BM, BN, WGM, WGN, STAGES, EPI, false>), grid3, block3, smem, st, p);
-    else
-      return hipErrorInvalidValue;
-  }
+  else
+    hipLaunchKernelGGL((gemm_kernel<BM, BN, WGM, WGN, STAGES, EPI, false>), grid3, block3, smem, st, p);
   return hipGetLastError();
 }
 
@@ -659,7 +652,6 @@ constexpr TileCfg kTileCfgs[] = {
     {13, 96, 128, 1, 0.120, 0.464, 2.58}, {14, 64, 128, 2, 0.425, 0.383, 1.69}, {15, 96, 64, 1, 0.291, 0.186, 2.22},
     {16, 64, 64, 1, 0.246, 0.158, 2.12},
 };
-constexpr bool masked_cfg(int id) { return id == 1 || id == 6 || id == 12 || id == 14 || id == 16; }
 constexpr double kLaunchUs = 2.49, kUsPerWeightMB = 0.187, kReduceUs = 2.37, kReduceUsPerMB = 0.30, kContention = 0.10;
 
 // Rounds of `tiles` work-groups of nk K-steps each.  In the last round, work-groups that leave CUs idle compute up
@@ -672,6 +664,10 @@ inline double rounds_us(const TileCfg& c, long long tiles, double nk) {
   };
   return full * round(c.occ, 1.0) + round(share, last / (256.0 * share));
 }
+// K not a multiple of BK: the tail masks are vector instructions beside the MFMAs, and weigh more where a K-step has fewer
+// of those.  Measured time over the model's (K 1000 to 15368, 129 to 30000 rows): 256 x 256 tiles 1.15, the others 1.16 to
+// 1.48; of the factors tried between them (1 to 1.2), 1.10 to 1.16 gave the choices that lost least.
+inline double masked_factor(const TileCfg& c, long long K) { return K % BK && c.id != 1 ? 1.12 : 1.0; }
 inline long long tiles_of(const TileCfg& c, long long M, long long cols) {
   return ((M + c.bm - 1) / c.bm) * ((cols + c.bn - 1) / c.bn);
 }
@@ -679,7 +675,7 @@ inline long long tiles_of(const TileCfg& c, long long M, long long cols) {
 inline double tile_cost_us(const TileCfg& c, long long M, long long cols, long long K, long long batch) {
   const double weights = (double)cols * K * 2 * batch / 1e6 * kUsPerWeightMB;
   const long long tiles = tiles_of(c, M, cols) * batch;
-  double work = rounds_us(c, tiles, (double)((K + BK - 1) / BK));
+  double work = rounds_us(c, tiles, (double)((K + BK - 1) / BK)) * masked_factor(c, K);
   // (over several rounds the smaller tiles lose a little more than the fit says)
   if (c.id != 1 && tiles > 512LL * c.occ) work *= 1.02;
   auto sq = [](double v) { return v * v; };
@@ -694,7 +690,6 @@ struct TileChoice { int id; double us; int tail_id; long long head_cols; };
 inline TileChoice choose_single(long long M, long long cols, long long K, long long batch) {
   TileChoice best{1, 1e300, 0, 0};
   for (const TileCfg& c : kTileCfgs) {      // ordered by area: ties go to the larger tile
-    if (K % BK && !masked_cfg(c.id)) continue;
     const double t = tile_cost_us(c, M, cols, K, batch);
     if (t < best.us) best = {c.id, t, 0, 0};
   }
@@ -702,14 +697,14 @@ inline TileChoice choose_single(long long M, long long cols, long long K, long l
 }
 inline TileChoice choose_tile(long long M, long long cols, long long K, long long batch) {
   TileChoice best = choose_single(M, cols, K, batch);
-  if (batch != 1 || K % BK || M <= 128) return best;
+  if (batch != 1 || M <= 128) return best;
   const double single = best.us;
   for (const TileCfg& c : kTileCfgs) {
     const long long tiles_m = (M + c.bm - 1) / c.bm, slots = 256LL * c.occ;
     const long long rounds = tiles_of(c, M, cols) / slots, head = rounds * slots / tiles_m;   // whole column tiles
     if (rounds < 1 || head < 1 || head * c.bn >= cols) continue;
     const TileChoice tail = choose_single(M, cols - head * c.bn, K, 1);
-    const double t = kLaunchUs + rounds_us(c, tiles_m * head, (double)(K / BK)) + tail.us;
+    const double t = kLaunchUs + rounds_us(c, tiles_m * head, (double)((K + BK - 1) / BK)) * masked_factor(c, K) + tail.us;
     // (the second launch waits for the last work-group of the first: worth it from 4 % on)
     if (t < best.us && t < 0.96 * single) best = {c.id, t, tail.id, head * c.bn};
   }
@@ -723,18 +718,18 @@ hipError_t launch_shape(int id, const GemmArgs& g, hipStream_t st, int n0, int n
     case 3: return launch_cfg<192, 256, 2, 2, 2, EPI>(g, st, n0, nc);
     case 4: return launch_cfg<160, 256, 2, 2, 2, EPI>(g, st, n0, nc);
     case 5: return launch_cfg<192, 192, 2, 2, 3, EPI>(g, st, n0, nc);
-    case 6: return launch_cfg<256, 128, 2, 2, 3, EPI, true>(g, st, n0, nc);
+    case 6: return launch_cfg<256, 128, 2, 2, 3, EPI>(g, st, n0, nc);
     case 7: return launch_cfg<128, 256, 2, 2, 3, EPI>(g, st, n0, nc);
     case 8: return launch_cfg<192, 128, 2, 2, 3, EPI>(g, st, n0, nc);
     case 9: return launch_cfg<128, 192, 2, 2, 3, EPI>(g, st, n0, nc);
     case 10: return launch_cfg<96, 256, 2, 2, 3, EPI>(g, st, n0, nc);
     case 11: return launch_cfg<160, 128, 2, 2, 3, EPI>(g, st, n0, nc);
-    case 12: return launch_cfg<128, 128, 2, 2, 4, EPI, true>(g, st, n0, nc);
+    case 12: return launch_cfg<128, 128, 2, 2, 4, EPI>(g, st, n0, nc);
     case 13: return launch_cfg<96, 128, 2, 2, 4, EPI>(g, st, n0, nc);
-    case 14: return launch_cfg<64, 128, 2, 2, 3, EPI, true>(g, st, n0, nc);
+    case 14: return launch_cfg<64, 128, 2, 2, 3, EPI>(g, st, n0, nc);
     case 15: return launch_cfg<96, 64, 2, 2, 4, EPI>(g, st, n0, nc);
-    case 16: return launch_cfg<64, 64, 2, 2, 6, EPI, true>(g, st, n0, nc);
-    default: return launch_cfg<256, 256, 2, 2, 2, EPI, true>(g, st, n0, nc);
+    case 16: return launch_cfg<64, 64, 2, 2, 6, EPI>(g, st, n0, nc);
+    default: return launch_cfg<256, 256, 2, 2, 2, EPI>(g, st, n0, nc);
   }
 }
 
@@ -745,7 +740,7 @@ hipError_t launch_epi(const GemmArgs& g, hipStream_t st) {
   // Building with -DPOP_FORCE_GEMM_TILE=1..16 forces one shape (tile-shape experiments, never the product
   // build): the choice is a compile-time constant and nothing in the environment can change it.
 #ifdef POP_FORCE_GEMM_TILE
-  const TileChoice pick{g.K % BK && !masked_cfg(POP_FORCE_GEMM_TILE) ? 16 : POP_FORCE_GEMM_TILE, 0.0, 0, 0};
+  const TileChoice pick{POP_FORCE_GEMM_TILE, 0.0, 0, 0};
 #else
   const TileChoice pick = choose_tile(g.M, cols, g.K, batch);
 #endif
@@ -875,11 +870,23 @@ hipError_t launch_gemm(const GemmArgs& g, hipStream_t st) {
       if (!gemm_kv_cache_supported(g.kv_heads, g.kv_hd) || g.N != 2 * g.kv_heads * g.kv_hd || !g.kv_dest ||
           !g.kv_slot || g.kv_page_size < 1)
         return hipErrorInvalidValue;
-      if (g.kv_hd == 64) return launch_cfg<256, 256, 2, 2, 2, EPI_KV64, true>(g, st);
-      if (g.kv_hd == 128) return launch_cfg<256, 256, 2, 2, 2, EPI_KV128, true>(g, st);
-      return launch_cfg<256, 256, 4, 1, 2, EPI_KV256, true>(g, st);
+      if (g.kv_hd == 64) return launch_cfg<256, 256, 2, 2, 2, EPI_KV64>(g, st);
+      if (g.kv_hd == 128) return launch_cfg<256, 256, 2, 2, 2, EPI_KV128>(g, st);
+      return launch_cfg<256, 256, 4, 1, 2, EPI_KV256>(g, st);
   }
   return hipErrorInvalidValue;
+}
+
+GemmPlan gemm_plan(const GemmArgs& g) {
+  const bool glu = g.epilogue == EPI_GLU_BF16;
+  const long long cols = glu ? 2LL * g.N : g.N;
+  const int S = choose_split(g);
+  const TileChoice pick = S > 1 ? choose_tile(g.M, cols, g.K / S, S) : choose_tile(g.M, cols, g.K, std::max(g.batch, 1));
+  auto cfg = [](int id) { return *std::find_if(std::begin(kTileCfgs), std::end(kTileCfgs), [id](const TileCfg& c) { return c.id == id; }); };
+  const TileCfg c = cfg(pick.id);
+  if (pick.tail_id == 0) return GemmPlan{c.bm, c.bn, S, g.N, 0, 0};
+  const TileCfg t = cfg(pick.tail_id);
+  return GemmPlan{c.bm, c.bn, S, (int)(glu ? pick.head_cols / 2 : pick.head_cols), t.bm, t.bn};
 }
 
 bool gemm_kv_cache_supported(int n_kv_heads, int hd) {

@@ -163,6 +163,12 @@ inline float residual_scale(const GemmArgs& g) { return g.scaled ? g.scale : 1.f
 // Returns hipSuccess or the launch error.  Requirements: K % 8 == 0, lda/ldw % 8 == 0,
 // A/W 16-byte aligned, ldc % 4 == 0, and every operand below 2^31 bytes.
 hipError_t launch_gemm(const GemmArgs& g, hipStream_t st);
+// What launch_gemm would launch for these sizes (host only): tile of the (first) launch, parts of the K range, and where
+// the columns go to two launches, the output columns of the first and the tile of the second (otherwise N, 0, 0).
+struct GemmPlan {
+  int tile_rows, tile_cols, k_parts, head_cols, tail_rows, tail_cols;
+};
+GemmPlan gemm_plan(const GemmArgs& g);
 
 // ---------------------------------------------------------------------------------------------
 // Causal GQA flash attention over packed variable-length sequences (pop_attention.hip)

@@ -93,6 +93,7 @@ lib.pop_generate.argtypes = [C.c_void_p, C.c_void_p, C.POINTER(pop_prefill_args)
 lib.pop_op_rmsnorm.argtypes = [C.c_void_p, C.c_void_p, C.c_void_p, C.c_int32, C.c_int32, C.c_float, C.c_void_p]
 lib.pop_op_gemm.argtypes = [C.c_void_p, C.c_int64, C.c_void_p, C.c_int64, C.c_void_p, C.c_int64, C.c_int32,
                             C.c_int32, C.c_int32, C.c_int32, C.c_int32, C.c_void_p]
+lib.pop_op_gemm_plan.argtypes = [C.c_int32, C.c_int32, C.c_int32, C.c_int32, C.c_size_t, _i32p]
 lib.pop_op_gemm_splitk.argtypes = [C.c_void_p, C.c_int64, C.c_void_p, C.c_int64, C.c_void_p, C.c_int64, C.c_int32,
                                    C.c_int32, C.c_int32, C.c_int32, C.c_void_p, C.c_size_t, C.c_void_p]
 lib.pop_static_scratch_bytes.argtypes = []
@@ -117,7 +118,7 @@ EXPORTED = ["pop_timing_enable", "pop_timing_read", "pop_last_error", "pop_versi
             "pop_workspace_bytes", "pop_cache_create", "pop_cache_destroy", "pop_cache_n_seqs",
             "pop_cache_seq_lens", "pop_cache_block_table", "pop_slot_map", "pop_prefill", "pop_decode_step", "pop_decode_step_gated", "pop_generate",
             "pop_generate_workspace_bytes", "pop_op_rmsnorm",
-            "pop_op_gemm", "pop_op_gemm_splitk", "pop_op_gemm_splitk_static", "pop_static_scratch_bytes", "pop_op_gemv", "pop_op_gemv_norm", "pop_op_rope_attention_workspace", "pop_op_rope_attention"]
+            "pop_op_gemm", "pop_op_gemm_plan", "pop_op_gemm_splitk", "pop_op_gemm_splitk_static", "pop_static_scratch_bytes", "pop_op_gemv", "pop_op_gemv_norm", "pop_op_rope_attention_workspace", "pop_op_rope_attention"]
 
 
 def _check(status: int) -> None:
@@ -406,6 +407,14 @@ def pop_op_gemm(A: torch.Tensor, W: torch.Tensor, epilogue: int = EPI_STORE_BF16
     _check(lib.pop_op_gemm(A.data_ptr(), A.stride(0), W.data_ptr(), W.stride(0), out.data_ptr(), out.stride(0),
                            M, N, K, epilogue, act, _stream(stream)))
     return out
+
+
+def pop_op_gemm_plan(M: int, N: int, K: int, epilogue: int = EPI_STORE_BF16, scratch_bytes: int = 0) -> Dict:
+    """How the library would run a projection: tile (rows, W rows), parts of K, output columns of the first launch, and
+    the second launch's tile (None: one launch).  Host only."""
+    p = (C.c_int32 * 6)()
+    _check(lib.pop_op_gemm_plan(M, N, K, epilogue, scratch_bytes, p))
+    return {"tile": (p[0], p[1]), "k_parts": p[2], "head_cols": p[3], "tail": (p[4], p[5]) if p[4] else None}
 
 
 def pop_op_gemm_splitk(A: torch.Tensor, W: torch.Tensor, epilogue: int = EPI_STORE_BF16,

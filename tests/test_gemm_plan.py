@@ -1,0 +1,35 @@
+"""Which tile shapes, K parts and launches the bf16 GEMM takes for a problem, as the library reports it.  No GPU needed."""
+import pytest
+
+pop = pytest.importorskip("paper_2602_03295_amd.pop", reason="libpop.so not built")
+
+
+@pytest.mark.parametrize("M,N,K,epi", [(2048, 14344, 4104, 2), (4096, 14344, 4104, 2), (1536, 6144, 4104, 3),
+                                       (768, 5632, 1000, 2), (2048, 4104, 4104, 1)])
+def test_partly_filled_rounds_with_any_k(M, N, K, epi):
+    """256 x 256 tiles would leave most of a round of work-groups idle here: with a K that is no multiple of a K-step, too,
+    smaller tiles or a second launch take their place."""
+    p = pop.pop_op_gemm_plan(M, N, K, epi)
+    assert p["tile"] != (256, 256) or p["tail"] is not None
+
+
+def test_shapes_for_any_k():
+    """All sixteen shapes are built for such K: nothing sends it to a few of them."""
+    masked, full = set(), set()
+    for M in range(16, 4200, 88):
+        for N, K in ((4096, 14336), (6144, 4096), (28672, 4096), (2048, 1024), (12288, 448)):
+            full.add(pop.pop_op_gemm_plan(M, N, K, 3)["tile"])
+            masked.add(pop.pop_op_gemm_plan(M, N, K - 8, 3)["tile"])
+    assert len(full) >= 12 and len(masked) >= 12, (sorted(full), sorted(masked))
+
+
+def test_plan_arguments():
+    for bad in [dict(M=0, N=8, K=8), dict(M=8, N=0, K=8), dict(M=8, N=8, K=0), dict(M=8, N=8, K=12),
+                dict(M=8, N=8, K=8, epilogue=4)]:
+        with pytest.raises(pop.PopError):
+            pop.pop_op_gemm_plan(**bad)
+    p = pop.pop_op_gemm_plan(8, 64, 64)
+    assert p["k_parts"] == 1 and p["head_cols"] == 64 and p["tail"] is None
+    # scratch for the parts is what a split needs
+    assert pop.pop_op_gemm_plan(16, 4096, 14336, 3)["k_parts"] == 1
+    assert pop.pop_op_gemm_plan(16, 4096, 14336, 3, scratch_bytes=32 * 16 * 4096)["k_parts"] > 1
