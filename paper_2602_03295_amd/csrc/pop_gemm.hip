@@ -668,6 +668,14 @@ inline double rounds_us(const TileCfg& c, long long tiles, double nk) {
 // of those.  Measured time over the model's (K 1000 to 15368, 129 to 30000 rows): 256 x 256 tiles 1.15, the others 1.16 to
 // 1.48; of the factors tried between them (1 to 1.2), 1.10 to 1.16 gave the choices that lost least.
 inline double masked_factor(const TileCfg& c, long long K) { return K % BK && c.id != 1 ? 1.12 : 1.0; }
+// Over several rounds the smaller tiles lose more than the fit, made up to 4096 rows, says: a little at K = 4096, and more
+// with a long K, whose rows of A no longer stay in the caches from one column tile to the next (K = 14336 and 15360, 5000
+// to 30000 rows, measured time over the fit's: 256 x 256 tiles 1.04, 192 x 192 1.11, 192 x 256 1.10, 160 x 256 1.07; at
+// K = 4096 all within 3 % of 1.00).  The first launch of a column split (`split`) takes the latter alone.
+inline double rounds_factor(const TileCfg& c, long long tiles, long long K, bool split) {
+  if (c.id == 1 || tiles <= 512LL * c.occ) return 1.0;
+  return (split ? 1.0 : 1.02) + 0.06 * std::min(std::max((K - 4096) / 11264.0, 0.0), 1.0);
+}
 inline long long tiles_of(const TileCfg& c, long long M, long long cols) {
   return ((M + c.bm - 1) / c.bm) * ((cols + c.bn - 1) / c.bn);
 }
@@ -675,9 +683,7 @@ inline long long tiles_of(const TileCfg& c, long long M, long long cols) {
 inline double tile_cost_us(const TileCfg& c, long long M, long long cols, long long K, long long batch) {
   const double weights = (double)cols * K * 2 * batch / 1e6 * kUsPerWeightMB;
   const long long tiles = tiles_of(c, M, cols) * batch;
-  double work = rounds_us(c, tiles, (double)((K + BK - 1) / BK)) * masked_factor(c, K);
-  // (over several rounds the smaller tiles lose a little more than the fit says)
-  if (c.id != 1 && tiles > 512LL * c.occ) work *= 1.02;
+  const double work = rounds_us(c, tiles, (double)((K + BK - 1) / BK)) * masked_factor(c, K) * rounds_factor(c, tiles, K, false);
   auto sq = [](double v) { return v * v; };
   return kLaunchUs + std::sqrt(std::sqrt(sq(sq(work)) + sq(sq(weights))));
 }
@@ -704,7 +710,8 @@ inline TileChoice choose_tile(long long M, long long cols, long long K, long lon
     const long long rounds = tiles_of(c, M, cols) / slots, head = rounds * slots / tiles_m;   // whole column tiles
     if (rounds < 1 || head < 1 || head * c.bn >= cols) continue;
     const TileChoice tail = choose_single(M, cols - head * c.bn, K, 1);
-    const double t = kLaunchUs + rounds_us(c, tiles_m * head, (double)((K + BK - 1) / BK)) * masked_factor(c, K) + tail.us;
+    const double t = kLaunchUs + rounds_us(c, tiles_m * head, (double)((K + BK - 1) / BK)) * masked_factor(c, K) *
+                                     rounds_factor(c, tiles_m * head, K, true) + tail.us;
     // (the second launch waits for the last work-group of the first: worth it from 4 % on)
     if (t < best.us && t < 0.96 * single) best = {c.id, t, tail.id, head * c.bn};
   }

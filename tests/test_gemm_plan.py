@@ -33,3 +33,10 @@ def test_plan_arguments():
     # scratch for the parts is what a split needs
     assert pop.pop_op_gemm_plan(16, 4096, 14336, 3)["k_parts"] == 1
     assert pop.pop_op_gemm_plan(16, 4096, 14336, 3, scratch_bytes=32 * 16 * 4096)["k_parts"] > 1
+
+
+@pytest.mark.parametrize("M,N,K", [(12000, 3840, 15360), (14000, 4096, 14336)])
+def test_long_k_and_many_rows_take_the_largest_tiles(M, N, K):
+    """Rows of A that are too long to stay cached between column tiles: smaller tiles fill the rounds better here but
+    fetch the rows more often."""
+    assert pop.pop_op_gemm_plan(M, N, K, 1)["tile"] == (256, 256)
