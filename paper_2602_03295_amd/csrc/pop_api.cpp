@@ -516,12 +516,17 @@ void record_kv_first(pop_cache* c, const pop_prefill_args* a, const PrunePlan& p
 }
 
 // Projection of the B rows of a decode-style layer.  The GEMV kernel (every weight row streamed once per group of 1, 2
-// or 4 rows) is the faster form for one and two rows, which it also normalises itself; from kRowsForGemm rows on the
+// or 4 rows) is the faster form for one and two rows, which it also normalises itself; from three rows on the
 // tiled MFMA GEMM with its small tiles, the staggered K start and the split of K is: at the Llama-3.1-8B shape, QKV,
 // O, gate|up and down of 2 rows take 12.6 / 9.6 / 45 / 24 us as GEMV and 14.2 / 12.7 / 41 / 26 us tiled, of 3 rows
 // 23 / 17 / 85 / 43 us (two groups) and 14.1 / 12.7 / 41 / 26 us, of 4 rows 18 / 13.6 / 56 / 32 us and the same.
-constexpr int kRowsForGemm = 3;
-constexpr int rows_for_gemm() { return kRowsForGemm; }
+// A K that is no multiple of 64 has neither the staggered start nor a split, and three and four rows stay with the GEMV
+// kernel's 4-row form (the same projections at K = 4104 / 14344: 14.5 / 14.2 / 45 / 34 us, tiled 20 / 19 / 49 / 58 us;
+// N = 3072, K = 2056 8.1 and 9.8 us) unless the matrix is small, where the tiled form has more waves for it (N = 1000, K =
+// 2744 10.7 and 9.7 us; gate|up of 2 x 5632 rows, K = 1000, 9.6 and 8.6 us).
+inline bool rows_take_gemm(int B, int N, int K) {
+  return B >= 5 || (B >= 3 && (K % 64 == 0 || K <= 1024 || N < 2048));
+}
 
 // parts_out (optional): the caller can add partial products itself.  If the K range was split, *parts_out receives
 // the number of parts (fp32 [parts][B][N] dense at the split scratch of the workspace) and `out` is not written;
@@ -529,7 +534,7 @@ constexpr int rows_for_gemm() { return kRowsForGemm; }
 pop_status few_rows_projection(const LayerCtx& x, const bf16_t* in, const void* W, void* out, int B, int N, int K,
                                int ldo, int gemv_epi, int act, int* parts_out = nullptr) {
   if (parts_out) *parts_out = 1;
-  if (B < rows_for_gemm() || ldo % 4) {   // (the tiled GEMM stores four columns at a time)
+  if (!rows_take_gemm(B, N, K) || ldo % 4) {   // (the tiled GEMM stores four columns at a time)
     pop::launch_gemv(in, (const bf16_t*)W, out, B, N, K, ldo, gemv_epi, act, x.st);
     return POP_OK;
   }
@@ -558,7 +563,7 @@ pop_status normed_few_rows_projection(const LayerCtx& x, float* rows, const floa
   const float eps = x.m->cfg.rms_eps;
   if (x.ab_gamma == gamma && gamma != nullptr)   // the previous projection's second kernel left them in `normed`
     return few_rows_projection(x, normed, W, out, B, N, K, ldo, gemv_epi, act, parts_out);
-  if (B < rows_for_gemm() && pop::gemv_norm_supported(B, K) && (B == 1 || N <= 8192)) {
+  if (B <= 2 && pop::gemv_norm_supported(B, K) && (B == 1 || N <= 8192)) {
     pop::launch_gemv_norm(rows, gamma, eps, (const bf16_t*)W, out, B, N, K, ldo, gemv_epi, act, x.st);
     return POP_OK;
   }
@@ -573,7 +578,7 @@ pop_status residual_few_rows_projection(const LayerCtx& x, const bf16_t* in, con
                                         const float* next_gamma, float scale /* the layer's virtual gate */) {
   float* xb = at<float>(x.ws, x.w->o_xb);
   x.ab_gamma = nullptr;
-  if (B < rows_for_gemm() || N % 4) {
+  if (!rows_take_gemm(B, N, K) || N % 4) {
     pop::launch_gemv(in, (const bf16_t*)W, xb, B, N, K, N, pop::GEMV_ADD_F32, 0, x.st, scale);
     return POP_OK;
   }

@@ -241,10 +241,16 @@ void launch_gemv_in(const GemvIn& in, const bf16_t* W, void* out, int M, int N, 
     if (mm == 1) launch_gemv_m<1>(xs, W, os, N, K, ldo, epilogue, act, st);
     else if (mm == 2) launch_gemv_m<2>(xs, W, os, N, K, ldo, epilogue, act, st);
     else if (mm <= 4) {
-      // 3 rows: 2 + 1 (exact sizes; padding to 4 would cost registers in the 2-row form's deep unrolling)
-      if (mm == 3) { launch_gemv_m<2>(xs, W, os, N, K, ldo, epilogue, act, st);
-                     launch_gemv_m<1>(rows_from(xs, 2, K), W, reinterpret_cast<char*>(os) + 2 * ldo * osz, N, K, ldo, epilogue, act, st); }
-      else launch_gemv_m<4>(xs, W, os, N, K, ldo, epilogue, act, st);
+      // 3 rows: the 4-row form with the last one repeated (never stored; the weights are streamed once), or 2 + 1 where the
+      // kernel normalises the rows
+      if (mm == 3 && !xs.xf) {
+        GemvIn x4 = xs;
+        x4.m_valid = mm;
+        launch_gemv_m<4>(x4, W, os, N, K, ldo, epilogue, act, st);
+      } else if (mm == 3) {
+        launch_gemv_m<2>(xs, W, os, N, K, ldo, epilogue, act, st);
+        launch_gemv_m<1>(rows_from(xs, 2, K), W, reinterpret_cast<char*>(os) + 2 * ldo * osz, N, K, ldo, epilogue, act, st);
+      } else launch_gemv_m<4>(xs, W, os, N, K, ldo, epilogue, act, st);
     } else if (mm == 8 || !xs.xf) {
       // 5..7 rows of bf16 input run the 8-row form with the missing rows repeating the last one (never stored):
       // the weights are streamed once

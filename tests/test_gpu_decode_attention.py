@@ -19,8 +19,8 @@ def pop():
     return p
 
 
-def check(pop, lens, steps, tol=TOL, l_keep=1, **kw):
-    cfg = synth.get_config("tiny", dtype=synth.DTYPE_BF16, n_layers=2, d_ffn=256, vocab=512, **kw)
+def check(pop, lens, steps, tol=TOL, l_keep=1, d_ffn=256, **kw):
+    cfg = synth.get_config("tiny", dtype=synth.DTYPE_BF16, n_layers=2, d_ffn=d_ffn, vocab=512, **kw)
     W = synth.make_weights(cfg, seed=21)
     synth.add_qk_norms(W, cfg)
     tokens = synth.make_tokens(cfg["vocab"], sum(lens), seed=22)
@@ -76,3 +76,10 @@ def test_two_key_groups_per_block(pop):
 def test_one_split_for_many_sequences(pop):
     """More (sequence, KV head) pairs than half the work-groups that run at once: one split, whatever the length."""
     check(pop, [EDGES[i % 9] + 40 * (i % 3) for i in range(49)], 1, head_dim=64, n_q_heads=8, n_kv_heads=8)
+
+
+@pytest.mark.parametrize("rows", [3, 4, 5])
+def test_few_rows_of_a_width_that_is_no_multiple_of_64(pop, rows):
+    """Projections of three and four rows by the GEMV kernel's 4-row form (QKV, O, gate|up and down, all of 2048 rows or
+    more), of five by the tiled GEMM."""
+    check(pop, [33, 20, 65, 7, 16][:rows], 2, d_model=2056, d_ffn=2072, head_dim=64, n_q_heads=24, n_kv_heads=4)
