@@ -515,18 +515,16 @@ void record_kv_first(pop_cache* c, const pop_prefill_args* a, const PrunePlan& p
     }
 }
 
-// Projection of the B rows of a decode-style layer.  The GEMV kernel (every weight row streamed once per group of 1, 2
-// or 4 rows) is the faster form for one and two rows, which it also normalises itself; from three rows on the
-// tiled MFMA GEMM with its small tiles, the staggered K start and the split of K is: at the Llama-3.1-8B shape, QKV,
-// O, gate|up and down of 2 rows take 12.6 / 9.6 / 45 / 24 us as GEMV and 14.2 / 12.7 / 41 / 26 us tiled, of 3 rows
-// 23 / 17 / 85 / 43 us (two groups) and 14.1 / 12.7 / 41 / 26 us, of 4 rows 18 / 13.6 / 56 / 32 us and the same.
+// Projection of the B rows of a decode-style layer.  The GEMV kernel (every weight row streamed once per group of 1, 2, 4
+// or 8 rows) is the faster form for one and two rows, which it also normalises itself; from three rows on the tiled
+// MFMA GEMM with its small tiles, the staggered K start and the split of K is: at the Llama-3.1-8B shape, QKV, O,
+// gate|up and down of 2 rows take 12.6 / 9.6 / 45 / 24 us as GEMV and 14.2 / 12.7 / 41 / 26 us tiled, of 3 and 4 rows
+// 18 / 13.6 / 56 / 32 us and 14.1 / 12.7 / 41 / 26 us.
 // A K that is no multiple of 64 has neither the staggered start nor a split, and three and four rows stay with the GEMV
 // kernel's 4-row form (the same projections at K = 4104 / 14344: 14.5 / 14.2 / 45 / 34 us, tiled 20 / 19 / 49 / 58 us;
-// N = 3072, K = 2056 8.1 and 9.8 us) unless the matrix is small, where the tiled form has more waves for it (N = 1000, K =
-// 2744 10.7 and 9.7 us; gate|up of 2 x 5632 rows, K = 1000, 9.6 and 8.6 us).
-inline bool rows_take_gemm(int B, int N, int K) {
-  return B >= 5 || (B >= 3 && (K % 64 == 0 || K <= 1024 || N < 2048));
-}
+// in a decode step N = 2040, K = 5640 12.8 and 24 us), except where K ends after two of its loads per lane (gate|up of
+// 2 x 5632 rows, K = 1000, 9.6 and 8.6 us; a step of three sequences with d = 1000 289 and 279 us).
+inline bool rows_take_gemm(int B, int K) { return B >= 5 || (B >= 3 && (K % 64 == 0 || K <= 1024)); }
 
 // parts_out (optional): the caller can add partial products itself.  If the K range was split, *parts_out receives
 // the number of parts (fp32 [parts][B][N] dense at the split scratch of the workspace) and `out` is not written;
@@ -534,7 +532,7 @@ inline bool rows_take_gemm(int B, int N, int K) {
 pop_status few_rows_projection(const LayerCtx& x, const bf16_t* in, const void* W, void* out, int B, int N, int K,
                                int ldo, int gemv_epi, int act, int* parts_out = nullptr) {
   if (parts_out) *parts_out = 1;
-  if (!rows_take_gemm(B, N, K) || ldo % 4) {   // (the tiled GEMM stores four columns at a time)
+  if (!rows_take_gemm(B, K) || ldo % 4) {   // (the tiled GEMM stores four columns at a time)
     pop::launch_gemv(in, (const bf16_t*)W, out, B, N, K, ldo, gemv_epi, act, x.st);
     return POP_OK;
   }
@@ -578,7 +576,7 @@ pop_status residual_few_rows_projection(const LayerCtx& x, const bf16_t* in, con
                                         const float* next_gamma, float scale /* the layer's virtual gate */) {
   float* xb = at<float>(x.ws, x.w->o_xb);
   x.ab_gamma = nullptr;
-  if (!rows_take_gemm(B, N, K) || N % 4) {
+  if (!rows_take_gemm(B, K) || N % 4) {
     pop::launch_gemv(in, (const bf16_t*)W, xb, B, N, K, N, pop::GEMV_ADD_F32, 0, x.st, scale);
     return POP_OK;
   }
