@@ -375,6 +375,8 @@ __global__ __launch_bounds__(256) void attention_tile_kernel(AttnF32 a) {
     const int lo = first_key(pos, b, a.window, a.kv_first);
     const int k_lo = __builtin_amdgcn_readfirstlane(lo);                        // lane 0 has row r0
     const int k_hi = __builtin_amdgcn_readlane(pos_i, r1 - 1 - t0);
+    // keys that all rows see: from the last row's first one (lane 15 has that row) to the first row's position
+    const int all_lo = __builtin_amdgcn_readlane(lo, 15), all_hi = __builtin_amdgcn_readfirstlane(pos);
     const int32_t* bt = a.block_table + (size_t)b * a.max_pages;
     auto entry = [&](const float* pool, int key) {
       return pool + (((size_t)bt[key / a.P] * a.n_kv_heads + kvh) * a.P + (key % a.P)) * HD;
@@ -431,12 +433,41 @@ __global__ __launch_bounds__(256) void attention_tile_kernel(AttnF32 a) {
       l_run = l_run * alpha + sum;       // this lane group's keys; the groups are added at the end
       m_run = m_new;
 #pragma unroll
-      for (int c = 0; c < C; ++c) {
+      for (int c = 0; c < C; ++c)
 #pragma unroll
         for (int v = 0; v < 4; ++v) o[c][v] *= alpha;
+      // A row must not meet a key that it does not see, not even with P = 0 if that key's V is not finite: such blocks
+      // (only those that some row sees in part can hold one) are added key by key.
+      bool by_key = false;
+      if (k0 < all_lo || k0 + 15 > all_hi) {
+        float z = 0.f;
 #pragma unroll
-        for (int j = 0; j < 4; ++j)
-          o[c] = __builtin_amdgcn_mfma_f32_16x16x4f32(HD <= 128 ? vf[c][j] : vp[j][c * 16], p[j], o[c], 0, 0, 0);
+        for (int c = 0; c < C; ++c)
+#pragma unroll
+          for (int j = 0; j < 4; ++j) z += 0.f * (HD <= 128 ? vf[c][j] : vp[j][c * 16]);
+        by_key = __builtin_amdgcn_ballot_w64(!(z == 0.f)) != 0;
+      }
+      if (by_key) {
+#pragma unroll 1
+        for (int kg = 0; kg < 4; ++kg) {
+#pragma unroll
+          for (int j = 0; j < 4; ++j) {
+            const int key = k0 + 4 * kg + j;
+            const float pk = __shfl(p[j], 16 * kg + r16, 64);
+            const bool seen = key >= lo && key <= pos;
+            const float* vk = entry(a.v_pool, min(key, k_hi)) + 4 * g;
+#pragma unroll
+            for (int c = 0; c < C; ++c)
+#pragma unroll
+              for (int v = 0; v < 4; ++v) o[c][v] += seen ? pk * vk[c * 16 + v] : 0.f;
+          }
+        }
+      } else {
+#pragma unroll
+        for (int c = 0; c < C; ++c)
+#pragma unroll
+          for (int j = 0; j < 4; ++j)
+            o[c] = __builtin_amdgcn_mfma_f32_16x16x4f32(HD <= 128 ? vf[c][j] : vp[j][c * 16], p[j], o[c], 0, 0, 0);
       }
     }
     l_run += __shfl_xor(l_run, 16, 64);

@@ -117,3 +117,35 @@ def test_fp32_kernel_shapes(pop, hd, hq, hkv, window, lens, d, f):
     for b, (Kc, Vc, _) in enumerate(outs):
         ref, _, _ = O.decode_step(cfg, W, O.embed_rows(W, step[b:b + 1], np.float64)[0], Kc, Vc)
         assert rel_err(got[b], ref) <= 1e-5
+
+
+@pytest.mark.parametrize("bad", [float("nan"), float("inf")])
+@pytest.mark.parametrize("window", [0, 24])
+@pytest.mark.parametrize("hd", [64, 128, 256])
+def test_fp32_rows_that_do_not_see_a_non_finite_row_keep_their_values(pop, hd, window, bad):
+    """One supplied row is not finite: the rows before it, and with a sliding window in every layer the rows that it has
+    left the reach of, hold the entries they hold without it."""
+    cfg = synth.get_config("tiny", n_layers=3, d_model=72, n_q_heads=2, n_kv_heads=1, head_dim=hd, d_ffn=40, vocab=64,
+                           sliding_window=window, global_every=8 if window else 0)
+    W = synth.make_weights(cfg, seed=5)
+    lens, at = [150, 30], 21
+    tokens = synth.make_tokens(cfg["vocab"], sum(lens), seed=6)
+    row = synth.make_visual_embeds(1, cfg["d_model"], seed=2, as_bf16=False).to(torch.float32)
+    got = []
+    for value in (None, bad):
+        emb = row.clone()
+        if value is not None:
+            emb[0, 3] = value
+        run = DeviceRun(pop, cfg, W, lens)
+        run.prefill(tokens, 2, embeds=emb.cuda(), embed_ranges=[(0, at, 1)])
+        got.append([run.kv(l, b) for l in range(3) for b in range(2)])
+    for i, (clean, dirty) in enumerate(zip(*got)):
+        l, b = divmod(i, 2)
+        # (layer l + 1 stores what l attentions have mixed: `window - 1` rows further each)
+        reached = range(0) if b else range(at, lens[0] if window == 0 else at + 1 + l * (window - 1))
+        for c, d in zip(clean, dirty):
+            keep = [r for r in range(lens[b]) if r not in reached]
+            # (the keys of a block that holds the row may be added in another order)
+            assert np.isfinite(d[keep]).all() and rel_err(d[keep], c[keep].astype(np.float64)) <= 1e-6, (l, b)
+            if b == 0:
+                assert not np.isfinite(d[at]).all()
