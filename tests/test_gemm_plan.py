@@ -1,6 +1,8 @@
 """Which tile shapes, K parts and launches the bf16 GEMM takes for a problem, as the library reports it.  No GPU needed."""
 import pytest
 
+from tests.test_gpu_gemm_tiles import SIZES, SPLIT_SIZES
+
 pop = pytest.importorskip("paper_2602_03295_amd.pop", reason="libpop.so not built")
 
 
@@ -40,3 +42,31 @@ def test_long_k_and_many_rows_take_the_largest_tiles(M, N, K):
     """Rows of A that are too long to stay cached between column tiles: smaller tiles fill the rounds better here but
     fetch the rows more often."""
     assert pop.pop_op_gemm_plan(M, N, K, 1)["tile"] == (256, 256)
+
+
+@pytest.mark.parametrize("M,N,K,tile,tail", SIZES)
+def test_sizes_of_the_tile_tests_take_the_shapes_they_name(M, N, K, tile, tail):
+    p = pop.pop_op_gemm_plan(M, N, K, 3)
+    if tile is not None:
+        assert p["tile"] == tile
+    if tail == "any":
+        assert p["tail"] is not None
+    elif tile is not None:
+        assert p["tail"] == tail
+
+
+def test_sizes_of_the_tile_tests_cover_every_shape():
+    """Plain and gate|up projections, K a multiple of a K-step and not: all sixteen shapes each."""
+    for epi in (3, 2):
+        for masked in (False, True):
+            seen = set()
+            for M, N, K, _, _ in SIZES:
+                if (K % 64 != 0) == masked:
+                    p = pop.pop_op_gemm_plan(M, N // 2 // 4 * 4 if epi == 2 else N, K, epi)
+                    seen |= {p["tile"], p["tail"]} - {None}
+            assert len(seen) == 16, (epi, masked, sorted(seen))
+
+
+def test_sizes_of_the_split_tests_are_split():
+    parts = [pop.pop_op_gemm_plan(M, N, K, 3, scratch_bytes=32 * M * N)["k_parts"] for M, N, K in SPLIT_SIZES]
+    assert min(parts) >= 2 and {2, 4, 8} <= set(parts), parts

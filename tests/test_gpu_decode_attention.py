@@ -1,5 +1,5 @@
 """Decode attention over the paged cache at the edges of its key blocks and splits: every bound of query heads per KV
-head, every head size, few rows (RoPE and append inside the kernel) and more, both cache types, a sliding window."""
+head, every head size, one and two rows (RoPE and append inside the kernel) and more, both cache types, a sliding window."""
 import numpy as np
 import pytest
 import torch
@@ -47,30 +47,50 @@ EDGES = [1, 15, 16, 17, 31, 63, 64, 65, 129]
 
 
 @pytest.mark.parametrize("hd,hq,hkv", [(64, 2, 2), (64, 6, 3), (128, 3, 1), (128, 8, 1), (256, 4, 2), (256, 5, 1)])
-@pytest.mark.parametrize("rows", [3, 9])
+@pytest.mark.parametrize("rows", [1, 2, 3, 9])
 def test_edges(pop, hd, hq, hkv, rows):
     for i in range(0, 9, rows):
         check(pop, EDGES[i:i + rows], 2, head_dim=hd, n_q_heads=hq, n_kv_heads=hkv)
 
 
-@pytest.mark.parametrize("rows", [3, 9])
+@pytest.mark.parametrize("rows", [1, 2, 3, 9])
 @pytest.mark.parametrize("hd", [64, 128, 256])
 def test_window_and_page_sizes(pop, rows, hd):
+    lens = [40, 129, 65, 16, 33, 100, 250, 7, 64]
     for P in (1, 8, 64):
-        check(pop, [40, 129, 65, 16, 33, 100, 250, 7, 64][:rows], 2, head_dim=hd, n_q_heads=4, n_kv_heads=2,
-              sliding_window=33, global_every=2, page_size=P)
+        for i in range(0, 9 if rows < 3 else 1, rows):
+            check(pop, lens[i:i + rows], 2, head_dim=hd, n_q_heads=4, n_kv_heads=2, sliding_window=33, global_every=2,
+                  page_size=P)
 
 
-@pytest.mark.parametrize("rows", [3, 9])
+@pytest.mark.parametrize("rows", [1, 2, 3, 9])
 @pytest.mark.parametrize("hd", [64, 128, 256])
 def test_8_bit_cache(pop, rows, hd):
     # code flips put one code step (6 to 12 % of an element) on a few entries: the bound of the 8-bit cache's own tests
-    check(pop, EDGES[:rows], 2, tol=8e-2, head_dim=hd, n_q_heads=4, n_kv_heads=2, kv_dtype=1, k_scale=0.02, v_scale=0.02)
+    for i in range(0, 9 if rows < 3 else 1, rows):
+        check(pop, EDGES[i:i + rows], 2, tol=8e-2, head_dim=hd, n_q_heads=4, n_kv_heads=2, kv_dtype=1, k_scale=0.02,
+              v_scale=0.02)
 
 
-def test_two_key_groups_per_block(pop):
-    """Enough sequences and keys that a split has 256 of them or more."""
-    check(pop, [3300, 3137, 3072, 3400, 3329, 3201], 1, l_keep=0, head_dim=64, n_q_heads=16, n_kv_heads=8)
+# lengths whose last block of 32 keys holds 31, 32, 1, 15, 16, 17, 18 of them
+LAST_BLOCKS = [31, 32, 33, 47, 48, 49, 50]
+
+
+@pytest.mark.parametrize("kv_dtype", [0, 1])
+@pytest.mark.parametrize("hd,hq,hkv", [(64, 16, 8), (128, 8, 8), (64, 32, 4)])
+def test_splits_of_256_keys_and_more(pop, hd, hq, hkv, kv_dtype):
+    """Six sequences x 8 KV heads (13 x 4) of about 3300 keys: at most 16 (14) splits of 256 keys, which an 8-bit cache
+    takes in blocks of two key groups and a bf16 cache in blocks of one; the last block of a sequence partly filled."""
+    n = 6 if hkv == 8 else 13
+    check(pop, [3264 + LAST_BLOCKS[i % 7] for i in range(n)], 1, l_keep=0, tol=8e-2 if kv_dtype else TOL, head_dim=hd,
+          n_q_heads=hq, n_kv_heads=hkv, kv_dtype=kv_dtype, k_scale=0.02, v_scale=0.02)
+
+
+@pytest.mark.parametrize("hd,hq", [(64, 32), (64, 64), (128, 32)])
+@pytest.mark.parametrize("lens", [[4672 + 31], [4672 + 33], [2336 + 15, 2336 + 17], [2336 + 16, 2336]])
+def test_splits_of_256_keys_with_rope_and_append_inside(pop, hd, hq, lens):
+    """One and two sequences of an 8-bit cache with 32 KV heads: at most 24 and 12 splits, so of 256 keys here."""
+    check(pop, lens, 2, l_keep=0, tol=8e-2, head_dim=hd, n_q_heads=hq, n_kv_heads=32, kv_dtype=1, k_scale=0.02, v_scale=0.02)
 
 
 def test_one_split_for_many_sequences(pop):

@@ -149,3 +149,28 @@ def test_fp32_rows_that_do_not_see_a_non_finite_row_keep_their_values(pop, hd, w
             assert np.isfinite(d[keep]).all() and rel_err(d[keep], c[keep].astype(np.float64)) <= 1e-6, (l, b)
             if b == 0:
                 assert not np.isfinite(d[at]).all()
+
+
+@pytest.mark.parametrize("gated", [False, True])
+def test_fp32_tiles_of_64_rows_per_wave(pop, gated):
+    """More than 4096 tiles of 32 x 32 in the q|k|v, output, down and K/V-only projections (66 x 65 and more; neither
+    rows nor columns a multiple of a work-group's 128): plain and normalised input, residual update with and without a
+    gate, one kept and one pruned layer."""
+    cfg = synth.get_config("tiny", n_layers=2, d_model=2056, n_q_heads=17, n_kv_heads=17, head_dim=64, d_ffn=72, vocab=131)
+    W = synth.make_weights(cfg, seed=15)
+    synth.randomize_norms(W, cfg)
+    lens = [1501, 610]
+    tokens = synth.make_tokens(cfg["vocab"], sum(lens), seed=16)
+    run = DeviceRun(pop, cfg, W, lens, shuffle_seed=3)
+    if not gated:
+        logits = run.prefill(tokens, 1)
+        compare_with_oracle(run, W, tokens, 1, logits, tol=TOL32)
+        return
+    gates = [0.625, 0.75]
+    run.prefill(tokens, 1, mode=pop.MODE_BODY_ONLY, gates=gates)
+    for b in range(len(lens)):
+        h = O.embed_rows(W, tokens[run.cu[b]:run.cu[b + 1]], np.float64)
+        Kc, Vc, _ = O.body_prefill(cfg, W, h, 1, gates=gates)
+        for l in range(2):
+            k, v = run.kv(l, b)
+            assert rel_err(k, Kc[l]) <= TOL32 and rel_err(v, Vc[l]) <= TOL32

@@ -127,11 +127,11 @@ def test_fp32_path_codes_and_values(pop, monkeypatch, l_keep):
     assert int(np.argmax(logits)) == int(np.argmax(ref)) or differing > 0
 
 
-@pytest.mark.parametrize("lens", [[128, 1, 77], [128, 1, 77, 30, 5]])
+@pytest.mark.parametrize("lens", [[128], [77, 1], [128, 1, 77], [128, 1, 77, 30, 5]])
 def test_bf16_path_ragged_batch_then_decode_steps(pop, monkeypatch, lens):
     """One-byte codes in the pools: kept layers (append kernel), pruned layers (few rows: the append kernel after the
-    batched GEMM), boundary rows and decode steps (three sequences: the decode attention forms and stores the codes
-    itself; five: the separate append kernel, then the decode attention reading codes)."""
+    batched GEMM), boundary rows and decode steps (one and two sequences: the decode attention forms and stores the
+    codes itself; three and five: the separate append kernel, then the decode attention reading codes)."""
     ks, vs = 1.0 / 64, 1.0 / 128
     cfg = synth.get_config("tiny", dtype=synth.DTYPE_BF16, kv_dtype=O.KV_FP8_E4M3, k_scale=ks, v_scale=vs)
     W = synth.make_weights(cfg, seed=1234)
