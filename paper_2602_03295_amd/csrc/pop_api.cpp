@@ -553,7 +553,8 @@ pop_status few_rows_projection(const LayerCtx& x, const bf16_t* in, const void* 
 
 // The same for fp32 rows that are RMS-normalised first (Sec. 2.1): with a few rows the GEMV kernel normalises
 // them itself (two rows for thousands of work-groups cost more than the norm's own launch: gate|up 45.4 us against
-// 40.3 + 2.5 us, LM head of 16032 rows 28.6 against 23.6 + 2.5 us; QKV, 6144 rows, 12.6 against 11.1 + 2.5 us); otherwise the norm kernel writes bf16 rows to `normed` and the projection reads those.
+// 40.3 + 2.5 us, LM head of 16032 rows 28.6 against 23.6 + 2.5 us; QKV, 6144 rows, 12.6 against 11.1 + 2.5 us);
+// otherwise the norm kernel writes bf16 rows to `normed` and the projection reads those.
 pop_status normed_few_rows_projection(const LayerCtx& x, float* rows, const float* gamma, bf16_t* normed, const void* W,
                                       void* out, int B, int N, int K, int ldo, int gemv_epi, int act,
                                       int* parts_out = nullptr) {

@@ -3,7 +3,8 @@
 // choice).
 // They carry the boundary token of Sec. 3.3 ("Boundary Handling for the Last Input Token": x_N is
 // the first decode step with the full model) and pop_decode_step (Sec. 3.2, decode operator).
-// Every projection streams its weights once: HBM-bound (three and more rows go through the tiled GEMM).
+// Every projection streams its weights once: HBM-bound (three and more rows go through the tiled GEMM, three and four of a
+// K that is no multiple of 64 through the GEMV kernel here).
 #include <algorithm>
 #include <type_traits>
 
@@ -890,14 +891,14 @@ void launch_argmax(const float* logits, int vocab, int32_t* tok, int32_t* out, i
 }
 
 // Splits of the key range: about three work-groups per CU (what the kernel's registers allow), but no split of fewer
-// than 64 keys (16 per wave); equal shares, in whole rounds of the four waves.  At most three, so that no few are left
+// than kDecodeKeysPerSplit = 64 keys (16 per wave); equal shares, in whole rounds of the four waves.  At most three, so that no few are left
 // for a second round (four layers of a decode step, us, rounded up -> down: 64 sequences of 400 / 700 keys 665 -> 653 /
 // 734 -> 706, 40 of 1000 664 -> 649, 8-bit 637 -> 619, 28 of 700 592 -> 587, 10 of 4000 632 -> 626); head size 256, with
 // twice the bytes per work-group, keeps the finer cut (20 sequences of 700 keys 916, rounded down 922).
 void choose_decode_splits(AttnDecodeArgs& a, int span) {
   const long long pairs = (long long)a.B * a.n_kv_heads;
   const long long per_pair = a.hd <= 128 ? 768 / pairs : (768 + pairs - 1) / pairs;
-  const int want = (int)std::max(1LL, std::min<long long>((span + 63) / 64, per_pair));
+  const int want = (int)std::max(1LL, std::min<long long>((span + kDecodeKeysPerSplit - 1) / kDecodeKeysPerSplit, per_pair));
   const int keys = (span + want - 1) / want;
   a.split_keys = (keys + 63) / 64 * 64;
   a.n_splits = (span + a.split_keys - 1) / a.split_keys;

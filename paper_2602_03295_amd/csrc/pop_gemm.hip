@@ -17,7 +17,7 @@
 //     SQ_LDS_BANK_CONFLICT 50 % of SQ_LDS_IDX_ACTIVE with the key r & 7, which collides rows r and
 //     r + 8).  The permutation is applied on the global side (each lane picks the chunk that belongs
 //     at its LDS position).
-//   * STAGES LDS stages (2 for 256x256 tiles, 3 for 256x128): the loads of K-step k+STAGES-1 are
+//   * STAGES LDS stages (2 for 256x256 tiles, 3 for 256x128, up to 6 for 64x64): the loads of K-step k+STAGES-1 are
 //     issued after the barrier that publishes K-step k, spread over the K-step between groups of
 //     four MFMAs, so they overlap MFMA work.  Every K-step each wave also touches a few cache lines
 //     several K-steps ahead (a share of the tiles its XCD neighbours will stage), which turns the
@@ -640,7 +640,8 @@ hipError_t launch_cfg(const GemmArgs& g, hipStream_t st, int n_first = 0, int n_
 // The three numbers of a shape and the four common ones are a least-squares fit to 19000 timings (MI355X; 10
 // projection shapes of K 3840 to 15360, 8 to 4096 rows, 1 to 8 K parts, weights from HBM; four compute times are
 // lowered by 4 to 5 % to centre the timings near the best from 500 rows on): 4 % rms; over those
-// problems the choice is on average 1.6 % slower than the best measured pair.  What the shapes between the powers
+// problems the choice is on average 1.6 % slower than the best measured pair (the timings of these shapes, with later ones
+// of other K and up to 30000 rows: profiles/gemm_tile_timings.csv).  What the shapes between the powers
 // of two are for is the rows in between: 528 rows are 3 tiles of 256 (69 % of their work useful) or of 192 (92 %).
 struct TileCfg { int id, bm, bn, occ; double floor_us, step_us, end_us; };
 constexpr TileCfg kTileCfgs[] = {
@@ -691,7 +692,8 @@ inline double tile_cost_us(const TileCfg& c, long long M, long long cols, long l
 // The fastest way for `batch` problems of M rows, `cols` W rows, K: one launch of a shape (tail_id 0), or its full
 // rounds of work-groups alone (the first head_cols W rows) and a second launch of another shape for the columns of the
 // partly filled last round: at M = 2048 the gate|up projection has 896 tiles of 256 x 256 = 3.5 rounds; 3 rounds and
-// one round of 128 x 256 tiles take 317 + 66 us where four rounds take 413.
+// one round of 256 x 128 tiles take 317 + 66 us where four rounds take 413.  (The choice is made anew at every launch: 2 to
+// 12 us of host time, beside a launch's own 4 to 5, while the GPU works on the launches before it.)
 struct TileChoice { int id; double us; int tail_id; long long head_cols; };
 inline TileChoice choose_single(long long M, long long cols, long long K, long long batch) {
   TileChoice best{1, 1e300, 0, 0};

@@ -191,35 +191,37 @@ struct AttnPrefillArgs {
 hipError_t launch_attention_prefill(const AttnPrefillArgs& a, hipStream_t st);
 
 // ---------------------------------------------------------------------------------------------
-// Decode-step kernels for the boundary rows (pop_decode.hip); rows = sequences, M <= 8 per launch
+// Decode-step kernels for the boundary rows (pop_decode.hip); rows = sequences.  One and two rows, and three and four of a K
+// that is no multiple of 64, take the GEMV kernel; the others the tiled GEMM (and the GEMV kernel, up to 8 rows a launch,
+// where that cannot store: N not a multiple of 4)
 // ---------------------------------------------------------------------------------------------
 enum GemvEpilogue { GEMV_STORE_F32 = 0, GEMV_ADD_F32 = 1, GEMV_GLU_BF16 = 2 };
-// out[m, n] (op)= sum_k x[m,k] * W[n,k], x bf16 [M, K] (M <= 8), W bf16 [N, K] ([2N, K] for GLU).
+// out[m, n] (op)= sum_k x[m,k] * W[n,k], x bf16 [M, K], W bf16 [N, K] ([2N, K] for GLU).
 void launch_gemv(const bf16_t* x, const bf16_t* W, void* out, int M, int N, int K, int64_t ldo,
                  int epilogue, int act, hipStream_t st, float scale = 1.f);   // GEMV_ADD_F32: out += scale * C
 // The same with the RMSNorm of the input fused in (Sec. 2.1): xf fp32 [M, K] is normalised with gamma / eps
 // inside the kernel (bit-identical to launch_rmsnorm followed by launch_gemv).  Only where
-// gemv_norm_supported(M, K): M <= 4 rows whose normalised copies fit 48 KB of LDS.
+// gemv_norm_supported(M, K): M <= 4 rows whose normalised copies fit 48 KB of LDS.  (Decode-style layers use it for one
+// row, and two of at most 8192 output columns.)
 bool gemv_norm_supported(int M, int K);
 void launch_gemv_norm(const float* xf, const float* gamma, float eps, const bf16_t* W, void* out, int M, int N, int K,
                       int64_t ldo, int epilogue, int act, hipStream_t st);
-// (n_parts > 1: qkv is given as that many fp32 partial products, part_stride elements apart, which are added in
-// index order first: the second kernel of a QKV projection whose K range was split)
 
-// Fewest keys per split of the decode attention: a 2K-token context already gives every CU a work-group
-// (len / 64 splits x KV heads x sequences).
+// Fewest keys per split of the decode attention (how many a split has is chosen at the launch: as many as make about
+// three work-groups per CU of the whole call); what the buffer of partial results is sized by.
 constexpr int kDecodeKeysPerSplit = 64;
 
-// Attention of one query row per sequence over its paged cache entries 0..len-1 (len = pos + 1),
-// split over the key range; `part` holds the per-split partial results.
 // RoPE of one new token per sequence + cache append: qkv fp32 [B, ld] -> q bf16 [B, Hq*hd] rotated,
-// k (rotated) and v stored at slot[b].
+// k (rotated) and v stored at slot[b].  n_parts > 1: qkv is given as that many fp32 partial products, part_stride
+// elements apart, which are added in index order first: the second kernel of a QKV projection whose K range was split.
 void launch_rope_append(const float* qkv, int ld, bf16_t* q_out, int n_q_heads, int n_kv_heads, int hd,
                         const int32_t* pos, const int32_t* slot, double theta, bf16_t* k_pool,
                         bf16_t* v_pool, int page_size, int B, hipStream_t st, const float* q_gamma = nullptr,
                         const float* k_gamma = nullptr, float qk_eps = 0.f, int n_parts = 1, size_t part_stride = 0,
                         KvQuant kvq = KvQuant{0, 1.f, 1.f, 1.f, 1.f});
 
+// Attention of one query row per sequence over its paged cache entries 0..len-1 (len = pos + 1),
+// split over the key range; `part` holds the per-split partial results.
 struct AttnDecodeArgs {
   const bf16_t* q;        // [B, Hq*hd] rotated query rows (launch_rope_append), unused when qkv_raw is given
   const bf16_t* k_pool;   // this layer's pools; with qkv_raw the query position's entry is written by the kernel

@@ -1,8 +1,12 @@
 """Which tile shapes, K parts and launches the bf16 GEMM takes for a problem, as the library reports it.  No GPU needed."""
+import csv
+import os
+
 import pytest
 
 from tests.test_gpu_gemm_tiles import SIZES, SPLIT_SIZES
 
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 pop = pytest.importorskip("paper_2602_03295_amd.pop", reason="libpop.so not built")
 
 
@@ -70,3 +74,25 @@ def test_sizes_of_the_tile_tests_cover_every_shape():
 def test_sizes_of_the_split_tests_are_split():
     parts = [pop.pop_op_gemm_plan(M, N, K, 3, scratch_bytes=32 * M * N)["k_parts"] for M, N, K in SPLIT_SIZES]
     assert min(parts) >= 2 and {2, 4, 8} <= set(parts), parts
+
+
+def test_choice_against_the_measured_times():
+    """profiles/gemm_tile_timings.csv: every shape's time for 488 problems (MI355X).  Where the library takes one launch and
+    no split, its choice is the fastest shape or near it."""
+    best, times = {}, {}
+    with open(os.path.join(ROOT, "profiles", "gemm_tile_timings.csv")) as f:
+        for row in csv.DictReader(f):
+            if row["k_parts"] != "1":
+                continue
+            problem = tuple(int(row[c]) for c in ("M", "N", "K", "epilogue"))
+            for name, t in row.items():
+                if "x" in name and t:
+                    times[problem + tuple(map(int, name.split("x")))] = float(t)
+                    best[problem] = min(best.get(problem, 1e30), float(t))
+    lost = []
+    for problem, t in best.items():
+        p = pop.pop_op_gemm_plan(*problem)
+        if p["tail"] is None and problem + p["tile"] in times:
+            lost.append(times[problem + p["tile"]] / t - 1)
+    assert len(lost) >= 400
+    assert sum(lost) / len(lost) <= 0.01 and max(lost) <= 0.12
