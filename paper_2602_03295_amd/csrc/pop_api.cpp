@@ -201,7 +201,7 @@ int down_split_parts(int T, int d, int f) {
 struct Workspace {
   // int32 meta (one upload per call)
   size_t meta_bytes;
-  size_t o_tokens, o_row_src, o_pos, o_slot, o_cu, o_vt_off, o_t64_seq, o_t64_start, o_ta_seq, o_ta_start, o_ta_start2,
+  size_t o_tokens, o_row_src, o_pos, o_slot, o_cu, o_vt_off, o_t64_seq, o_t64_start, o_ta,
       o_bnd_row, o_bnd_pos, o_bnd_slot, o_bt, o_kv_first, o_wl_full, o_wl_tail, o_kvd_full, o_kvd_tail, o_tr_row, o_tr_pos, o_tr_slot,
       o_tr_cu, o_tr_t64_seq, o_tr_t64_start;
   // device buffers
@@ -240,9 +240,7 @@ Workspace carve(const pop_config& c, int T, int B, int maxp) {
   w.o_vt_off = take(4 * (size_t)B);
   w.o_t64_seq = take(4 * (size_t)w.nt64_max);
   w.o_t64_start = take(4 * (size_t)w.nt64_max);
-  w.o_ta_seq = take(4 * (size_t)w.nta_max);
-  w.o_ta_start = take(4 * (size_t)w.nta_max);
-  w.o_ta_start2 = take(4 * (size_t)w.nta_max);
+  w.o_ta = take(sizeof(pop::AttnTile) * (size_t)w.nta_max);
   w.o_bnd_row = take(4 * (size_t)B);
   w.o_bnd_pos = take(4 * (size_t)B);
   w.o_bnd_slot = take(4 * (size_t)B);
@@ -360,38 +358,50 @@ pop_status slot_map_impl(const int32_t* cu, int n_seqs, const int32_t* bt, int m
   return POP_OK;
 }
 
-// Work list of the prefill attention kernel.  A work-group processes one or two query tiles of 128
-// rows of one sequence: the k-th latest tile (most keys) is paired with the k-th earliest (fewest),
-// so every work-group of a sequence sees the same number of key tiles and the causal triangle is
-// balanced.  Longer sequences (more work per pair) come first.  Where the tiles of all heads do not fill the chip once,
-// each gets a work-group of its own instead (prompts of 77 + 301 + 150 tokens, 32 heads: the paired work-groups took 26
-// us for 7 key tiles in a row).  Returns the number of entries.
-int build_attention_work(const int32_t* cu, int B, int n_heads, int32_t* seq_out, int32_t* start_out, int32_t* start2_out) {
-  struct Item { int work, seq, a, b; };
-  std::vector<Item> items;
-  long long tiles = 0;
-  for (int b = 0; b < B; ++b) tiles += (cu[b + 1] - cu[b] + 127) / 128;
-  const bool single = tiles * n_heads <= 256;
+// Work list of the prefill attention kernel.  Returns the number of entries.
+int build_attention_work(const int32_t* cu, int B, int n_heads, int hd, pop::AttnTile* out, int* tile_rows) {
+  std::vector<pop::AttnTile> items;
+  auto work = [](const pop::AttnTile& t) { return t.start + (t.start2 < 0 ? 0 : t.start2); };
+  // Head sizes 64 and 128 have two forms (see the kernel): tiles of 256 rows that step through their keys 64 at a time, and
+  // tiles of 128 rows, 128 keys at a time.  Estimated time of a form: its longest tile or an even share of all steps on
+  // each of 256 CUs, and a fixed part per work-group.  The constants (us; head size 128) are read off timings of 60 to 8192
+  // tokens, 32 heads, with both forms: 128 tokens 10.0 / 11.4 us (256 / 128 rows), 1000 31.2 / 22.8, 2048 56.6 / 48.6, 2500
+  // 70.8 / 75.0, 8192 520 / 565, four prompts of 500 24.1 / 25.7; of 26 sizes the rule misses one by 0.3 us.
+  auto us = [&](int rows, int per_step, double longest_us, double share_us, double fixed_us) {
+    double longest = 0, total = 0, wgs = 0;
+    for (int b = 0; b < B; ++b)
+      for (int end = 0, len = cu[b + 1] - cu[b]; end < len;) {
+        end = std::min(end + rows, len);
+        const int steps = ((end + 63) / 64 + per_step - 1) / per_step;
+        longest = std::max<double>(longest, steps);
+        total += (double)steps * n_heads;
+        wgs += n_heads;
+      }
+    return std::max(longest * longest_us, total / 256 * share_us) + std::max(1.0, wgs / 256) * fixed_us;
+  };
+  auto tiles = [&](int rows) {
+    long long n = 0;
+    for (int b = 0; b < B; ++b) n += (cu[b + 1] - cu[b] + rows - 1) / rows;
+    return n * n_heads;
+  };
+  *tile_rows = hd <= 128 && us(256, 1, 1.5, 1.9, 8.6) <= us(128, 2, 1.95, 1.95, 9.7) ? 256 : 128;
+  const int rows = *tile_rows;
+  // Head size 256: one or two query tiles of a sequence; the k-th latest tile (most keys) is paired with the k-th earliest
+  // (fewest), which balances the causal triangle.  Where the tiles of all heads do not fill the chip once, each gets a
+  // work-group of its own instead.
+  const bool pairs = hd > 128 && tiles(128) > 256;
+  int vt_off = 0;
   for (int b = 0; b < B; ++b) {
-    const int len = cu[b + 1] - cu[b];
-    const int nt = (len + 127) / 128;
-    if (single) {
-      for (int k = 0; k < nt; ++k) items.push_back(Item{k + 1, b, k * 128, -1});
-      continue;
+    const int len = cu[b + 1] - cu[b], nt = (len + rows - 1) / rows;
+    for (int k = 0; k < (pairs ? (nt + 1) / 2 : nt); ++k) {
+      const int late = nt - 1 - k;
+      items.push_back(pop::AttnTile{late * rows, pairs && k < late ? k * rows : -1, cu[b], len, vt_off, {0, 0, 0}});
     }
-    for (int k = 0; k < (nt + 1) / 2; ++k) {
-      const int heavy = nt - 1 - k, light = k;
-      items.push_back(Item{heavy == light ? heavy + 1 : nt + 1, b, heavy * 128, heavy == light ? -1 : light * 128});
-    }
+    vt_off += (int)round_up(len, 64);
   }
-  std::stable_sort(items.begin(), items.end(), [](const Item& x, const Item& y) { return x.work > y.work; });
-  int n = 0;
-  for (const Item& it : items) {
-    seq_out[n] = it.seq;
-    start_out[n] = it.a;
-    start2_out[n++] = it.b;
-  }
-  return n;
+  std::stable_sort(items.begin(), items.end(), [&](const pop::AttnTile& x, const pop::AttnTile& y) { return work(x) > work(y); });
+  std::copy(items.begin(), items.end(), out);
+  return (int)items.size();
 }
 
 struct LayerCtx {
@@ -1151,7 +1161,7 @@ pop_status pop_prefill(pop_model* m, pop_cache* c, const pop_prefill_args* a, fl
   std::copy(row_src.begin(), row_src.end(), mi(w.o_row_src));
   std::copy(slots.begin(), slots.end(), mi(w.o_slot));
   std::copy(a->cu_seqlens, a->cu_seqlens + B + 1, mi(w.o_cu));
-  int n_t64 = 0, n_ta = 0, Tp = 0, max_len = 0;
+  int n_t64 = 0, n_ta = 0, ta_rows = 0, Tp = 0, max_len = 0;
   for (int b = 0; b < B; ++b) {
     const int s0 = a->cu_seqlens[b], len = a->cu_seqlens[b + 1] - s0;
     max_len = std::max(max_len, len);
@@ -1167,7 +1177,8 @@ pop_status pop_prefill(pop_model* m, pop_cache* c, const pop_prefill_args* a, fl
     mi(w.o_bnd_slot)[b] = slots[s0 + len - 1];
     std::copy(a->block_table + (size_t)b * maxp, a->block_table + (size_t)(b + 1) * maxp, mi(w.o_bt) + (size_t)b * maxp);
   }
-  n_ta = build_attention_work(a->cu_seqlens, B, cfg.n_q_heads, mi(w.o_ta_seq), mi(w.o_ta_start), mi(w.o_ta_start2));
+  n_ta = build_attention_work(a->cu_seqlens, B, cfg.n_q_heads, cfg.head_dim, reinterpret_cast<pop::AttnTile*>(meta.data() + w.o_ta),
+                              &ta_rows);
   record_kv_first(c, a, plan, mi(w.o_kv_first));
   // Pruned layers in two lists: those that store an entry for every row, and (window_kv_writes) the
   // sliding-window ones that store the tail rows only.  A run of consecutive pruned layers is a range of each.
@@ -1305,9 +1316,7 @@ pop_status pop_prefill(pop_model* m, pop_cache* c, const pop_prefill_args* a, fl
     ap.qkv = qkv; ap.ld = Dqkv; ap.q_col = 0; ap.k_col = Dq; ap.vT = vT; ap.Tp = Tp; ap.out = attn;
     ap.T = T; ap.n_q_heads = cfg.n_q_heads; ap.n_kv_heads = cfg.n_kv_heads; ap.hd = hd;
     ap.window = glob ? 0 : cfg.sliding_window;
-    ap.cu_seqlens = d_cu; ap.vt_off = d_vt_off;
-    ap.tile_seq = at<int32_t>(ws, w.o_ta_seq); ap.tile_start = at<int32_t>(ws, w.o_ta_start);
-    ap.tile_start2 = at<int32_t>(ws, w.o_ta_start2); ap.n_tiles = n_ta;
+    ap.tiles = at<pop::AttnTile>(ws, w.o_ta); ap.n_tiles = n_ta; ap.tile_rows = ta_rows;
     {
       StepTimer tm(m, st, POP_STEP_ATTENTION);
       hipError_t e = pop::launch_attention_prefill(ap, st);
@@ -1768,7 +1777,7 @@ pop_status pop_op_gemv_norm(const void* x, const void* gamma, float eps, const v
 
 namespace {
 struct RopeAttnWs {
-  size_t o_pos, o_cu, o_vt_off, o_t64_seq, o_t64_start, o_ta_seq, o_ta_start, o_ta_start2, meta_bytes, o_cs, o_vT, total;
+  size_t o_pos, o_cu, o_vt_off, o_t64_seq, o_t64_start, o_ta, meta_bytes, o_cs, o_vT, total;
   int Tp_max;
 };
 RopeAttnWs carve_rope_attn(int T, int B, int Hkv, int hd) {
@@ -1781,9 +1790,7 @@ RopeAttnWs carve_rope_attn(int T, int B, int Hkv, int hd) {
   w.o_vt_off = take(4 * (size_t)B);
   w.o_t64_seq = take(4 * ((size_t)T / 64 + B));
   w.o_t64_start = take(4 * ((size_t)T / 64 + B));
-  w.o_ta_seq = take(4 * ((size_t)T / 128 + B));
-  w.o_ta_start = take(4 * ((size_t)T / 128 + B));
-  w.o_ta_start2 = take(4 * ((size_t)T / 128 + B));
+  w.o_ta = take(sizeof(pop::AttnTile) * ((size_t)T / 128 + B));
   w.meta_bytes = o;
   w.o_cs = take(8 * (size_t)T * (hd / 2));
   w.o_vT = take(2 * (size_t)Hkv * hd * w.Tp_max);
@@ -1814,7 +1821,7 @@ pop_status pop_op_rope_attention(void* qkv, const int32_t* cu, int32_t B, int32_
   std::vector<unsigned char> meta(w.meta_bytes, 0);
   auto mi = [&](size_t off) { return reinterpret_cast<int32_t*>(meta.data() + off); };
   std::copy(cu, cu + B + 1, mi(w.o_cu));
-  int n64 = 0, nta = 0, Tp = 0;
+  int n64 = 0, Tp = 0;
   for (int b = 0; b < B; ++b) {
     const int len = cu[b + 1] - cu[b];
     for (int t = 0; t < len; ++t) mi(w.o_pos)[cu[b] + t] = t;
@@ -1822,7 +1829,8 @@ pop_status pop_op_rope_attention(void* qkv, const int32_t* cu, int32_t B, int32_
     Tp += (int)round_up(len, 64);
     for (int p0 = 0; p0 < len; p0 += 64) { mi(w.o_t64_seq)[n64] = b; mi(w.o_t64_start)[n64++] = p0; }
   }
-  nta = build_attention_work(cu, B, Hq, mi(w.o_ta_seq), mi(w.o_ta_start), mi(w.o_ta_start2));
+  int ta_rows = 0;
+  const int nta = build_attention_work(cu, B, Hq, hd, reinterpret_cast<pop::AttnTile*>(meta.data() + w.o_ta), &ta_rows);
   hipStream_t st = reinterpret_cast<hipStream_t>(stream);
   POP_HIP(hipMemcpyAsync(workspace, meta.data(), w.meta_bytes, hipMemcpyHostToDevice, st));
   POP_HIP(hipStreamSynchronize(st));   // `meta` is pageable memory of this call: wait until it has been read
@@ -1844,10 +1852,7 @@ pop_status pop_op_rope_attention(void* qkv, const int32_t* cu, int32_t B, int32_
   pop::AttnPrefillArgs ap{};
   ap.qkv = (const bf16_t*)qkv; ap.ld = ld; ap.q_col = 0; ap.k_col = Dq; ap.vT = vT; ap.Tp = Tp; ap.out = (bf16_t*)out;
   ap.T = T; ap.n_q_heads = Hq; ap.n_kv_heads = Hkv; ap.hd = hd; ap.window = window;
-  ap.cu_seqlens = rw.cu_seqlens; ap.vt_off = rw.vt_off;
-  ap.tile_seq = at<int32_t>(workspace, w.o_ta_seq); ap.tile_start = at<int32_t>(workspace, w.o_ta_start);
-  ap.tile_start2 = at<int32_t>(workspace, w.o_ta_start2);
-  ap.n_tiles = nta;
+  ap.tiles = at<pop::AttnTile>(workspace, w.o_ta); ap.n_tiles = nta; ap.tile_rows = ta_rows;
   hipError_t e = pop::launch_attention_prefill(ap, st);
   if (e != hipSuccess) return fail(POP_EHIP, "attention launch failed: %s", hipGetErrorString(e));
   return POP_OK;

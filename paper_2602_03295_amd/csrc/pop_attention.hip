@@ -1,9 +1,10 @@
 // Causal grouped-query flash attention for the prompt body (the Attn block of Sec. 2.1 applied to
 // all body rows of a kept layer at once), packed variable-length sequences, optional sliding window.
 //
-// One work-group = one or two tiles of 128 query rows of one query head (a late tile paired with an
-// early one, which balances the causal triangle); 4 waves x 32 rows.  Keys/values stream through
-// LDS in tiles of 64, staged with buffer_load ... lds and double buffered.
+// A wave owns 32 query rows of one query head.  Keys/values stream through LDS in tiles of 64, staged with
+// buffer_load ... lds in a ring.  What bounds it at head size 128 (one work-group of the 32768-token prompt is busy for
+// 512 steps): the matrix pipe is 67 to 69 % busy at the 1.55 to 1.6 GHz that the power limit leaves; per step of 64 keys and 256
+// rows, 2048 cycles of MFMAs, 2 x 785 of vector instructions, 512 of the address unit for the staged tiles.
 //
 // Inside this kernel Q, K, V and P are fp16 (the RoPE/append kernel hands over fp16 copies; the cache
 // itself stays bf16): with random-like V the softmax average shrinks signal and rounding noise alike, so
@@ -54,9 +55,11 @@ __device__ __forceinline__ int k_swz(int row) {
   return ROW_BYTES >= 256 ? (row & 15) : ((row >> 1) & 7);
 }
 
-template <int HD>
-__global__ __launch_bounds__(256) void attn_prefill_kernel(AttnPrefillArgs a, float scale_log2) {
+// Head size 256, whose O and Q leave no registers for two waves per SIMD: one or two tiles of 128 query rows of one query head
+// per work-group (a late tile paired with an early one, which balances the causal triangle); 4 waves x 32 rows, one per SIMD.
+__global__ __launch_bounds__(256) void attn_prefill256_kernel(AttnPrefillArgs a, float scale_log2) {
 #if defined(__HIP_DEVICE_COMPILE__)  // the buffer-resource builtins exist in the device pass only
+  constexpr int HD = 256;
   constexpr int KS = HD / 16;            // MFMA steps over the head dim for S
   constexpr int OB = HD / 32;            // 32-row blocks of O^T
   constexpr int K_ROW_BYTES = HD * 2;
@@ -65,7 +68,7 @@ __global__ __launch_bounds__(256) void attn_prefill_kernel(AttnPrefillArgs a, fl
   constexpr int K_BYTES = BKV * K_ROW_BYTES;
   constexpr int V_BYTES = HD * BKV * 2;  // V^T tile: HD rows of 64 keys (128 B)
   constexpr int STAGE = K_BYTES + V_BYTES;
-  constexpr int NST = HD <= 128 ? 3 : 2;   // LDS ring: K and V^T tiles are requested NST-1 iterations ahead
+  constexpr int NST = 2;                 // LDS ring: K and V^T tiles are requested NST-1 iterations ahead
   constexpr int DPF = NST - 1;
   constexpr uint32_t kOOB = 0x80000000u;   // pushes a byte offset out of range: the lane stages zeros
   constexpr int K_LOADS = K_BYTES / 1024 / 4, V_LOADS = V_BYTES / 1024 / 4;  // per wave
@@ -73,18 +76,16 @@ __global__ __launch_bounds__(256) void attn_prefill_kernel(AttnPrefillArgs a, fl
 
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
 
-  const int tile = blockIdx.x;
+  const AttnTile tile = a.tiles[blockIdx.x];
   const int head = blockIdx.y;
   const int kvh = head / (a.n_q_heads / a.n_kv_heads);
-  const int b = a.tile_seq[tile];
-  const int seq0 = a.cu_seqlens[b];
-  const int len = a.cu_seqlens[b + 1] - seq0;
+  const int seq0 = tile.seq0, len = tile.len;
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int h = lane >> 5;
   // one or two query tiles per work-group (a late and an early tile of the same sequence)
   for (int part = 0; part < 2; ++part) {
-  const int q0 = part == 0 ? a.tile_start[tile] : a.tile_start2[tile];
+  const int q0 = part == 0 ? tile.start : tile.start2;
   if (q0 < 0) break;
   if (part == 1) __builtin_amdgcn_s_barrier();  // everyone is done with the first tile's LDS stages
   const int qrow = q0 + wave * 32 + (lane & 31);  // position of this lane's query row
@@ -116,7 +117,7 @@ __global__ __launch_bounds__(256) void attn_prefill_kernel(AttnPrefillArgs a, fl
   for (int j = 0; j < V_LOADS; ++j) {
     const int row = (j * 4 + wave) * 8 + (lane >> 3);
     const int c = (lane & 7) ^ ((row >> 1) & 7);
-    offV[j] = (uint32_t)((((long long)kvh * HD + row) * a.Tp + a.vt_off[b] + c * 8) * 2);
+    offV[j] = (uint32_t)((((long long)kvh * HD + row) * a.Tp + tile.vt_off + c * 8) * 2);
   }
   // The key offset goes into the per-lane offset (not the scalar one) so that rows beyond the end of
   // the buffer are range-checked and read as zero.
@@ -181,11 +182,10 @@ __global__ __launch_bounds__(256) void attn_prefill_kernel(AttnPrefillArgs a, fl
   constexpr int SN = 2 * KS;           // MFMAs of one S tile, index ks*2 + kb
   constexpr int NM = PVN + SN;
   constexpr int DIST = 4;              // fragment reads run this many MFMAs ahead
-  constexpr bool UNROLL2 = HD <= 128;  // head_dim 256 has no registers to spare for the unrolled form
-  // S^T of tile t lives in sbuf[t & 1] and the packed fp16 P^T of tile t in pbuf[t & 1]; the loop is
-  // unrolled by two so that these indices are compile-time constants (no register copies).
-  floatx16_t sbuf[2][2];
-  uint32_t pbuf[2][2][2][4];
+  // S^T of the current and of the next tile, the packed fp16 P^T of the current and of the last one (copied at the end of an
+  // iteration: there are no registers to spare for a loop unrolled by two)
+  floatx16_t s_cur[2], s_next[2];
+  uint32_t pw[2][2][4], pw_prev[2][2][4];
   typedef _Float16 half2_t __attribute__((ext_vector_type(2)));
   typedef float float2_t __attribute__((ext_vector_type(2)));
   const floatx16_t zero16 = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
@@ -210,13 +210,8 @@ __global__ __launch_bounds__(256) void attn_prefill_kernel(AttnPrefillArgs a, fl
   // half of the row (mx_other, lane ^ 32, fetched through the LDS crossbar)
   float mx_part = -INFINITY, mx_other = -INFINITY;
 
-  auto body = [&](int t, auto par_c, auto has_pv_c, auto has_s_c) {
-    constexpr int PAR = decltype(par_c)::value;   // t & 1
+  auto body = [&](int t, auto has_pv_c, auto has_s_c) {
     constexpr bool HAS_PV = decltype(has_pv_c)::value, HAS_S = decltype(has_s_c)::value;
-    floatx16_t(&s_cur)[2] = sbuf[PAR];
-    floatx16_t(&s_next)[2] = sbuf[PAR ^ 1];
-    uint32_t(&pw)[2][2][4] = pbuf[PAR];
-    uint32_t(&pw_prev)[2][2][4] = pbuf[PAR ^ 1];
     // MFMAs of this iteration in issue order: S^T of tile t+1 (slots 0..15), then the O update with
     // tile t-1 (slots 16..31).  Once S^T is complete its row maximum is formed in the later slots, so
     // the next iteration starts its exponentials at once.
@@ -336,15 +331,13 @@ __global__ __launch_bounds__(256) void attn_prefill_kernel(AttnPrefillArgs a, fl
     }
     l_run += psum;
     m_run = m_new;
-    if (!UNROLL2) {   // single-parity form: move the results to where the next iteration expects them
 #pragma unroll
-      for (int kb = 0; kb < 2; ++kb) {
-        if (HAS_S) s_cur[kb] = s_next[kb];
+    for (int kb = 0; kb < 2; ++kb) {
+      if (HAS_S) s_cur[kb] = s_next[kb];
 #pragma unroll
-        for (int g = 0; g < 2; ++g)
+      for (int g = 0; g < 2; ++g)
 #pragma unroll
-          for (int e = 0; e < 4; ++e) pw_prev[kb][g][e] = pw[kb][g][e];
-      }
+        for (int e = 0; e < 4; ++e) pw_prev[kb][g][e] = pw[kb][g][e];
     }
   };
   using std::true_type;
@@ -365,18 +358,17 @@ __global__ __launch_bounds__(256) void attn_prefill_kernel(AttnPrefillArgs a, fl
 #pragma unroll
       for (int kb = 0; kb < 2; ++kb) {
         const f16x8_t kf = *reinterpret_cast<const f16x8_t*>(smem + k_frag + kb * 32 * K_ROW_BYTES + pc);
-        sbuf[0][kb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(kf, qf[ks], ks == 0 ? zero16 : sbuf[0][kb], 0, 0, 0);
+        s_cur[kb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(kf, qf[ks], ks == 0 ? zero16 : s_cur[kb], 0, 0, 0);
       }
     }
-    if (tile_needs_mask(j_begin)) mask_tile(sbuf[0], j_begin);
+    if (tile_needs_mask(j_begin)) mask_tile(s_cur, j_begin);
 #pragma unroll
     for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
-      for (int v = 0; v < 16; ++v) mx_part = fmaxf(mx_part, sbuf[0][kb][v]);
+      for (int v = 0; v < 16; ++v) mx_part = fmaxf(mx_part, s_cur[kb][v]);
     mx_other = __shfl_xor(mx_part, 32, 64);
     // O update of the last tile (all remaining loads are masked ones; drain them before the ring is reused)
-    auto last_pv = [&](auto par_c) {
-      constexpr int PAR = decltype(par_c)::value;
+    auto last_pv = [&] {
       asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
       __builtin_amdgcn_s_barrier();
       const unsigned char* sv = smem + ((n_kv - 1) % NST) * STAGE + K_BYTES;
@@ -385,7 +377,7 @@ __global__ __launch_bounds__(256) void attn_prefill_kernel(AttnPrefillArgs a, fl
 #pragma unroll
         for (int g = 0; g < 2; ++g) {
           const int pc = ((4 * kb + 2 * g + h) ^ v_sw) * 16;
-          const uint4 w4 = make_uint4(pbuf[PAR][kb][g][0], pbuf[PAR][kb][g][1], pbuf[PAR][kb][g][2], pbuf[PAR][kb][g][3]);
+          const uint4 w4 = make_uint4(pw_prev[kb][g][0], pw_prev[kb][g][1], pw_prev[kb][g][2], pw_prev[kb][g][3]);
 #pragma unroll
           for (int i = 0; i < OB; ++i) {
             const f16x8_t vf = *reinterpret_cast<const f16x8_t*>(sv + v_frag + i * 32 * 128 + pc);
@@ -393,33 +385,14 @@ __global__ __launch_bounds__(256) void attn_prefill_kernel(AttnPrefillArgs a, fl
           }
         }
     };
-    typedef std::integral_constant<int, 0> P0;
-    typedef std::integral_constant<int, 1> P1;
     if (n_kv == 1) {
-      body(0, P0{}, false_type{}, false_type{});
-      if (UNROLL2) last_pv(P0{});
-      else last_pv(P1{});
-    } else if (!UNROLL2) {
-      body(0, P0{}, false_type{}, true_type{});
-      for (int t = 1; t < n_kv - 1; ++t) body(t, P0{}, true_type{}, true_type{});
-      body(n_kv - 1, P0{}, true_type{}, false_type{});
-      last_pv(P1{});
+      body(0, false_type{}, false_type{});
     } else {
-      body(0, P0{}, false_type{}, true_type{});
-      int t = 1;
-      for (; t + 1 < n_kv - 1; t += 2) {
-        body(t, P1{}, true_type{}, true_type{});
-        body(t + 1, P0{}, true_type{}, true_type{});
-      }
-      if (t < n_kv - 1) {   // one more middle tile, then the last one has even parity
-        body(t, P1{}, true_type{}, true_type{});
-        body(t + 1, P0{}, true_type{}, false_type{});
-        last_pv(P0{});
-      } else {
-        body(t, P1{}, true_type{}, false_type{});
-        last_pv(P1{});
-      }
+      body(0, false_type{}, true_type{});
+      for (int t = 1; t < n_kv - 1; ++t) body(t, true_type{}, true_type{});
+      body(n_kv - 1, true_type{}, false_type{});
     }
+    last_pv();
   }
 
   // ---- normalise and store: lane owns query row qrow, head-dim i*32 + (v/4)*8 + 4h + v%4
@@ -440,15 +413,355 @@ __global__ __launch_bounds__(256) void attn_prefill_kernel(AttnPrefillArgs a, fl
 #endif
 }
 
-template <int HD>
-hipError_t launch_hd(const AttnPrefillArgs& a, hipStream_t st) {
-  constexpr int smem = (HD <= 128 ? 3 : 2) * (BKV * HD * 2 + HD * BKV * 2);
-  // once per head size; the initialisation of a function-local static is thread-safe
-  static const hipError_t attr_err = hipFuncSetAttribute(reinterpret_cast<const void*>(&attn_prefill_kernel<HD>),
+// Head sizes 64 and 128: eight waves of 32 query rows, two per SIMD.  A wave's work on a tile of 64 keys is a matrix phase
+// (S^T of the next tile, then O^T += V^T P^T of the last one: 32 MFMAs at head size 128) and a vector phase (softmax of
+// S^T).  Waves 4-7 meet a step's barrier half a step later than waves 0-3, so that on every SIMD one wave feeds the matrix
+// pipe while the other one computes exponentials.
+//   SPLIT false: a tile of 256 query rows; a step is one tile of 64 keys that all waves share.
+//   SPLIT true:  a tile of 128 query rows; a step is two tiles of keys, one for waves 0-3 and one for waves 4-7 (the same
+//                rows), merged through LDS at the end: half the steps, for calls whose tiles do not fill the chip.
+// One wave per SIMD that interleaved both phases (128 rows, three slots), against this kernel: 300 tokens 12.7 -> 11.8 us, 1000
+// 27.2 -> 22.8, 2048 55.6 -> 48.6, 6144 378 -> 315, 8192 634 -> 520, 32768 9.9 -> 7.8 ms (0.87 -> 1.1 PFLOP/s).  Two key
+// tiles per step throughout (twice the bytes through the address unit) took 9.1 ms there.
+template <int HD, bool SPLIT>
+__global__ __launch_bounds__(512) void attn_prefill8_kernel(AttnPrefillArgs a, float scale_log2) {
+#if defined(__HIP_DEVICE_COMPILE__)  // the buffer-resource builtins exist in the device pass only
+  constexpr int KS = HD / 16;            // MFMA steps over the head dim for S
+  constexpr int OB = HD / 32;            // 32-row blocks of O^T
+  constexpr int ROW = HD * 2;            // bytes of a K row
+  constexpr int K_CPR = HD / 8;          // 16-byte chunks per K row
+  constexpr int K_RPL = 64 / K_CPR;      // K rows per wave-load
+  constexpr int TILE = BKV * ROW;        // bytes of a K tile, and of a V^T tile (HD rows of 64 keys)
+  constexpr int TPS = SPLIT ? 2 : 1;     // key tiles per step
+  constexpr int NST = SPLIT ? 2 : 4;     // LDS slots, of a step's K tiles and V^T tiles
+  constexpr int SLOT = 2 * TPS * TILE;
+  constexpr int LOADS = TPS * TILE / 1024 / 8;   // wave-loads of K (and of V^T) per wave and step
+  constexpr uint32_t kOOB = 0x80000000u;       // pushes a byte offset out of range: the lane stages zeros
+
+  extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
+
+  // consecutive work-groups (neighbouring XCDs) take different KV heads: the query heads of one share an XCD's L2
+  const int kvh = blockIdx.x % a.n_kv_heads;
+  const int head = kvh * (a.n_q_heads / a.n_kv_heads) + blockIdx.x / a.n_kv_heads;
+  const AttnTile tile = a.tiles[blockIdx.y];
+  const int q0 = tile.start, seq0 = tile.seq0, len = tile.len;
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int grp = wave >> 2;
+  const int h = lane >> 5;
+  // query positions of this wave (the two waves of a SIMD, w and w + 4, take neighbouring rows: nearly the same keys)
+  const int wave_first = q0 + (SPLIT ? wave & 3 : (wave & 3) * 2 + grp) * 32, wave_last = wave_first + 31;
+  const int qrow = wave_first + (lane & 31);      // position of this lane's query row
+  const bool qvalid = qrow < len;
+
+  // ---- key range of this query tile
+  const int q_last = min(q0 + (SPLIT ? 128 : 256), len) - 1;
+  int j_begin = 0;
+  if (a.window > 0) j_begin = max(0, q0 - a.window + 1) & ~(BKV - 1);
+  const int n_kv = (q_last + 1 - j_begin + BKV - 1) / BKV;
+  const int n_steps = (n_kv + TPS - 1) / TPS;
+
+  const __amdgpu_buffer_rsrc_t rK = __builtin_amdgcn_make_buffer_rsrc(
+      const_cast<bf16_t*>(a.qkv), 0, (uint32_t)((long long)a.T * a.ld * 2), 0x00020000);
+  const __amdgpu_buffer_rsrc_t rV = __builtin_amdgcn_make_buffer_rsrc(
+      const_cast<bf16_t*>(a.vT), 0, (uint32_t)((long long)a.n_kv_heads * HD * a.Tp * 2), 0x00020000);
+
+  // ---- Q fragments (B operand: lane = query row, 8 consecutive head-dim values per step)
+  f16x8_t qf[KS];
+  {
+    const bf16_t* qp = a.qkv + ((long long)seq0 + (qvalid ? qrow : 0)) * a.ld + a.q_col + head * HD + h * 8;
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) qf[ks] = *reinterpret_cast<const f16x8_t*>(qp + ks * 16);
+  }
+
+  // staging offsets of this wave's first wave-load (K: rows = keys; V^T: rows = head-dim index); the j-th one is 8 KB further
+  // on in LDS: 8 * K_RPL keys, or 64 head-dim rows and from TILE on the second tile's keys
+  uint32_t offK, offV;
+  {
+    const int row = wave * K_RPL + lane / K_CPR;
+    const int c = (lane % K_CPR) ^ k_swz<ROW>(row);
+    offK = (uint32_t)((((long long)seq0 + row) * a.ld + a.k_col + kvh * HD + c * 8) * 2);
+    const int vrow = wave * 8 + (lane >> 3);
+    const int vc = (lane & 7) ^ ((vrow >> 1) & 7);
+    offV = (uint32_t)((((long long)kvh * HD + vrow) * a.Tp + tile.vt_off + vc * 8) * 2);
+  }
+  // Step t reads K of its tiles and V^T of those of step t - 1 (the O update runs a step behind), from slot t % NST.  The key
+  // offset goes into the per-lane offset (not the scalar one) so that rows beyond the end of the buffer are range-checked
+  // and read as zero; tiles outside the range are requested with every lane out of range, which keeps the number of loads
+  // per step uniform for the vmcnt bookkeeping below.
+  auto issue1 = [&](int t, int j) {      // wave-load j of step t: K, then V^T
+    unsigned char* base = smem + (t % NST) * SLOT + wave * 1024;
+    const int jj = j % LOADS, sub = jj * TPS / LOADS;            // sub: which of the step's tiles
+    if (j < LOADS)
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(
+          rK, (lds_ptr_t)(base + jj * 8192), 16,
+          (offK + (uint32_t)((j_begin + t * TPS * BKV + jj * 8 * K_RPL) * a.ld * 2)) | (t * TPS + sub < n_kv ? 0u : kOOB), 0, 0, 0);
+    else
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(
+          rV, (lds_ptr_t)(base + TPS * TILE + jj * 8192), 16,
+          (offV + (uint32_t)((j_begin + ((t - 1) * TPS + sub) * BKV + (jj % (LOADS / TPS)) * 64 * a.Tp) * 2)) |
+              (t > 0 && (t - 1) * TPS + sub < n_kv ? 0u : kOOB), 0, 0, 0);
+  };
+  auto issue = [&](int t) {
+#pragma unroll
+    for (int j = 0; j < 2 * LOADS; ++j) issue1(t, j);
+  };
+  // Barrier t: step t's tiles have landed (loads return in order) and nobody reads those of step t - 1 any more, whose slot is
+  // refilled during step t.  With four slots those of step t + 1 have landed too (only the loads of step t + 2 may still
+  // be in flight), which lets a wave read its first fragments ahead of the barrier.
+  constexpr bool AHEAD = NST == 4;
+  auto sync = [&] {
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(AHEAD ? 2 * LOADS : 0) : "memory");
+    __builtin_amdgcn_s_barrier();
+  };
+#pragma unroll
+  for (int t = 0; t < NST - 1; ++t) issue(t);
+
+  // LDS fragment addresses: chunk c of a row is at c ^ key(row), so that steps over the head dim (K) or the keys (V^T) are an
+  // exclusive or on the address
+  const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_ptr_t)smem;
+  const int krow = key_of_row(lane & 31);        // (same key for krow + 32)
+  const uint32_t k_frag = lds0 + (SPLIT ? grp : 0) * TILE + krow * ROW + (h ^ k_swz<ROW>(krow)) * 16;
+  const uint32_t v_frag = lds0 + (TPS + (SPLIT ? grp : 0)) * TILE + (lane & 31) * 128 + (h ^ (((lane & 31) >> 1) & 7)) * 16;
+  typedef const __attribute__((address_space(3))) f16x8_t* lds_frag_t;
+
+  typedef _Float16 half2_t __attribute__((ext_vector_type(2)));
+  typedef float float2_t __attribute__((ext_vector_type(2)));
+  const floatx16_t zero16 = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+  floatx16_t o[OB];
+#pragma unroll
+  for (int i = 0; i < OB; ++i) o[i] = zero16;
+  float m_run = -INFINITY, m_use = 0.f, l_run = 0.f;
+  floatx16_t s[2];                     // S^T of the current tile
+  uint32_t pw[2][2][4];                // and its packed fp16 P^T
+
+  // the steps t_lo .. t_hi - 1 bring this wave a tile with a key that some of its rows see
+  const int j_own = j_begin + (SPLIT ? grp : 0) * BKV;   // first key of this wave's tile in step 0
+  int t_lo = 0, t_hi = 0;
+  if (wave_first < len) {
+    t_hi = min(n_steps, (wave_last - j_own + TPS * BKV) / (TPS * BKV));
+    if (a.window > 0)      // tiles whose last key is before the window of the first row
+      t_lo = max(0, wave_first - a.window + 1 - j_own - BKV + TPS * BKV) / (TPS * BKV);
+  }
+  constexpr int PVN = 4 * OB, SN = 2 * KS, DIST = 6;   // fragment reads run DIST MFMAs ahead
+  f16x8_t pre[DIST];                     // the first fragments of the next matrix phase
+  auto read_k = [&](int t, int n) {      // fragment of the n-th S^T MFMA of step t
+    const int ks = n / 2, kb = n % 2;
+    return *(lds_frag_t)(((k_frag + (uint32_t)(t % NST) * SLOT) ^ (ks * 32)) + kb * 32 * ROW);
+  };
+  auto prefetch = [&](int t) {
+#pragma unroll
+    for (int n = 0; n < DIST; ++n) pre[n] = read_k(t, n);
+  };
+  // matrix phase of step t; its share of the loads of step t + NST - 1 goes between the MFMAs (in one burst behind the
+  // barrier the eight waves queue at the CU's one address unit)
+  auto matrix_phase = [&](int t, auto has_s_c, auto has_pv_c) {
+    constexpr bool HAS_S = decltype(has_s_c)::value, HAS_PV = decltype(has_pv_c)::value;
+    constexpr int NS = HAS_S ? SN : 0, CNT = NS + (HAS_PV ? PVN : 0), GAP = CNT / (2 * LOADS);
+    const uint32_t sv = v_frag + (uint32_t)(t % NST) * SLOT;
+    f16x8_t fr[CNT];
+    auto frag_read = [&](int n) {
+      if (n < NS) {
+        fr[n] = read_k(t, n);
+      } else {
+        const int idx = n - NS, kb = idx / (2 * OB), g = (idx / OB) % 2, i = idx % OB;
+        fr[n] = *(lds_frag_t)((sv ^ (kb * 64 + g * 32)) + i * 32 * 128);
+      }
+    };
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int n = 0; n < DIST && n < CNT; ++n) {
+      if (HAS_S && AHEAD) fr[n] = pre[n];
+      else frag_read(n);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int n = 0; n < CNT; ++n) {
+      if (n + DIST < CNT) frag_read(n + DIST);
+      if (n < NS) {
+        const int ks = n / 2, kb = n % 2;
+        s[kb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(fr[n], qf[ks], ks == 0 ? zero16 : s[kb], 0, 0, 0);
+      } else {
+        const int idx = n - NS, kb = idx / (2 * OB), g = (idx / OB) % 2, i = idx % OB;
+        const uint4 w4 = make_uint4(pw[kb][g][0], pw[kb][g][1], pw[kb][g][2], pw[kb][g][3]);
+        o[i] = __builtin_amdgcn_mfma_f32_32x32x16_f16(fr[n], __builtin_bit_cast(f16x8_t, w4), o[i], 0, 0, 0);
+      }
+      if (n % GAP == 0) issue1(t + NST - 1, n / GAP);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  };
+  // vector phase: softmax of S^T of tile t (register v of block kb on lane-half h: key j0 + kb*32 + 16*(v/8) + 8*h + v%8)
+  auto vector_phase = [&](int t) {
+    const int j0 = j_own + t * TPS * BKV;
+    if (j0 + BKV - 1 > wave_first || (a.window > 0 && j0 < wave_last - a.window + 1)) {
+#pragma unroll
+      for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+          const int key = j0 + kb * 32 + 16 * (v >> 3) + 8 * h + (v & 7);
+          bool ok = key <= qrow;
+          if (a.window > 0) ok = ok && (key > qrow - a.window);
+          if (!ok) s[kb][v] = -INFINITY;
+        }
+    }
+    float mxa = -INFINITY, mxb = -INFINITY;
+#pragma unroll
+    for (int v = 0; v < 16; v += 2) {
+      mxa = fmaxf(fmaxf(mxa, s[0][v]), s[0][v + 1]);
+      mxb = fmaxf(fmaxf(mxb, s[1][v]), s[1][v + 1]);
+    }
+    // a lane sees half of its row's keys; the other half (lane ^ 32) matters only where some lane outgrows the maximum
+    const float mx = fmaxf(mxa, mxb);
+    if (__builtin_amdgcn_ballot_w64(mx * scale_log2 > m_run + kMaxLag)) {
+      const float row_max = fmaxf(mx, __shfl_xor(mx, 32, 64)) * scale_log2;
+      const bool raise = row_max > m_run + kMaxLag;                // (m_run = -inf: any finite maximum)
+      const float m_new = raise ? row_max : m_run;
+      const float alpha = raise ? __builtin_amdgcn_exp2f(m_run - m_new) : 1.f;   // m_run = -inf -> 0
+      l_run *= alpha;
+#pragma unroll
+      for (int i = 0; i < OB; ++i)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) o[i][v] *= alpha;
+      m_run = m_new;
+      m_use = m_new == -INFINITY ? 0.f : m_new;
+    }
+    float sum0 = 0.f, sum1 = 0.f;
+#pragma unroll
+    for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+      for (int v = 0; v < 16; v += 2) {
+        const float e0 = __builtin_amdgcn_exp2f(s[kb][v] * scale_log2 - m_use);
+        const float e1 = __builtin_amdgcn_exp2f(s[kb][v + 1] * scale_log2 - m_use);
+        sum0 += e0;
+        sum1 += e1;
+        // 0 <= P <= 2^kMaxLag: plain round-to-nearest packing, no saturation needed
+        const float2_t pp = {e0, e1};
+        pw[kb][v >> 3][(v & 7) >> 1] = __builtin_bit_cast(uint32_t, __builtin_convertvector(pp, half2_t));
+      }
+    l_run += sum0 + sum1;
+    __builtin_amdgcn_sched_barrier(0);
+    if (AHEAD) prefetch(t + 1);
+  };
+  using std::true_type;
+  using std::false_type;
+  // Waves 0-3 meet barrier t before their matrix phase t, waves 4-7 meet barrier t + 1 after it: the same work in the same
+  // order, half a step apart.  (Loops with the test at the end: with it at the start the compiler keeps two copies of O.)
+  auto before = [&](int t) { if (grp == 0 && t > 0) sync(); };
+  auto after = [&](int t) { if (grp == 1 && t < n_steps) sync(); };
+  auto idle = [&](int t) { before(t); issue(t + NST - 1); after(t); };
+  sync();
+  int t = 0;
+  if (t_hi > t_lo) {
+    for (; t < t_lo; ++t) idle(t);
+    before(t);
+    if (AHEAD) prefetch(t);
+    matrix_phase(t, true_type{}, false_type{});
+    after(t);
+    vector_phase(t);
+    ++t;
+    if (t < t_hi) {
+      do {
+        before(t);
+        matrix_phase(t, true_type{}, true_type{});
+        after(t);
+        vector_phase(t);
+      } while (++t < t_hi);
+    }
+    before(t);
+    matrix_phase(t, false_type{}, true_type{});
+    after(t);
+    ++t;
+  }
+  for (; t <= n_steps; ++t) idle(t);
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the masked loads of the last steps still target this group's LDS
+
+  // ---- normalise and store.  A lane holds head-dims 32 i + 8 g + 4 h + (0..3) of its row; the halves of two groups g change
+  // places with lane ^ 32, so that a lane stores 16 consecutive bytes.
+  bf16_t* op = a.out + ((long long)seq0 + qrow) * ((long long)a.n_q_heads * HD) + head * HD + h * 8;
+  auto store_pair = [&](bf16_t* p, uint2 lo, uint2 hi) {      // groups g, g + 1
+    typedef uint32_t u2_t __attribute__((ext_vector_type(2)));
+    const u2_t x = __builtin_amdgcn_permlane32_swap(lo.x, hi.x, false, false);
+    const u2_t y = __builtin_amdgcn_permlane32_swap(lo.y, hi.y, false, false);
+    if (qvalid) *reinterpret_cast<uint4*>(p) = make_uint4(x[0], y[0], x[1], y[1]);
+  };
+  if constexpr (!SPLIT) {
+    const float l_tot = l_run + __shfl_xor(l_run, 32, 64);
+    const float inv = l_tot > 0.f ? 1.f / l_tot : 0.f;
+#pragma unroll
+    for (int i = 0; i < OB; ++i)
+#pragma unroll
+      for (int g = 0; g < 4; g += 2) {
+        uint2 pk[2];
+#pragma unroll
+        for (int e = 0; e < 2; ++e) {
+          const int v = (g + e) * 4;
+          pk[e] = make_uint2(pack_bf16x2(o[i][v] * inv, o[i][v + 1] * inv), pack_bf16x2(o[i][v + 2] * inv, o[i][v + 3] * inv));
+        }
+        store_pair(op + i * 32 + g * 8, pk[0], pk[1]);
+      }
+  } else {
+    // the waves w and w + 4 hold partial results of the same rows: each hands half of its O blocks over (in the ring, which is
+    // free once all have arrived) and stores the other half
+    __builtin_amdgcn_s_barrier();
+    constexpr int HB = OB / 2;
+    float4* const mo = reinterpret_cast<float4*>(smem);                       // [wave][HB * 4][64]
+    float2* const ms = reinterpret_cast<float2*>(smem + 8 * HB * 4 * 1024);   // [wave][64]
+#pragma unroll
+    for (int i = 0; i < HB; ++i)
+#pragma unroll
+      for (int g = 0; g < 4; ++g) {
+        const floatx16_t& x = grp == 0 ? o[i + HB] : o[i];
+        mo[(wave * HB * 4 + i * 4 + g) * 64 + lane] = make_float4(x[g * 4], x[g * 4 + 1], x[g * 4 + 2], x[g * 4 + 3]);
+      }
+    ms[wave * 64 + lane] = make_float2(m_run, l_run);
+    __syncthreads();
+    const float2 other = ms[(wave ^ 4) * 64 + lane];
+    const float m_all = fmaxf(m_run, other.x), m_ref = m_all == -INFINITY ? 0.f : m_all;
+    const float f_own = __builtin_amdgcn_exp2f(m_run - m_ref), f_other = __builtin_amdgcn_exp2f(other.x - m_ref);
+    float l_tot = l_run * f_own + other.y * f_other;
+    l_tot += __shfl_xor(l_tot, 32, 64);
+    const float inv = l_tot > 0.f ? 1.f / l_tot : 0.f;
+    const float wo = f_own * inv, wx = f_other * inv;
+#pragma unroll
+    for (int i = 0; i < HB; ++i)
+#pragma unroll
+      for (int g = 0; g < 4; g += 2) {
+        uint2 pk[2];
+#pragma unroll
+        for (int e = 0; e < 2; ++e) {
+          const floatx16_t& x = grp == 0 ? o[i] : o[i + HB];
+          const float4 y = mo[((wave ^ 4) * HB * 4 + i * 4 + g + e) * 64 + lane];
+          const int v = (g + e) * 4;
+          pk[e] = make_uint2(pack_bf16x2(x[v] * wo + y.x * wx, x[v + 1] * wo + y.y * wx),
+                             pack_bf16x2(x[v + 2] * wo + y.z * wx, x[v + 3] * wo + y.w * wx));
+        }
+        store_pair(op + (grp * HB + i) * 32 + g * 8, pk[0], pk[1]);
+      }
+  }
+#endif
+}
+
+template <int HD, bool SPLIT>
+hipError_t launch8(const AttnPrefillArgs& a, hipStream_t st) {
+  constexpr int smem = 8 * BKV * HD * 2;
+  static_assert(smem >= 8 * (HD / 64) * 4 * 1024 + 8 * 64 * 8, "the merge uses the ring");
+  // once per form; the initialisation of a function-local static is thread-safe
+  static const hipError_t attr_err = hipFuncSetAttribute(reinterpret_cast<const void*>(&attn_prefill8_kernel<HD, SPLIT>),
                                                          hipFuncAttributeMaxDynamicSharedMemorySize, smem);
   if (attr_err != hipSuccess) return attr_err;
   const float scale_log2 = 1.4426950408889634f / sqrtf((float)HD);
-  hipLaunchKernelGGL((attn_prefill_kernel<HD>), dim3(a.n_tiles, a.n_q_heads), dim3(256), smem, st, a, scale_log2);
+  hipLaunchKernelGGL((attn_prefill8_kernel<HD, SPLIT>), dim3(a.n_q_heads, a.n_tiles), dim3(512), smem, st, a, scale_log2);
+  return hipGetLastError();
+}
+
+hipError_t launch256(const AttnPrefillArgs& a, hipStream_t st) {
+  constexpr int smem = 2 * 2 * BKV * 256 * 2;
+  // once; the initialisation of a function-local static is thread-safe
+  static const hipError_t attr_err = hipFuncSetAttribute(reinterpret_cast<const void*>(&attn_prefill256_kernel),
+                                                         hipFuncAttributeMaxDynamicSharedMemorySize, smem);
+  if (attr_err != hipSuccess) return attr_err;
+  const float scale_log2 = 1.4426950408889634f / 16.f;
+  hipLaunchKernelGGL(attn_prefill256_kernel, dim3(a.n_tiles, a.n_q_heads), dim3(256), smem, st, a, scale_log2);
   return hipGetLastError();
 }
 
@@ -460,9 +773,9 @@ hipError_t launch_attention_prefill(const AttnPrefillArgs& a, hipStream_t st) {
   if ((long long)a.T * a.ld * 2 >= (1LL << 31) || (long long)a.n_kv_heads * a.hd * a.Tp * 2 >= (1LL << 31))
     return hipErrorInvalidValue;
   switch (a.hd) {
-    case 64: return launch_hd<64>(a, st);
-    case 128: return launch_hd<128>(a, st);
-    case 256: return launch_hd<256>(a, st);
+    case 64: return a.tile_rows == 128 ? launch8<64, true>(a, st) : launch8<64, false>(a, st);
+    case 128: return a.tile_rows == 128 ? launch8<128, true>(a, st) : launch8<128, false>(a, st);
+    case 256: return launch256(a, st);
   }
   return hipErrorInvalidValue;
 }

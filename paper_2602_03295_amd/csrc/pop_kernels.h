@@ -173,6 +173,14 @@ GemmPlan gemm_plan(const GemmArgs& g);
 // ---------------------------------------------------------------------------------------------
 // Causal GQA flash attention over packed variable-length sequences (pop_attention.hip)
 // ---------------------------------------------------------------------------------------------
+// An entry of the work list: a tile of query rows of one sequence.
+struct AttnTile {
+  int32_t start;       // first position, and of a second tile of the same sequence (or -1; head size 256 only)
+  int32_t start2;
+  int32_t seq0, len;   // first packed row and length of the sequence
+  int32_t vt_off;      // its first column of vT
+  int32_t pad[3];
+};
 struct AttnPrefillArgs {
   const bf16_t* qkv;  // rotated q and k inside [T, ld], as fp16 (written by launch_rope_write with fp16_inplace)
   int ld, q_col, k_col;
@@ -181,12 +189,9 @@ struct AttnPrefillArgs {
   bf16_t* out;        // [T, Hq*hd] bf16
   int T, n_q_heads, n_kv_heads, hd;
   int window;         // 0 = global
-  const int32_t* cu_seqlens;
-  const int32_t* vt_off;
-  const int32_t* tile_seq;    // work list: sequence, first position of a 128-row query tile, and
-  const int32_t* tile_start;  // first position of a second tile of the same sequence (or -1)
-  const int32_t* tile_start2;
+  const AttnTile* tiles;
   int n_tiles;
+  int tile_rows;      // query rows of a tile: 256 or 128 (head size 256: always 128)
 };
 hipError_t launch_attention_prefill(const AttnPrefillArgs& a, hipStream_t st);
 
