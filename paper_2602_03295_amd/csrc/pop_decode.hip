@@ -409,10 +409,13 @@ __device__ __forceinline__ int fold_keys(float (&v)[N], int lane) {
 //   The next block's K is requested as soon as S is formed, its V as soon as P V is: a wave has 8 to 16 KB in flight.
 // A work-group per 64 keys with everything on the vector ALU spent its time there and on 130 partial values per head
 // and 64 keys; at 8 sequences: 2048 keys 27 us, 8192 keys of the 8-bit cache 70 + 10 us (with the merge).
+// Per 32 keys of the 8-bit cache a wave issues about 480 vector instructions (row numbers formed once per key and passed
+// between lanes, codes to bf16 two per instruction), 750 before; three work-groups per CU need the launch bound (180
+// registers without it: 650 us a step).  8 sequences of 8192 tokens: 585 -> 568 us a step, one of 2048 tokens 407 -> 405.
 // GT: compile-time bound of the number of query heads per KV head (registers and loops are sized by it).
 // FUSED: RoPE + append inside this kernel (a.qkv_raw given).
 template <int HD, int GT, bool FUSED, bool FP8, int NB>
-__global__ __launch_bounds__(256) void attn_decode_split_kernel(AttnDecodeArgs a, float scale) {
+__global__ __launch_bounds__(256, (HD <= 128 && GT <= 4) ? 3 : 1 /* work-groups per CU */) void attn_decode_split_kernel(AttnDecodeArgs a, float scale) {
   constexpr int KS = HD / 32;                       // MFMA steps over the head dim
   constexpr int LPK = HD / 8, KPL = 64 / LPK;       // lanes per V row, V rows per load
   constexpr int VL = 16 / KPL;                      // V loads per 16 keys
@@ -444,44 +447,43 @@ __global__ __launch_bounds__(256) void attn_decode_split_kernel(AttnDecodeArgs a
   }
   const chunk_t* k_pool = reinterpret_cast<const chunk_t*>(a.k_pool);
   const chunk_t* v_pool = reinterpret_cast<const chunk_t*>(a.v_pool);
-  // chunk index of entry `key` (in page `page`)
-  auto entry = [&](int key, int page) {
-    return (((size_t)page * a.n_kv_heads + kvh) * P + (key & (P - 1))) * LPK;
-  };
+  // row (of HD elements) of entry `key` in page `page`; chunk index of a row
+  auto row_of = [&](int key, int page) { return ((uint32_t)(page * a.n_kv_heads + kvh) << lgP) + (uint32_t)(key & (P - 1)); };
+  auto chunk_of = [&](uint32_t row) { return (size_t)row * LPK; };
   // Key kk of the split (kk beyond the last one repeats it, masked below).
   auto key_of = [&](int kk) { return k_first + min(kk, n_keys - 1); };
   const int n_blocks = (n_keys + NB * 16 - 1) / (NB * 16);
-  int page_k[NB];                                   // page of this lane's key (r16) in each group of the next block
+  uint32_t row_k[NB];                               // row of this lane's key (r16) in each group of the next block
   chunk_t kw[NB][KS], vw[NB][VL];
   auto load_pages = [&](int blk) {
 #pragma unroll
-    for (int n = 0; n < NB; ++n) page_k[n] = bt[key_of((blk * NB + n) * 16 + r16) >> lgP];
+    for (int n = 0; n < NB; ++n) {
+      const int key = key_of((blk * NB + n) * 16 + r16);
+      row_k[n] = row_of(key, bt[key >> lgP]);
+    }
   };
-  auto load_k = [&](int blk) {
+  auto load_k = [&] {
 #pragma unroll
     for (int n = 0; n < NB; ++n) {
-      const chunk_t* p = k_pool + entry(key_of((blk * NB + n) * 16 + r16), page_k[n]) + g4;
+      const chunk_t* p = k_pool + chunk_of(row_k[n]) + g4;
 #pragma unroll
       for (int ks = 0; ks < KS; ++ks) kw[n][ks] = p[ks * 4];
     }
   };
-  int page_v[NB];                                   // pages of the block whose V is loaded next
-  auto load_v = [&](int blk) {
+  uint32_t row_v[NB];                               // rows of the block whose V is loaded next
+  auto load_v = [&] {
 #pragma unroll
     for (int n = 0; n < NB; ++n)
 #pragma unroll
-      for (int i = 0; i < VL; ++i) {
-        const int k16 = i * KPL + vs;
-        vw[n][i] = v_pool[entry(key_of((blk * NB + n) * 16 + k16), __shfl(page_v[n], k16, 64)) + li];
-      }
+      for (int i = 0; i < VL; ++i) vw[n][i] = v_pool[chunk_of((uint32_t)__shfl((int)row_v[n], i * KPL + vs, 64)) + li];
   };
   // the first block's entries travel while the query rows are prepared
   load_pages(wave);
 #pragma unroll
-  for (int n = 0; n < NB; ++n) page_v[n] = page_k[n];
+  for (int n = 0; n < NB; ++n) row_v[n] = row_k[n];
   if (wave < n_blocks) {
-    load_k(wave);
-    load_v(wave);
+    load_k();
+    load_v();
   }
 
   // ---- query rows: lane l holds head r16 (zeros beyond G), dims 32 ks + 8 g4 .. + 7, as bf16.  The other member of
@@ -580,7 +582,7 @@ __global__ __launch_bounds__(256) void attn_decode_split_kernel(AttnDecodeArgs a
 #pragma unroll
       for (int ks = 0; ks < KS; ++ks) kw[n][ks] = as_chunk(k_new[ks]);
       if (kk == n_keys - 1) {
-        chunk_t* o = reinterpret_cast<chunk_t*>(const_cast<bf16_t*>(a.k_pool)) + entry(key, bt[key >> lgP]) + g4;
+        chunk_t* o = reinterpret_cast<chunk_t*>(const_cast<bf16_t*>(a.k_pool)) + chunk_of(row_of(key, bt[key >> lgP])) + g4;
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) o[ks * 4] = as_chunk(k_new[ks]);
       }
@@ -595,23 +597,13 @@ __global__ __launch_bounds__(256) void attn_decode_split_kernel(AttnDecodeArgs a
         if (key != qpos) continue;
         vw[n][i] = as_chunk(v_new);
         if (kk == n_keys - 1)
-          reinterpret_cast<chunk_t*>(const_cast<bf16_t*>(a.v_pool))[entry(key, bt[key >> lgP]) + li] = as_chunk(v_new);
+          reinterpret_cast<chunk_t*>(const_cast<bf16_t*>(a.v_pool))[chunk_of(row_of(key, bt[key >> lgP])) + li] = as_chunk(v_new);
       }
   };
   // a chunk of K as the MFMA operand
   auto k_operand = [&](const chunk_t& w) {
-    if constexpr (FP8) {     // e4m3 values have 4 significant bits: their bf16 is the upper half of their fp32
-      float f[8];
-      e4m3_decode4_hw(w.x, f);
-      e4m3_decode4_hw(w.y, f + 4);
-      uint32_t u[4];
-#pragma unroll
-      for (int e = 0; e < 4; ++e)
-        u[e] = (__builtin_bit_cast(uint32_t, f[2 * e]) >> 16) | (__builtin_bit_cast(uint32_t, f[2 * e + 1]) & 0xffff0000u);
-      return __builtin_bit_cast(bf16x8_t, make_uint4(u[0], u[1], u[2], u[3]));
-    } else {
-      return __builtin_bit_cast(bf16x8_t, w);
-    }
+    if constexpr (FP8) return e4m3_to_bf16x8(w);
+    else return __builtin_bit_cast(bf16x8_t, w);
   };
   const float s_scale = FP8 ? scale * a.kvq.k_scale : scale;
   float acc[GT][8];
@@ -636,7 +628,7 @@ __global__ __launch_bounds__(256) void attn_decode_split_kernel(AttnDecodeArgs a
       for (int ks = 0; ks < KS; ++ks)
         s[n] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(k_operand(kw[n][ks]), qf[ks], s[n], 0, 0, 0);
     }
-    if (blk + 4 < n_blocks) load_k(blk + 4);
+    if (blk + 4 < n_blocks) load_k();
     // s[n][v]: query head r16, key 16 n + 4 g4 + v of the block
     float mx = -INFINITY;
 #pragma unroll
@@ -656,10 +648,15 @@ __global__ __launch_bounds__(256) void attn_decode_split_kernel(AttnDecodeArgs a
     for (int n = 0; n < NB; ++n)
 #pragma unroll
       for (int v = 0; v < 4; ++v) {
-        const float pv = __expf(s[n][v] - m_new);
-        if (r16 < G) ps[wave][n * 16 + 4 * g4 + v][r16 % GT] = pv;
-        sum += pv;
+        s[n][v] = __expf(s[n][v] - m_new);
+        sum += s[n][v];
       }
+    if (r16 < G) {
+#pragma unroll
+      for (int n = 0; n < NB; ++n)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) ps[wave][n * 16 + 4 * g4 + v][r16 % GT] = s[n][v];
+    }
     l_run = l_run * alpha + sum;
     const bool moved = __builtin_amdgcn_ballot_w64(r16 < G && alpha != 1.f) != 0;
     if (moved && g4 == 0 && r16 < G) al[wave][r16 % GT] = alpha;
@@ -689,7 +686,7 @@ __global__ __launch_bounds__(256) void attn_decode_split_kernel(AttnDecodeArgs a
         }
 #pragma unroll
         for (int g = 0; g < GT; ++g)
-          if (g < G) {
+          if (GT <= 4 || g < G) {     // (three of four heads: the fourth's sums are formed and dropped)
             const float pv = ps[wave][n * 16 + i * KPL + vs][g];
 #pragma unroll
             for (int e = 0; e < 8; ++e) acc[g][e] += pv * vf[e];
@@ -697,8 +694,8 @@ __global__ __launch_bounds__(256) void attn_decode_split_kernel(AttnDecodeArgs a
       }
     if (blk + 4 < n_blocks) {
 #pragma unroll
-      for (int n = 0; n < NB; ++n) page_v[n] = page_k[n];
-      load_v(blk + 4);
+      for (int n = 0; n < NB; ++n) row_v[n] = row_k[n];
+      load_v();
     }
     asm volatile("" ::: "memory");                  // the next block's P is written after this block's was read
   }

@@ -73,6 +73,17 @@ __device__ __forceinline__ void e4m3_decode4_hw(uint32_t w, float* f) {
   const f2_t lo = __builtin_amdgcn_cvt_pk_f32_fp8((int)w, false), hi = __builtin_amdgcn_cvt_pk_f32_fp8((int)w, true);
   f[0] = lo.x; f[1] = lo.y; f[2] = hi.x; f[3] = hi.y;
 }
+// Eight codes -> eight bf16 values (exact: e4m3 has 4 significant bits), two per instruction.
+__device__ __forceinline__ bf16x8_t e4m3_to_bf16x8(const uint2& w) {
+#if defined(__HIP_DEVICE_COMPILE__)  // the builtin exists in the device pass only
+  typedef __bf16 bf2_t __attribute__((ext_vector_type(2)));
+  const bf2_t a = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(w.x, 1.f, false), b = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(w.x, 1.f, true);
+  const bf2_t c = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(w.y, 1.f, false), d = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(w.y, 1.f, true);
+  return bf16x8_t{a.x, a.y, b.x, b.y, c.x, c.y, d.x, d.y};
+#else
+  return bf16x8_t{};
+#endif
+}
 // Four values -> four codes in one 32-bit word (element 0 in the low byte).
 __device__ __forceinline__ uint32_t e4m3_pack4(float a, float b, float c, float d) {
   return e4m3_encode(a) | (e4m3_encode(b) << 8) | (e4m3_encode(c) << 16) | (e4m3_encode(d) << 24);
