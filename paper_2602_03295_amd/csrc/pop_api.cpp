@@ -207,7 +207,7 @@ struct Workspace {
   // device buffers
   size_t o_h, o_a, o_qkv, o_attn, o_u, o_vT, o_cs_g, o_cs_l, o_cs_tail, o_a_multi, o_kv_out;
   size_t o_dcs_g, o_dcs_l;   // (cos, sin) of the decode-style rows' positions, [B][hd/2] per RoPE base
-  size_t o_xb, o_ab, o_qkvb, o_qb, o_attnb, o_ub, o_part, o_splitk;
+  size_t o_xb, o_ab, o_qkvb, o_qb, o_attnb, o_ub, o_part, o_sumsq, o_splitk;
   size_t splitk_bytes;
   // scratch for the K parts of a kept layer's projections: the split scratch, or the buffers of the K/V-only path
   // (not in use while a kept layer runs) where they are larger
@@ -278,6 +278,7 @@ Workspace carve(const pop_config& c, int T, int B, int maxp) {
   w.o_attnb = take(2 * (size_t)B * Dq);
   w.o_ub = take(2 * (size_t)B * f);
   w.o_part = take(4 * (size_t)B * c.n_q_heads * w.n_splits_max * (hd + 2));
+  w.o_sumsq = take(4 * (size_t)B * (d / 16));
   // fp32 partial products of a projection whose K range is split (short prompts only)
   // (all packed rows of a short batch; otherwise the boundary rows, which are projected on their own)
   const size_t split_rows = T <= 512 ? (size_t)T : (B <= 512 ? (size_t)B : 0);
@@ -414,17 +415,28 @@ struct LayerCtx {
   // The norm scale with which the bf16 scratch rows `ab` hold RMSNorm(xb), or nullptr when they do not: a split
   // projection with a residual epilogue normalises its result for the next projection in its second kernel.
   mutable const float* ab_gamma = nullptr;
+  // > 0: the rows of `ab` lack their 1 / rms; this many partial sums of squares per row are in the workspace (pop_rows.hip)
+  mutable int ab_sums = 0;
   const float* gates = nullptr;       // HOST [n_layers] virtual gates of the stage this context runs, or nullptr
   float gate(int l /*1-based*/) const { return gates ? gates[l - 1] : 1.f; }
 };
 
+// Whether the projections of B decode-style rows run as pop_rows.hip has them (3 to 32 rows): QKV with RoPE and the append in
+// its epilogue, O and down with the residual update and the next norm's input in theirs, which leaves five launches per layer
+// (and the attention's merge) of nine.
+bool rows_path(const pop_config& c, int B) {
+  const int Dq = c.n_q_heads * c.head_dim, Dqkv = Dq + 2 * c.n_kv_heads * c.head_dim;
+  return c.dtype != POP_DTYPE_F32 && c.vocab % 4 == 0 && c.d_model / 16 <= pop::kRowScaledSums && pop::rows_supported(B, Dqkv, c.d_model) &&
+         pop::rows_supported(B, c.d_model, Dq) && pop::rows_supported(B, c.d_model, c.d_ffn);
+}
+
 // (cos, sin) tables of the B decode-style rows at positions pos[0..B-1], one per RoPE base in use: what the decode
 // attention kernel rotates the query token's q and k with.  Once per pass over the layers (the separate append kernel
-// of larger batches forms its angles itself).
+// of larger batches forms its angles itself).  The same for the projections of rows_path.
 pop::RopeTables decode_rope_tables(const LayerCtx& x, const int32_t* pos, int B) {
   pop::RopeTables tabs;
-  if (B > kFusedAppendRows) return tabs;
   const pop_config& c = x.m->cfg;
+  if (B > kFusedAppendRows && !rows_path(c, B)) return tabs;
   tabs.add(pos, at<float2>(x.ws, x.w->o_dcs_g), B, c.head_dim, (double)c.rope_theta);
   bool any_local = false;
   for (int l = 1; l <= c.n_layers; ++l) any_local = any_local || !layer_is_global(c, l);
@@ -556,6 +568,9 @@ pop_status few_rows_projection(const LayerCtx& x, const bf16_t* in, const void* 
   g.splitk_ws_bytes = x.w->splitk_bytes;
   g.partials_only = parts_out != nullptr;
   g.split_used = parts_out;
+  if (in == at<bf16_t>(x.ws, x.w->o_ab) && x.ab_sums > 0) {
+    g.row_sumsq = at<float>(x.ws, x.w->o_sumsq); g.n_sumsq = x.ab_sums; g.d_norm = K; g.eps = x.m->cfg.rms_eps;
+  }
   hipError_t e = pop::launch_gemm(g, x.st);
   if (e != hipSuccess) return fail(POP_EHIP, "projection launch failed: %s", hipGetErrorString(e));
   return POP_OK;
@@ -577,6 +592,7 @@ pop_status normed_few_rows_projection(const LayerCtx& x, float* rows, const floa
     return POP_OK;
   }
   pop::launch_rmsnorm(rows, nullptr, nullptr, gamma, normed, nullptr, B, K, eps, x.st);
+  x.ab_sums = 0;
   return few_rows_projection(x, normed, W, out, B, N, K, ldo, gemv_epi, act, parts_out);
 }
 
@@ -587,6 +603,20 @@ pop_status residual_few_rows_projection(const LayerCtx& x, const bf16_t* in, con
                                         const float* next_gamma, float scale /* the layer's virtual gate */) {
   float* xb = at<float>(x.ws, x.w->o_xb);
   x.ab_gamma = nullptr;
+  x.ab_sums = 0;
+  // (from 17 rows on a long K, all of whose activations every work-group reads, is faster split over the chip: down of 32 rows
+  // 29.8 us here, 24.1 and a second kernel there; O 11.0 and 9.7)
+  if (rows_path(x.m->cfg, B) && (B <= 16 || K <= 8192)) {
+    pop::RowsArgs r{};
+    r.x = in; r.W = (const bf16_t*)W; r.M = B; r.N = N; r.K = K; r.epilogue = pop::ROWS_ADD;
+    r.out = xb; r.ldo = N; r.scale = scale;
+    r.gamma = next_gamma; r.xn = at<bf16_t>(x.ws, x.w->o_ab); r.sumsq_out = at<float>(x.ws, x.w->o_sumsq);
+    if (hipError_t e = pop::launch_rows(r, x.st); e != hipSuccess)
+      return fail(POP_EHIP, "projection launch failed: %s", hipGetErrorString(e));
+    x.ab_gamma = next_gamma;
+    x.ab_sums = next_gamma ? N / 16 : 0;
+    return POP_OK;
+  }
   if (!rows_take_gemm(B, K) || N % 4) {
     pop::launch_gemv(in, (const bf16_t*)W, xb, B, N, K, N, pop::GEMV_ADD_F32, 0, x.st, scale);
     return POP_OK;
@@ -634,12 +664,32 @@ pop_status decode_layer(const LayerCtx& x, int l /*1-based*/, int B, const int32
   // fused and separate: 4 sequences of 850 tokens 503 and 486 us, with heads of 256 910 and 775 us; 8 of 2048 tokens 597
   // and 547 us; one of 139 tokens 403 and 409 us).
   const bool fused_append = B <= kFusedAppendRows;
+  pop::AttnDecodeArgs ad{};
   int qkv_parts = 1;
-  if (pop_status s = normed_few_rows_projection(x, xb, (const float*)lw.norm_in, ab, lw.wqkv, qkvb, B, Dqkv, d, Dqkv,
+  const bool rows = rows_path(c, B);
+  if (rows) {
+    // (per-head norms need a whole head, which no work-group of the projection holds: fp32 rows, then the separate kernel)
+    const bool qk_norm = lw.q_norm || lw.k_norm;
+    if (x.ab_gamma != (const float*)lw.norm_in) {
+      pop::launch_rmsnorm(xb, nullptr, nullptr, (const float*)lw.norm_in, ab, nullptr, B, d, c.rms_eps, x.st);
+      x.ab_sums = 0;
+    }
+    pop::RowsArgs r{};
+    r.x = ab; r.W = (const bf16_t*)lw.wqkv; r.M = B; r.N = Dqkv; r.K = d;
+    r.epilogue = qk_norm ? pop::ROWS_STORE : pop::ROWS_QKV;
+    r.sumsq_in = at<float>(x.ws, x.w->o_sumsq); r.n_sumsq = x.ab_sums; r.d_norm = d; r.eps = c.rms_eps;
+    r.out = qkvb; r.ldo = Dqkv;
+    r.hd = c.head_dim; r.n_q_heads = c.n_q_heads; r.n_kv_heads = c.n_kv_heads; r.page_size = c.page_size;
+    r.cs = at<float2>(x.ws, glob ? x.w->o_dcs_g : x.w->o_dcs_l); r.slot = slot;
+    r.q_out = at<bf16_t>(x.ws, x.w->o_qb); r.k_pool = x.c->k_pool(l - 1); r.v_pool = x.c->v_pool(l - 1); r.kvq = kv_quant(c);
+    if (hipError_t e = pop::launch_rows(r, x.st); e != hipSuccess)
+      return fail(POP_EHIP, "projection launch failed: %s", hipGetErrorString(e));
+    ad.q = r.q_out;
+  } else if (pop_status s = normed_few_rows_projection(x, xb, (const float*)lw.norm_in, ab, lw.wqkv, qkvb, B, Dqkv, d, Dqkv,
                                                 pop::GEMV_STORE_F32, 0, fused_append ? nullptr : &qkv_parts))
     return s;
-  pop::AttnDecodeArgs ad{};
-  if (fused_append) {
+  if (rows && !(lw.q_norm || lw.k_norm)) {
+  } else if (fused_append) {
     ad.qkv_raw = qkvb;
     ad.ld = Dqkv;
     ad.cs = at<float2>(x.ws, glob ? x.w->o_dcs_g : x.w->o_dcs_l);

@@ -64,6 +64,9 @@ struct GemmParams {
   long long strideA, strideC, strideW;
   const bf16_t* const* W_list;
   float scale;           // EPI_ADD_F32: out += scale * C
+  const float* row_sumsq;   // row-scaled epilogues (GemmArgs)
+  int n_sumsq, d_norm;
+  float eps;
   // KV-cache epilogues
   const KvDest* kv_dest;
   const int32_t* kv_slot;
@@ -78,7 +81,13 @@ constexpr int EPI_KV64 = 1064, EPI_KV128 = 1128, EPI_KV256 = 1256;   // (apart f
 constexpr bool epi_is_kv(int e) { return e == EPI_KV64 || e == EPI_KV128 || e == EPI_KV256; }
 constexpr int epi_kv_hd(int e) { return e == EPI_KV64 ? 64 : e == EPI_KV128 ? 128 : 256; }
 
+// The GLU and fp32-store epilogues with the rows of C scaled by 1 / rms first (GemmArgs::row_sumsq); few rows only.
+constexpr int EPI_GLU_RS = 2001, EPI_STORE_F32_RS = 2002;
+constexpr bool epi_is_rs(int e) { return e == EPI_GLU_RS || e == EPI_STORE_F32_RS; }
+constexpr bool epi_is_glu(int e) { return e == EPI_GLU_BF16 || e == EPI_GLU_RS; }
+
 typedef __attribute__((address_space(3))) void* lds_ptr_t;
+typedef __attribute__((__vector_size__(16))) unsigned int u32x4_t;
 
 // SiLU: g * sigmoid(g); tanh-GELU: 0.5 g (1 + tanh(u)) = g * sigmoid(2u), u = sqrt(2/pi) (g + 0.044715 g^3).
 // Both are g / (1 + 2^(-g (k0 + k1 g^2))): one v_exp_f32 and one v_rcp_f32, constants chosen per
@@ -103,7 +112,7 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_kernel(GemmParams p) {
   constexpr int MB = WTM / 16, NB = WTN / 16;   // 16x16 output blocks of a wave tile
   constexpr int LA = BM / 8 / NW, LB = BN / 8 / NW;  // wave-loads per stage and wave
   static_assert(BM % (8 * NW) == 0 && BN % (8 * NW) == 0, "tile/wave mismatch");
-  static_assert(EPI != EPI_GLU_BF16 || NB % 2 == 0, "GLU needs an even number of column blocks");
+  static_assert(!epi_is_glu(EPI) || NB % 2 == 0, "GLU needs an even number of column blocks");
   constexpr int A_BYTES = BM * BK * 2, B_BYTES = BN * BK * 2, STAGE = A_BYTES + B_BYTES;
 
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
@@ -125,7 +134,7 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_kernel(GemmParams p) {
     tm = band * 8 + r % rows;
   }
   const int m0 = tm * BM;
-  constexpr int BN_OUT = EPI == EPI_GLU_BF16 ? BN / 2 : BN;
+  constexpr int BN_OUT = epi_is_glu(EPI) ? BN / 2 : BN;
   const int n0 = p.n_first + tn * BN_OUT;  // first output column of the tile
 
   const int z = blockIdx.z;
@@ -138,7 +147,7 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_kernel(GemmParams p) {
 
   // ---- buffer descriptors; rows beyond the operand are out of range and load zeros
   const uint32_t a_bytes = (uint32_t)(((long long)(p.M - 1) * p.lda + p.K) * 2);
-  const int w_rows = EPI == EPI_GLU_BF16 ? 2 * p.N : p.N;
+  const int w_rows = epi_is_glu(EPI) ? 2 * p.N : p.N;
   const uint32_t w_bytes = (uint32_t)(((long long)(w_rows - 1) * p.ldw + p.K) * 2);
   const __amdgpu_buffer_rsrc_t rA =
       __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(A), 0, a_bytes, 0x00020000);
@@ -162,7 +171,7 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_kernel(GemmParams p) {
     const int jn = (j * NW + wave) * 8 + lr;  // row of the LDS B tile
     int wrow;
     bool ok;
-    if (EPI == EPI_GLU_BF16) {
+    if (epi_is_glu(EPI)) {
       const int w2 = jn / WTN, r = jn % WTN;
       const int up = r >= WTN / 2;
       const int oc = n0 + w2 * (WTN / 2) + (r % (WTN / 2));
@@ -231,7 +240,7 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_kernel(GemmParams p) {
     if (wave == 0) {
       const int jn = (tm & 7) * (BN / 8) + (lane % (BN / 8));   // row of the LDS B tile
       int wrow; bool ok = lane < BN / 8;
-      if (EPI == EPI_GLU_BF16) {
+      if (epi_is_glu(EPI)) {
         const int w2 = jn / WTN, r = jn % WTN;
         const int oc = n0 + w2 * (WTN / 2) + (r % (WTN / 2));
         ok = ok && oc < p.N;
@@ -273,6 +282,22 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_kernel(GemmParams p) {
   const int frag_hi = lane >> 4;
   const int a_base = (wm * WTM + frag_row) * 128;
   const int b_base = (wn * WTN + frag_row) * 128;
+
+  // Row-scaled epilogues: the partial sums of squares of the rows (eight lanes share a row's) are requested here and added
+  // behind the K loop; range-checked loads return zeros for rows and columns that do not exist.
+  constexpr int SSQ = epi_is_rs(EPI) ? kRowScaledSums / 32 : 1;
+  static_assert(!epi_is_rs(EPI) || (kRowScaledRows == 32 && NW == 4), "256 threads, eight per row");
+  u32x4_t ssq[SSQ];
+  if constexpr (epi_is_rs(EPI)) {
+    const __amdgpu_buffer_rsrc_t rS = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(p.row_sumsq), 0,
+                                                                        (uint32_t)p.M * p.n_sumsq * 4, 0x00020000);
+    const int m = (int)(threadIdx.x >> 3), q0 = (threadIdx.x & 7) * 4;
+#pragma unroll
+    for (int i = 0; i < SSQ; ++i) {
+      const int q = q0 + i * 32;
+      ssq[i] = __builtin_amdgcn_raw_buffer_load_b128(rS, q < p.n_sumsq ? (uint32_t)(m * p.n_sumsq + q) * 4 : kOOB, 0, 0);
+    }
+  }
 
   static_assert(STAGES >= 2 && STAGES <= 8, "2 to 8 LDS stages");
   static_assert(1 + (STAGES - 2) * (LOADS + 1) < 64, "vmcnt is a 6-bit counter");
@@ -410,11 +435,23 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_kernel(GemmParams p) {
   }
   // masked staging loads and prefetches of the last iterations still target this group's LDS
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  float* const rstd = reinterpret_cast<float*>(pf_scratch + 512);
+  if constexpr (epi_is_rs(EPI)) {
+    float ss = 0.f;
+#pragma unroll
+    for (int i = 0; i < SSQ; ++i) {
+      const float4 v = __builtin_bit_cast(float4, ssq[i]);
+      ss += (v.x + v.y) + (v.z + v.w);
+    }
+    ss = group_sum<8>(ss);
+    if ((threadIdx.x & 7) == 0) rstd[threadIdx.x >> 3] = rsqrtf(ss / (float)p.d_norm + p.eps);
+    __syncthreads();
+  }
 
   // ---- epilogue.  acc[i][j][v]: row m = .. + j*16 + (lane & 15); column block i, columns
   //      4 (lane >> 4) + v inside it: 4 consecutive columns per lane.
   const int m_lane = m0 + wm * WTM + frag_row;
-  if (EPI == EPI_GLU_BF16) {
+  if (epi_is_glu(EPI)) {
     const float act_k0 = p.act == 0 ? 1.4426950408889634f : 2.302208198f;
     const float act_k1 = p.act == 0 ? 0.f : 0.1029432396f;
     bf16_t* out = reinterpret_cast<bf16_t*>(p.out) + (long long)z * p.strideC;
@@ -428,9 +465,14 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_kernel(GemmParams p) {
         if (m >= p.M) continue;
         {
           const int n = n0 + wn * (WTN / 2) + i * 16 + frag_hi * 4;
+          const float rs = epi_is_rs(EPI) ? rstd[m - m0] : 1.f;
           float r[4];
 #pragma unroll
-          for (int e = 0; e < 4; ++e) r[e] = glu_act(acc[i][j][e], act_k0, act_k1) * acc[i + NB / 2][j][e];
+          for (int e = 0; e < 4; ++e) {
+            const float gate = epi_is_rs(EPI) ? acc[i][j][e] * rs : acc[i][j][e];
+            const float up = epi_is_rs(EPI) ? acc[i + NB / 2][j][e] * rs : acc[i + NB / 2][j][e];
+            r[e] = glu_act(gate, act_k0, act_k1) * up;
+          }
           bf16_t* o = out + (long long)m * p.ldc + n;
           if (n + 3 < p.N) {
             uint2 pk;
@@ -554,8 +596,12 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_kernel(GemmParams p) {
         {
           const int n = n0 + wn * WTN + i * 16 + frag_hi * 4;
           if (n >= p.N) continue;
-          const float r0 = acc[i][j][0], r1 = acc[i][j][1];
-          const float r2 = acc[i][j][2], r3 = acc[i][j][3];
+          float r0 = acc[i][j][0], r1 = acc[i][j][1];
+          float r2 = acc[i][j][2], r3 = acc[i][j][3];
+          if constexpr (epi_is_rs(EPI)) {
+            const float rs = rstd[m - m0];
+            r0 *= rs; r1 *= rs; r2 *= rs; r3 *= rs;
+          }
           if (EPI == EPI_STORE_BF16 || EPI == EPI_STORE_F16) {
             bf16_t* o = reinterpret_cast<bf16_t*>(p.out) + (long long)z * p.strideC + (long long)m * p.ldc + n;
             if (n + 3 < p.N) {
@@ -569,7 +615,7 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_kernel(GemmParams p) {
               for (int e = 0; e < 4; ++e)
                 if (n + e < p.N) o[e] = EPI == EPI_STORE_F16 ? f32_to_f16_sat(r[e]) : f32_to_bf16(r[e]);
             }
-          } else {   // EPI_STORE_F32
+          } else {   // EPI_STORE_F32(_RS)
             float* o = reinterpret_cast<float*>(p.out) + (long long)z * p.strideC + (long long)m * p.ldc + n;
             if (n + 3 < p.N) {
               *reinterpret_cast<float4*>(o) = make_float4(r0, r1, r2, r3);
@@ -596,7 +642,7 @@ inline bool stagger_k(const GemmArgs& g) {
 
 template <int BM, int BN, int WGM, int WGN, int STAGES, int EPI>
 hipError_t launch_cfg(const GemmArgs& g, hipStream_t st, int n_first = 0, int n_cols = -1 /* output columns; -1: to the end */) {
-  constexpr int BN_OUT = EPI == EPI_GLU_BF16 ? BN / 2 : BN;
+  constexpr int BN_OUT = epi_is_glu(EPI) ? BN / 2 : BN;
   constexpr int smem = STAGES * (BM + BN) * BK * 2 + 1024;  // stages + prefetch scratch
   static_assert(smem <= 160 * 1024, "LDS budget of a gfx950 CU");
   GemmParams p;
@@ -605,6 +651,7 @@ hipError_t launch_cfg(const GemmArgs& g, hipStream_t st, int n_first = 0, int n_
   p.lda = (int)g.lda; p.ldw = (int)g.ldw; p.ldc = (int)g.ldc;
   p.act = g.act;
   p.scale = residual_scale(g);
+  p.row_sumsq = g.row_sumsq; p.n_sumsq = g.n_sumsq; p.d_norm = g.d_norm; p.eps = g.eps;
   p.kv_dest = g.kv_dest; p.kv_slot = g.kv_slot; p.kv_heads = g.kv_heads; p.kv_page = g.kv_page_size;
   p.kv_pool_stride = g.kv_pool_stride;
   p.kvq = g.kvq;
@@ -742,6 +789,15 @@ hipError_t launch_shape(int id, const GemmArgs& g, hipStream_t st, int n0, int n
   }
 }
 
+// Row-scaled forms: one row tile, and of the shapes for so few rows the two that serve wide outputs best.
+template <int EPI>
+hipError_t launch_row_scaled(const GemmArgs& g, hipStream_t st) {
+  const long long cols = EPI == EPI_GLU_RS ? 2LL * g.N : g.N;
+  // up to 160 column tiles of 128 leave a third of the chip idle (LM head of 16032 rows, 8 rows: 26 us with 64 columns)
+  if ((cols + 127) / 128 <= 160) return launch_cfg<64, 64, 2, 2, 6, EPI>(g, st);
+  return launch_cfg<64, 128, 2, 2, 3, EPI>(g, st);
+}
+
 template <int EPI>
 hipError_t launch_epi(const GemmArgs& g, hipStream_t st) {
   const long long batch = g.batch > 0 ? g.batch : 1;
@@ -833,6 +889,12 @@ hipError_t launch_gemm(const GemmArgs& g, hipStream_t st) {
   const long long w_rows = g.epilogue == EPI_GLU_BF16 ? 2LL * g.N : g.N;
   if (((long long)(g.M - 1) * g.lda + g.K) * 2 >= (1LL << 31) || ((w_rows - 1) * g.ldw + g.K) * 2 >= (1LL << 31))
     return hipErrorInvalidValue;
+  if (g.row_sumsq) {
+    if (g.M > kRowScaledRows || g.batch > 1 || g.n_sumsq < 4 || g.n_sumsq % 4 || g.n_sumsq > kRowScaledSums || g.d_norm < 1) return hipErrorInvalidValue;
+    if (g.epilogue == EPI_GLU_BF16) return launch_row_scaled<EPI_GLU_RS>(g, st);
+    if (g.epilogue == EPI_STORE_F32) return launch_row_scaled<EPI_STORE_F32_RS>(g, st);
+    return hipErrorInvalidValue;
+  }
   if (const int S = choose_split(g); S > 1) {
     GemmArgs part = g;
     part.K = g.K / S;

@@ -119,6 +119,7 @@ struct KvDest {
   bf16_t* k_pool;      // the layer's K pool [page][Hkv][P][hd]; its V pool follows kv_pool_stride elements later
   const float2* cs;    // [M, hd/2] (cos, sin) of every row's position with the layer's RoPE base
 };
+constexpr int kRowScaledRows = 32, kRowScaledSums = 512;   // limits of GemmArgs::row_sumsq
 struct GemmArgs {
   const bf16_t* A;   // [M, lda]
   const bf16_t* W;   // [N, ldw]   (EPI_GLU: [2N, ldw])
@@ -149,6 +150,12 @@ struct GemmArgs {
   // out += C.  A caller that adds partial products itself (partials_only) applies the scale there.
   bool scaled;
   float scale;
+  // EPI_GLU_BF16 and EPI_STORE_F32, up to kRowScaledRows rows, row_sumsq != nullptr: the rows of A are h * gamma, and
+  // row_sumsq[m][n_sumsq] (fp32, n_sumsq a multiple of 4, up to kRowScaledSums) add up to the sum of h^2 over the d_norm elements of row m (RowsArgs);
+  // C's rows are multiplied by rsqrt(sum / d_norm + eps) before the epilogue.
+  const float* row_sumsq;
+  int n_sumsq, d_norm;
+  float eps;
   // EPI_KV_CACHE only
   const KvDest* kv_dest;     // DEVICE [batch]
   const int32_t* kv_slot;    // DEVICE [M] cache slot of every row
@@ -211,6 +218,36 @@ void launch_gemv(const bf16_t* x, const bf16_t* W, void* out, int M, int N, int 
 bool gemv_norm_supported(int M, int K);
 void launch_gemv_norm(const float* xf, const float* gamma, float eps, const bf16_t* W, void* out, int M, int N, int K,
                       int64_t ldo, int epilogue, int act, hipStream_t st);
+
+// Projections of 3 to 32 rows with what follows them in the epilogue (pop_rows.hip): out[m, n] (op)= sum_k x[m,k] * W[n,k].
+enum RowsEpilogue { ROWS_STORE = 0, ROWS_ADD = 1, ROWS_QKV = 2 };
+struct RowsArgs {
+  const bf16_t* x;          // bf16 [M, K]
+  const bf16_t* W;          // bf16 [N, K]
+  int M, N, K, epilogue;
+  // n_sumsq > 0: the rows of x are h * gamma, and sumsq_in[m][n_sumsq] add up to the sum of h^2 over the d_norm elements of
+  // row m: the sums are multiplied by rsqrt(sum / d_norm + eps)
+  const float* sumsq_in;
+  int n_sumsq, d_norm;
+  float eps;
+  float* out;               // STORE: fp32 [M, ldo]; ADD: the same, out += scale * C
+  int ldo;
+  float scale;
+  // ADD, gamma != nullptr: also xn bf16 [M, N] = out * gamma, sumsq_out [M][N / 16]
+  const float* gamma;
+  bf16_t* xn;
+  float* sumsq_out;
+  // QKV: the columns are heads of hd values, q | k | v: q (rotated) to q_out bf16 [M, Hq * hd], k (rotated) and v to slot[m]
+  int hd, n_q_heads, n_kv_heads, page_size;
+  const float2* cs;         // [M, hd/2] (cos, sin)
+  const int32_t* slot;
+  bf16_t* q_out;
+  bf16_t* k_pool;
+  bf16_t* v_pool;
+  KvQuant kvq;
+};
+bool rows_supported(int M, int N, int K);
+hipError_t launch_rows(const RowsArgs& a, hipStream_t st);
 
 // Fewest keys per split of the decode attention (how many a split has is chosen at the launch: as many as make about
 // three work-groups per CU of the whole call); what the buffer of partial results is sized by.
