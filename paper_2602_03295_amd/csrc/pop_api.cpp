@@ -744,7 +744,7 @@ struct WorkspaceF32 {
   size_t meta_bytes;
   size_t o_tokens, o_row_src, o_pos, o_slot, o_row_seq, o_bnd_row, o_bnd_pos, o_bnd_slot, o_bnd_seq, o_bt, o_kv_first, o_tr_row, o_tr_pos,
       o_tr_slot;
-  size_t o_h, o_qkv, o_attn, o_u, o_xb, o_qkvb, o_attnb, o_ub;
+  size_t o_h, o_qkv, o_attn, o_u, o_xb, o_qkvb, o_attnb, o_ub, o_cs_g, o_cs_l;
   size_t total;
 };
 
@@ -781,6 +781,11 @@ WorkspaceF32 carve_f32(const pop_config& c, int T, int B, int maxp) {
   w.o_qkvb = take(4 * (size_t)B * Dqkv);
   w.o_attnb = take(4 * (size_t)B * Dq);
   w.o_ub = take(4 * (size_t)B * f);
+  // RoPE tables of the rows, per base in use
+  bool any_local = false;
+  for (int l = 1; l <= c.n_layers; ++l) any_local = any_local || !layer_is_global(c, l);
+  w.o_cs_g = take(4 * (size_t)T * hd);
+  w.o_cs_l = any_local ? take(4 * (size_t)T * hd) : w.o_cs_g;
   w.total = o;
   return w;
 }
@@ -797,22 +802,51 @@ struct CtxF32 {
   float gate(int l /*1-based*/) const { return gates ? gates[l - 1] : 1.f; }
 };
 
-// One layer of Sec. 2.1 for `rows` rows of x (fp32 [rows, d], updated in place); qkv / attn / u are
-// scratch of matching height.  row_seq / pos / slot are device arrays [rows].  packed: prompt rows, sequence by
-// sequence (otherwise one row per sequence).
-pop_status layer_f32(const CtxF32& x, int l /*1-based*/, int rows, float* xh, float* qkv, float* attn, float* u,
-                     const int32_t* row_seq, const int32_t* pos, const int32_t* slot, int max_len, bool packed) {
+// The tables of `rows` rows at the positions pos, which the launch that gathers the rows' embeddings computes.
+pop::RopeTables rope_tables_f32(const CtxF32& x, const int32_t* pos, int rows) {
+  const pop_config& c = x.m->cfg;
+  pop::RopeTables tabs;
+  tabs.add(pos, at<float2>(x.ws, x.w->o_cs_g), rows, c.head_dim, (double)c.rope_theta);
+  if (x.w->o_cs_l != x.w->o_cs_g) tabs.add(pos, at<float2>(x.ws, x.w->o_cs_l), rows, c.head_dim, (double)c.rope_theta_local);
+  return tabs;
+}
+
+// q | k | v of LN(x[row_idx ? row_idx[m] : m]) with q and k rotated and k, v appended at slot; kv_only: k and v alone (qkv is
+// then scratch).  cs_row: the rows' indices in the tables (nullptr: 0, 1, ..).
+void qkv_f32(const CtxF32& x, int l /*1-based*/, int rows, const float* xh, const int32_t* row_idx, float* qkv, const int32_t* pos,
+             const int32_t* slot, const int32_t* cs_row, bool kv_only) {
   const pop_config& c = x.m->cfg;
   const pop_layer_weights& lw = x.m->layers[l - 1];
-  const int d = c.d_model, f = c.d_ffn, hd = c.head_dim, Dq = x.m->Dq, Dkv = x.m->Dkv, Dqkv = x.m->Dqkv;
+  const int d = c.d_model, hd = c.head_dim, Dq = kv_only ? 0 : x.m->Dq, Dkv = x.m->Dkv, N = Dq + 2 * Dkv;
+  const bool glob = layer_is_global(c, l);
+  const float* W = (const float*)lw.wqkv + (kv_only ? (size_t)x.m->Dq * d : 0);
+  namespace F = pop::f32;
+  // (per-head norms need a whole head, which no work-group of the projection holds)
+  if (!(lw.q_norm && !kv_only) && !lw.k_norm && F::norm_qkv_supported(rows, N, hd)) {
+    const F::RopeAppend ra{hd, Dq / hd, c.n_kv_heads, c.page_size, at<float2>(x.ws, glob ? x.w->o_cs_g : x.w->o_cs_l), cs_row,
+                           slot, x.c->k_pool_f32(l - 1), x.c->v_pool_f32(l - 1), kv_quant(c)};
+    F::launch_norm_qkv(xh, row_idx, (const float*)lw.norm_in, c.rms_eps, W, qkv, N, rows, d, ra, x.st);
+    return;
+  }
+  F::launch_norm_gemm(xh, row_idx, (const float*)lw.norm_in, c.rms_eps, W, qkv, N, rows, N, d, F::EPI_STORE, 0, x.st);
+  F::launch_rope_write(qkv, N, kv_only ? -1 : 0, Dq, Dq + Dkv, c.n_q_heads, c.n_kv_heads, hd, pos, slot,
+                       glob ? (double)c.rope_theta : (double)c.rope_theta_local, x.c->k_pool_f32(l - 1),
+                       x.c->v_pool_f32(l - 1), c.page_size, rows, x.st, kv_only ? nullptr : (const float*)lw.q_norm,
+                       (const float*)lw.k_norm, c.rms_eps, kv_quant(c));
+}
+
+// One layer of Sec. 2.1 for `rows` rows of x (fp32 [rows, d], updated in place); qkv / attn / u are
+// scratch of matching height.  row_seq / pos / slot / cs_row are device arrays [rows].  packed: prompt rows, sequence by
+// sequence (otherwise one row per sequence).
+pop_status layer_f32(const CtxF32& x, int l /*1-based*/, int rows, float* xh, float* qkv, float* attn, float* u,
+                     const int32_t* row_seq, const int32_t* pos, const int32_t* slot, const int32_t* cs_row, int max_len,
+                     bool packed) {
+  const pop_config& c = x.m->cfg;
+  const pop_layer_weights& lw = x.m->layers[l - 1];
+  const int d = c.d_model, f = c.d_ffn, hd = c.head_dim, Dq = x.m->Dq, Dqkv = x.m->Dqkv;
   const bool glob = layer_is_global(c, l);
   namespace F = pop::f32;
-  F::launch_norm_gemm(xh, nullptr, (const float*)lw.norm_in, c.rms_eps, (const float*)lw.wqkv, qkv, Dqkv, rows, Dqkv, d,
-                      F::EPI_STORE, 0, x.st);
-  F::launch_rope_write(qkv, Dqkv, 0, Dq, Dq + Dkv, c.n_q_heads, c.n_kv_heads, hd, pos, slot,
-                       glob ? (double)c.rope_theta : (double)c.rope_theta_local, x.c->k_pool_f32(l - 1),
-                       x.c->v_pool_f32(l - 1), c.page_size, rows, x.st, (const float*)lw.q_norm, (const float*)lw.k_norm,
-                       c.rms_eps, kv_quant(c));
+  qkv_f32(x, l, rows, xh, nullptr, qkv, pos, slot, cs_row, false);
   hipError_t e = F::launch_attention(qkv, Dqkv, 0, attn, row_seq, pos, x.c->k_pool_f32(l - 1), x.c->v_pool_f32(l - 1),
                                      at<int32_t>(x.ws, x.w->o_bt), x.c->max_pages, c.page_size,
                                      glob ? 0 : c.sliding_window,
@@ -898,7 +932,8 @@ pop_status prefill_f32(pop_model* m, pop_cache* c, const pop_prefill_args* a, co
   x.B = B;
   x.gates = a->gates;
   F::launch_embed((const float*)m->w.embed, at<int32_t>(ws, w.o_tokens),
-                  a->n_ranges > 0 ? at<int32_t>(ws, w.o_row_src) : nullptr, (const float*)a->embeds, h, T, d, st);
+                  a->n_ranges > 0 ? at<int32_t>(ws, w.o_row_src) : nullptr, (const float*)a->embeds, h, T, d, st,
+                  rope_tables_f32(x, d_pos, T));
   // Layers in order.  A kept layer runs over all rows (Sec. 2.1).  A run of pruned layers leaves h alone
   // (Sec. 2.2) and stores each layer's K/V projection of it with the layer's own norm scale, W^K, W^V and
   // RoPE (Sec. 3.3); the boundary rows, which are never pruned, leave h for that run and pass its layers
@@ -908,7 +943,7 @@ pop_status prefill_f32(pop_model* m, pop_cache* c, const pop_prefill_args* a, co
   const bool boundary = a->mode == POP_MODE_POP;
   for (int l = 1; l <= cfg.n_layers;) {
     if (!plan.pruned[l]) {
-      if (pop_status s = layer_f32(x, l, T, h, qkv, attn, u, at<int32_t>(ws, w.o_row_seq), d_pos, d_slot, max_len, true))
+      if (pop_status s = layer_f32(x, l, T, h, qkv, attn, u, at<int32_t>(ws, w.o_row_seq), d_pos, d_slot, nullptr, max_len, true))
         return s;
       ++l;
       continue;
@@ -917,17 +952,11 @@ pop_status prefill_f32(pop_model* m, pop_cache* c, const pop_prefill_args* a, co
     while (plan.pruned[r + 1]) ++r;
     if (plan.kv_projection)
       for (int j = l; j <= r; ++j) {
-        const pop_layer_weights& lw = m->layers[j - 1];
         // a sliding-window layer may store only the tail rows a later token can see (window_kv_writes)
         const bool tail = plan.window_writes && !layer_is_global(cfg, j);
-        const int rows = tail ? tr.n : T;
-        F::launch_norm_gemm(h, tail ? at<int32_t>(ws, w.o_tr_row) : nullptr, (const float*)lw.norm_in, cfg.rms_eps,
-                            (const float*)lw.wqkv + (size_t)Dq * d, qkv, 2 * Dkv, rows, 2 * Dkv, d, F::EPI_STORE, 0, st);
-        F::launch_rope_write(qkv, 2 * Dkv, -1, 0, Dkv, cfg.n_q_heads, cfg.n_kv_heads, hd,
-                             tail ? at<int32_t>(ws, w.o_tr_pos) : d_pos, tail ? at<int32_t>(ws, w.o_tr_slot) : d_slot,
-                             layer_is_global(cfg, j) ? (double)cfg.rope_theta : (double)cfg.rope_theta_local,
-                             c->k_pool_f32(j - 1), c->v_pool_f32(j - 1), cfg.page_size, rows, st, nullptr,
-                             (const float*)lw.k_norm, cfg.rms_eps, kv_quant(cfg));
+        const int32_t* tr_row = tail ? at<int32_t>(ws, w.o_tr_row) : nullptr;
+        qkv_f32(x, j, tail ? tr.n : T, h, tr_row, qkv, tail ? at<int32_t>(ws, w.o_tr_pos) : d_pos,
+                tail ? at<int32_t>(ws, w.o_tr_slot) : d_slot, tr_row, true);
       }
     POP_HIP(hipGetLastError());
     if (boundary) {
@@ -935,7 +964,7 @@ pop_status prefill_f32(pop_model* m, pop_cache* c, const pop_prefill_args* a, co
       for (int j = l; j <= r; ++j)
         if (pop_status s = layer_f32(x, j, B, xb, at<float>(ws, w.o_qkvb), at<float>(ws, w.o_attnb),
                                      at<float>(ws, w.o_ub), at<int32_t>(ws, w.o_bnd_seq), at<int32_t>(ws, w.o_bnd_pos),
-                                     at<int32_t>(ws, w.o_bnd_slot), max_len, false))
+                                     at<int32_t>(ws, w.o_bnd_slot), bnd_row, max_len, false))
           return s;
       pop::launch_scatter_rows(xb, bnd_row, h, B, d, st);
     }
@@ -981,11 +1010,12 @@ pop_status decode_step_f32(pop_model* m, pop_cache* c, const int32_t* host_token
   x.B = B;
   x.gates = host_gates;
   float* xb = at<float>(ws, w.o_xb);
-  pop::f32::launch_embed((const float*)m->w.embed, at<int32_t>(ws, w.o_tokens), nullptr, nullptr, xb, B, cfg.d_model, st);
+  pop::f32::launch_embed((const float*)m->w.embed, at<int32_t>(ws, w.o_tokens), nullptr, nullptr, xb, B, cfg.d_model, st,
+                         rope_tables_f32(x, at<int32_t>(ws, w.o_bnd_pos), B));
   for (int l = 1; l <= cfg.n_layers; ++l)
     if (pop_status s = layer_f32(x, l, B, xb, at<float>(ws, w.o_qkvb), at<float>(ws, w.o_attnb),
                                  at<float>(ws, w.o_ub), at<int32_t>(ws, w.o_bnd_seq), at<int32_t>(ws, w.o_bnd_pos),
-                                 at<int32_t>(ws, w.o_bnd_slot), max_len, false))
+                                 at<int32_t>(ws, w.o_bnd_slot), nullptr, max_len, false))
       return s;
   return lm_head_f32(x, B, dev_logits);
 }
@@ -1702,11 +1732,12 @@ pop_status pop_generate(pop_model* m, pop_cache* c, const pop_prefill_args* a, i
     x.B = B;
     float* xb = at<float>(ws, w.o_xb);
     for (int s = 1; s < n_new; ++s) {
-      pop::f32::launch_embed((const float*)m->w.embed, d_tok, nullptr, nullptr, xb, B, cfg.d_model, st);
+      pop::f32::launch_embed((const float*)m->w.embed, d_tok, nullptr, nullptr, xb, B, cfg.d_model, st,
+                             rope_tables_f32(x, d_gpos + (size_t)(s - 1) * B, B));
       for (int l = 1; l <= cfg.n_layers; ++l)
         if (pop_status e = layer_f32(x, l, B, xb, at<float>(ws, w.o_qkvb), at<float>(ws, w.o_attnb),
                                      at<float>(ws, w.o_ub), at<int32_t>(ws, w.o_bnd_seq), d_gpos + (size_t)(s - 1) * B,
-                                     d_gslot + (size_t)(s - 1) * B, max_len + s, false))
+                                     d_gslot + (size_t)(s - 1) * B, nullptr, max_len + s, false))
           return e;
       if (pop_status e = lm_head_f32(x, B, dev_logits)) return e;
       pop::launch_argmax(dev_logits, cfg.vocab, d_tok, dev_tokens_out, n_new, s, eos_token, B, st);

@@ -3,6 +3,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "pop_kernels.h"
+
 namespace pop {
 
 constexpr int kWave = 64;  // CDNA wavefront width
@@ -137,6 +139,27 @@ __device__ __forceinline__ float wave_max_rows(float v) {
   v = group_max<16>(v);
   v = fmaxf(v, __shfl_xor(v, 16, 64));
   return fmaxf(v, __shfl_xor(v, 32, 64));
+}
+
+// Block `t` (256 threads) of those that compute the tables.
+__device__ __forceinline__ void rope_tables_block(const RopeTables& tabs, int t) {
+#pragma unroll
+  for (int j = 0; j < 3; ++j) {
+    if (j >= tabs.n) break;
+    const RopeTable& tab = tabs.t[j];
+    const int n = tab.T * tab.half, blocks = (n + 255) / 256;
+    if (t >= blocks) {
+      t -= blocks;
+      continue;
+    }
+    const int i = t * 256 + threadIdx.x;
+    if (i >= n) return;
+    const int r = i / tab.half, f = i - r * tab.half;
+    double s, c;
+    sincos((double)tab.pos[r] * exp2((double)f * tab.neg2_over_hd_log2theta), &s, &c);
+    tab.cs[i] = make_float2((float)c, (float)s);
+    return;
+  }
 }
 
 }  // namespace pop

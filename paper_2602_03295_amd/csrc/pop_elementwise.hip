@@ -8,16 +8,6 @@
 namespace pop {
 
 // ------------------------------------------------------------------------------------- embed + RoPE tables
-__device__ __forceinline__ void rope_table_entries(const RopeTable& t, int i) {
-  if (i >= t.T * t.half) return;
-  const int r = i / t.half, f = i - r * t.half;
-  const double inv_freq = exp2((double)f * t.neg2_over_hd_log2theta);
-  const double ang = (double)t.pos[r] * inv_freq;
-  double s, c;
-  sincos(ang, &s, &c);
-  t.cs[i] = make_float2((float)c, (float)s);
-}
-
 // One launch for what a call starts with: blocks 0 .. T-1 take an embedding row each, the blocks after them 256 entries
 // of the RoPE tables (a launch of its own costs a decode step of one sequence 4.5 us of 410, whatever its size).
 __global__ __launch_bounds__(256) void embed_kernel(const bf16_t* __restrict__ table,
@@ -25,19 +15,9 @@ __global__ __launch_bounds__(256) void embed_kernel(const bf16_t* __restrict__ t
                                                     const int32_t* __restrict__ row_src,
                                                     const bf16_t* __restrict__ embeds,
                                                     float* __restrict__ h, int T, int d, RopeTables tabs) {
-  int t = blockIdx.x;
+  const int t = blockIdx.x;
   if (t >= T) {
-    t -= T;
-#pragma unroll
-    for (int j = 0; j < 3; ++j) {
-      if (j >= tabs.n) break;
-      const int blocks = (tabs.t[j].T * tabs.t[j].half + 255) / 256;
-      if (t < blocks) {
-        rope_table_entries(tabs.t[j], t * 256 + threadIdx.x);
-        return;
-      }
-      t -= blocks;
-    }
+    rope_tables_block(tabs, t - T);
     return;
   }
   const int src = row_src ? row_src[t] : -1;
@@ -60,7 +40,7 @@ void launch_embed(const bf16_t* table, const int32_t* tokens, const int32_t* row
                   const bf16_t* embeds, float* h, int T, int d, hipStream_t st, const RopeTables& tabs) {
   if (T <= 0 && tabs.n == 0) return;
   int blocks = std::max(T, 0);
-  for (int j = 0; j < tabs.n; ++j) blocks += (tabs.t[j].T * tabs.t[j].half + 255) / 256;
+  blocks += tabs.blocks();
   hipLaunchKernelGGL(embed_kernel, dim3(blocks), dim3(256), 0, st, table, tokens, row_src, embeds, h, std::max(T, 0), d, tabs);
 }
 
@@ -69,17 +49,7 @@ __global__ __launch_bounds__(256) void gather_rows_kernel(const float* __restric
                                                           const int32_t* __restrict__ idx,
                                                           float* __restrict__ dst, int rows, int d, RopeTables tabs) {
   if ((int)blockIdx.x >= rows) {
-    int t = blockIdx.x - rows;
-#pragma unroll
-    for (int j = 0; j < 3; ++j) {
-      if (j >= tabs.n) break;
-      const int blocks = (tabs.t[j].T * tabs.t[j].half + 255) / 256;
-      if (t < blocks) {
-        rope_table_entries(tabs.t[j], t * 256 + threadIdx.x);
-        return;
-      }
-      t -= blocks;
-    }
+    rope_tables_block(tabs, blockIdx.x - rows);
     return;
   }
   const float* s = src + (size_t)idx[blockIdx.x] * d;
@@ -92,7 +62,7 @@ void launch_gather_rows(const float* src, const int32_t* idx, float* dst, int ro
                         const RopeTables& tabs) {
   if (rows <= 0) return;
   int blocks = rows;
-  for (int j = 0; j < tabs.n; ++j) blocks += (tabs.t[j].T * tabs.t[j].half + 255) / 256;
+  blocks += tabs.blocks();
   hipLaunchKernelGGL(gather_rows_kernel, dim3(blocks), dim3(256), 0, st, src, idx, dst, rows, d, tabs);
 }
 

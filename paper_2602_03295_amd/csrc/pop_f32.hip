@@ -19,8 +19,12 @@ namespace impl {
 // h[t,:] = row_src[t] < 0 ? table[tokens[t],:] : embeds[row_src[t],:]
 __global__ void embed_kernel(const float* __restrict__ table, const int32_t* __restrict__ tokens,
                              const int32_t* __restrict__ row_src, const float* __restrict__ embeds,
-                             float* __restrict__ h, int d) {
+                             float* __restrict__ h, int T, int d, RopeTables tabs) {
   const int t = blockIdx.x;
+  if (t >= T) {                // the blocks after the rows: the RoPE tables
+    rope_tables_block(tabs, t - T);
+    return;
+  }
   const int rs = row_src ? row_src[t] : -1;
   const float* src = rs < 0 ? table + (size_t)tokens[t] * d : embeds + (size_t)rs * d;
   for (int i = threadIdx.x; i < d; i += blockDim.x) h[(size_t)t * d + i] = src[i];
@@ -42,7 +46,11 @@ __device__ __forceinline__ float glu_act(float g, int act) {
 // took 47 us, this 5 us; N = 256, K = 688: 160 and 6 us).
 // NORM: the rows of A are RMS-normalised on the way (the LN of Sec. 2.1): C = rstd (A * gamma) W^T, with the sum of
 // squares taken from the same loads.  row_idx: row m of A is A[row_idx[m]].
-// EPI: 0 store, 1 out += scale C, 2 out = act(A Wg^T) * (A Wu^T) with Wg = W rows 0..N-1, Wu = rows N..2N-1.
+// EPI: 0 store, 1 out += scale C, 2 out = act(A Wg^T) * (A Wu^T) with Wg = W rows 0..N-1, Wu = rows N..2N-1,
+// EPI_QKV (KW > 1): RoPE and the append (RopeAppend).  A work-group's columns are then rotation pairs, the first half of them
+// dims pair0, pair0 + 1, .. of a head and the others their partners, and the tables are read before the products.  The append
+// as a kernel of its own, which formed its angles in fp64, was one launch in six: 8 layers of 128 rows 288 -> 271 us.
+constexpr int EPI_QKV = 3;
 struct GemmF32 {
   const float* A;
   const float* W;
@@ -51,6 +59,7 @@ struct GemmF32 {
   const float* gamma;
   int lda, ldw, ldc, M, N, K, act;
   float eps, scale;
+  RopeAppend ra;     // EPI_QKV
 };
 
 template <int TM, int TN, int KW, int EPI, bool NORM>
@@ -64,6 +73,9 @@ __global__ __launch_bounds__(KW == 1 ? 256 : 64 * KW) void gemm_kernel(GemmF32 p
   const int kw = KW > 1 ? wave : 0;
   const int m0 = (KW > 1 ? blockIdx.y : blockIdx.y * 2 + (wave >> 1)) * TM * 16;
   const int n0 = (KW > 1 ? blockIdx.x : blockIdx.x * 2 + (wave & 1)) * TN * 16;
+  static_assert(EPI != EPI_QKV || (KW >= TM && KW > 1 && TN <= 2), "a wave finishes all columns of 16 rows");
+  const int hd = EPI == EPI_QKV ? p.ra.hd : 0, half = hd >> 1;
+  const int head = EPI == EPI_QKV ? n0 / hd : 0, pair0 = EPI == EPI_QKV ? n0 % hd / 2 : 0;
   // rows and columns beyond the matrix repeat its last one (never stored)
   const float* ar[TM];
   const float* wr[NB];
@@ -74,7 +86,11 @@ __global__ __launch_bounds__(KW == 1 ? 256 : 64 * KW) void gemm_kernel(GemmF32 p
   }
 #pragma unroll
   for (int j = 0; j < NB; ++j) {
-    const int n = min(n0 + (j % TN) * 16 + r16, p.N - 1);
+    int n = min(n0 + (j % TN) * 16 + r16, p.N - 1);
+    if (EPI == EPI_QKV) {      // (N is a multiple of the tile's columns)
+      const int c = j * 16 + r16;
+      n = head * hd + pair0 + c % (TN * 8) + c / (TN * 8) * half;
+    }
     wr[j] = p.W + (size_t)(j < TN ? n : p.N + n) * p.ldw + 4 * g;
   }
   floatx4_t acc[TM][NB];
@@ -84,6 +100,17 @@ __global__ __launch_bounds__(KW == 1 ? 256 : 64 * KW) void gemm_kernel(GemmF32 p
     ss[i] = 0.f;
 #pragma unroll
     for (int j = 0; j < NB; ++j) acc[i][j] = floatx4_t{0.f, 0.f, 0.f, 0.f};
+  }
+  // EPI_QKV: (cos, sin) of the pairs that this wave will finish, four per lane, and the rows' slots
+  float4 cs01, cs23;
+  int slot = 0;
+  if (EPI == EPI_QKV) {
+    const int m = min(m0 + min(wave, TM - 1) * 16 + r16, p.M - 1);
+    const float4* cs = reinterpret_cast<const float4*>(p.ra.cs + (size_t)(p.ra.cs_row ? p.ra.cs_row[m] : m) * half + pair0 +
+                                                       (TN == 1 ? 4 * (g & 1) : 4 * g));
+    cs01 = cs[0];
+    cs23 = cs[1];
+    slot = p.ra.slot[m];
   }
   const int chunks = (p.K + 15) >> 4, per = (chunks + KW - 1) / KW;
   const int c_end = min(chunks, (kw + 1) * per);
@@ -144,19 +171,21 @@ __global__ __launch_bounds__(KW == 1 ? 256 : 64 * KW) void gemm_kernel(GemmF32 p
     __syncthreads();
   }
   // wave w of a split finishes blocks w, w + KW, ...; without a split every wave its own
-  for (int blk = KW > 1 ? wave : 0; blk < TM * TN; blk += KW) {
-    const int i = blk / TN, j = blk % TN;
+  // (EPI_QKV: 16 rows with all their columns)
+  constexpr int JN = EPI == EPI_QKV ? 1 : TN, UP = EPI == EPI_GLU ? TN : EPI == EPI_QKV ? TN - 1 : 0;   // `up`: the block UP on
+  for (int blk = KW > 1 ? wave : 0; blk < TM * JN; blk += KW) {
+    const int i = blk / JN, j = blk % JN;
     float4 c, up;
     float sq = 0.f;
     if (KW > 1) {
       c = red[0][i * NB + j][lane];
-      up = red[0][i * NB + (EPI == EPI_GLU ? TN + j : j)][lane];
+      up = red[0][i * NB + UP + j][lane];
       if (NORM) sq = red_ss[0][i][r16];
       for (int k = 1; k < KW; ++k) {
         const float4 x = red[k][i * NB + j][lane];
         c.x += x.x; c.y += x.y; c.z += x.z; c.w += x.w;
-        if (EPI == EPI_GLU) {
-          const float4 y = red[k][i * NB + TN + j][lane];
+        if (UP > 0) {
+          const float4 y = red[k][i * NB + UP + j][lane];
           up.x += y.x; up.y += y.y; up.z += y.z; up.w += y.w;
         }
         if (NORM) sq += red_ss[k][i][r16];
@@ -174,6 +203,46 @@ __global__ __launch_bounds__(KW == 1 ? 256 : 64 * KW) void gemm_kernel(GemmF32 p
     }
     const float rstd = NORM ? 1.0f / sqrtf(sq / (float)p.K + p.eps) : 1.f;
     const int m = m0 + i * 16 + r16, n = n0 + j * 16 + 4 * g;
+    if constexpr (EPI == EPI_QKV) {
+      // x: this lane's values (with 32 columns the low halves of its pairs), y: their partners.  16 columns: lane groups 0, 1
+      // have the low halves of 8 pairs, lane groups 2, 3 the high ones
+      float x[4] = {c.x * rstd, c.y * rstd, c.z * rstd, c.w * rstd}, y[4];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) y[e] = TN == 1 ? __shfl_xor(x[e], 32, 64) : (&up.x)[e] * rstd;
+      const bool low = TN == 2 || g < 2;
+      const RopeAppend& ra = p.ra;
+      const bool rotate = head < ra.n_q_heads + ra.n_kv_heads;
+      if (rotate) {
+        const float cc[4] = {cs01.x, cs01.z, cs23.x, cs23.z}, sn[4] = {cs01.y, cs01.w, cs23.y, cs23.w};
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const float a = low ? x[e] * cc[e] - y[e] * sn[e] : x[e] * cc[e] + y[e] * sn[e];
+          y[e] = y[e] * cc[e] + x[e] * sn[e];      // (used with 32 columns)
+          x[e] = a;
+        }
+      }
+      if (m >= p.M) continue;
+      auto store = [&](const float (&v)[4], int dim) {
+        if (head < ra.n_q_heads) {
+          *reinterpret_cast<float4*>(p.out + (size_t)m * p.ldc + head * hd + dim) = make_float4(v[0], v[1], v[2], v[3]);
+          return;
+        }
+        const int hh = rotate ? head - ra.n_q_heads : head - ra.n_q_heads - ra.n_kv_heads;
+        float* o = (rotate ? ra.k_pool : ra.v_pool) +
+                   (((size_t)(slot / ra.page_size) * ra.n_kv_heads + hh) * ra.page_size + slot % ra.page_size) * hd + dim;
+        float w[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e)   // 8-bit cache: the fp32 entry holds the value of the e4m3 code the element rounds to
+          w[e] = !ra.kvq.fp8 ? v[e]
+                             : e4m3_decode(e4m3_encode(v[e] * (rotate ? ra.kvq.k_inv : ra.kvq.v_inv))) *
+                                   (rotate ? ra.kvq.k_scale : ra.kvq.v_scale);
+        *reinterpret_cast<float4*>(o) = make_float4(w[0], w[1], w[2], w[3]);
+      };
+      const int dim = pair0 + (TN == 1 ? 4 * (g & 1) : 4 * g);
+      store(x, low ? dim : dim + half);
+      if (TN == 2) store(y, dim + half);
+      continue;
+    }
     if (m >= p.M) continue;
     float* o = p.out + (size_t)m * p.ldc + n;
     if (n + 3 < p.N && (p.ldc & 3) == 0) {     // four columns at once
@@ -502,9 +571,9 @@ __global__ __launch_bounds__(256) void attention_tile_kernel(AttnF32 a) {
 }  // namespace impl
 
 void launch_embed(const float* table, const int32_t* tokens, const int32_t* row_src, const float* embeds, float* h,
-                  int T, int d, hipStream_t st) {
+                  int T, int d, hipStream_t st, const RopeTables& tabs) {
   if (T <= 0) return;
-  hipLaunchKernelGGL(impl::embed_kernel, dim3(T), dim3(256), 0, st, table, tokens, row_src, embeds, h, d);
+  hipLaunchKernelGGL(impl::embed_kernel, dim3(T + tabs.blocks()), dim3(256), 0, st, table, tokens, row_src, embeds, h, T, d, tabs);
 }
 
 namespace impl {
@@ -522,6 +591,8 @@ void launch_gemm_en(const GemmF32& p, hipStream_t st) {
     hipLaunchKernelGGL((gemm_kernel<4, TN, 1, EPI, NORM>), dim3(up(p.N, 32 * TN), up(p.M, 128)), dim3(256), 0, st, p);
   }
 }
+// The two forms whose waves split K; more work than that (where one launch less is nothing) takes the append kernel.
+bool qkv_small(int M, int N) { return (long long)((M + 15) / 16) * ((N + 15) / 16) <= 512; }
 template <bool NORM>
 void launch_gemm_n(const GemmF32& p, int epi, hipStream_t st) {
   if (p.M <= 0 || p.N <= 0) return;
@@ -533,12 +604,27 @@ void launch_gemm_n(const GemmF32& p, int epi, hipStream_t st) {
 
 void launch_gemm(const float* A, int lda, const float* W, int ldw, float* out, int ldc, int M, int N, int K, int epi,
                  int act, hipStream_t st, float scale) {
-  impl::launch_gemm_n<false>(impl::GemmF32{A, W, out, nullptr, nullptr, lda, ldw, ldc, M, N, K, act, 0.f, scale}, epi, st);
+  impl::launch_gemm_n<false>(impl::GemmF32{A, W, out, nullptr, nullptr, lda, ldw, ldc, M, N, K, act, 0.f, scale, {}}, epi, st);
 }
 
 void launch_norm_gemm(const float* x, const int32_t* row_idx, const float* gamma, float eps, const float* W, float* out,
                       int ldc, int M, int N, int K, int epi, int act, hipStream_t st) {
-  impl::launch_gemm_n<true>(impl::GemmF32{x, W, out, row_idx, gamma, K, K, ldc, M, N, K, act, eps, 1.f}, epi, st);
+  impl::launch_gemm_n<true>(impl::GemmF32{x, W, out, row_idx, gamma, K, K, ldc, M, N, K, act, eps, 1.f, {}}, epi, st);
+}
+
+bool norm_qkv_supported(int M, int N, int hd) {
+  return hd % 32 == 0 && N % hd == 0 && (impl::qkv_small(M, N) || (long long)((M + 31) / 32) * ((N + 31) / 32) <= 4096);
+}
+
+void launch_norm_qkv(const float* x, const int32_t* row_idx, const float* gamma, float eps, const float* W, float* out,
+                     int ldc, int M, int K, const RopeAppend& ra, hipStream_t st) {
+  if (M <= 0) return;
+  const int N = (ra.n_q_heads + 2 * ra.n_kv_heads) * ra.hd;
+  const impl::GemmF32 p{x, W, out, row_idx, gamma, K, K, ldc, M, N, K, 0, eps, 1.f, ra};
+  if (impl::qkv_small(M, N))
+    hipLaunchKernelGGL((impl::gemm_kernel<1, 1, 8, impl::EPI_QKV, true>), dim3(N / 16, (M + 15) / 16), dim3(512), 0, st, p);
+  else
+    hipLaunchKernelGGL((impl::gemm_kernel<2, 2, 4, impl::EPI_QKV, true>), dim3(N / 32, (M + 31) / 32), dim3(256), 0, st, p);
 }
 
 void launch_rope_write(float* qkv, int ld, int q_col, int k_col, int v_col, int n_q_heads, int n_kv_heads, int hd,

@@ -36,6 +36,11 @@ struct RopeTables {
   int n = 0;
   RopeTable t[3];
   void add(const int32_t* pos, float2* cs, int T, int hd, double theta);
+  int blocks() const {       // of 256 threads, for all tables
+    int b = 0;
+    for (int j = 0; j < n; ++j) b += (t[j].T * t[j].half + 255) / 256;
+    return b;
+  }
 };
 // h[t,:] = row_src[t] < 0 ? table[tokens[t],:] : embeds[row_src[t],:]      (fp32 residual stream), and the tables.
 void launch_embed(const bf16_t* table, const int32_t* tokens, const int32_t* row_src,
@@ -301,13 +306,26 @@ namespace f32 {
 constexpr int kMaxContext = 15000;  // scores of one query row are held in LDS
 enum { EPI_STORE = 0, EPI_ADD = 1, EPI_GLU = 2 };
 void launch_embed(const float* table, const int32_t* tokens, const int32_t* row_src, const float* embeds, float* h,
-                  int T, int d, hipStream_t st);
+                  int T, int d, hipStream_t st, const RopeTables& tabs);
 // out (op)= A[M,K] W[N,K]^T ; EPI_GLU: W is [2N,K] (gate rows, then up rows)
 void launch_gemm(const float* A, int lda, const float* W, int ldw, float* out, int ldc, int M, int N, int K, int epi,
                  int act, hipStream_t st, float scale = 1.f);   // EPI_ADD: out += scale * C
 // The same with A = LN(x[row_idx ? row_idx[m] : m, :]) (rows of K values, scale gamma), normalised inside the kernel.
 void launch_norm_gemm(const float* x, const int32_t* row_idx, const float* gamma, float eps, const float* W, float* out,
                       int ldc, int M, int N, int K, int epi, int act, hipStream_t st);
+// LN, the projection to q | k | v (n_q_heads 0: k | v), RoPE and the append in one launch: rotated q at out[m, :] (row stride
+// ldc), k and v at slot[m] of the pages.  cs: tables of hd/2 pairs per row, row m's at index cs_row ? cs_row[m] : m.
+struct RopeAppend {
+  int hd, n_q_heads, n_kv_heads, page_size;
+  const float2* cs;
+  const int32_t* cs_row;
+  const int32_t* slot;
+  float *k_pool, *v_pool;
+  KvQuant kvq;
+};
+bool norm_qkv_supported(int M, int N, int hd);
+void launch_norm_qkv(const float* x, const int32_t* row_idx, const float* gamma, float eps, const float* W, float* out,
+                     int ldc, int M, int K, const RopeAppend& ra, hipStream_t st);
 // rotate q (unless q_col < 0) and k of `rows` rows in place, append k, v at slot[row]
 void launch_rope_write(float* qkv, int ld, int q_col, int k_col, int v_col, int n_q_heads, int n_kv_heads, int hd,
                        const int32_t* pos, const int32_t* slot, double theta, float* k_pool, float* v_pool, int P,

@@ -174,3 +174,26 @@ def test_fp32_tiles_of_64_rows_per_wave(pop, gated):
         for l in range(2):
             k, v = run.kv(l, b)
             assert rel_err(k, Kc[l]) <= TOL32 and rel_err(v, Vc[l]) <= TOL32
+
+
+@pytest.mark.parametrize("lens", [[1, 15, 16, 17, 33, 2], [257, 400, 31]])   # tiles of 16 x 16 and of 32 x 32
+@pytest.mark.parametrize("hd", [64, 128, 256])
+def test_fp32_projection_that_rotates_and_appends(pop, hd, lens):
+    """RoPE and the append in the epilogue of the projection: all rows against the oracle, and the gathered tail rows of
+    pruned sliding-window layers against the entries that a call without that option leaves."""
+    window = 20
+    cfg = synth.get_config("tiny", n_layers=4, d_model=136, n_q_heads=3, n_kv_heads=1, head_dim=hd, d_ffn=72, vocab=67,
+                           sliding_window=window, global_every=2, rope_theta_local=100.0)
+    W = synth.make_weights(cfg, seed=21)
+    synth.randomize_norms(W, cfg)
+    tokens = synth.make_tokens(cfg["vocab"], sum(lens), seed=22)
+    full, tail = (DeviceRun(pop, cfg, W, lens, shuffle_seed=5) for _ in range(2))
+    logits = full.prefill(tokens, 1)
+    compare_with_oracle(full, W, tokens, 1, logits, tol=TOL32)
+    # (the same products in another tile: fp32 roundings alone)
+    assert rel_err(tail.prefill(tokens, 1, window_kv_writes=True), logits.astype(np.float64)) <= TOL32
+    for l in range(cfg["n_layers"]):
+        for b, n in enumerate(lens):
+            first = max(0, n - window) if l in (2,) else 0          # layer 3 of 4 is pruned and local
+            for a, c in zip(full.kv(l, b), tail.kv(l, b)):
+                assert rel_err(c[first:], a[first:].astype(np.float64)) <= TOL32
