@@ -7,6 +7,7 @@
 #include <math.h>
 
 #include <algorithm>
+#include <type_traits>
 
 #include "pop_device.h"
 #include "pop_kernels.h"
@@ -44,6 +45,8 @@ __device__ __forceinline__ float glu_act(float g, int act) {
 // Bound by latency at the sizes this path is for, hence the split of K inside the work-group: 128 rows, N = 512,
 // K = 256: 256 work-groups of 8 waves with 2 chunks each (64 x 64 tiles with one wave's worth of parallelism per SIMD
 // took 47 us, this 5 us; N = 256, K = 688: 160 and 6 us).
+// A wave's last chunks are loaded two at a time: with four, of which K = 256 leaves a wave two, the masked ones cost as much as the
+// others (128 rows: gate|up of 2 x 688 columns 10.5 -> 7.7 us, O 4.6 -> 3.8; a call of 8 layers 271 -> 232 us).
 // NORM: the rows of A are RMS-normalised on the way (the LN of Sec. 2.1): C = rstd (A * gamma) W^T, with the sum of
 // squares taken from the same loads.  row_idx: row m of A is A[row_idx[m]].
 // EPI: 0 store, 1 out += scale C, 2 out = act(A Wg^T) * (A Wu^T) with Wg = W rows 0..N-1, Wu = rows N..2N-1,
@@ -65,7 +68,7 @@ struct GemmF32 {
 template <int TM, int TN, int KW, int EPI, bool NORM>
 __global__ __launch_bounds__(KW == 1 ? 256 : 64 * KW) void gemm_kernel(GemmF32 p) {
   constexpr int NB = EPI == EPI_GLU ? 2 * TN : TN;     // W blocks of a wave
-  constexpr int U = TM * NB >= 8 ? 2 : 4;              // chunks of 16 k requested together
+  constexpr int U = TM * NB >= 8 ? 2 : 4;              // chunks of 16 k requested together (2 where no more are left)
   __shared__ float4 red[KW > 1 ? KW : 1][KW > 1 ? TM * NB : 1][64];
   __shared__ float red_ss[KW][TM][16];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -114,7 +117,8 @@ __global__ __launch_bounds__(KW == 1 ? 256 : 64 * KW) void gemm_kernel(GemmF32 p
   }
   const int chunks = (p.K + 15) >> 4, per = (chunks + KW - 1) / KW;
   const int c_end = min(chunks, (kw + 1) * per);
-  for (int c0 = kw * per; c0 < c_end; c0 += U) {
+  auto step = [&](int c0, auto u_c) {
+    constexpr int U = decltype(u_c)::value;
     // Loads without branches, so that all of a step are in flight together: a lane beyond K, or of a chunk beyond
     // this wave's, reads the row's start and its activations are replaced by zeros.
     float4 a[U][TM], w[U][NB], gm[U];
@@ -152,7 +156,11 @@ __global__ __launch_bounds__(KW == 1 ? 256 : 64 * KW) void gemm_kernel(GemmF32 p
           for (int i = 0; i < TM; ++i)
             acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32((&w[u][j].x)[e], (&a[u][i].x)[e], acc[i][j], 0, 0, 0);
     }
-  }
+  };
+  int c0 = kw * per;
+  if (U > 2)
+    for (; c_end - c0 > 2; c0 += U) step(c0, std::integral_constant<int, U>{});
+  for (; c0 < c_end; c0 += 2) step(c0, std::integral_constant<int, 2>{});
   // acc[i][j][v]: row m0 + 16 i + lane % 16, column n0 + 16 j + 4 (lane / 16) + v
   if (NORM) {
 #pragma unroll
