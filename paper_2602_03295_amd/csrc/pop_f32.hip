@@ -358,12 +358,21 @@ struct AttnF32 {
 
 // Attn of Sec. 2.1 for one (row, query head) per work-group against the paged cache of the row's sequence (rows of
 // different sequences: decode steps, boundary rows).  HD/4 lanes share a key, 16 bytes each; scores live in LDS.
-template <int HD>
-__global__ __launch_bounds__(256) void attention_kernel(AttnF32 a) {
-  constexpr int LPK = HD / 4, KPI = 256 / LPK;     // lanes per key, keys per pass of the work-group
+// Every four passes wait for the block table and then for the entries, for K and again for V, hence NT = 1024 threads where
+// 256 take more than four passes (heads of 64: 64 keys) and the work-groups find a CU each: one row of 4 heads over 128 keys
+// 8.2 -> 6.5 us.  With fewer keys the barriers of 16 waves cost more (5 rows over 4 to 12 keys, a call 222 us, 224 with 1024).
+template <int HD, int NT>
+__global__ __launch_bounds__(NT) void attention_kernel(AttnF32 a) {
+  constexpr int LPK = HD / 4, KPI = NT / LPK, NW = NT / 64;   // lanes per key, keys per pass of the work-group, waves
   extern __shared__ float sc[];                    // [n keys]
-  __shared__ float red[4];
-  __shared__ float4 red_o[KPI][LPK];
+  __shared__ float red[NW];
+  __shared__ float4 red_o[NW][LPK];
+  auto over_waves = [&](auto op) {
+    float v = red[0];
+#pragma unroll
+    for (int w = 1; w < NW; ++w) v = op(v, red[w]);
+    return v;
+  };
   const int r = blockIdx.x, head = blockIdx.y, tid = threadIdx.x;
   const int b = a.row_seq[r], pos = a.row_pos[r];
   const int lo = first_key(pos, b, a.window, a.kv_first);
@@ -394,10 +403,10 @@ __global__ __launch_bounds__(256) void attention_kernel(AttnF32 a) {
   mx = wave_max(mx);
   if ((tid & 63) == 0) red[tid >> 6] = mx;
   __syncthreads();
-  mx = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
+  mx = over_waves([](float x, float y) { return fmaxf(x, y); });
   __syncthreads();
   float sum = 0.f;
-  for (int j = tid; j < n; j += 256) {
+  for (int j = tid; j < n; j += NT) {
     const float pv = expf(sc[j] - mx);
     sc[j] = pv;
     sum += pv;
@@ -405,7 +414,7 @@ __global__ __launch_bounds__(256) void attention_kernel(AttnF32 a) {
   sum = wave_sum(sum);
   if ((tid & 63) == 0) red[tid >> 6] = sum;
   __syncthreads();
-  const float tot = (red[0] + red[1]) + (red[2] + red[3]);
+  const float tot = over_waves([](float x, float y) { return x + y; });
   float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
 #pragma unroll 4
   for (int j = ks; j < n; j += KPI) {
@@ -413,12 +422,19 @@ __global__ __launch_bounds__(256) void attention_kernel(AttnF32 a) {
     const float pv = sc[j];
     acc.x += pv * v.x; acc.y += pv * v.y; acc.z += pv * v.z; acc.w += pv * v.w;
   }
-  red_o[ks][li] = acc;
+  // the keys of a wave, then the waves in order
+#pragma unroll
+  for (int w = LPK; w < 64; w *= 2) {
+    acc.x += __shfl_xor(acc.x, w, 64); acc.y += __shfl_xor(acc.y, w, 64);
+    acc.z += __shfl_xor(acc.z, w, 64); acc.w += __shfl_xor(acc.w, w, 64);
+  }
+  if ((tid & 63) < LPK) red_o[tid >> 6][li] = acc;
   __syncthreads();
   if (tid < LPK) {
     float4 o = red_o[0][tid];
-    for (int k = 1; k < KPI; ++k) {
-      const float4 x = red_o[k][tid];
+#pragma unroll
+    for (int w = 1; w < NW; ++w) {
+      const float4 x = red_o[w][tid];
       o.x += x.x; o.y += x.y; o.z += x.z; o.w += x.w;
     }
     *reinterpret_cast<float4*>(a.out + (size_t)r * a.n_q_heads * HD + head * HD + tid * 4) =
@@ -655,7 +671,15 @@ hipError_t launch_attention_hd(const AttnF32& a, bool packed, int max_len, hipSt
     if (attr_err != hipSuccess) return attr_err;
     hipLaunchKernelGGL(attention_tile_kernel<HD>, dim3((a.rows + 15) / 16, a.n_q_heads), dim3(256), smem, st, a);
   } else {
-    hipLaunchKernelGGL(attention_kernel<HD>, dim3(a.rows, a.n_q_heads), dim3(256), (size_t)max_len * sizeof(float), st, a);
+    const dim3 grid(a.rows, a.n_q_heads);
+    if (max_len > 64 && (long long)a.rows * a.n_q_heads <= 256) {
+      static const hipError_t attr_err = hipFuncSetAttribute(reinterpret_cast<const void*>(&attention_kernel<HD, 1024>),
+                                                             hipFuncAttributeMaxDynamicSharedMemorySize, kMaxContext * (int)sizeof(float));
+      if (attr_err != hipSuccess) return attr_err;
+      hipLaunchKernelGGL((attention_kernel<HD, 1024>), grid, dim3(1024), (size_t)max_len * sizeof(float), st, a);
+    } else {
+      hipLaunchKernelGGL((attention_kernel<HD, 256>), grid, dim3(256), (size_t)max_len * sizeof(float), st, a);
+    }
   }
   return hipGetLastError();
 }

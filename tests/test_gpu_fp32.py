@@ -197,3 +197,20 @@ def test_fp32_projection_that_rotates_and_appends(pop, hd, lens):
             first = max(0, n - window) if l in (2,) else 0          # layer 3 of 4 is pruned and local
             for a, c in zip(full.kv(l, b), tail.kv(l, b)):
                 assert rel_err(c[first:], a[first:].astype(np.float64)) <= TOL32
+
+
+@pytest.mark.parametrize("hd", [64, 128, 256])
+@pytest.mark.parametrize("lens", [[62], [63], [64, 3], [130], [64] * 66])   # 64 keys, 65, more rows than CUs
+def test_fp32_decode_attention_thread_counts(pop, hd, lens):
+    """One row per sequence: 256 and 1024 threads per row and head, keys at the edges of their passes."""
+    cfg = synth.get_config("tiny", n_layers=1, d_model=72, n_q_heads=4, n_kv_heads=2, head_dim=hd, d_ffn=40, vocab=64)
+    W = synth.make_weights(cfg, seed=25)
+    tokens = synth.make_tokens(cfg["vocab"], sum(lens), seed=26)
+    run = DeviceRun(pop, cfg, W, lens, shuffle_seed=6)
+    run.prefill(tokens, 1)
+    step = synth.make_tokens(cfg["vocab"], len(lens), seed=27)
+    got = run.decode(step)
+    outs = O.pop_prefill_batch(cfg, W, tokens, run.cu, 1)
+    for b in range(0, len(lens), 13):
+        ref, _, _ = O.decode_step(cfg, W, O.embed_rows(W, step[b:b + 1], np.float64)[0], outs[b][0], outs[b][1])
+        assert rel_err(got[b], ref) <= TOL32
