@@ -937,12 +937,15 @@ pop_status prefill_f32(pop_model* m, pop_cache* c, const pop_prefill_args* a, co
   // Layers in order.  A kept layer runs over all rows (Sec. 2.1).  A run of pruned layers leaves h alone
   // (Sec. 2.2) and stores each layer's K/V projection of it with the layer's own norm scale, W^K, W^V and
   // RoPE (Sec. 3.3); the boundary rows, which are never pruned, leave h for that run and pass its layers
-  // in full against the cache (Sec. 3.3, boundary handling), then return to their rows of h.
+  // in full against the cache (Sec. 3.3, boundary handling), then return to their rows of h if a kept layer follows.
   float* xb = at<float>(ws, w.o_xb);
   const int32_t* bnd_row = at<int32_t>(ws, w.o_bnd_row);
   const bool boundary = a->mode == POP_MODE_POP;
+  bool rows_in_xb = false;   // the boundary rows' current state is in xb rather than in h
   for (int l = 1; l <= cfg.n_layers;) {
     if (!plan.pruned[l]) {
+      if (rows_in_xb) pop::launch_scatter_rows(xb, bnd_row, h, B, d, st);
+      rows_in_xb = false;
       if (pop_status s = layer_f32(x, l, T, h, qkv, attn, u, at<int32_t>(ws, w.o_row_seq), d_pos, d_slot, nullptr, max_len, true))
         return s;
       ++l;
@@ -966,14 +969,14 @@ pop_status prefill_f32(pop_model* m, pop_cache* c, const pop_prefill_args* a, co
                                      at<float>(ws, w.o_ub), at<int32_t>(ws, w.o_bnd_seq), at<int32_t>(ws, w.o_bnd_pos),
                                      at<int32_t>(ws, w.o_bnd_slot), bnd_row, max_len, false))
           return s;
-      pop::launch_scatter_rows(xb, bnd_row, h, B, d, st);
+      rows_in_xb = true;
     }
     l = r + 1;
   }
   // logits of each sequence's last row: the boundary token's (full depth), or, without boundary handling,
   // the pruned model's output for it
   if (a->mode != POP_MODE_BODY_ONLY) {
-    pop::launch_gather_rows(h, bnd_row, xb, B, d, st);
+    if (!rows_in_xb) pop::launch_gather_rows(h, bnd_row, xb, B, d, st);
     if (pop_status s = lm_head_f32(x, B, dev_logits)) return s;
   }
   POP_HIP(hipGetLastError());
