@@ -78,6 +78,10 @@ pop_status pop_op_rope_attention(void* qkv, const int32_t* host_cu_seqlens, int3
                                  int32_t n_kv_heads, int32_t head_dim, float rope_theta, int32_t window,
                                  void* out, void* workspace, size_t workspace_bytes, pop_stream stream);
 
+/* Query rows of a work-group with which pop_op_rope_attention (and the prefill) would run a batch: 256, 128 or 64 with head
+ * sizes 64 and 128, 128 with head size 256; 0 for arguments that it refuses.  Nothing is launched and no device is needed. */
+int32_t pop_op_rope_attention_tile_rows(const int32_t* host_cu_seqlens, int32_t n_seqs, int32_t n_q_heads, int32_t head_dim);
+
 #ifdef __cplusplus
 }
 #endif

@@ -386,6 +386,10 @@ int build_attention_work(const int32_t* cu, int B, int n_heads, int hd, pop::Att
     return n * n_heads;
   };
   *tile_rows = hd <= 128 && us(256, 1, 1.5, 1.9, 8.6) <= us(128, 2, 1.95, 1.95, 9.7) ? 256 : 128;
+  // Where no sequence is longer than a key tile (64), each is one tile of a third form.
+  int longest = 0;
+  for (int b = 0; b < B; ++b) longest = std::max(longest, cu[b + 1] - cu[b]);
+  if (hd <= 128 && longest <= 64) *tile_rows = 64;
   const int rows = *tile_rows;
   // Head size 256: one or two query tiles of a sequence; the k-th latest tile (most keys) is paired with the k-th earliest
   // (fewest), which balances the causal triangle.  Where the tiles of all heads do not fill the chip once, each gets a
@@ -1886,6 +1890,16 @@ RopeAttnWs carve_rope_attn(int T, int B, int Hkv, int hd) {
 size_t pop_op_rope_attention_workspace(int32_t T, int32_t n_seqs, int32_t n_kv_heads, int32_t head_dim) {
   if (T < 1 || n_seqs < 1 || n_kv_heads < 1 || head_dim < 2) return 0;
   return carve_rope_attn(T, n_seqs, n_kv_heads, head_dim).total;
+}
+
+int32_t pop_op_rope_attention_tile_rows(const int32_t* cu, int32_t B, int32_t Hq, int32_t hd) {
+  if (!cu || B < 1 || Hq < 1 || (hd != 64 && hd != 128 && hd != 256) || cu[0] != 0) return 0;
+  for (int b = 0; b < B; ++b)
+    if (cu[b + 1] <= cu[b]) return 0;
+  std::vector<pop::AttnTile> tiles((size_t)cu[B] / 128 + B);
+  int rows = 0;
+  build_attention_work(cu, B, Hq, hd, tiles.data(), &rows);
+  return rows;
 }
 
 pop_status pop_op_rope_attention(void* qkv, const int32_t* cu, int32_t B, int32_t Hq, int32_t Hkv, int32_t hd,

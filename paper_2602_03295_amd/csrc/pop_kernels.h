@@ -203,7 +203,7 @@ struct AttnPrefillArgs {
   int window;         // 0 = global
   const AttnTile* tiles;
   int n_tiles;
-  int tile_rows;      // query rows of a tile: 256 or 128 (head size 256: always 128)
+  int tile_rows;      // query rows of a tile: 256, 128 or (no sequence longer than that) 64; head size 256: always 128
 };
 hipError_t launch_attention_prefill(const AttnPrefillArgs& a, hipStream_t st);
 

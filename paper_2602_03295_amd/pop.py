@@ -108,6 +108,7 @@ lib.pop_op_rope_attention_workspace.argtypes = [C.c_int32] * 4
 lib.pop_op_rope_attention_workspace.restype = C.c_size_t
 lib.pop_op_rope_attention.argtypes = [C.c_void_p, _i32p, C.c_int32, C.c_int32, C.c_int32, C.c_int32, C.c_float,
                                       C.c_int32, C.c_void_p, C.c_void_p, C.c_size_t, C.c_void_p]
+lib.pop_op_rope_attention_tile_rows.argtypes = [_i32p, C.c_int32, C.c_int32, C.c_int32]
 
 lib.pop_timing_enable.argtypes = [C.c_void_p, C.c_int32]
 lib.pop_timing_read.argtypes = [C.c_void_p, C.POINTER(C.c_float), _i32p]
@@ -118,7 +119,8 @@ EXPORTED = ["pop_timing_enable", "pop_timing_read", "pop_last_error", "pop_versi
             "pop_workspace_bytes", "pop_cache_create", "pop_cache_destroy", "pop_cache_n_seqs",
             "pop_cache_seq_lens", "pop_cache_block_table", "pop_slot_map", "pop_prefill", "pop_decode_step", "pop_decode_step_gated", "pop_generate",
             "pop_generate_workspace_bytes", "pop_op_rmsnorm",
-            "pop_op_gemm", "pop_op_gemm_plan", "pop_op_gemm_splitk", "pop_op_gemm_splitk_static", "pop_static_scratch_bytes", "pop_op_gemv", "pop_op_gemv_norm", "pop_op_rope_attention_workspace", "pop_op_rope_attention"]
+            "pop_op_gemm", "pop_op_gemm_plan", "pop_op_gemm_splitk", "pop_op_gemm_splitk_static", "pop_static_scratch_bytes", "pop_op_gemv", "pop_op_gemv_norm", "pop_op_rope_attention_workspace", "pop_op_rope_attention",
+            "pop_op_rope_attention_tile_rows"]
 
 
 def _check(status: int) -> None:
@@ -474,3 +476,9 @@ def pop_op_rope_attention(qkv: torch.Tensor, cu_seqlens, n_q_heads: int, n_kv_he
                                      rope_theta, window, out.data_ptr(), ws.data_ptr(), ws.numel(),
                                      _stream(stream)))
     return out
+
+
+def pop_op_rope_attention_tile_rows(cu_seqlens, n_q_heads: int, head_dim: int) -> int:
+    """Query rows of a work-group of the attention kernel for these sequences.  Host only."""
+    cu = _i32(cu_seqlens)
+    return lib.pop_op_rope_attention_tile_rows(_ptr(cu), len(cu) - 1, n_q_heads, head_dim)

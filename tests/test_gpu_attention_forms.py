@@ -1,18 +1,37 @@
-"""Prefill attention, head sizes 64 and 128: both forms of the kernel (256 query rows that share their key tiles, 128 rows with
-the key tiles dealt to two groups of waves), at the edges of waves, tiles and windows."""
+"""Prefill attention, head sizes 64 and 128: the forms of the kernel (256 query rows that share their key tiles, 128 rows with
+the key tiles dealt to two groups of waves, sequences of one key tile by themselves or among longer ones), at the edges of
+waves, tiles and windows."""
 import numpy as np
 import pytest
 import torch
 
 from oracle import pop_oracle as O
 
-pytestmark = pytest.mark.gpu
-
-
 # The form is chosen by the estimated time of each: many short sequences (few key tiles each) take the 256-row form, a single
-# one whose tiles do not fill the chip the 128-row form.
-@pytest.mark.parametrize("lens,hq,hkv", [([1, 31, 32, 33, 63, 64, 65, 127, 128, 129, 255, 256, 257, 300], 32, 4),     # 256 rows
-                                         ([700], 24, 2), ([257], 4, 4), ([65, 640, 130], 6, 1), ([513], 3, 1)])       # 128 rows
+# one whose tiles do not fill the chip the 128-row form, sequences of up to 64 tokens alone a form of their own.
+FORMS = [([1, 31, 32, 33, 63, 64, 65, 127, 128, 129, 255, 256, 257, 300], 32, 4, 256), ([700], 24, 2, 128), ([257], 4, 4, 128),
+         ([65, 640, 130], 6, 1, 128), ([513], 3, 1, 128), ([50, 400, 64], 4, 2, 128), ([1, 2, 31, 32, 33, 63, 64], 6, 2, 64),
+         ([64], 1, 1, 64), ([17], 8, 1, 64)]
+
+
+@pytest.mark.parametrize("lens,hq,hkv,rows", FORMS)
+@pytest.mark.parametrize("hd", [64, 128, 256])
+def test_forms_are_what_the_cases_name(lens, hq, hkv, rows, hd):
+    pop = pytest.importorskip("paper_2602_03295_amd.pop", reason="libpop.so not built")
+    cu = np.concatenate([[0], np.cumsum(lens)])
+    assert pop.pop_op_rope_attention_tile_rows(cu, hq, hd) == (rows if hd <= 128 else 128)
+
+
+@pytest.mark.parametrize("n,length,rows", [(32, 16, 64), (64, 64, 64), (1, 64, 64), (64, 65, 128), (1, 65, 256), (32, 300, 256)])
+def test_short_sequences_have_a_form_of_their_own(n, length, rows):
+    """32 query heads of 128.  Two waves a sequence: with eight, 32 sequences of 64 tokens took 67 us, with four 63, with two 52."""
+    pop = pytest.importorskip("paper_2602_03295_amd.pop", reason="libpop.so not built")
+    assert pop.pop_op_rope_attention_tile_rows(np.arange(n + 1) * length, 32, 128) == rows
+    assert pop.pop_op_rope_attention_tile_rows([0, 5, 5], 32, 128) == 0
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("lens,hq,hkv", [f[:3] for f in FORMS])
 @pytest.mark.parametrize("hd", [64, 128])
 @pytest.mark.parametrize("window", [0, 1, 64, 97, 200])
 def test_forms(lens, hq, hkv, hd, window):
