@@ -1817,6 +1817,11 @@ pop_status pop_op_gemm_plan(int32_t M, int32_t N, int32_t K, int32_t epilogue, s
   return POP_OK;
 }
 
+int32_t pop_op_gemm_row_scaled_tile_cols(int32_t M, int32_t N, int32_t K, int32_t epilogue) {
+  if (M < 1 || M > pop::kRowScaledRows || N < 1 || K < 1 || K % 8 || (epilogue != 2 && epilogue != 3)) return 0;
+  return pop::gemm_row_scaled_tile_cols(M, N, K, epilogue == 2);
+}
+
 pop_status pop_op_gemm_splitk(const void* A, int64_t lda, const void* W, int64_t ldw, void* out, int64_t ldc, int32_t M,
                               int32_t N, int32_t K, int32_t epilogue, void* dev_scratch, size_t scratch_bytes,
                               pop_stream stream) {

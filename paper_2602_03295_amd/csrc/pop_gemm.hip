@@ -789,12 +789,19 @@ hipError_t launch_shape(int id, const GemmArgs& g, hipStream_t st, int n0, int n
   }
 }
 
-// Row-scaled forms: one row tile, and of the shapes for so few rows the two that serve wide outputs best.
+// Row-scaled forms: one row tile, of 64 or of 128 columns, whichever the cost model has as the faster one.  In effect 64 until
+// those tiles fill the chip once (LM head of 16032 rows of 4096, 8 rows: 26 us, with 128 columns a third of the chip idles and it is 33),
+// then 128: a second round of 64-column tiles costs more than CUs that idle (four layers of a decode step of 32 sequences,
+// gate|up of 2 x 8448 to 2 x 10240 rows of 4096: 503 to 530 us with 64 columns, 473 to 495 with 128; 8 sequences 401 to 423 and 384 to 395).
+inline int row_scaled_tile(int M, long long cols, int K) {
+  const TileCfg &narrow = kTileCfgs[15], &wide = kTileCfgs[13];
+  static_assert(kTileCfgs[15].id == 16 && kTileCfgs[13].id == 14, "64 x 64 and 64 x 128");
+  return tile_cost_us(narrow, M, cols, K, 1) < tile_cost_us(wide, M, cols, K, 1) ? narrow.id : wide.id;
+}
 template <int EPI>
 hipError_t launch_row_scaled(const GemmArgs& g, hipStream_t st) {
   const long long cols = EPI == EPI_GLU_RS ? 2LL * g.N : g.N;
-  // up to 160 column tiles of 128 leave a third of the chip idle (LM head of 16032 rows, 8 rows: 26 us with 64 columns)
-  if ((cols + 127) / 128 <= 160) return launch_cfg<64, 64, 2, 2, 6, EPI>(g, st);
+  if (row_scaled_tile(g.M, cols, g.K) == 16) return launch_cfg<64, 64, 2, 2, 6, EPI>(g, st);
   return launch_cfg<64, 128, 2, 2, 3, EPI>(g, st);
 }
 
@@ -958,6 +965,10 @@ GemmPlan gemm_plan(const GemmArgs& g) {
   if (pick.tail_id == 0) return GemmPlan{c.bm, c.bn, S, g.N, 0, 0};
   const TileCfg t = cfg(pick.tail_id);
   return GemmPlan{c.bm, c.bn, S, (int)(glu ? pick.head_cols / 2 : pick.head_cols), t.bm, t.bn};
+}
+
+int gemm_row_scaled_tile_cols(int M, int N, int K, bool glu) {
+  return row_scaled_tile(M, glu ? 2LL * N : N, K) == 16 ? 64 : 128;
 }
 
 bool gemm_kv_cache_supported(int n_kv_heads, int hd) {

@@ -181,6 +181,8 @@ struct GemmPlan {
   int tile_rows, tile_cols, k_parts, head_cols, tail_rows, tail_cols;
 };
 GemmPlan gemm_plan(const GemmArgs& g);
+// Columns (W rows) of a tile of the row-scaled forms (GemmArgs::row_sumsq); glu: N gate and N up columns.
+int gemm_row_scaled_tile_cols(int M, int N, int K, bool glu);
 
 // ---------------------------------------------------------------------------------------------
 // Causal GQA flash attention over packed variable-length sequences (pop_attention.hip)

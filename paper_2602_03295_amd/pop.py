@@ -94,6 +94,7 @@ lib.pop_op_rmsnorm.argtypes = [C.c_void_p, C.c_void_p, C.c_void_p, C.c_int32, C.
 lib.pop_op_gemm.argtypes = [C.c_void_p, C.c_int64, C.c_void_p, C.c_int64, C.c_void_p, C.c_int64, C.c_int32,
                             C.c_int32, C.c_int32, C.c_int32, C.c_int32, C.c_void_p]
 lib.pop_op_gemm_plan.argtypes = [C.c_int32, C.c_int32, C.c_int32, C.c_int32, C.c_size_t, _i32p]
+lib.pop_op_gemm_row_scaled_tile_cols.argtypes = [C.c_int32] * 4
 lib.pop_op_gemm_splitk.argtypes = [C.c_void_p, C.c_int64, C.c_void_p, C.c_int64, C.c_void_p, C.c_int64, C.c_int32,
                                    C.c_int32, C.c_int32, C.c_int32, C.c_void_p, C.c_size_t, C.c_void_p]
 lib.pop_static_scratch_bytes.argtypes = []
@@ -119,7 +120,7 @@ EXPORTED = ["pop_timing_enable", "pop_timing_read", "pop_last_error", "pop_versi
             "pop_workspace_bytes", "pop_cache_create", "pop_cache_destroy", "pop_cache_n_seqs",
             "pop_cache_seq_lens", "pop_cache_block_table", "pop_slot_map", "pop_prefill", "pop_decode_step", "pop_decode_step_gated", "pop_generate",
             "pop_generate_workspace_bytes", "pop_op_rmsnorm",
-            "pop_op_gemm", "pop_op_gemm_plan", "pop_op_gemm_splitk", "pop_op_gemm_splitk_static", "pop_static_scratch_bytes", "pop_op_gemv", "pop_op_gemv_norm", "pop_op_rope_attention_workspace", "pop_op_rope_attention",
+            "pop_op_gemm", "pop_op_gemm_plan", "pop_op_gemm_row_scaled_tile_cols", "pop_op_gemm_splitk", "pop_op_gemm_splitk_static", "pop_static_scratch_bytes", "pop_op_gemv", "pop_op_gemv_norm", "pop_op_rope_attention_workspace", "pop_op_rope_attention",
             "pop_op_rope_attention_tile_rows"]
 
 
@@ -417,6 +418,11 @@ def pop_op_gemm_plan(M: int, N: int, K: int, epilogue: int = EPI_STORE_BF16, scr
     p = (C.c_int32 * 6)()
     _check(lib.pop_op_gemm_plan(M, N, K, epilogue, scratch_bytes, p))
     return {"tile": (p[0], p[1]), "k_parts": p[2], "head_cols": p[3], "tail": (p[4], p[5]) if p[4] else None}
+
+
+def pop_op_gemm_row_scaled_tile_cols(M: int, N: int, K: int, epilogue: int) -> int:
+    """Tile columns of a decode step's gate|up projection or LM head of 3 to 32 rows.  Host only."""
+    return lib.pop_op_gemm_row_scaled_tile_cols(M, N, K, epilogue)
 
 
 def pop_op_gemm_splitk(A: torch.Tensor, W: torch.Tensor, epilogue: int = EPI_STORE_BF16,

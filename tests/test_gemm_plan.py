@@ -96,3 +96,18 @@ def test_choice_against_the_measured_times():
             lost.append(times[problem + p["tile"]] / t - 1)
     assert len(lost) >= 400
     assert sum(lost) / len(lost) <= 0.01 and max(lost) <= 0.12
+
+
+@pytest.mark.parametrize("M", [3, 8, 32])
+@pytest.mark.parametrize("N,K,epi,cols", [(8192, 4096, 2, 64), (8448, 4096, 2, 128), (9216, 4096, 2, 128), (10240, 4096, 2, 128),
+                                          (14336, 4096, 2, 128), (9728, 2560, 2, 128), (8960, 1536, 2, 128), (5632, 4096, 2, 64),
+                                          (16032, 4096, 3, 64), (16384, 4096, 3, 64), (16864, 4096, 3, 128), (28672, 4096, 3, 128)])
+def test_row_scaled_tiles_do_not_start_a_second_round(M, N, K, epi, cols):
+    """Gate|up and LM head of 3 to 32 rows: 64-column tiles are one work-group per CU, and from 16385 columns on a second round
+    of them is slower than 128-column tiles (gate|up of 2 x 8448 rows of 4096, 32 rows: a step of four layers 504 and 473 us)."""
+    assert pop.pop_op_gemm_row_scaled_tile_cols(M, N, K, epi) == cols
+
+
+def test_row_scaled_tile_arguments():
+    for bad in [(0, 8, 8, 2), (33, 8, 8, 2), (8, 0, 8, 2), (8, 8, 12, 2), (8, 8, 8, 1)]:
+        assert pop.pop_op_gemm_row_scaled_tile_cols(*bad) == 0
