@@ -486,11 +486,18 @@ __global__ __launch_bounds__(256, (HD <= 128 && GT <= 4) ? 3 : 1 /* work-groups 
     load_v();
   }
 
+  auto as_chunk = [](const uint4& w) {
+    if constexpr (FP8) return make_uint2(w.x, w.y);
+    else return w;
+  };
+
   // ---- query rows: lane l holds head r16 (zeros beyond G), dims 32 ks + 8 g4 .. + 7, as bf16.  The other member of
   //      a rotation pair, HALF dims on, is the same lane's chunk ks + KS / 2.
   bf16x8_t qf[KS];
-  uint4 k_new[KS];                                  // FUSED: the query position's own entry, as loaded from the pools
-  uint4 v_new = make_uint4(0, 0, 0, 0);
+  // FUSED: the query position's own entry (K row, V row), a copy per wave.  In registers it made the form for three and four
+  // heads of 128 over an 8-bit cache spill at three work-groups per CU (four layers of a step, us: 1 sequence of 32000 tokens
+  // 493 -> 470, of 64000 567 -> 544, with three heads per KV head 482 -> 465 and 562 -> 540).
+  __shared__ chunk_t entry_new[FUSED ? 4 : 1][2][LPK];
   const bool has_new = FUSED && qpos - k_first < a.split_keys;     // (uniform) its key falls into this split
   if constexpr (FUSED) {
     // the 8 * KS values of this lane of the head at column `col`: optionally RMS-normalised over the head (its four
@@ -553,12 +560,14 @@ __global__ __launch_bounds__(256, (HD <= 128 && GT <= 4) ? 3 : 1 /* work-groups 
     if (has_new) {
       head_row((a.n_q_heads + kvh) * HD, a.k_gamma, x);
 #pragma unroll
-      for (int ks = 0; ks < KS; ++ks) k_new[ks] = pack8(x[ks], a.kvq.k_inv);
+      for (int ks = 0; ks < KS; ++ks)
+        if (r16 == 0) entry_new[wave][0][ks * 4 + g4] = as_chunk(pack8(x[ks], a.kvq.k_inv));
       float v8[8];
       const float* row = a.qkv_raw + (size_t)b * a.ld + (a.n_q_heads + a.n_kv_heads + kvh) * HD + li * 8;
 #pragma unroll
       for (int e = 0; e < 8; ++e) v8[e] = row[e];
-      v_new = pack8(v8, a.kvq.v_inv);
+      if (vs == 0) entry_new[wave][1][li] = as_chunk(pack8(v8, a.kvq.v_inv));
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");     // the wave's own LDS writes, read by its other lanes
     }
   } else {
     const bf16_t* q = a.q + ((size_t)b * a.n_q_heads + kvh * G + min(r16, G - 1)) * HD + g4 * 8;
@@ -568,10 +577,6 @@ __global__ __launch_bounds__(256, (HD <= 128 && GT <= 4) ? 3 : 1 /* work-groups 
       qf[ks] = __builtin_bit_cast(bf16x8_t, r16 < G ? w : make_uint4(0, 0, 0, 0));
     }
   }
-  auto as_chunk = [](const uint4& w) {
-    if constexpr (FP8) return make_uint2(w.x, w.y);
-    else return w;
-  };
   // FUSED, in the block that holds the query position's key (the split's last): the chunks loaded for it, also by
   // lanes that repeat it, are replaced by the new entry, and the lanes whose key it is store it.
   auto patch_k = [&](int blk) {
@@ -580,11 +585,11 @@ __global__ __launch_bounds__(256, (HD <= 128 && GT <= 4) ? 3 : 1 /* work-groups 
       const int kk = (blk * NB + n) * 16 + r16, key = key_of(kk);
       if (key != qpos) continue;
 #pragma unroll
-      for (int ks = 0; ks < KS; ++ks) kw[n][ks] = as_chunk(k_new[ks]);
+      for (int ks = 0; ks < KS; ++ks) kw[n][ks] = entry_new[wave][0][ks * 4 + g4];
       if (kk == n_keys - 1) {
         chunk_t* o = reinterpret_cast<chunk_t*>(const_cast<bf16_t*>(a.k_pool)) + chunk_of(row_of(key, bt[key >> lgP])) + g4;
 #pragma unroll
-        for (int ks = 0; ks < KS; ++ks) o[ks * 4] = as_chunk(k_new[ks]);
+        for (int ks = 0; ks < KS; ++ks) o[ks * 4] = kw[n][ks];
       }
     }
   };
@@ -595,9 +600,9 @@ __global__ __launch_bounds__(256, (HD <= 128 && GT <= 4) ? 3 : 1 /* work-groups 
       for (int i = 0; i < VL; ++i) {
         const int kk = (blk * NB + n) * 16 + i * KPL + vs, key = key_of(kk);
         if (key != qpos) continue;
-        vw[n][i] = as_chunk(v_new);
+        vw[n][i] = entry_new[wave][1][li];
         if (kk == n_keys - 1)
-          reinterpret_cast<chunk_t*>(const_cast<bf16_t*>(a.v_pool))[chunk_of(row_of(key, bt[key >> lgP])) + li] = as_chunk(v_new);
+          reinterpret_cast<chunk_t*>(const_cast<bf16_t*>(a.v_pool))[chunk_of(row_of(key, bt[key >> lgP])) + li] = vw[n][i];
       }
   };
   // a chunk of K as the MFMA operand
