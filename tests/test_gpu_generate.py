@@ -81,6 +81,18 @@ def test_generate_matches_teacher_forced_oracle(pop, dtype, tol):
     assert exact > 0
 
 
+@pytest.mark.parametrize("lens", [[40, 1, 97], [9] * 20])
+def test_generate_with_projections_that_finish_their_rows(pop, lens):
+    """3 to 32 sequences and sizes in whole K-steps (bf16): the steps' projections rotate, append, add and scale by themselves."""
+    cfg = synth.get_config("tiny", dtype=synth.DTYPE_BF16, n_layers=4, d_ffn=704, sliding_window=12, global_every=2,
+                           rope_theta_local=100.0)
+    W = synth.make_weights(cfg, seed=27)
+    synth.randomize_norms(W, cfg)
+    tokens = synth.make_tokens(cfg["vocab"], sum(lens), seed=11)
+    got, last_logits, cache, bt, cu = generate(pop, cfg, W, lens, tokens, 2, 6, shuffle_seed=4)
+    assert check_against_oracle(cfg, W, lens, tokens, 2, 6, got, last_logits, cache, bt, cu, TOL) > 0
+
+
 def test_generate_fp32_equals_free_running_oracle(pop):
     """At fp32 precision the GPU's free-running token sequence is the oracle's own."""
     cfg = synth.get_config("tiny")
