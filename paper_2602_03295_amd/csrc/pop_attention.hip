@@ -483,14 +483,17 @@ __device__ __forceinline__ void attend_one_tile(const AttnPrefillArgs& a, float 
       }
     mx = fmaxf(mx, __shfl_xor(mx, 32, 64)) * scale_log2;
     if (mx == -INFINITY) mx = 0.f;
+    float sum0 = 0.f, sum1 = 0.f;
 #pragma unroll
     for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
       for (int v = 0; v < 16; v += 2) {
         const float2_t pp = {__builtin_amdgcn_exp2f(s[kb][v] * scale_log2 - mx), __builtin_amdgcn_exp2f(s[kb][v + 1] * scale_log2 - mx)};
-        l_run += pp.x + pp.y;
+        sum0 += pp.x;      // (two chains, as in the loop of the eight-wave kernel: the same bits)
+        sum1 += pp.y;
         pw[kb][v >> 3][(v & 7) >> 1] = __builtin_bit_cast(uint32_t, __builtin_convertvector(pp, half2_t));
       }
+    l_run = sum0 + sum1;
   }
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");                  // V^T has
   __builtin_amdgcn_s_barrier();
