@@ -217,3 +217,16 @@ def test_qk_norm(pop, dtype, head_dim, lens):
     worst = check_against_oracle(pop, cfg, W, lens, tokens, (3, 4), True, True, tol, n_decode=3, seed=3,
                                  window_kv_writes=True)
     print("qk-norm", dtype, head_dim, f"{worst:.2e}")
+
+
+@pytest.mark.parametrize("kv_projection", [True, False])
+def test_skip_sets_with_projections_that_finish_their_rows(pop, kv_projection):
+    """Two runs of pruned layers with a kept one between them, five sequences and sizes in whole K-steps: the boundary rows and
+    the decode steps go through the projections of 3 to 32 rows, which hand the next one its input without its norm."""
+    cfg = synth.get_config("tiny", dtype=synth.DTYPE_BF16, n_layers=6, d_ffn=704, sliding_window=24, global_every=3,
+                           rope_theta_local=100.0)
+    W = synth.make_weights(cfg, seed=33)
+    synth.randomize_norms(W, cfg)
+    lens = [150, 10, 70, 24, 25]
+    tokens = synth.make_tokens(cfg["vocab"], sum(lens), seed=14)
+    check_against_oracle(pop, cfg, W, lens, tokens, (2, 4, 5), kv_projection, True, TOL, n_decode=3, seed=4)
