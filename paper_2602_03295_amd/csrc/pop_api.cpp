@@ -367,7 +367,9 @@ int build_attention_work(const int32_t* cu, int B, int n_heads, int hd, pop::Att
   // tiles of 128 rows, 128 keys at a time.  Estimated time of a form: its longest tile or an even share of all steps on
   // each of 256 CUs, and a fixed part per work-group.  The constants (us; head size 128) are read off timings of 60 to 8192
   // tokens, 32 heads, with both forms: 128 tokens 10.0 / 11.4 us (256 / 128 rows), 1000 31.2 / 22.8, 2048 56.6 / 48.6, 2500
-  // 70.8 / 75.0, 8192 520 / 565, four prompts of 500 24.1 / 25.7; of 26 sizes the rule misses one by 0.3 us.
+  // 70.8 / 75.0, 8192 520 / 565, four prompts of 500 24.1 / 25.7; of 26 sizes the rule misses one by 0.3 us.  Head size 64 and
+  // sliding windows, for which a tile has less work than it is counted with, take the same rule: of 210 batches (both head sizes, 8
+  // to 32 heads, windows 0, 256 and 1024, one prompt of 60 to 16384 tokens or several) none was slower than with one wave per SIMD.
   auto us = [&](int rows, int per_step, double longest_us, double share_us, double fixed_us) {
     double longest = 0, total = 0, wgs = 0;
     for (int b = 0; b < B; ++b)
@@ -427,7 +429,9 @@ struct LayerCtx {
 
 // Whether the projections of B decode-style rows run as pop_rows.hip has them (3 to 32 rows): QKV with RoPE and the append in
 // its epilogue, O and down with the residual update and the next norm's input in theirs, which leaves five launches per layer
-// (and the attention's merge) of nine.
+// (and the attention's merge) of nine.  Decode step of four layers over 512 tokens, Llama-3.1-8B / Qwen3-VL-8B-style /
+// Gemma-3-12B-style shapes, us without it -> with it: 4 sequences 483 -> 441, 471 -> 420, 745 -> 671; 16 518 -> 477, 491 ->
+// 470, 820 -> 784; 20 530 -> 489, 501 -> 474, 845 -> 816; 32 561 -> 551, 532 -> 532, 912 -> 908.
 bool rows_path(const pop_config& c, int B) {
   const int Dq = c.n_q_heads * c.head_dim, Dqkv = Dq + 2 * c.n_kv_heads * c.head_dim;
   return c.dtype != POP_DTYPE_F32 && c.vocab % 4 == 0 && c.d_model / 16 <= pop::kRowScaledSums && pop::rows_supported(B, Dqkv, c.d_model) &&
@@ -541,7 +545,8 @@ void record_kv_first(pop_cache* c, const pop_prefill_args* a, const PrunePlan& p
     }
 }
 
-// Projection of the B rows of a decode-style layer.  The GEMV kernel (every weight row streamed once per group of 1, 2, 4
+// Projection of the B rows of a decode-style layer where rows_path does not have it (its gate|up and LM head come here too).  The
+// GEMV kernel (every weight row streamed once per group of 1, 2, 4
 // or 8 rows) is the faster form for one and two rows, which it also normalises itself; from three rows on the tiled
 // MFMA GEMM with its small tiles, the staggered K start and the split of K is: at the Llama-3.1-8B shape, QKV, O,
 // gate|up and down of 2 rows take 12.6 / 9.6 / 45 / 24 us as GEMV and 14.2 / 12.7 / 41 / 26 us tiled, of 3 and 4 rows
@@ -589,7 +594,8 @@ pop_status normed_few_rows_projection(const LayerCtx& x, float* rows, const floa
                                       int* parts_out = nullptr) {
   if (parts_out) *parts_out = 1;
   const float eps = x.m->cfg.rms_eps;
-  if (x.ab_gamma == gamma && gamma != nullptr)   // the previous projection's second kernel left them in `normed`
+  // (the previous projection left them in `normed`: normalised, or with x.ab_sums > 0 as h * gamma without the rows' 1 / rms)
+  if (x.ab_gamma == gamma && gamma != nullptr)
     return few_rows_projection(x, normed, W, out, B, N, K, ldo, gemv_epi, act, parts_out);
   if (B <= 2 && pop::gemv_norm_supported(B, K) && (B == 1 || N <= 8192)) {
     pop::launch_gemv_norm(rows, gamma, eps, (const bf16_t*)W, out, B, N, K, ldo, gemv_epi, act, x.st);
@@ -601,8 +607,9 @@ pop_status normed_few_rows_projection(const LayerCtx& x, float* rows, const floa
 }
 
 // xb += in W^T for the B rows of a decode-style layer.  With next_gamma the caller announces the norm scale of the
-// projection that follows: when this one runs as a split GEMM its second kernel then also writes
-// RMSNorm(xb; next_gamma) to ab (and records that in x.ab_gamma), which saves that projection's norm launch.
+// projection that follows, and saves that projection's norm launch: with rows_path this one's epilogue also writes
+// bf16(xb * next_gamma) to ab and the sums of squares that the next one scales its result by (x.ab_sums), as a split GEMM its second
+// kernel writes RMSNorm(xb; next_gamma) there.  x.ab_gamma records either.
 pop_status residual_few_rows_projection(const LayerCtx& x, const bf16_t* in, const void* W, int B, int N, int K,
                                         const float* next_gamma, float scale /* the layer's virtual gate */) {
   float* xb = at<float>(x.ws, x.w->o_xb);
@@ -663,10 +670,10 @@ pop_status decode_layer(const LayerCtx& x, int l /*1-based*/, int B, const int32
   const bool glob = layer_is_global(c, l);
   // Up to kFusedAppendRows rows: RoPE and the append of the new entries happen inside the attention kernel (one
   // launch less; decode_rope_tables has run for these positions, the slot is implied by the block table).  With more
-  // rows the n_splits x Hkv x B work-groups would all repeat the preparation of their query heads, from the parts of a
-  // split projection, and a separate kernel that does it once per row and head, and adds the parts, is faster (a step,
-  // fused and separate: 4 sequences of 850 tokens 503 and 486 us, with heads of 256 910 and 775 us; 8 of 2048 tokens 597
-  // and 547 us; one of 139 tokens 403 and 409 us).
+  // rows the n_splits x Hkv x B work-groups would all repeat the preparation of their query heads.  Up to 32 rows the QKV
+  // projection then rotates and appends (rows_path); otherwise, and with per-head norms, a separate kernel does, once per row and
+  // head, and adds the parts of a split projection (a step, inside the attention and separate: 4 sequences of 850 tokens 503
+  // and 486 us, with heads of 256 910 and 775 us; 8 of 2048 tokens 597 and 547 us; one of 139 tokens 403 and 409 us).
   const bool fused_append = B <= kFusedAppendRows;
   pop::AttnDecodeArgs ad{};
   int qkv_parts = 1;
@@ -692,13 +699,13 @@ pop_status decode_layer(const LayerCtx& x, int l /*1-based*/, int B, const int32
   } else if (pop_status s = normed_few_rows_projection(x, xb, (const float*)lw.norm_in, ab, lw.wqkv, qkvb, B, Dqkv, d, Dqkv,
                                                 pop::GEMV_STORE_F32, 0, fused_append ? nullptr : &qkv_parts))
     return s;
-  if (rows && !(lw.q_norm || lw.k_norm)) {
-  } else if (fused_append) {
+  const bool appended = rows && !(lw.q_norm || lw.k_norm);
+  if (!appended && fused_append) {
     ad.qkv_raw = qkvb;
     ad.ld = Dqkv;
     ad.cs = at<float2>(x.ws, glob ? x.w->o_dcs_g : x.w->o_dcs_l);
     ad.q_gamma = (const float*)lw.q_norm; ad.k_gamma = (const float*)lw.k_norm; ad.qk_eps = c.rms_eps;
-  } else {
+  } else if (!appended) {
     bf16_t* qb = at<bf16_t>(x.ws, x.w->o_qb);
     pop::launch_rope_append(qkv_parts > 1 ? at<float>(x.ws, x.w->o_splitk) : qkvb, Dqkv, qb, c.n_q_heads, c.n_kv_heads,
                             c.head_dim, pos, slot, glob ? (double)c.rope_theta : (double)c.rope_theta_local,

@@ -2,9 +2,10 @@
 // all body rows of a kept layer at once), packed variable-length sequences, optional sliding window.
 //
 // A wave owns 32 query rows of one query head.  Keys/values stream through LDS in tiles of 64, staged with
-// buffer_load ... lds in a ring.  What bounds it at head size 128 (one work-group of the 32768-token prompt is busy for
-// 512 steps): the matrix pipe is 67 to 69 % busy at the 1.55 to 1.6 GHz that the power limit leaves; per step of 64 keys and 256
-// rows, 2048 cycles of MFMAs, 2 x 785 of vector instructions, 512 of the address unit for the staged tiles.
+// buffer_load ... lds in a ring.  What bounds it at head size 128: power.  The matrix pipe is busy 63 % of the cycles at 8192
+// tokens and 70 % at 32768, at the 1.62 and 1.56 GHz that the power limit leaves; per step of 64 keys and 256 rows, 2048
+// cycles of MFMAs, 2 x 790 of vector instructions, 512 of the address unit for the staged tiles.  At 2048 tokens it is busy 37 %
+// at 1.84 GHz: two rounds of work-groups of unequal length, with a start and an end each (profiles/attention_prefill_hd128_*).
 //
 // Inside this kernel Q, K, V and P are fp16 (the RoPE/append kernel hands over fp16 copies; the cache
 // itself stays bf16): with random-like V the softmax average shrinks signal and rounding noise alike, so

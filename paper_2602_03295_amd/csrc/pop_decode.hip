@@ -411,7 +411,8 @@ __device__ __forceinline__ int fold_keys(float (&v)[N], int lane) {
 // and 64 keys; at 8 sequences: 2048 keys 27 us, 8192 keys of the 8-bit cache 70 + 10 us (with the merge).
 // Per 32 keys of the 8-bit cache a wave issues about 480 vector instructions (row numbers formed once per key and passed
 // between lanes, codes to bf16 two per instruction), 750 before; three work-groups per CU need the launch bound (180
-// registers without it: 650 us a step).  8 sequences of 8192 tokens: 585 -> 568 us a step, one of 2048 tokens 407 -> 405.
+// registers without it: 650 us a step).  8 sequences of 8192 tokens: 623 -> 605 us a step of four layers; steps over bf16 entries
+// take what they took.
 // GT: compile-time bound of the number of query heads per KV head (registers and loops are sized by it).
 // FUSED: RoPE + append inside this kernel (a.qkv_raw given).
 template <int HD, int GT, bool FUSED, bool FP8, int NB>
