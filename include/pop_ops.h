@@ -74,7 +74,7 @@ pop_status pop_op_gemv_norm(const void* x, const void* gamma, float eps, const v
                             int32_t M, int32_t N, int32_t K, int32_t epilogue, int32_t act, pop_stream stream);
 
 /* RoPE on q and k followed by causal GQA attention (Sec. 2.1: K/V generation and Attn) over packed
- * sequences.  qkv DEVICE bf16 [T, (Hq + 2 Hkv) * hd], rows q | k | v, q and k are rotated IN PLACE;
+ * sequences.  qkv DEVICE bf16 [T, (Hq + 2 Hkv) * hd], rows q | k | v, q and k are rotated IN PLACE and left as fp16;
  * out DEVICE bf16 [T, Hq * hd].  host_cu_seqlens HOST [n_seqs + 1].  window 0 = global.
  * workspace: at least pop_op_rope_attention_workspace(...) bytes. */
 size_t pop_op_rope_attention_workspace(int32_t T, int32_t n_seqs, int32_t n_kv_heads, int32_t head_dim);

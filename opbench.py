@@ -8,7 +8,7 @@
 Shapes default to the Llama-3.1-8B projection shapes; `--shape N K` times one plain-store GEMM of
 that size instead, and `--vendor` times the same shapes through torch.matmul (hipBLASLt), without
 the fused epilogues, as the comparison the counter summaries quote.  Inputs are seeded random numbers; the timed
-region is `iters` back-to-back calls between two events on the launch stream.  Also the program that
+region is `iters` back-to-back calls between two events on the launch stream (attention: each call between its own).  Also the program that
 the counter summaries under profiles/ were collected on (rocprofv3 --pmc ... -- python3 opbench.py ...).
 """
 import argparse
@@ -27,8 +27,8 @@ GEMM_SHAPES = {  # name: (N, K, epilogue)
 }
 
 
-def _time(fn, iters):
-    for _ in range(3):
+def _time(fn, iters, warmup=3):
+    for _ in range(warmup):
         fn()
     torch.cuda.synchronize()
     e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
@@ -68,8 +68,12 @@ def bench_attention(tokens, hq, hkv, hd, window, iters):
     ld = (hq + 2 * hkv) * hd
     qkv = torch.randn(tokens, ld, device="cuda", generator=gen).to(torch.bfloat16)
     cu = np.array([0, tokens], dtype=np.int32)
-    # the call rotates q and k in place (norm-preserving), so repeated calls stay well conditioned
-    ms = _time(lambda: pop.pop_op_rope_attention(qkv, cu, hq, hkv, hd, 10000.0, window), iters)
+    # the call leaves q and k rotated, as fp16: every call gets the inputs anew, outside its pair of events
+    work, ms = torch.empty_like(qkv), []
+    for _ in range(iters + 3):
+        work.copy_(qkv)
+        ms.append(_time(lambda: pop.pop_op_rope_attention(work, cu, hq, hkv, hd, 10000.0, window), 1, warmup=0))
+    ms = sum(ms[3:]) / iters
     if window == 0:
         flops = 2.0 * tokens * tokens * hq * hd
     else:
