@@ -495,10 +495,14 @@ __global__ __launch_bounds__(256, (HD <= 128 && GT <= 4) ? 3 : 1 /* work-groups 
   // ---- query rows: lane l holds head r16 (zeros beyond G), dims 32 ks + 8 g4 .. + 7, as bf16.  The other member of
   //      a rotation pair, HALF dims on, is the same lane's chunk ks + KS / 2.
   bf16x8_t qf[KS];
-  // FUSED: the query position's own entry (K row, V row), a copy per wave.  In registers it made the form for three and four
-  // heads of 128 over an 8-bit cache spill at three work-groups per CU (four layers of a step, us: 1 sequence of 32000 tokens
-  // 493 -> 470, of 64000 567 -> 544, with three heads per KV head 482 -> 465 and 562 -> 540).
-  __shared__ chunk_t entry_new[FUSED ? 4 : 1][2][LPK];
+  // FUSED: the query position's own entry, in registers as loaded from the pools; with two key groups per block in LDS (K row, V
+  // row), a copy per wave: in registers it made the form for three and four heads of 128 spill at three work-groups per CU
+  // (four layers of a step over an 8-bit cache, us: 1 sequence of 32000 tokens 493 -> 470, of 64000 567 -> 544, with three heads
+  // per KV head 482 -> 465 and 562 -> 540).  Where nothing spills the way through LDS only delays
+  // the wave (bf16 entries, one sequence of 2048 tokens: 406.7 -> 408.3).
+  constexpr bool NEW_IN_LDS = FUSED && NB == 2;
+  __shared__ chunk_t entry_new[NEW_IN_LDS ? 4 : 1][2][LPK];
+  chunk_t k_new[KS], v_new = as_chunk(make_uint4(0, 0, 0, 0));
   const bool has_new = FUSED && qpos - k_first < a.split_keys;     // (uniform) its key falls into this split
   if constexpr (FUSED) {
     // the 8 * KS values of this lane of the head at column `col`: optionally RMS-normalised over the head (its four
@@ -561,14 +565,19 @@ __global__ __launch_bounds__(256, (HD <= 128 && GT <= 4) ? 3 : 1 /* work-groups 
     if (has_new) {
       head_row((a.n_q_heads + kvh) * HD, a.k_gamma, x);
 #pragma unroll
-      for (int ks = 0; ks < KS; ++ks)
-        if (r16 == 0) entry_new[wave][0][ks * 4 + g4] = as_chunk(pack8(x[ks], a.kvq.k_inv));
+      for (int ks = 0; ks < KS; ++ks) {
+        k_new[ks] = as_chunk(pack8(x[ks], a.kvq.k_inv));
+        if (NEW_IN_LDS && r16 == 0) entry_new[wave][0][ks * 4 + g4] = k_new[ks];
+      }
       float v8[8];
       const float* row = a.qkv_raw + (size_t)b * a.ld + (a.n_q_heads + a.n_kv_heads + kvh) * HD + li * 8;
 #pragma unroll
       for (int e = 0; e < 8; ++e) v8[e] = row[e];
-      if (vs == 0) entry_new[wave][1][li] = as_chunk(pack8(v8, a.kvq.v_inv));
-      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");     // the wave's own LDS writes, read by its other lanes
+      v_new = as_chunk(pack8(v8, a.kvq.v_inv));
+      if constexpr (NEW_IN_LDS) {
+        if (vs == 0) entry_new[wave][1][li] = v_new;
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");     // the wave's own LDS writes, read by its other lanes
+      }
     }
   } else {
     const bf16_t* q = a.q + ((size_t)b * a.n_q_heads + kvh * G + min(r16, G - 1)) * HD + g4 * 8;
@@ -586,7 +595,7 @@ __global__ __launch_bounds__(256, (HD <= 128 && GT <= 4) ? 3 : 1 /* work-groups 
       const int kk = (blk * NB + n) * 16 + r16, key = key_of(kk);
       if (key != qpos) continue;
 #pragma unroll
-      for (int ks = 0; ks < KS; ++ks) kw[n][ks] = entry_new[wave][0][ks * 4 + g4];
+      for (int ks = 0; ks < KS; ++ks) kw[n][ks] = NEW_IN_LDS ? entry_new[wave][0][ks * 4 + g4] : k_new[ks];
       if (kk == n_keys - 1) {
         chunk_t* o = reinterpret_cast<chunk_t*>(const_cast<bf16_t*>(a.k_pool)) + chunk_of(row_of(key, bt[key >> lgP])) + g4;
 #pragma unroll
@@ -601,7 +610,7 @@ __global__ __launch_bounds__(256, (HD <= 128 && GT <= 4) ? 3 : 1 /* work-groups 
       for (int i = 0; i < VL; ++i) {
         const int kk = (blk * NB + n) * 16 + i * KPL + vs, key = key_of(kk);
         if (key != qpos) continue;
-        vw[n][i] = entry_new[wave][1][li];
+        vw[n][i] = NEW_IN_LDS ? entry_new[wave][1][li] : v_new;
         if (kk == n_keys - 1)
           reinterpret_cast<chunk_t*>(const_cast<bf16_t*>(a.v_pool))[chunk_of(row_of(key, bt[key >> lgP])) + li] = vw[n][i];
       }
