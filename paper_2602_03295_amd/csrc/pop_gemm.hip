@@ -20,8 +20,8 @@
 //   * STAGES LDS stages (2 for 256x256 tiles, 3 for 256x128, up to 6 for 64x64): the loads of K-step k+STAGES-1 are
 //     issued after the barrier that publishes K-step k, spread over the K-step between groups of
 //     four MFMAs, so they overlap MFMA work.  Every K-step each wave also touches a few cache lines
-//     several K-steps ahead (a share of the tiles its XCD neighbours will stage), which turns the
-//     staging loads into L2 hits.
+//     several K-steps ahead (a share of the W tile that its XCD neighbours will stage too), which turns the
+//     staging loads of W into L2 hits.
 //   * The main loop is software pipelined by one 32-wide sub-step and rotated so that MFMAs with
 //     operands already in registers follow the barrier; when K is a multiple of 64 it contains no
 //     vector-ALU instruction besides the MFMAs (they share an issue port).
@@ -61,6 +61,7 @@ struct GemmParams {
   int tiles_m, tiles_n;  // per batch, of this launch
   int n_first;           // first output column of this launch (a GEMM may be split into two launches)
   int stagger;           // 1: column tile tn starts its K loop at K-step tn * nk / tiles_n and wraps around
+  int touch_a;           // 1: the rows of A are pulled into L2 too (see the prefetch)
   long long strideA, strideC, strideW;
   const bf16_t* const* W_list;
   float scale;           // EPI_ADD_F32: out += scale * C
@@ -125,13 +126,13 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_kernel(GemmParams p) {
   // Tiles are numbered in bands of 8 row tiles: inside a band the row tile runs fastest, then the
   // column tile.  The 32 CUs of an XCD then work on 8 row tiles x 4 column tiles at a time whatever M
   // is (each W tile is shared by 8 of them, each A tile by 4), which is what their L2 can hold.
-  int tm, tn;
+  int tm, tn, sharers;                                 // sharers: row tiles of the band, which read the same W tile
   {
     const int band = logical / (8 * p.tiles_n);
-    const int rows = min(8, p.tiles_m - band * 8);     // the last band may be narrower
+    sharers = min(8, p.tiles_m - band * 8);            // the last band may be narrower
     const int r = logical - band * 8 * p.tiles_n;
-    tn = r / rows;
-    tm = band * 8 + r % rows;
+    tn = r / sharers;
+    tm = band * 8 + r % sharers;
   }
   const int m0 = tm * BM;
   constexpr int BN_OUT = epi_is_glu(EPI) ? BN / 2 : BN;
@@ -225,44 +226,48 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_kernel(GemmParams p) {
   const int nk_full = p.K / BK;  // K-steps that need no tail mask
   const uint32_t last_mask = (nk_full * BK + lc * 8 < p.K) ? 0u : kOOB;
 
-  // L2 prefetch.  The work-groups that run together on one XCD share their W tile (same tn, eight
-  // consecutive tm) and their A tile (same tm, four tn), and all of them walk K in step, so an L2
-  // miss of one is a miss of all: every staged line then pays HBM latency, which bounds the loading
-  // rate.  Each K-step every wave therefore touches (4-byte DMA load into a scratch line of LDS) a
-  // few cache lines PF_DIST K-steps ahead: wave 0 one eighth of the W tile's rows (slice tm % 8),
-  // waves 1 and 2 one quarter of the A tile's rows (slice tn % 4).  Together the sharers cover both
-  // tiles, and the real loads later hit in L2.
+  // L2 prefetch of W.  The row tiles of a band (same tn, up to eight consecutive tm) run together on one XCD and walk K in
+  // step, so an L2 miss of one is a miss of all: every staged line of W then pays HBM latency, and a CU, whose loads return
+  // in order through the 256 lines of its L1, has no more than 32 KB on the way whatever LDS has room for.  Each K-step
+  // the work-group therefore touches (4-byte DMA loads into a scratch area of LDS) its share of the W tile's lines PF_DIST
+  // K-steps ahead, a slice of BN / sharers rows spread over the waves; together the sharers cover the tile, and the staging
+  // loads of W hit in L2.  A row tile that shares with nobody touches nothing (its lines would only travel twice), nor do two
+  // small tiles, whose ring is deep enough (down, 128 x 128 tiles in four K parts, 200 rows: 46.4 us touched, 42.3 not).
+  // The rows of A, which the column tiles that run together all read, are left to L2: touching a quarter of them too takes
+  // room in the L1 (down of 1024 rows 115 us, 110 without).  Only the tiles of two stages below 256 x 256 need it where A
+  // is long and beyond the caches (p.touch_a; down of 5000 rows, 160 x 256 tiles: 450 us, 487 without).
+  // Before: an eighth of the W tile and a quarter of the A tile per work-group, whatever the number of row tiles.  gate|up
+  // (28672 x 4096), us: 100 rows 51 -> 46, 256 rows 69 -> 62, 1024 rows 206 -> 183; down (4096 x 14336), four K parts:
+  // 528 rows 88 -> 73; from 2048 rows on 0 to 3 % less.
   constexpr int PF_DIST = STAGES + 1;
+  constexpr bool CAN_TOUCH_A = STAGES == 2 && BM * BN < 65536;
   unsigned char* pf_scratch = smem + STAGES * STAGE;
+  const bool touch_a = CAN_TOUCH_A && p.touch_a && (wave == 1 || wave == 2);   // waves 1 and 2: A; 0 and 3: W
   uint32_t pf_off;
-  {
-    const int l32 = lane & 31;
-    if (wave == 0) {
-      const int jn = (tm & 7) * (BN / 8) + (lane % (BN / 8));   // row of the LDS B tile
-      int wrow; bool ok = lane < BN / 8;
-      if (epi_is_glu(EPI)) {
-        const int w2 = jn / WTN, r = jn % WTN;
-        const int oc = n0 + w2 * (WTN / 2) + (r % (WTN / 2));
-        ok = ok && oc < p.N;
-        wrow = (r >= WTN / 2 ? p.N : 0) + oc;
-      } else {
-        wrow = n0 + jn;
-        ok = ok && wrow < p.N;
-      }
-      pf_off = ok ? (uint32_t)((long long)wrow * p.ldw * 2) : kOOB;
-    } else if (wave <= 2) {
-      const int row = m0 + (tn & 3) * (BM / 4) + (wave - 1) * 32 + l32;
-      const bool ok = lane < 32 && (wave - 1) * 32 + l32 < BM / 4 && row < p.M;
-      pf_off = ok ? (uint32_t)((long long)row * p.lda * 2) : kOOB;
+  if (touch_a) {
+    const int r = (wave - 1) * 32 + (lane & 31), row = m0 + (tn & 3) * (BM / 4) + r;
+    pf_off = lane < 32 && r < BM / 4 && row < p.M ? (uint32_t)((long long)row * p.lda * 2) : kOOB;
+  } else {
+    const int slice = (BN + sharers - 1) / sharers, q = CAN_TOUCH_A && p.touch_a ? lane * 2 + (wave >> 1) : lane * NW + wave;
+    const int jn = (tm & 7) * slice + q;             // row of the LDS B tile
+    int wrow;
+    bool ok = sharers > (BM * BN <= 24576 ? 2 : 1) && q < slice && jn < BN;
+    if (epi_is_glu(EPI)) {
+      const int w2 = jn / WTN, r = jn % WTN;
+      const int oc = n0 + w2 * (WTN / 2) + (r % (WTN / 2));
+      ok = ok && oc < p.N;
+      wrow = (r >= WTN / 2 ? p.N : 0) + oc;
     } else {
-      pf_off = kOOB;
+      wrow = n0 + jn;
+      ok = ok && wrow < p.N;
     }
+    pf_off = ok ? (uint32_t)((long long)wrow * p.ldw * 2) : kOOB;
   }
-  auto prefetch = [&](int kt) {   // one DMA load per wave; lanes beyond K or beyond the tile are masked
+  auto prefetch = [&](int kt) {   // one DMA load per wave; lanes beyond K or beyond the slice are masked
     const uint32_t off = KFULL ? pf_off : ((kt * BK < p.K) ? pf_off : kOOB);
-    const int kk = k_step(kt);
-    if (wave == 0) __builtin_amdgcn_raw_ptr_buffer_load_lds(rW, (lds_ptr_t)pf_scratch, 4, off, kk * BK * 2, 0, 0);
-    else __builtin_amdgcn_raw_ptr_buffer_load_lds(rA, (lds_ptr_t)(pf_scratch + 256), 4, off, kk * BK * 2, 0, 0);
+    const int k0 = k_step(kt) * BK;
+    if (touch_a) __builtin_amdgcn_raw_ptr_buffer_load_lds(rA, (lds_ptr_t)pf_scratch, 4, off, k0 * 2, 0, 0);
+    else __builtin_amdgcn_raw_ptr_buffer_load_lds(rW, (lds_ptr_t)pf_scratch, 4, off, k0 * 2, 0, 0);
   };
 
   // v_mfma_f32_16x16x32_bf16: D[16 x 16] += A[16 x 32] B[32 x 16].  Lane l supplies row l % 16 of A
@@ -659,6 +664,7 @@ hipError_t launch_cfg(const GemmArgs& g, hipStream_t st, int n_first = 0, int n_
   p.n_first = n_first;
   p.tiles_n = ((n_cols < 0 ? g.N - n_first : n_cols) + BN_OUT - 1) / BN_OUT;
   p.stagger = stagger_k(g) ? 1 : 0;
+  p.touch_a = g.K >= 8192 && (long long)g.M * g.K * 2 > (96LL << 20) ? 1 : 0;   // (2048 rows of 14336, 59 MB: 195 us touched, 190 not)
   p.strideA = g.strideA; p.strideC = g.strideC; p.strideW = g.W_list ? 0 : g.strideW;
   p.W_list = g.batch > 1 || g.W_list ? g.W_list : nullptr;
   // once per instantiation; the initialisation of a function-local static is thread-safe
