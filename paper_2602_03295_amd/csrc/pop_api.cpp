@@ -563,6 +563,18 @@ inline bool rows_take_gemm(int B, int K) { return B >= 5 || (B >= 3 && (K % 64 =
 pop_status few_rows_projection(const LayerCtx& x, const bf16_t* in, const void* W, void* out, int B, int N, int K,
                                int ldo, int gemv_epi, int act, int* parts_out = nullptr) {
   if (parts_out) *parts_out = 1;
+  const int rows_epi = gemv_epi == pop::GEMV_GLU_BF16 ? pop::ROWS_GLU : pop::ROWS_STORE;
+  if (gemv_epi != pop::GEMV_ADD_F32 && rows_path(x.m->cfg, B) && ldo % 4 == 0 && pop::rows_wide_supported(B, N, K, rows_epi)) {
+    pop::RowsArgs r{};
+    r.x = in; r.W = (const bf16_t*)W; r.M = B; r.N = N; r.K = K; r.epilogue = rows_epi;
+    if (in == at<bf16_t>(x.ws, x.w->o_ab) && x.ab_sums > 0) {
+      r.sumsq_in = at<float>(x.ws, x.w->o_sumsq); r.n_sumsq = x.ab_sums; r.d_norm = K; r.eps = x.m->cfg.rms_eps;
+    }
+    r.out = (float*)out; r.xn = (bf16_t*)out; r.ldo = ldo; r.act = act;
+    if (hipError_t e = pop::launch_rows(r, x.st); e != hipSuccess)
+      return fail(POP_EHIP, "projection launch failed: %s", hipGetErrorString(e));
+    return POP_OK;
+  }
   if (!rows_take_gemm(B, K) || ldo % 4) {   // (the tiled GEMM stores four columns at a time)
     pop::launch_gemv(in, (const bf16_t*)W, out, B, N, K, ldo, gemv_epi, act, x.st);
     return POP_OK;

@@ -91,6 +91,15 @@ __device__ __forceinline__ uint32_t e4m3_pack4(float a, float b, float c, float 
   return e4m3_encode(a) | (e4m3_encode(b) << 8) | (e4m3_encode(c) << 16) | (e4m3_encode(d) << 24);
 }
 
+// SiLU: g * sigmoid(g); tanh-GELU: 0.5 g (1 + tanh(u)) = g * sigmoid(2u), u = sqrt(2/pi) (g + 0.044715 g^3).
+// Both are g / (1 + 2^(-g (k0 + k1 g^2))): one v_exp_f32 and one v_rcp_f32, constants chosen per
+// activation (SiLU: k0 = log2(e), k1 = 0; GELU: k0 = 2 sqrt(2/pi) log2(e), k1 = 0.044715 k0).
+__device__ __forceinline__ float glu_act(float g, float k0, float k1) {
+  return g * __builtin_amdgcn_rcpf(1.f + __builtin_amdgcn_exp2f(-g * (k0 + k1 * g * g)));
+}
+__device__ __forceinline__ float glu_k0(int act) { return act == 0 ? 1.4426950408889634f : 2.302208198f; }
+__device__ __forceinline__ float glu_k1(int act) { return act == 0 ? 0.f : 0.1029432396f; }
+
 __device__ __forceinline__ float wave_sum(float v) {
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);

@@ -90,13 +90,6 @@ constexpr bool epi_is_glu(int e) { return e == EPI_GLU_BF16 || e == EPI_GLU_RS; 
 typedef __attribute__((address_space(3))) void* lds_ptr_t;
 typedef __attribute__((__vector_size__(16))) unsigned int u32x4_t;
 
-// SiLU: g * sigmoid(g); tanh-GELU: 0.5 g (1 + tanh(u)) = g * sigmoid(2u), u = sqrt(2/pi) (g + 0.044715 g^3).
-// Both are g / (1 + 2^(-g (k0 + k1 g^2))): one v_exp_f32 and one v_rcp_f32, constants chosen per
-// activation (SiLU: k0 = log2(e), k1 = 0; GELU: k0 = 2 sqrt(2/pi) log2(e), k1 = 0.044715 k0).
-__device__ __forceinline__ float glu_act(float g, float k0, float k1) {
-  return g * __builtin_amdgcn_rcpf(1.f + __builtin_amdgcn_exp2f(-g * (k0 + k1 * g * g)));
-}
-
 template <typename F, int... I>
 __device__ __forceinline__ void for_each_index(F&& f, std::integer_sequence<int, I...>) {
   (f(std::integral_constant<int, I>{}), ...);
@@ -457,8 +450,7 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_kernel(GemmParams p) {
   //      4 (lane >> 4) + v inside it: 4 consecutive columns per lane.
   const int m_lane = m0 + wm * WTM + frag_row;
   if (epi_is_glu(EPI)) {
-    const float act_k0 = p.act == 0 ? 1.4426950408889634f : 2.302208198f;
-    const float act_k1 = p.act == 0 ? 0.f : 0.1029432396f;
+    const float act_k0 = glu_k0(p.act), act_k1 = glu_k1(p.act);
     bf16_t* out = reinterpret_cast<bf16_t*>(p.out) + (long long)z * p.strideC;
     // rows outer, column blocks inner: the stores that complete one 128-byte line of a row follow
     // each other directly

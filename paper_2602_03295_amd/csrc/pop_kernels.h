@@ -227,10 +227,10 @@ void launch_gemv_norm(const float* xf, const float* gamma, float eps, const bf16
                       int64_t ldo, int epilogue, int act, hipStream_t st);
 
 // Projections of 3 to 32 rows with what follows them in the epilogue (pop_rows.hip): out[m, n] (op)= sum_k x[m,k] * W[n,k].
-enum RowsEpilogue { ROWS_STORE = 0, ROWS_ADD = 1, ROWS_QKV = 2 };
+enum RowsEpilogue { ROWS_STORE = 0, ROWS_ADD = 1, ROWS_QKV = 2, ROWS_GLU = 3 };
 struct RowsArgs {
   const bf16_t* x;          // bf16 [M, K]
-  const bf16_t* W;          // bf16 [N, K]
+  const bf16_t* W;          // bf16 [N, K] (GLU: [2N, K], gate rows, then up rows)
   int M, N, K, epilogue;
   // n_sumsq > 0: the rows of x are h * gamma, and sumsq_in[m][n_sumsq] add up to the sum of h^2 over the d_norm elements of
   // row m: the sums are multiplied by rsqrt(sum / d_norm + eps)
@@ -242,8 +242,9 @@ struct RowsArgs {
   float scale;
   // ADD, gamma != nullptr: also xn bf16 [M, N] = out * gamma, sumsq_out [M][N / 16]
   const float* gamma;
-  bf16_t* xn;
+  bf16_t* xn;               // GLU: act(gate) * up, bf16 [M, ldo]
   float* sumsq_out;
+  int act;                  // GLU: 0 SiLU, 1 tanh-GELU
   // QKV: the columns are heads of hd values, q | k | v: q (rotated) to q_out bf16 [M, Hq * hd], k (rotated) and v to slot[m]
   int hd, n_q_heads, n_kv_heads, page_size;
   const float2* cs;         // [M, hd/2] (cos, sin)
@@ -254,6 +255,8 @@ struct RowsArgs {
   KvQuant kvq;
 };
 bool rows_supported(int M, int N, int K);
+// ROWS_GLU, and the form of ROWS_STORE for many columns (12289 to 32768 weight rows)
+bool rows_wide_supported(int M, int N, int K, int epilogue);
 hipError_t launch_rows(const RowsArgs& a, hipStream_t st);
 
 // Fewest keys per split of the decode attention (how many a split has is chosen at the launch: as many as make about

@@ -9,9 +9,12 @@
 //               its fp32 sums (bf16 rounds relative to the value: h * gamma carries the same error as h * rstd * gamma)
 //   ROWS_QKV    RoPE and the append to the paged cache; a work-group's columns are rotation pairs
 //   ROWS_STORE  fp32 rows
+// gate|up and the LM head, whose columns are enough for 64 to 128 per work-group on every CU, have a kernel of their own below
+// (rows_wide_kernel; ROWS_GLU and, for many columns, ROWS_STORE).
 // Each wave stages its weights and activations (128 bytes of a row per K-step) into a ring of its own with buffer_load ... lds
 // and waits for its own loads alone: no barrier before the sums are added.
 #include <algorithm>
+#include <type_traits>
 
 #include "pop_device.h"
 #include "pop_kernels.h"
@@ -22,6 +25,13 @@ namespace rows_impl {
 
 typedef __attribute__((address_space(3))) void* lds_ptr_t;
 constexpr uint32_t kOOB = 0x80000000u;   // byte offset beyond any buffer accepted (< 2^31 bytes)
+
+// rows_wide_kernel: blocks of 16 weight rows per work-group (one round of 256 work-groups), stages of a wave's ring.
+constexpr int wide_blocks(long long w_rows) { return (int)((w_rows + 4095) / 4096); }
+constexpr int wide_stages(int a8, int nb) {
+  const int st = 160 / (4 * (2 * nb + a8));
+  return st < 4 ? st : 4;
+}
 
 // A8: groups of 8 activation rows; NB: blocks of 16 columns; ST: stages of a wave's ring
 template <int A8, int NB, int ST, int EPI>
@@ -237,6 +247,191 @@ __global__ __launch_bounds__(256) void rows_kernel(RowsArgs p) {
 #endif
 }
 
+// gate|up (ROWS_GLU) and LM head (ROWS_STORE): a work-group owns NB blocks of 16 weight rows, NB chosen so that the work-groups
+// are one round of at most 256.  What counts is that every CU streams weights and all of them the same amount: a CU has no
+// more than the 32 KB of its L1 on the way, so that CUs without a work-group are bandwidth lost (the 64 x 128 tiles of the tiled
+// GEMM leave 32 of 256 idle at 28672 columns, 64 at 24576, 124 at 16864).  The activations, which every work-group reads
+// whole, are 1 : 2 NB of the weights with 8 rows.  Waves split K and add their sums in LDS as in rows_kernel.
+// ROWS_GLU: a block of 16 weight rows is 8 gate and the 8 up rows of the same output columns, which makes any number of blocks a
+// whole number of columns; lane l + 32 holds the up values of lane l's gate values.
+template <int A8, int NB, int EPI>
+__global__ __launch_bounds__(256) void rows_wide_kernel(RowsArgs p) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  constexpr int MB = (A8 + 1) / 2;
+  constexpr int STAGE = NB * 2048 + A8 * 1024, LOADS = 2 * NB + A8, ST = wide_stages(A8, NB);
+  static_assert(ST >= 2 && (ST - 1) * LOADS < 64, "vmcnt is a 6-bit counter");
+  extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];   // [4][ST][STAGE], then float4 [4][MB][NB][64], rstd
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int wg = blockIdx.x;
+  unsigned char* const ring = smem + wave * (ST * STAGE);
+  float4* const sums = reinterpret_cast<float4*>(smem);
+  float* const rstd = reinterpret_cast<float*>(sums + 4 * MB * NB * 64);
+
+  typedef __attribute__((__vector_size__(16))) unsigned int u32x4_t;
+  u32x4_t ssq[2 * A8][2];                           // the rows' sums of squares (see rows_kernel)
+  if (p.n_sumsq > 0) {
+    const __amdgpu_buffer_rsrc_t rS = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(p.sumsq_in), 0,
+                                                                        (uint32_t)p.M * p.n_sumsq * 4, 0x00020000);
+#pragma unroll
+    for (int i = 0; i < 2 * A8; ++i)
+#pragma unroll
+      for (int u = 0; u < 2; ++u) {
+        const int q = u * 256 + lane * 4;
+        ssq[i][u] = __builtin_amdgcn_raw_buffer_load_b128(
+            rS, q < p.n_sumsq ? (uint32_t)((wave * 2 * A8 + i) * p.n_sumsq + q) * 4 : kOOB, 0, 0);
+      }
+  }
+
+  constexpr bool GLU = EPI == ROWS_GLU;
+  constexpr int COLS = GLU ? NB * 8 : NB * 16;      // output columns of the work-group
+  const __amdgpu_buffer_rsrc_t rA = __builtin_amdgcn_make_buffer_rsrc(
+      const_cast<bf16_t*>(p.x), 0, (uint32_t)((long long)p.M * p.K * 2), 0x00020000);
+  const __amdgpu_buffer_rsrc_t rW = __builtin_amdgcn_make_buffer_rsrc(
+      const_cast<bf16_t*>(p.W), 0, (uint32_t)((long long)p.N * (GLU ? 2 : 1) * p.K * 2), 0x00020000);
+  const int lr = lane >> 3;
+  uint32_t off_w[2 * NB], off_a[A8];
+#pragma unroll
+  for (int j = 0; j < 2 * NB; ++j) {
+    const int col = wg * COLS + (GLU ? (j >> 1) * 8 + lr : j * 8 + lr);
+    const int row = col + (GLU && (j & 1) ? p.N : 0);
+    off_w[j] = col < p.N ? (uint32_t)((long long)row * p.K * 2) + ((lane & 7) ^ (((j & 1) * 4 + (lr >> 1)) & 7)) * 16 : kOOB;
+  }
+#pragma unroll
+  for (int j = 0; j < A8; ++j) {
+    const int row = j * 8 + lr;
+    off_a[j] = row < p.M ? (uint32_t)((long long)row * p.K * 2) + ((lane & 7) ^ (((j & 1) * 4 + (lr >> 1)) & 7)) * 16 : kOOB;
+  }
+  const int nk_all = p.K >> 6, k_lo = nk_all * wave / 4, nk = nk_all * (wave + 1) / 4 - k_lo;
+  const int rot = (int)((long long)wg * nk / gridDim.x);
+  auto issue = [&](int i, int stage) {              // the wave's i-th K-step (beyond the last: masked)
+    int k = i + rot;
+    if (k >= nk) k -= nk;
+    const uint32_t mask = i < nk ? 0u : kOOB;
+    const int off = (k_lo + k) * 128;
+    unsigned char* s = ring + stage * STAGE;
+#pragma unroll
+    for (int j = 0; j < 2 * NB; ++j)
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rW, (lds_ptr_t)(s + j * 1024), 16, off_w[j] | mask, off, 0, 2 /* streamed */);
+#pragma unroll
+    for (int j = 0; j < A8; ++j)
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rA, (lds_ptr_t)(s + NB * 2048 + j * 1024), 16, off_a[j] | mask, off, 0, 0);
+  };
+#pragma unroll
+  for (int i = 0; i < ST - 1; ++i) issue(i, i);
+
+  const int r16 = lane & 15, g4 = lane >> 4;
+  const int frag = r16 * 128, key = (r16 >> 1) & 7;
+  const int frag_last = A8 % 2 ? (r16 & 7) * 128 : frag, key_last = A8 % 2 ? ((r16 & 7) >> 1) & 7 : key;
+  floatx4_t acc[MB][NB];
+#pragma unroll
+  for (int j = 0; j < MB; ++j)
+#pragma unroll
+    for (int n = 0; n < NB; ++n) acc[j][n] = floatx4_t{0.f, 0.f, 0.f, 0.f};
+  int stage = 0;
+  for (int i = 0; i < nk; ++i) {
+    issue(i + ST - 1, stage == 0 ? ST - 1 : stage - 1);
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"((ST - 1) * LOADS) : "memory");
+    const unsigned char* s = ring + stage * STAGE;
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks) {
+      bf16x8_t w[NB], a[MB];
+#pragma unroll
+      for (int n = 0; n < NB; ++n)
+        w[n] = *reinterpret_cast<const bf16x8_t*>(s + n * 2048 + frag + ((4 * ks + g4) ^ key) * 16);
+#pragma unroll
+      for (int j = 0; j < MB; ++j) {
+        const bool odd = A8 % 2 && j == MB - 1;
+        a[j] = *reinterpret_cast<const bf16x8_t*>(s + NB * 2048 + j * 2048 + (odd ? frag_last : frag) +
+                                                  ((4 * ks + g4) ^ (odd ? key_last : key)) * 16);
+      }
+#pragma unroll
+      for (int j = 0; j < MB; ++j)
+#pragma unroll
+        for (int n = 0; n < NB; ++n) acc[j][n] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[n], a[j], acc[j][n], 0, 0, 0);
+    }
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // the next iteration refills this slot's predecessor, then this slot
+    stage = stage == ST - 1 ? 0 : stage + 1;
+  }
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // masked loads still target this group's LDS
+  __syncthreads();                                   // the sums take the place of the rings
+#pragma unroll
+  for (int j = 0; j < MB; ++j)
+#pragma unroll
+    for (int n = 0; n < NB; ++n)
+      sums[((wave * MB + j) * NB + n) * 64 + lane] = make_float4(acc[j][n][0], acc[j][n][1], acc[j][n][2], acc[j][n][3]);
+  if (p.n_sumsq > 0) {
+#pragma unroll
+    for (int i = 0; i < 2 * A8; ++i) {
+      const float4 a = __builtin_bit_cast(float4, ssq[i][0]), b = __builtin_bit_cast(float4, ssq[i][1]);
+      const float total = wave_sum_rows(((a.x + a.y) + (a.z + a.w)) + ((b.x + b.y) + (b.z + b.w)));
+      if (lane == 0) rstd[wave * 2 * A8 + i] = rsqrtf(total / (float)p.d_norm + p.eps);
+    }
+  } else if (lane < 2 * A8) {
+    rstd[wave * 2 * A8 + lane] = 1.f;
+  }
+  __syncthreads();
+  const float k0 = glu_k0(p.act), k1 = glu_k1(p.act);
+  for (int blk = wave; blk < MB * NB; blk += 4) {    // 16 rows x 16 weight rows each
+    const int mb = blk / NB, n = blk % NB, m = mb * 16 + r16;
+    const bool valid = m < p.M;
+    const float rs = valid ? rstd[m] : 0.f;
+    float c[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int w = 0; w < 4; ++w) {
+      const float4 v = sums[((w * MB + mb) * NB + n) * 64 + lane];
+      c[0] += v.x; c[1] += v.y; c[2] += v.z; c[3] += v.w;
+    }
+    if constexpr (GLU) {
+      const int col = wg * COLS + n * 8 + (g4 & 1) * 4;
+      float u[4];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const float up = __shfl_xor(c[e], 32, 64);   // (lanes 0 to 31; the others compute nothing of use)
+        u[e] = glu_act(c[e] * rs, k0, k1) * (up * rs);
+      }
+      if (valid && g4 < 2 && col < p.N)
+        *reinterpret_cast<uint2*>(p.xn + (size_t)m * p.ldo + col) = make_uint2(pack_bf16x2(u[0], u[1]), pack_bf16x2(u[2], u[3]));
+    } else {
+      const int col = wg * COLS + n * 16 + g4 * 4;
+      if (valid && col < p.N)
+        *reinterpret_cast<float4*>(p.out + (size_t)m * p.ldo + col) = make_float4(c[0] * rs, c[1] * rs, c[2] * rs, c[3] * rs);
+    }
+  }
+#endif
+}
+
+template <int A8, int NB, int EPI>
+hipError_t launch_wide_cfg(const RowsArgs& a, hipStream_t st) {
+  constexpr int MB = (A8 + 1) / 2, ring = 4 * wide_stages(A8, NB) * (NB * 2048 + A8 * 1024), sums = 4 * MB * NB * 1024 + 8 * A8 * 4;
+  constexpr int smem = ring > sums ? ring : sums;
+  static_assert(smem <= 160 * 1024, "LDS budget of a gfx950 CU");
+  static const hipError_t attr_err = hipFuncSetAttribute(reinterpret_cast<const void*>(&rows_wide_kernel<A8, NB, EPI>),
+                                                         hipFuncAttributeMaxDynamicSharedMemorySize, smem);
+  if (attr_err != hipSuccess) return attr_err;
+  constexpr int cols = EPI == ROWS_GLU ? NB * 8 : NB * 16;
+  hipLaunchKernelGGL((rows_wide_kernel<A8, NB, EPI>), dim3((a.N + cols - 1) / cols), dim3(256), smem, st, a);
+  return hipGetLastError();
+}
+
+template <int EPI>
+hipError_t launch_wide(const RowsArgs& a, hipStream_t st) {
+  auto rows = [&](auto nb_c) {
+    constexpr int NB = decltype(nb_c)::value;
+    if (a.M <= 8) return launch_wide_cfg<1, NB, EPI>(a, st);
+    if (a.M <= 16) return launch_wide_cfg<2, NB, EPI>(a, st);
+    if (a.M <= 24) return launch_wide_cfg<3, NB, EPI>(a, st);
+    return launch_wide_cfg<4, NB, EPI>(a, st);
+  };
+  switch (wide_blocks(EPI == ROWS_GLU ? 2LL * a.N : a.N)) {
+    case 4: return rows(std::integral_constant<int, 4>{});
+    case 5: return rows(std::integral_constant<int, 5>{});
+    case 6: return rows(std::integral_constant<int, 6>{});
+    case 7: return rows(std::integral_constant<int, 7>{});
+    default: return rows(std::integral_constant<int, 8>{});
+  }
+}
+
 template <int A8, int NB, int ST, int EPI>
 hipError_t launch_cfg(const RowsArgs& a, hipStream_t st) {
   constexpr int MB = (A8 + 1) / 2;
@@ -269,14 +464,25 @@ bool rows_supported(int M, int N, int K) {
   return M >= 3 && M <= 32 && N % 32 == 0 && K % 64 == 0 && K >= 256 && (long long)N * K * 2 < (1LL << 31);
 }
 
+// 64 to 128 weight rows per CU: fewer leave the ring's loads short of the memory, more are several rounds, for which the tiled
+// GEMM with two work-groups per CU is the better one.
+bool rows_wide_supported(int M, int N, int K, int epilogue) {
+  const long long w_rows = epilogue == ROWS_GLU ? 2LL * N : N;
+  return (epilogue == ROWS_GLU || epilogue == ROWS_STORE) && M >= 3 && M <= 32 && N % (epilogue == ROWS_GLU ? 8 : 4) == 0 &&
+         K % 64 == 0 && K >= 256 && wide_blocks(w_rows) >= 4 && wide_blocks(w_rows) <= 8 && w_rows * K * 2 < (1LL << 31);
+}
+
 hipError_t launch_rows(const RowsArgs& a, hipStream_t st) {
-  if (!rows_supported(a.M, a.N, a.K) || a.ldo % 4 || a.n_sumsq % 4 || a.n_sumsq > kRowScaledSums) return hipErrorInvalidValue;
+  const bool wide = rows_wide_supported(a.M, a.N, a.K, a.epilogue);
+  if (!(wide || rows_supported(a.M, a.N, a.K)) || a.ldo % 4 || a.n_sumsq % 4 || a.n_sumsq > kRowScaledSums) return hipErrorInvalidValue;
+  if (wide) return a.epilogue == ROWS_GLU ? launch_wide<ROWS_GLU>(a, st) : launch_wide<ROWS_STORE>(a, st);
   switch (a.epilogue) {
     case ROWS_ADD: return launch_epi<ROWS_ADD>(a, st);
     case ROWS_QKV:
       if (a.hd % 32 || a.N != (a.n_q_heads + 2 * a.n_kv_heads) * a.hd || a.page_size < 1) return hipErrorInvalidValue;
       return launch_epi<ROWS_QKV>(a, st);
-    default: return launch_epi<ROWS_STORE>(a, st);
+    case ROWS_STORE: return launch_epi<ROWS_STORE>(a, st);
+    default: return hipErrorInvalidValue;
   }
 }
 
