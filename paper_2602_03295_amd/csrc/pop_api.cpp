@@ -597,7 +597,9 @@ pop_status few_rows_projection(const LayerCtx& x, const bf16_t* in, const void* 
   return POP_OK;
 }
 
-// The same for fp32 rows that are RMS-normalised first (Sec. 2.1): with a few rows the GEMV kernel normalises
+// The same for fp32 rows that are RMS-normalised first (Sec. 2.1).  One or two rows of gate|up and the LM head, where the
+// columns give every CU 64 to 128 weight rows, run as the wide row projections have them, norm included (four layers of a step,
+// us: Llama shape, one sequence 410 -> 402, two 457 -> 432; Gemma shape, six layers, 636 -> 605 and 714 -> 680); with other widths the GEMV kernel normalises
 // them itself (two rows for thousands of work-groups cost more than the norm's own launch: gate|up 45.4 us against
 // 40.3 + 2.5 us, LM head of 16032 rows 28.6 against 23.6 + 2.5 us; QKV, 6144 rows, 12.6 against 11.1 + 2.5 us);
 // otherwise the norm kernel writes bf16 rows to `normed` and the projection reads those.
@@ -609,6 +611,16 @@ pop_status normed_few_rows_projection(const LayerCtx& x, float* rows, const floa
   // (the previous projection left them in `normed`: normalised, or with x.ab_sums > 0 as h * gamma without the rows' 1 / rms)
   if (x.ab_gamma == gamma && gamma != nullptr)
     return few_rows_projection(x, normed, W, out, B, N, K, ldo, gemv_epi, act, parts_out);
+  const int rows_epi = gemv_epi == pop::GEMV_GLU_BF16 ? pop::ROWS_GLU : pop::ROWS_STORE;
+  if (gemv_epi != pop::GEMV_ADD_F32 && ldo % 4 == 0 && pop::rows_wide_norm_supported(B, N, K, rows_epi)) {
+    pop::RowsArgs r{};
+    r.xf = rows; r.gamma = gamma; r.eps = eps;
+    r.W = (const bf16_t*)W; r.M = B; r.N = N; r.K = K; r.epilogue = rows_epi;
+    r.out = (float*)out; r.xn = (bf16_t*)out; r.ldo = ldo; r.act = act;
+    if (hipError_t e = pop::launch_rows(r, x.st); e != hipSuccess)
+      return fail(POP_EHIP, "projection launch failed: %s", hipGetErrorString(e));
+    return POP_OK;
+  }
   if (B <= 2 && pop::gemv_norm_supported(B, K) && (B == 1 || N <= 8192)) {
     pop::launch_gemv_norm(rows, gamma, eps, (const bf16_t*)W, out, B, N, K, ldo, gemv_epi, act, x.st);
     return POP_OK;

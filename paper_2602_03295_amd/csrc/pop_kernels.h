@@ -230,6 +230,7 @@ void launch_gemv_norm(const float* xf, const float* gamma, float eps, const bf16
 enum RowsEpilogue { ROWS_STORE = 0, ROWS_ADD = 1, ROWS_QKV = 2, ROWS_GLU = 3 };
 struct RowsArgs {
   const bf16_t* x;          // bf16 [M, K]
+  const float* xf;          // not nullptr (rows_wide_norm_supported): fp32 [M, K], RMS-normalised with gamma and eps first
   const bf16_t* W;          // bf16 [N, K] (GLU: [2N, K], gate rows, then up rows)
   int M, N, K, epilogue;
   // n_sumsq > 0: the rows of x are h * gamma, and sumsq_in[m][n_sumsq] add up to the sum of h^2 over the d_norm elements of
@@ -240,7 +241,7 @@ struct RowsArgs {
   float* out;               // STORE: fp32 [M, ldo]; ADD: the same, out += scale * C
   int ldo;
   float scale;
-  // ADD, gamma != nullptr: also xn bf16 [M, N] = out * gamma, sumsq_out [M][N / 16]
+  // (xf: gamma is the scale of the norm)  ADD, gamma != nullptr: also xn bf16 [M, N] = out * gamma, sumsq_out [M][N / 16]
   const float* gamma;
   bf16_t* xn;               // GLU: act(gate) * up, bf16 [M, ldo]
   float* sumsq_out;
@@ -257,6 +258,8 @@ struct RowsArgs {
 bool rows_supported(int M, int N, int K);
 // ROWS_GLU, and the form of ROWS_STORE for many columns (12289 to 32768 weight rows)
 bool rows_wide_supported(int M, int N, int K, int epilogue);
+// the same of one or two rows given as fp32 (RowsArgs::xf)
+bool rows_wide_norm_supported(int M, int N, int K, int epilogue);
 hipError_t launch_rows(const RowsArgs& a, hipStream_t st);
 
 // Fewest keys per split of the decode attention (how many a split has is chosen at the launch: as many as make about

@@ -28,10 +28,12 @@ constexpr uint32_t kOOB = 0x80000000u;   // byte offset beyond any buffer accept
 
 // rows_wide_kernel: blocks of 16 weight rows per work-group (one round of 256 work-groups), stages of a wave's ring.
 constexpr int wide_blocks(long long w_rows) { return (int)((w_rows + 4095) / 4096); }
-constexpr int wide_stages(int a8, int nb) {
-  const int st = 160 / (4 * (2 * nb + a8));
+constexpr int wide_stages(int a8, int nb) {        // (a8 = 0: 32 KB are left for the normalised rows)
+  const int st = (a8 ? 160 : 128) / (4 * (2 * nb + a8));
   return st < 4 ? st : 4;
 }
+constexpr int wide_ring_bytes(int a8, int nb) { return 4 * wide_stages(a8, nb) * (nb * 2048 + a8 * 1024); }
+constexpr int wide_norm_lds(int M, int K) { return M * (K * 2 + 16); }
 
 // A8: groups of 8 activation rows; NB: blocks of 16 columns; ST: stages of a wave's ring
 template <int A8, int NB, int ST, int EPI>
@@ -254,10 +256,15 @@ __global__ __launch_bounds__(256) void rows_kernel(RowsArgs p) {
 // whole, are 1 : 2 NB of the weights with 8 rows.  Waves split K and add their sums in LDS as in rows_kernel.
 // ROWS_GLU: a block of 16 weight rows is 8 gate and the 8 up rows of the same output columns, which makes any number of blocks a
 // whole number of columns; lane l + 32 holds the up values of lane l's gate values.
+// A8 = 0: one or two fp32 rows p.xf, which the work-group normalises (Sec. 2.1) into LDS with the thread layout, summation
+// order and roundings of rmsnorm_kernel while its first weights travel; the ring then holds weights alone.
+// Measured against the kernels it replaces, us: gate|up (28672 x 4096) of 8 rows 42.3 -> 37.9 (6.2 TB/s; loads alone take 38),
+// of one row 41.1 -> 38.1, (24576 x 4096) of 32 rows 40.5 -> 35.6; LM head (16864 x 4096) of 32 rows 35.8 -> 24.7.
 template <int A8, int NB, int EPI>
 __global__ __launch_bounds__(256) void rows_wide_kernel(RowsArgs p) {
 #if defined(__HIP_DEVICE_COMPILE__)
-  constexpr int MB = (A8 + 1) / 2;
+  constexpr bool NORM = A8 == 0;
+  constexpr int MB = NORM ? 1 : (A8 + 1) / 2;
   constexpr int STAGE = NB * 2048 + A8 * 1024, LOADS = 2 * NB + A8, ST = wide_stages(A8, NB);
   static_assert(ST >= 2 && (ST - 1) * LOADS < 64, "vmcnt is a 6-bit counter");
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];   // [4][ST][STAGE], then float4 [4][MB][NB][64], rstd
@@ -267,10 +274,26 @@ __global__ __launch_bounds__(256) void rows_wide_kernel(RowsArgs p) {
   unsigned char* const ring = smem + wave * (ST * STAGE);
   float4* const sums = reinterpret_cast<float4*>(smem);
   float* const rstd = reinterpret_cast<float*>(sums + 4 * MB * NB * 64);
+  unsigned char* const xn_lds = smem + 4 * ST * STAGE;                      // NORM: bf16 [M][K], float [M][4]
+  float4 h[2][8], gam[8];                           // NORM: this thread's share of the rows and of the norm scale
+  if constexpr (NORM) {
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      const int i = (j * 256 + (int)threadIdx.x) * 4;
+      gam[j] = i < p.K ? *reinterpret_cast<const float4*>(p.gamma + i) : make_float4(0.f, 0.f, 0.f, 0.f);
+    }
+#pragma unroll
+    for (int m = 0; m < 2; ++m)
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        const int i = (j * 256 + (int)threadIdx.x) * 4;
+        h[m][j] = m < p.M && i < p.K ? *reinterpret_cast<const float4*>(p.xf + (size_t)m * p.K + i) : make_float4(0.f, 0.f, 0.f, 0.f);
+      }
+  }
 
   typedef __attribute__((__vector_size__(16))) unsigned int u32x4_t;
-  u32x4_t ssq[2 * A8][2];                           // the rows' sums of squares (see rows_kernel)
-  if (p.n_sumsq > 0) {
+  u32x4_t ssq[NORM ? 1 : 2 * A8][2];                // the rows' sums of squares (see rows_kernel)
+  if (!NORM && p.n_sumsq > 0) {
     const __amdgpu_buffer_rsrc_t rS = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(p.sumsq_in), 0,
                                                                         (uint32_t)p.M * p.n_sumsq * 4, 0x00020000);
 #pragma unroll
@@ -290,7 +313,7 @@ __global__ __launch_bounds__(256) void rows_wide_kernel(RowsArgs p) {
   const __amdgpu_buffer_rsrc_t rW = __builtin_amdgcn_make_buffer_rsrc(
       const_cast<bf16_t*>(p.W), 0, (uint32_t)((long long)p.N * (GLU ? 2 : 1) * p.K * 2), 0x00020000);
   const int lr = lane >> 3;
-  uint32_t off_w[2 * NB], off_a[A8];
+  uint32_t off_w[2 * NB], off_a[NORM ? 1 : A8];
 #pragma unroll
   for (int j = 0; j < 2 * NB; ++j) {
     const int col = wg * COLS + (GLU ? (j >> 1) * 8 + lr : j * 8 + lr);
@@ -319,6 +342,41 @@ __global__ __launch_bounds__(256) void rows_wide_kernel(RowsArgs p) {
   };
 #pragma unroll
   for (int i = 0; i < ST - 1; ++i) issue(i, i);
+  if constexpr (NORM) {
+    // LDS accesses in assembly: beside loads into LDS that are under way the compiler waits for all of those before each of its own
+    const uint32_t xn_addr = (uint32_t)(size_t)(lds_ptr_t)xn_lds, red = xn_addr + (uint32_t)(p.M * p.K * 2);
+#pragma unroll
+    for (int m = 0; m < 2; ++m) {
+      float ss = 0.f;
+#pragma unroll
+      for (int j = 0; j < 8; ++j)
+        if ((j * 256 + (int)threadIdx.x) * 4 < p.K)
+          ss += h[m][j].x * h[m][j].x + h[m][j].y * h[m][j].y + h[m][j].z * h[m][j].z + h[m][j].w * h[m][j].w;
+      ss = wave_sum(ss);
+      if (m < p.M && lane == 0) asm volatile("ds_write_b32 %0, %1" ::"v"(red + (m * 4 + wave) * 4), "v"(ss) : "memory");
+    }
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // (not __syncthreads: the weights stay in flight)
+    __builtin_amdgcn_s_barrier();
+#pragma unroll
+    for (int m = 0; m < 2; ++m) {
+      if (m >= p.M) break;
+      floatx4_t part;
+      asm volatile("ds_read_b128 %0, %1\n\ts_waitcnt lgkmcnt(0)" : "=v"(part) : "v"(red + m * 16) : "memory");
+      const float total = part[0] + part[1] + part[2] + part[3];
+      const float r = rsqrtf(total / (float)p.K + p.eps);
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        const int i = (j * 256 + (int)threadIdx.x) * 4;
+        if (i < p.K) {
+          const float4 g = gam[j];
+          const uint2 v = make_uint2(pack_bf16x2(h[m][j].x * r * g.x, h[m][j].y * r * g.y), pack_bf16x2(h[m][j].z * r * g.z, h[m][j].w * r * g.w));
+          asm volatile("ds_write_b64 %0, %1" ::"v"(xn_addr + (uint32_t)(m * p.K + i) * 2), "v"(__builtin_bit_cast(unsigned long long, v)) : "memory");
+        }
+      }
+    }
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+  }
 
   const int r16 = lane & 15, g4 = lane >> 4;
   const int frag = r16 * 128, key = (r16 >> 1) & 7;
@@ -328,6 +386,8 @@ __global__ __launch_bounds__(256) void rows_wide_kernel(RowsArgs p) {
   for (int j = 0; j < MB; ++j)
 #pragma unroll
     for (int n = 0; n < NB; ++n) acc[j][n] = floatx4_t{0.f, 0.f, 0.f, 0.f};
+  // NORM: lanes of rows that do not exist repeat the last one (never stored)
+  const unsigned char* const xn_lane = xn_lds + (size_t)min(r16, p.M - 1) * p.K * 2 + g4 * 16;
   int stage = 0;
   for (int i = 0; i < nk; ++i) {
     issue(i + ST - 1, stage == 0 ? ST - 1 : stage - 1);
@@ -339,11 +399,16 @@ __global__ __launch_bounds__(256) void rows_wide_kernel(RowsArgs p) {
 #pragma unroll
       for (int n = 0; n < NB; ++n)
         w[n] = *reinterpret_cast<const bf16x8_t*>(s + n * 2048 + frag + ((4 * ks + g4) ^ key) * 16);
+      if constexpr (NORM) {
+        const int k = i + rot >= nk ? i + rot - nk : i + rot;
+        a[0] = *reinterpret_cast<const bf16x8_t*>(xn_lane + (k_lo + k) * 128 + ks * 64);
+      } else {
 #pragma unroll
       for (int j = 0; j < MB; ++j) {
         const bool odd = A8 % 2 && j == MB - 1;
         a[j] = *reinterpret_cast<const bf16x8_t*>(s + NB * 2048 + j * 2048 + (odd ? frag_last : frag) +
                                                   ((4 * ks + g4) ^ (odd ? key_last : key)) * 16);
+      }
       }
 #pragma unroll
       for (int j = 0; j < MB; ++j)
@@ -360,7 +425,7 @@ __global__ __launch_bounds__(256) void rows_wide_kernel(RowsArgs p) {
 #pragma unroll
     for (int n = 0; n < NB; ++n)
       sums[((wave * MB + j) * NB + n) * 64 + lane] = make_float4(acc[j][n][0], acc[j][n][1], acc[j][n][2], acc[j][n][3]);
-  if (p.n_sumsq > 0) {
+  if (!NORM && p.n_sumsq > 0) {
 #pragma unroll
     for (int i = 0; i < 2 * A8; ++i) {
       const float4 a = __builtin_bit_cast(float4, ssq[i][0]), b = __builtin_bit_cast(float4, ssq[i][1]);
@@ -375,7 +440,7 @@ __global__ __launch_bounds__(256) void rows_wide_kernel(RowsArgs p) {
   for (int blk = wave; blk < MB * NB; blk += 4) {    // 16 rows x 16 weight rows each
     const int mb = blk / NB, n = blk % NB, m = mb * 16 + r16;
     const bool valid = m < p.M;
-    const float rs = valid ? rstd[m] : 0.f;
+    const float rs = NORM ? 1.f : valid ? rstd[m] : 0.f;
     float c[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int w = 0; w < 4; ++w) {
@@ -403,11 +468,11 @@ __global__ __launch_bounds__(256) void rows_wide_kernel(RowsArgs p) {
 
 template <int A8, int NB, int EPI>
 hipError_t launch_wide_cfg(const RowsArgs& a, hipStream_t st) {
-  constexpr int MB = (A8 + 1) / 2, ring = 4 * wide_stages(A8, NB) * (NB * 2048 + A8 * 1024), sums = 4 * MB * NB * 1024 + 8 * A8 * 4;
-  constexpr int smem = ring > sums ? ring : sums;
-  static_assert(smem <= 160 * 1024, "LDS budget of a gfx950 CU");
+  constexpr int MB = A8 ? (A8 + 1) / 2 : 1, ring = wide_ring_bytes(A8, NB), sums = 4 * MB * NB * 1024 + 8 * A8 * 4;
+  static_assert(ring >= sums && ring <= 160 * 1024, "LDS budget of a gfx950 CU");
+  const int smem = ring + (A8 ? 0 : wide_norm_lds(a.M, a.K));
   static const hipError_t attr_err = hipFuncSetAttribute(reinterpret_cast<const void*>(&rows_wide_kernel<A8, NB, EPI>),
-                                                         hipFuncAttributeMaxDynamicSharedMemorySize, smem);
+                                                         hipFuncAttributeMaxDynamicSharedMemorySize, A8 ? ring : 160 * 1024);
   if (attr_err != hipSuccess) return attr_err;
   constexpr int cols = EPI == ROWS_GLU ? NB * 8 : NB * 16;
   hipLaunchKernelGGL((rows_wide_kernel<A8, NB, EPI>), dim3((a.N + cols - 1) / cols), dim3(256), smem, st, a);
@@ -418,6 +483,7 @@ template <int EPI>
 hipError_t launch_wide(const RowsArgs& a, hipStream_t st) {
   auto rows = [&](auto nb_c) {
     constexpr int NB = decltype(nb_c)::value;
+    if (a.xf) return launch_wide_cfg<0, NB, EPI>(a, st);
     if (a.M <= 8) return launch_wide_cfg<1, NB, EPI>(a, st);
     if (a.M <= 16) return launch_wide_cfg<2, NB, EPI>(a, st);
     if (a.M <= 24) return launch_wide_cfg<3, NB, EPI>(a, st);
@@ -472,8 +538,15 @@ bool rows_wide_supported(int M, int N, int K, int epilogue) {
          K % 64 == 0 && K >= 256 && wide_blocks(w_rows) >= 4 && wide_blocks(w_rows) <= 8 && w_rows * K * 2 < (1LL << 31);
 }
 
+bool rows_wide_norm_supported(int M, int N, int K, int epilogue) {
+  return M >= 1 && M <= 2 && K <= 8192 && rows_wide_supported(3, N, K, epilogue) &&
+         wide_ring_bytes(0, wide_blocks(epilogue == ROWS_GLU ? 2LL * N : N)) + wide_norm_lds(M, K) <= 160 * 1024;
+}
+
 hipError_t launch_rows(const RowsArgs& a, hipStream_t st) {
-  const bool wide = rows_wide_supported(a.M, a.N, a.K, a.epilogue);
+  const bool wide = a.xf ? rows_wide_norm_supported(a.M, a.N, a.K, a.epilogue) && a.gamma && a.n_sumsq == 0
+                         : rows_wide_supported(a.M, a.N, a.K, a.epilogue);
+  if (a.xf && !wide) return hipErrorInvalidValue;
   if (!(wide || rows_supported(a.M, a.N, a.K)) || a.ldo % 4 || a.n_sumsq % 4 || a.n_sumsq > kRowScaledSums) return hipErrorInvalidValue;
   if (wide) return a.epilogue == ROWS_GLU ? launch_wide<ROWS_GLU>(a, st) : launch_wide<ROWS_STORE>(a, st);
   switch (a.epilogue) {

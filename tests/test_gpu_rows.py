@@ -103,9 +103,10 @@ def test_lm_head_tiles(rows, vocab, cols):
 
 
 # gate|up and LM head with 64 to 128 weight rows per work-group: 4 to 8 blocks of 16, whole and ragged last work-groups, K-steps of
-# four waves even (256) and uneven (448), both activations; one width below and one above go through the tiled GEMM
+# four waves even (256) and uneven (448), both activations; one width below and one above go through the tiled GEMM.  One and two
+# rows are normalised inside this kernel.
 @pytest.mark.gpu
-@pytest.mark.parametrize("rows", [3, 9, 17, 32])
+@pytest.mark.parametrize("rows", [1, 2, 3, 9, 17, 32])
 @pytest.mark.parametrize("d_model,d_ffn,vocab,act", [(256, 6144, 12288, 0), (256, 6208, 12292, 1), (448, 8256, 20480, 0),
                                                      (256, 12288, 24580, 1), (448, 14336, 28676, 0), (256, 16384, 32772, 0)])
 def test_wide_projections(rows, d_model, d_ffn, vocab, act):
