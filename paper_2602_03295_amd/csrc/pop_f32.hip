@@ -77,6 +77,11 @@ __global__ __launch_bounds__(KW == 1 ? 256 : 64 * KW) void gemm_kernel(GemmF32 p
   const int m0 = (KW > 1 ? blockIdx.y : blockIdx.y * 2 + (wave >> 1)) * TM * 16;
   const int n0 = (KW > 1 ? blockIdx.x : blockIdx.x * 2 + (wave & 1)) * TN * 16;
   static_assert(EPI != EPI_QKV || (KW >= TM && KW > 1 && TN <= 2), "a wave finishes all columns of 16 rows");
+  // Who finishes a block of a split (EPI_QKV: 16 rows with all their columns): with more waves than blocks ES waves, each NE of
+  // the four columns that a lane holds, where one wave added eight parts and evaluated four activations per lane while the
+  // others idled (128 rows: gate|up of 2 x 688 columns 7.7 -> 7.4 us, QKV 4.8 -> 4.7).
+  constexpr int JN = EPI == EPI_QKV ? 1 : TN, UP = EPI == EPI_GLU ? TN : EPI == EPI_QKV ? TN - 1 : 0;   // `up`: the block UP on
+  constexpr int ES = KW < 2 * TM * JN ? 1 : KW < 4 * TM * JN ? 2 : 4, NE = 4 / ES;
   const int hd = EPI == EPI_QKV ? p.ra.hd : 0, half = hd >> 1;
   const int head = EPI == EPI_QKV ? n0 / hd : 0, pair0 = EPI == EPI_QKV ? n0 % hd / 2 : 0;
   // rows and columns beyond the matrix repeat its last one (never stored)
@@ -104,15 +109,14 @@ __global__ __launch_bounds__(KW == 1 ? 256 : 64 * KW) void gemm_kernel(GemmF32 p
 #pragma unroll
     for (int j = 0; j < NB; ++j) acc[i][j] = floatx4_t{0.f, 0.f, 0.f, 0.f};
   }
-  // EPI_QKV: (cos, sin) of the pairs that this wave will finish, four per lane, and the rows' slots
-  float4 cs01, cs23;
+  // EPI_QKV: (cos, sin) of the pairs that this wave will finish, NE per lane, and the rows' slots
+  float2 cs[NE];
   int slot = 0;
   if (EPI == EPI_QKV) {
-    const int m = min(m0 + min(wave, TM - 1) * 16 + r16, p.M - 1);
-    const float4* cs = reinterpret_cast<const float4*>(p.ra.cs + (size_t)(p.ra.cs_row ? p.ra.cs_row[m] : m) * half + pair0 +
-                                                       (TN == 1 ? 4 * (g & 1) : 4 * g));
-    cs01 = cs[0];
-    cs23 = cs[1];
+    const int m = min(m0 + min(wave / ES, TM - 1) * 16 + r16, p.M - 1);
+    const float2* c = p.ra.cs + (size_t)(p.ra.cs_row ? p.ra.cs_row[m] : m) * half + pair0 + (TN == 1 ? 4 * (g & 1) : 4 * g) + wave % ES * NE;
+#pragma unroll
+    for (int e = 0; e < NE; ++e) cs[e] = c[e];
     slot = p.ra.slot[m];
   }
   const int chunks = (p.K + 15) >> 4, per = (chunks + KW - 1) / KW;
@@ -178,23 +182,25 @@ __global__ __launch_bounds__(KW == 1 ? 256 : 64 * KW) void gemm_kernel(GemmF32 p
         red[kw][i * NB + j][lane] = make_float4(acc[i][j][0], acc[i][j][1], acc[i][j][2], acc[i][j][3]);
     __syncthreads();
   }
-  // wave w of a split finishes blocks w, w + KW, ...; without a split every wave its own
-  // (EPI_QKV: 16 rows with all their columns)
-  constexpr int JN = EPI == EPI_QKV ? 1 : TN, UP = EPI == EPI_GLU ? TN : EPI == EPI_QKV ? TN - 1 : 0;   // `up`: the block UP on
-  for (int blk = KW > 1 ? wave : 0; blk < TM * JN; blk += KW) {
-    const int i = blk / JN, j = blk % JN;
-    float4 c, up;
+  // wave w of a split finishes blocks w / ES, (w + KW) / ES, ...; without a split every wave its own
+  for (int item = KW > 1 ? wave : 0; item < TM * JN * ES; item += KW) {
+    const int blk = item / ES, e0 = item % ES * NE, i = blk / JN, j = blk % JN;
+    float c[NE], up[NE];
     float sq = 0.f;
     if (KW > 1) {
-      c = red[0][i * NB + j][lane];
-      up = red[0][i * NB + UP + j][lane];
+      auto part = [&](int k, int b) { return reinterpret_cast<const float*>(&red[k][i * NB + b][lane]) + e0; };
+#pragma unroll
+      for (int e = 0; e < NE; ++e) {
+        c[e] = part(0, j)[e];
+        up[e] = part(0, UP + j)[e];
+      }
       if (NORM) sq = red_ss[0][i][r16];
+#pragma unroll
       for (int k = 1; k < KW; ++k) {
-        const float4 x = red[k][i * NB + j][lane];
-        c.x += x.x; c.y += x.y; c.z += x.z; c.w += x.w;
-        if (UP > 0) {
-          const float4 y = red[k][i * NB + UP + j][lane];
-          up.x += y.x; up.y += y.y; up.z += y.z; up.w += y.w;
+#pragma unroll
+        for (int e = 0; e < NE; ++e) {
+          c[e] += part(k, j)[e];
+          if (UP > 0) up[e] += part(k, UP + j)[e];
         }
         if (NORM) sq += red_ss[k][i][r16];
       }
@@ -204,75 +210,86 @@ __global__ __launch_bounds__(KW == 1 ? 256 : 64 * KW) void gemm_kernel(GemmF32 p
       for (int q = 0; q < TM * TN; ++q)
         if (q == blk) {
           const floatx4_t x = acc[q / TN][q % TN], y = acc[q / TN][EPI == EPI_GLU ? TN + q % TN : q % TN];
-          c = make_float4(x[0], x[1], x[2], x[3]);
-          up = make_float4(y[0], y[1], y[2], y[3]);
+#pragma unroll
+          for (int e = 0; e < NE; ++e) {
+            c[e] = x[e];
+            up[e] = y[e];
+          }
           sq = ss[q / TN];
         }
     }
     const float rstd = NORM ? 1.0f / sqrtf(sq / (float)p.K + p.eps) : 1.f;
-    const int m = m0 + i * 16 + r16, n = n0 + j * 16 + 4 * g;
+    const int m = m0 + i * 16 + r16, n = n0 + j * 16 + 4 * g + e0;
+    auto store_ne = [&](float* o, const float (&v)[NE]) {
+      if constexpr (NE == 4) *reinterpret_cast<float4*>(o) = make_float4(v[0], v[1], v[2], v[3]);
+      else if constexpr (NE == 2) *reinterpret_cast<float2*>(o) = make_float2(v[0], v[1]);
+      else *o = v[0];
+    };
     if constexpr (EPI == EPI_QKV) {
       // x: this lane's values (with 32 columns the low halves of its pairs), y: their partners.  16 columns: lane groups 0, 1
       // have the low halves of 8 pairs, lane groups 2, 3 the high ones
-      float x[4] = {c.x * rstd, c.y * rstd, c.z * rstd, c.w * rstd}, y[4];
+      float x[NE], y[NE];
 #pragma unroll
-      for (int e = 0; e < 4; ++e) y[e] = TN == 1 ? __shfl_xor(x[e], 32, 64) : (&up.x)[e] * rstd;
+      for (int e = 0; e < NE; ++e) {
+        x[e] = c[e] * rstd;
+        y[e] = TN == 1 ? __shfl_xor(x[e], 32, 64) : up[e] * rstd;
+      }
       const bool low = TN == 2 || g < 2;
       const RopeAppend& ra = p.ra;
       const bool rotate = head < ra.n_q_heads + ra.n_kv_heads;
       if (rotate) {
-        const float cc[4] = {cs01.x, cs01.z, cs23.x, cs23.z}, sn[4] = {cs01.y, cs01.w, cs23.y, cs23.w};
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const float a = low ? x[e] * cc[e] - y[e] * sn[e] : x[e] * cc[e] + y[e] * sn[e];
-          y[e] = y[e] * cc[e] + x[e] * sn[e];      // (used with 32 columns)
+        for (int e = 0; e < NE; ++e) {
+          const float a = low ? x[e] * cs[e].x - y[e] * cs[e].y : x[e] * cs[e].x + y[e] * cs[e].y;
+          y[e] = y[e] * cs[e].x + x[e] * cs[e].y;      // (used with 32 columns)
           x[e] = a;
         }
       }
       if (m >= p.M) continue;
-      auto store = [&](const float (&v)[4], int dim) {
+      auto store = [&](const float (&v)[NE], int dim) {
         if (head < ra.n_q_heads) {
-          *reinterpret_cast<float4*>(p.out + (size_t)m * p.ldc + head * hd + dim) = make_float4(v[0], v[1], v[2], v[3]);
+          store_ne(p.out + (size_t)m * p.ldc + head * hd + dim, v);
           return;
         }
         const int hh = rotate ? head - ra.n_q_heads : head - ra.n_q_heads - ra.n_kv_heads;
         float* o = (rotate ? ra.k_pool : ra.v_pool) +
                    (((size_t)(slot / ra.page_size) * ra.n_kv_heads + hh) * ra.page_size + slot % ra.page_size) * hd + dim;
-        float w[4];
+        float w[NE];
 #pragma unroll
-        for (int e = 0; e < 4; ++e)   // 8-bit cache: the fp32 entry holds the value of the e4m3 code the element rounds to
+        for (int e = 0; e < NE; ++e)   // 8-bit cache: the fp32 entry holds the value of the e4m3 code the element rounds to
           w[e] = !ra.kvq.fp8 ? v[e]
                              : e4m3_decode(e4m3_encode(v[e] * (rotate ? ra.kvq.k_inv : ra.kvq.v_inv))) *
                                    (rotate ? ra.kvq.k_scale : ra.kvq.v_scale);
-        *reinterpret_cast<float4*>(o) = make_float4(w[0], w[1], w[2], w[3]);
+        store_ne(o, w);
       };
-      const int dim = pair0 + (TN == 1 ? 4 * (g & 1) : 4 * g);
+      const int dim = pair0 + (TN == 1 ? 4 * (g & 1) : 4 * g) + e0;
       store(x, low ? dim : dim + half);
       if (TN == 2) store(y, dim + half);
       continue;
     }
     if (m >= p.M) continue;
     float* o = p.out + (size_t)m * p.ldc + n;
-    if (n + 3 < p.N && (p.ldc & 3) == 0) {     // four columns at once
-      float4 r = make_float4(c.x * rstd, c.y * rstd, c.z * rstd, c.w * rstd);
+    if (n + NE - 1 < p.N && (p.ldc & 3) == 0) {     // all columns at once
+      float old[NE], r[NE];
       if (EPI == EPI_ADD) {
-        const float4 old = *reinterpret_cast<const float4*>(o);
-        r = make_float4(old.x + r.x * p.scale, old.y + r.y * p.scale, old.z + r.z * p.scale, old.w + r.w * p.scale);
-      } else if (EPI == EPI_GLU) {
-        r = make_float4(glu_act(r.x, p.act) * (up.x * rstd), glu_act(r.y, p.act) * (up.y * rstd),
-                        glu_act(r.z, p.act) * (up.z * rstd), glu_act(r.w, p.act) * (up.w * rstd));
+#pragma unroll
+        for (int e = 0; e < NE; ++e) old[e] = o[e];
       }
-      *reinterpret_cast<float4*>(o) = r;
+#pragma unroll
+      for (int e = 0; e < NE; ++e) {
+        const float x = c[e] * rstd;
+        r[e] = EPI == EPI_ADD ? old[e] + x * p.scale : EPI == EPI_GLU ? glu_act(x, p.act) * (up[e] * rstd) : x;
+      }
+      store_ne(o, r);
       continue;
     }
-    const float cv[4] = {c.x, c.y, c.z, c.w}, uv[4] = {up.x, up.y, up.z, up.w};
 #pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      if (n + v >= p.N) break;
-      const float x = cv[v] * rstd;
-      if (EPI == EPI_STORE) o[v] = x;
-      else if (EPI == EPI_ADD) o[v] += x * p.scale;
-      else o[v] = glu_act(x, p.act) * (uv[v] * rstd);
+    for (int e = 0; e < NE; ++e) {
+      if (n + e >= p.N) break;
+      const float x = c[e] * rstd;
+      if (EPI == EPI_STORE) o[e] = x;
+      else if (EPI == EPI_ADD) o[e] += x * p.scale;
+      else o[e] = glu_act(x, p.act) * (up[e] * rstd);
     }
   }
 }
@@ -350,7 +367,7 @@ struct AttnF32 {
   const float* k_pool;
   const float* v_pool;
   const int32_t* block_table;
-  int max_pages, P, window;
+  int max_pages, lgP, window;      // pages of 2^lgP entries
   const int32_t* kv_first;
   int rows, n_q_heads, n_kv_heads;
   float scale;
@@ -382,7 +399,7 @@ __global__ __launch_bounds__(NT) void attention_kernel(AttnF32 a) {
   const int li = tid % LPK, ks = tid / LPK;
   auto entry = [&](const float* pool, int key) {
     return *reinterpret_cast<const float4*>(
-        pool + (((size_t)bt[key / a.P] * a.n_kv_heads + kvh) * a.P + (key % a.P)) * HD + li * 4);
+        pool + ((((size_t)bt[key >> a.lgP] * a.n_kv_heads + kvh) << a.lgP) + (key & ((1 << a.lgP) - 1))) * HD + li * 4);
   };
   const float4 qv = *reinterpret_cast<const float4*>(a.q + (size_t)r * a.ldq + a.q_col + head * HD + li * 4);
   float mx = -INFINITY;
@@ -442,17 +459,18 @@ __global__ __launch_bounds__(NT) void attention_kernel(AttnF32 a) {
   }
 }
 
-// The same for packed prompt rows: a work-group takes 16 consecutive rows of one query head, its four waves every
-// fourth block of 16 keys.  S^T = K Q^T and O^T += V^T P^T on the MFMA with a running maximum and sum per wave; a
+// The same for packed prompt rows: a work-group takes 16 consecutive rows of one query head, its waves the blocks of 16
+// keys in turn (four waves up to 64 keys; eight beyond, where a second block per wave is a second chain of dependent loads: 128
+// rows of 4 heads 7.0 -> 6.7 us, pages found by shifts instead of divisions included).  S^T = K Q^T and O^T += V^T P^T on the MFMA with a running maximum and sum per wave; a
 // lane then holds 4 keys of one row, which are the operand of the second product as they are (MFMA j takes key
 // 4 g + j from lane group g).  The waves' results meet in LDS.  Rows of different sequences in one tile are taken
 // sequence by sequence.  One work-group per row and head re-read every entry 16 times as often and waited for each
 // (30 us for 128 rows of 4 heads, 5 us now).
-template <int HD>
-__global__ __launch_bounds__(256) void attention_tile_kernel(AttnF32 a) {
+template <int HD, int NW>
+__global__ __launch_bounds__(64 * NW) void attention_tile_kernel(AttnF32 a) {
   constexpr int C = HD / 16;
-  extern __shared__ float smem[];                  // [4 waves][16 rows][HD + 4]
-  __shared__ float red_m[4][16], red_l[4][16];
+  extern __shared__ float smem[];                  // [NW waves][16 rows][HD + 4]
+  __shared__ float red_m[NW][16], red_l[NW][16], red_f[NW][16];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int r16 = lane & 15, g = lane >> 4;
   const int head = blockIdx.y, kvh = head / (a.n_q_heads / a.n_kv_heads);
@@ -472,7 +490,7 @@ __global__ __launch_bounds__(256) void attention_tile_kernel(AttnF32 a) {
     const int all_lo = __builtin_amdgcn_readlane(lo, 15), all_hi = __builtin_amdgcn_readfirstlane(pos);
     const int32_t* bt = a.block_table + (size_t)b * a.max_pages;
     auto entry = [&](const float* pool, int key) {
-      return pool + (((size_t)bt[key / a.P] * a.n_kv_heads + kvh) * a.P + (key % a.P)) * HD;
+      return pool + ((((size_t)bt[key >> a.lgP] * a.n_kv_heads + kvh) << a.lgP) + (key & ((1 << a.lgP) - 1))) * HD;
     };
     float4 qf[C];
 #pragma unroll
@@ -482,7 +500,7 @@ __global__ __launch_bounds__(256) void attention_tile_kernel(AttnF32 a) {
 #pragma unroll
     for (int c = 0; c < C; ++c) o[c] = floatx4_t{0.f, 0.f, 0.f, 0.f};
     float m_run = -INFINITY, l_run = 0.f;
-    for (int k0 = k_lo + wave * 16; k0 <= k_hi; k0 += 64) {
+    for (int k0 = k_lo + wave * 16; k0 <= k_hi; k0 += NW * 16) {
       // keys beyond the last one repeat it (masked below)
       const float* kp = entry(a.k_pool, min(k0 + r16, k_hi)) + 4 * g;
       const float* vp[4];
@@ -572,14 +590,21 @@ __global__ __launch_bounds__(256) void attention_tile_kernel(AttnF32 a) {
       *reinterpret_cast<float4*>(smem + (wave * 16 + r16) * (HD + 4) + c * 16 + 4 * g) =
           make_float4(o[c][0], o[c][1], o[c][2], o[c][3]);
     __syncthreads();
-    for (int it = threadIdx.x; it < (r1 - r0) * (HD / 4); it += 256) {
+    if (threadIdx.x < NW * 16) {                                 // every wave's factor, once
+      const int w = threadIdx.x >> 4, r = threadIdx.x & 15;
+      float m = red_m[0][r];
+#pragma unroll
+      for (int v = 1; v < NW; ++v) m = fmaxf(m, red_m[v][r]);
+      red_f[w][r] = expf(red_m[w][r] - m);                       // (a wave without keys: exp(-inf) = 0)
+    }
+    __syncthreads();
+    for (int it = threadIdx.x; it < (r1 - r0) * (HD / 4); it += 64 * NW) {
       const int r = it / (HD / 4), i = it % (HD / 4) * 4;
-      const float m = fmaxf(fmaxf(red_m[0][r], red_m[1][r]), fmaxf(red_m[2][r], red_m[3][r]));
       float4 num = make_float4(0.f, 0.f, 0.f, 0.f);
       float den = 0.f;
 #pragma unroll
-      for (int w = 0; w < 4; ++w) {
-        const float f = expf(red_m[w][r] - m);                  // (a wave without keys: exp(-inf) = 0)
+      for (int w = 0; w < NW; ++w) {
+        const float f = red_f[w][r];
         const float4 x = *reinterpret_cast<const float4*>(smem + (w * 16 + r) * (HD + 4) + i);
         num.x += f * x.x; num.y += f * x.y; num.z += f * x.z; num.w += f * x.w;
         den += f * red_l[w][r];
@@ -661,15 +686,21 @@ void launch_rope_write(float* qkv, int ld, int q_col, int k_col, int v_col, int 
 }
 
 namespace impl {
+template <int HD, int NW>
+hipError_t launch_attention_tile(const AttnF32& a, hipStream_t st) {
+  constexpr size_t smem = (size_t)NW * 16 * (HD + 4) * sizeof(float);
+  // once per form; the initialisation of a function-local static is thread-safe
+  static const hipError_t attr_err = hipFuncSetAttribute(reinterpret_cast<const void*>(&attention_tile_kernel<HD, NW>),
+                                                         hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
+  if (attr_err != hipSuccess) return attr_err;
+  hipLaunchKernelGGL((attention_tile_kernel<HD, NW>), dim3((a.rows + 15) / 16, a.n_q_heads), dim3(64 * NW), smem, st, a);
+  return hipGetLastError();
+}
 template <int HD>
 hipError_t launch_attention_hd(const AttnF32& a, bool packed, int max_len, hipStream_t st) {
   if (packed) {
-    constexpr size_t smem = (size_t)4 * 16 * (HD + 4) * sizeof(float);
-    // once per head size; the initialisation of a function-local static is thread-safe
-    static const hipError_t attr_err = hipFuncSetAttribute(reinterpret_cast<const void*>(&attention_tile_kernel<HD>),
-                                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
-    if (attr_err != hipSuccess) return attr_err;
-    hipLaunchKernelGGL(attention_tile_kernel<HD>, dim3((a.rows + 15) / 16, a.n_q_heads), dim3(256), smem, st, a);
+    if (HD <= 128 && max_len > 64) return launch_attention_tile<HD, 8>(a, st);
+    return launch_attention_tile<HD, 4>(a, st);
   } else {
     const dim3 grid(a.rows, a.n_q_heads);
     if (max_len > 64 && (long long)a.rows * a.n_q_heads <= 256) {
@@ -691,7 +722,7 @@ hipError_t launch_attention(const float* q, int ldq, int q_col, float* out, cons
                             int n_kv_heads, int hd, int max_len, bool packed, hipStream_t st) {
   if (rows <= 0) return hipSuccess;
   if (max_len > kMaxContext) return hipErrorInvalidValue;
-  const impl::AttnF32 a{q, ldq, q_col, out, row_seq, row_pos, k_pool, v_pool, block_table, max_pages, P, window, kv_first,
+  const impl::AttnF32 a{q, ldq, q_col, out, row_seq, row_pos, k_pool, v_pool, block_table, max_pages, __builtin_ctz(P), window, kv_first,
                         rows, n_q_heads, n_kv_heads, 1.f / sqrtf((float)hd)};
   switch (hd) {
     case 64: return impl::launch_attention_hd<64>(a, packed, max_len, st);
