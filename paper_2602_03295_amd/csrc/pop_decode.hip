@@ -6,6 +6,7 @@
 // Every projection streams its weights once: HBM-bound (three and more rows go through the tiled GEMM, three and four of a
 // K that is no multiple of 64 through the GEMV kernel here).
 #include <algorithm>
+#include <cmath>
 #include <type_traits>
 
 #include "pop_device.h"
@@ -374,45 +375,22 @@ namespace decode_impl {
 
 constexpr int GMAX = 8;   // query heads per KV head
 
-// Reduces values that the lanes li, li + LPK, ... of a wave hold for the same head-dim slice, by a butterfly that
-// halves the number of values a lane carries at every step (a lane sends the half its partner keeps): N values cost
-// N (1 - LPK / 64) exchanges.  Returns the index of this lane's v[0]; the first N * LPK / 64 entries are its results.
-template <int LPK, int N>
-__device__ __forceinline__ int fold_keys(float (&v)[N], int lane) {
-  int first = 0;
-  auto fold = [&](auto n_c, int o) {
-    constexpr int H = decltype(n_c)::value / 2;
-    const bool upper = (lane & o) != 0;
-#pragma unroll
-    for (int i = 0; i < H; ++i) {
-      const float send = upper ? v[i] : v[i + H];
-      const float keep = upper ? v[i + H] : v[i];
-      v[i] = keep + __shfl_xor(send, o, 64);
-    }
-    if (upper) first += H;
-  };
-  constexpr int N2 = LPK <= 32 ? N / 2 : N, N3 = LPK <= 16 ? N2 / 2 : N2;
-  static_assert(N * LPK >= 64, "a lane keeps at least one value");
-  if constexpr (LPK <= 32) fold(std::integral_constant<int, N>{}, 32);
-  if constexpr (LPK <= 16) fold(std::integral_constant<int, N2>{}, 16);
-  if constexpr (LPK <= 8) fold(std::integral_constant<int, N3>{}, 8);
-  return first;
-}
-
 // grid (n_splits, Hkv, B), 256 threads.  Split s of sequence b covers keys lo + s * split_keys .., lo = first visible
 // key (window start, or the first position the layer holds an entry for); wave w of the work-group takes its key
 // blocks (NB groups of 16 keys) w, w + 4, ... with a running maximum and sum of its own.
-//   S = K Q^T on the MFMA (v_mfma_f32_16x16x32_bf16; the G query heads of the KV head are columns, the others zero):
-//   lane l loads 16-byte chunks of key l % 16, which are the operand as they are (8-bit codes become bf16, exactly).
-//   O += P V on the vector ALU in fp32 with P in fp32: V's rows are contiguous in the head-dim, so an MFMA would need
-//   them transposed; LPK = HD / 8 lanes share a V row, P crosses lanes through LDS inside the wave.
-//   The next block's K is requested as soon as S is formed, its V as soon as P V is: a wave has 8 to 16 KB in flight.
-// A work-group per 64 keys with everything on the vector ALU spent its time there and on 130 partial values per head
-// and 64 keys; at 8 sequences: 2048 keys 27 us, 8192 keys of the 8-bit cache 70 + 10 us (with the merge).
-// Per 32 keys of the 8-bit cache a wave issues about 480 vector instructions (row numbers formed once per key and passed
-// between lanes, codes to bf16 two per instruction), 750 before; three work-groups per CU need the launch bound (180
-// registers without it: 650 us a step).  8 sequences of 8192 tokens: 623 -> 605 us a step of four layers; steps over bf16 entries
-// take what they took.
+//   S = K Q^T on the MFMA (v_mfma_f32_16x16x32_bf16): lane l takes chunks of 8 dims of key l % 16, which are the operand as they
+//   are (8-bit codes become bf16, exactly).  Column c of the 16 is query head c % GT: the heads stand there several times.
+//   O^T += V^T P^T on the MFMA (v_mfma_f32_16x16x16_bf16) without rounding P: the 24 bits of a probability are three bf16 numbers
+//   (cut off, not rounded, so that their sum is the probability), which go to three columns of the same head, c / GT = 0, 1, 2, and
+//   are added at the end (eight heads: two columns each, and a second product for the third).  A lane then scales and splits
+//   the four keys that S left it, and nothing crosses lanes.  V, whose rows are contiguous in the head-dim, goes through LDS
+//   (a wave's own 16 rows per group) and comes back transposed, four keys of a dim per lane (ds_read_b64_tr_b16); 32-byte pieces of
+//   row r lie at piece ^ (r & 7), so that the 16 rows of a read fall on different banks.
+//   K goes through LDS too, as it is stored, so that every load takes whole rows (16 bytes of 16 rows per load, the operand's
+//   own layout, reads slower), and the next block's K and V are requested as soon as this block's are in LDS.
+// Where the time goes: with P V in fp32 on the vector ALU and K loaded in operand layout a step's attention took, per layer of 8
+// sequences, 15.0 us (2048 keys) and 35.0 (8192, 8-bit); P V on the MFMA alone changed nothing (15.0, 35.6), loads of whole rows
+// 14.1 and 28.8, fewer splits the rest (see choose_decode_splits).  Three work-groups per CU need the launch bound.
 // GT: compile-time bound of the number of query heads per KV head (registers and loops are sized by it).
 // FUSED: RoPE + append inside this kernel (a.qkv_raw given).
 template <int HD, int GT, bool FUSED, bool FP8, int NB>
@@ -421,10 +399,16 @@ __global__ __launch_bounds__(256, (HD <= 128 && GT <= 4) ? 3 : 1 /* work-groups 
   constexpr int LPK = HD / 8, KPL = 64 / LPK;       // lanes per V row, V rows per load
   constexpr int VL = 16 / KPL;                      // V loads per 16 keys
   constexpr int HALF = HD / 2;
-  typedef typename std::conditional<FP8, uint2, uint4>::type chunk_t;   // 8 elements
-  __shared__ float ps[4][NB * 16][GT];              // P of a wave's block, then unused
-  __shared__ float al[4][GT];                       // rescaling factors of a wave
-  __shared__ float red[4][GT][HD];
+  typedef uint32_t u32x2_t __attribute__((ext_vector_type(2)));
+  typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
+  typedef typename std::conditional<FP8, u32x2_t, u32x4_t>::type chunk_t;   // 8 elements
+  typedef short s16x4_t __attribute__((ext_vector_type(4)));
+  constexpr int HB = HD / 16;                       // 16-dim blocks of a head
+  // K (as stored) and V (bf16) of a wave's block; after its last one V's place holds the wave's float [GT][HD]
+  __shared__ __attribute__((aligned(16))) unsigned char k_lds[4][NB * 16 * LPK * sizeof(chunk_t)];
+  __shared__ __attribute__((aligned(16))) unsigned char v_lds[4][NB * 16 * HD * 2];
+  static_assert(GT * 4 <= NB * 32, "the wave's sums fit its share");
+  auto red = [&](int w, int g, int e) -> float& { return reinterpret_cast<float*>(v_lds[w])[g * HD + e]; };
   __shared__ float stat[4][2][GT];
 
   const int split = blockIdx.x, kvh = blockIdx.y, b = blockIdx.z;
@@ -437,7 +421,8 @@ __global__ __launch_bounds__(256, (HD <= 128 && GT <= 4) ? 3 : 1 /* work-groups 
   const int n_keys = min(a.split_keys, qpos + 1 - k_first);  // <= 0: this split is empty
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int r16 = lane & 15, g4 = lane >> 4;        // key (K operand) or query head (Q operand); k chunk
+  const int r16 = lane & 15, g4 = lane >> 4;        // key (K operand) or column (Q operand); k chunk
+  const int hcol = r16 % GT, piece = r16 / GT;      // the column's query head, and which bf16 piece of its probabilities
   const int li = lane % LPK, vs = lane / LPK;       // V: head-dim chunk, row of the load
   const int32_t* bt = a.block_table + (size_t)b * a.max_pages;
   float* part = a.part + (((size_t)b * a.n_q_heads + (size_t)kvh * G) * a.n_splits + split) * (HD + 2);
@@ -454,55 +439,48 @@ __global__ __launch_bounds__(256, (HD <= 128 && GT <= 4) ? 3 : 1 /* work-groups 
   // Key kk of the split (kk beyond the last one repeats it, masked below).
   auto key_of = [&](int kk) { return k_first + min(kk, n_keys - 1); };
   const int n_blocks = (n_keys + NB * 16 - 1) / (NB * 16);
-  uint32_t row_k[NB];                               // row of this lane's key (r16) in each group of the next block
-  chunk_t kw[NB][KS], vw[NB][VL];
+  // A load takes KPL whole rows, K and V alike: lane (vs, li) has chunk li of row i * KPL + vs of each group of 16 keys.
+  chunk_t kw[NB][VL], vw[NB][VL];
+  // Pages are looked up a block further ahead than entries are: loads return in order, so that a page looked up when its entries
+  // are due arrives behind the rows on their way.
+  int32_t page[NB];                                 // page of key r16 of each group of the block after
   auto load_pages = [&](int blk) {
 #pragma unroll
-    for (int n = 0; n < NB; ++n) {
-      const int key = key_of((blk * NB + n) * 16 + r16);
-      row_k[n] = row_of(key, bt[key >> lgP]);
-    }
+    for (int n = 0; n < NB; ++n) page[n] = bt[key_of((blk * NB + n) * 16 + r16) >> lgP];
   };
-  auto load_k = [&] {
+  auto load_kv = [&](int blk) {                     // (its pages have been looked up)
+    uint32_t row[NB];
 #pragma unroll
-    for (int n = 0; n < NB; ++n) {
-      const chunk_t* p = k_pool + chunk_of(row_k[n]) + g4;
-#pragma unroll
-      for (int ks = 0; ks < KS; ++ks) kw[n][ks] = p[ks * 4];
-    }
-  };
-  uint32_t row_v[NB];                               // rows of the block whose V is loaded next
-  auto load_v = [&] {
+    for (int n = 0; n < NB; ++n) row[n] = row_of(key_of((blk * NB + n) * 16 + r16), page[n]);
+    load_pages(blk + 4);
+    size_t at[NB][VL];
 #pragma unroll
     for (int n = 0; n < NB; ++n)
 #pragma unroll
-      for (int i = 0; i < VL; ++i) vw[n][i] = v_pool[chunk_of((uint32_t)__shfl((int)row_v[n], i * KPL + vs, 64)) + li];
+      for (int i = 0; i < VL; ++i) at[n][i] = chunk_of((uint32_t)__shfl((int)row[n], i * KPL + vs, 64)) + li;
+#pragma unroll
+    for (int n = 0; n < NB; ++n)
+#pragma unroll
+      for (int i = 0; i < VL; ++i) kw[n][i] = k_pool[at[n][i]];
+#pragma unroll
+    for (int n = 0; n < NB; ++n)
+#pragma unroll
+      for (int i = 0; i < VL; ++i) vw[n][i] = v_pool[at[n][i]];
   };
   // the first block's entries travel while the query rows are prepared
   load_pages(wave);
-#pragma unroll
-  for (int n = 0; n < NB; ++n) row_v[n] = row_k[n];
-  if (wave < n_blocks) {
-    load_k();
-    load_v();
-  }
+  if (wave < n_blocks) load_kv(wave);
 
   auto as_chunk = [](const uint4& w) {
-    if constexpr (FP8) return make_uint2(w.x, w.y);
-    else return w;
+    if constexpr (FP8) return chunk_t{w.x, w.y};
+    else return __builtin_bit_cast(chunk_t, w);
   };
 
-  // ---- query rows: lane l holds head r16 (zeros beyond G), dims 32 ks + 8 g4 .. + 7, as bf16.  The other member of
+  // ---- query rows: lane l holds head hcol (zeros beyond G), dims 32 ks + 8 g4 .. + 7, as bf16.  The other member of
   //      a rotation pair, HALF dims on, is the same lane's chunk ks + KS / 2.
   bf16x8_t qf[KS];
-  // FUSED: the query position's own entry, in registers as loaded from the pools; with two key groups per block in LDS (K row, V
-  // row), a copy per wave: in registers it made the form for three and four heads of 128 spill at three work-groups per CU
-  // (four layers of a step over an 8-bit cache, us: 1 sequence of 32000 tokens 493 -> 470, of 64000 567 -> 544, with three heads
-  // per KV head 482 -> 465 and 562 -> 540).  Where nothing spills the way through LDS only delays
-  // the wave (bf16 entries, one sequence of 2048 tokens: 406.7 -> 408.3).
-  constexpr bool NEW_IN_LDS = FUSED && NB == 2;
-  __shared__ chunk_t entry_new[NEW_IN_LDS ? 4 : 1][2][LPK];
-  chunk_t k_new[KS], v_new = as_chunk(make_uint4(0, 0, 0, 0));
+  // FUSED: the query position's own entry (K row, V row), a copy per wave
+  __shared__ chunk_t entry_new[FUSED ? 4 : 1][2][LPK];
   const bool has_new = FUSED && qpos - k_first < a.split_keys;     // (uniform) its key falls into this split
   if constexpr (FUSED) {
     // the 8 * KS values of this lane of the head at column `col`: optionally RMS-normalised over the head (its four
@@ -554,97 +532,103 @@ __global__ __launch_bounds__(256, (HD <= 128 && GT <= 4) ? 3 : 1 /* work-groups 
       return make_uint4(pack_bf16x2(x[0], x[1]), pack_bf16x2(x[2], x[3]), pack_bf16x2(x[4], x[5]), pack_bf16x2(x[6], x[7]));
     };
     float x[KS][8];
-    head_row((kvh * G + min(r16, G - 1)) * HD, a.q_gamma, x);
+    head_row((kvh * G + min(hcol, G - 1)) * HD, a.q_gamma, x);
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) {
-      const uint4 w = r16 < G ? make_uint4(pack_bf16x2(x[ks][0], x[ks][1]), pack_bf16x2(x[ks][2], x[ks][3]),
-                                           pack_bf16x2(x[ks][4], x[ks][5]), pack_bf16x2(x[ks][6], x[ks][7]))
-                              : make_uint4(0, 0, 0, 0);
+      const uint4 w = hcol < G ? make_uint4(pack_bf16x2(x[ks][0], x[ks][1]), pack_bf16x2(x[ks][2], x[ks][3]),
+                                            pack_bf16x2(x[ks][4], x[ks][5]), pack_bf16x2(x[ks][6], x[ks][7]))
+                               : make_uint4(0, 0, 0, 0);
       qf[ks] = __builtin_bit_cast(bf16x8_t, w);
     }
     if (has_new) {
       head_row((a.n_q_heads + kvh) * HD, a.k_gamma, x);
 #pragma unroll
-      for (int ks = 0; ks < KS; ++ks) {
-        k_new[ks] = as_chunk(pack8(x[ks], a.kvq.k_inv));
-        if (NEW_IN_LDS && r16 == 0) entry_new[wave][0][ks * 4 + g4] = k_new[ks];
-      }
+      for (int ks = 0; ks < KS; ++ks)
+        if (r16 == 0) entry_new[wave][0][ks * 4 + g4] = as_chunk(pack8(x[ks], a.kvq.k_inv));
       float v8[8];
       const float* row = a.qkv_raw + (size_t)b * a.ld + (a.n_q_heads + a.n_kv_heads + kvh) * HD + li * 8;
 #pragma unroll
       for (int e = 0; e < 8; ++e) v8[e] = row[e];
-      v_new = as_chunk(pack8(v8, a.kvq.v_inv));
-      if constexpr (NEW_IN_LDS) {
-        if (vs == 0) entry_new[wave][1][li] = v_new;
-        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");     // the wave's own LDS writes, read by its other lanes
-      }
+      if (vs == 0) entry_new[wave][1][li] = as_chunk(pack8(v8, a.kvq.v_inv));
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");     // the wave's own LDS writes, read by its other lanes
     }
   } else {
-    const bf16_t* q = a.q + ((size_t)b * a.n_q_heads + kvh * G + min(r16, G - 1)) * HD + g4 * 8;
+    const bf16_t* q = a.q + ((size_t)b * a.n_q_heads + kvh * G + min(hcol, G - 1)) * HD + g4 * 8;
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) {
       const uint4 w = *reinterpret_cast<const uint4*>(q + ks * 32);
-      qf[ks] = __builtin_bit_cast(bf16x8_t, r16 < G ? w : make_uint4(0, 0, 0, 0));
+      qf[ks] = __builtin_bit_cast(bf16x8_t, hcol < G ? w : make_uint4(0, 0, 0, 0));
     }
   }
   // FUSED, in the block that holds the query position's key (the split's last): the chunks loaded for it, also by
   // lanes that repeat it, are replaced by the new entry, and the lanes whose key it is store it.
-  auto patch_k = [&](int blk) {
-#pragma unroll
-    for (int n = 0; n < NB; ++n) {
-      const int kk = (blk * NB + n) * 16 + r16, key = key_of(kk);
-      if (key != qpos) continue;
-#pragma unroll
-      for (int ks = 0; ks < KS; ++ks) kw[n][ks] = NEW_IN_LDS ? entry_new[wave][0][ks * 4 + g4] : k_new[ks];
-      if (kk == n_keys - 1) {
-        chunk_t* o = reinterpret_cast<chunk_t*>(const_cast<bf16_t*>(a.k_pool)) + chunk_of(row_of(key, bt[key >> lgP])) + g4;
-#pragma unroll
-        for (int ks = 0; ks < KS; ++ks) o[ks * 4] = kw[n][ks];
-      }
-    }
-  };
-  auto patch_v = [&](int blk) {
+  auto patch = [&](int blk) {
+    const chunk_t kn = entry_new[FUSED ? wave : 0][0][li], vn = entry_new[FUSED ? wave : 0][1][li];
 #pragma unroll
     for (int n = 0; n < NB; ++n)
 #pragma unroll
       for (int i = 0; i < VL; ++i) {
         const int kk = (blk * NB + n) * 16 + i * KPL + vs, key = key_of(kk);
         if (key != qpos) continue;
-        vw[n][i] = NEW_IN_LDS ? entry_new[wave][1][li] : v_new;
-        if (kk == n_keys - 1)
-          reinterpret_cast<chunk_t*>(const_cast<bf16_t*>(a.v_pool))[chunk_of(row_of(key, bt[key >> lgP])) + li] = vw[n][i];
+        kw[n][i] = kn;
+        vw[n][i] = vn;
+        if (kk == n_keys - 1) {
+          const size_t at = chunk_of(row_of(key, bt[key >> lgP])) + li;
+          reinterpret_cast<chunk_t*>(const_cast<bf16_t*>(a.k_pool))[at] = kn;
+          reinterpret_cast<chunk_t*>(const_cast<bf16_t*>(a.v_pool))[at] = vn;
+        }
       }
   };
   // a chunk of K as the MFMA operand
   auto k_operand = [&](const chunk_t& w) {
-    if constexpr (FP8) return e4m3_to_bf16x8(w);
+    if constexpr (FP8) return e4m3_to_bf16x8(make_uint2(w.x, w.y));
     else return __builtin_bit_cast(bf16x8_t, w);
   };
   const float s_scale = FP8 ? scale * a.kvq.k_scale : scale;
-  float acc[GT][8];
+  const uint32_t is_piece[3] = {piece == 0 ? ~0u : 0u, piece == 1 ? ~0u : 0u, piece == 2 ? ~0u : 0u};
+  floatx4_t o[HB], o3[GT == 8 ? HB : 1];            // o[c][v]: dim 16 c + 4 g4 + v of column r16; o3: the third pieces
 #pragma unroll
-  for (int g = 0; g < GT; ++g)
+  for (int c = 0; c < HB; ++c) o[c] = floatx4_t{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int e = 0; e < 8; ++e) acc[g][e] = 0.f;
-  float m_run = -INFINITY, l_run = 0.f;             // of query head r16; l_run: this lane's keys
+  for (int c = 0; c < (GT == 8 ? HB : 1); ++c) o3[c] = floatx4_t{0.f, 0.f, 0.f, 0.f};
+  float m_run = -INFINITY, l_run = 0.f;             // of query head hcol; l_run: this lane's keys
+  // V in LDS: 32-byte piece q of row r at q ^ key(r).  Written in 16-byte chunks, read back by lane i of a group of 16 as the four
+  // rows 4 g4 + 0..3 of dim 16 c + i, for which lanes 4 r .. 4 r + 3 of the group point at row r
+  auto swz = [](int r) { return HD == 64 ? (r >> 1) & 3 : r & 7; };
+  unsigned char* const v_wave = v_lds[wave];
+  const int tr_row = 4 * g4 + (r16 >> 2), tr_key = swz(tr_row);
+  const unsigned char* const tr_lane = v_wave + tr_row * (HD * 2) + (r16 & 3) * 8;
+  // K in LDS: chunk c of row r at c ^ key(r), so that the 16 rows of an operand read (two reads' worth of 8-byte chunks) fall on
+  // different banks
+  auto kswz = [](int r) { return FP8 ? (HD == 64 ? (r >> 2 & 3) << 1 : HD == 128 ? (r >> 1 & 7) << 1 : (r & 15) << 1)
+                                     : HD == 64 ? r >> 1 & 7 : r & 15; };
+  chunk_t* const k_wave = reinterpret_cast<chunk_t*>(k_lds[wave]);
+  const chunk_t* const k_lane = k_wave + r16 * LPK;
+  const int k_key = kswz(r16);
 
   for (int blk = wave; blk < n_blocks; blk += 4) {
-    const bool last_block = blk == n_blocks - 1;
-    if (FUSED && has_new && last_block) {
-      patch_k(blk);
-      patch_v(blk);
-    }
-    if (blk + 4 < n_blocks) load_pages(blk + 4);
+    if (FUSED && has_new && blk == n_blocks - 1) patch(blk);
+#pragma unroll
+    for (int n = 0; n < NB; ++n)
+#pragma unroll
+      for (int i = 0; i < VL; ++i) {
+        const int r = i * KPL + vs;                 // row of the group
+        k_wave[(n * 16 + r) * LPK + (li ^ kswz(r))] = kw[n][i];
+        u32x4_t w;
+        if constexpr (FP8) w = __builtin_bit_cast(u32x4_t, e4m3_to_bf16x8(make_uint2(vw[n][i].x, vw[n][i].y)));
+        else w = vw[n][i];
+        *reinterpret_cast<u32x4_t*>(v_wave + (n * 16 + r) * (HD * 2) + ((li >> 1) ^ swz(r)) * 32 + (li & 1) * 16) = w;
+      }
+    if (blk + 4 < n_blocks) load_kv(blk + 4);
     floatx4_t s[NB];
 #pragma unroll
     for (int n = 0; n < NB; ++n) {
       s[n] = floatx4_t{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
       for (int ks = 0; ks < KS; ++ks)
-        s[n] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(k_operand(kw[n][ks]), qf[ks], s[n], 0, 0, 0);
+        s[n] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(k_operand(k_lane[n * 16 * LPK + ((ks * 4 + g4) ^ k_key)]), qf[ks], s[n], 0, 0, 0);
     }
-    if (blk + 4 < n_blocks) load_k();
-    // s[n][v]: query head r16, key 16 n + 4 g4 + v of the block
+    // s[n][v]: query head hcol, key 16 n + 4 g4 + v of the block
     float mx = -INFINITY;
 #pragma unroll
     for (int n = 0; n < NB; ++n)
@@ -666,53 +650,47 @@ __global__ __launch_bounds__(256, (HD <= 128 && GT <= 4) ? 3 : 1 /* work-groups 
         s[n][v] = __expf(s[n][v] - m_new);
         sum += s[n][v];
       }
-    if (r16 < G) {
-#pragma unroll
-      for (int n = 0; n < NB; ++n)
-#pragma unroll
-        for (int v = 0; v < 4; ++v) ps[wave][n * 16 + 4 * g4 + v][r16 % GT] = s[n][v];
-    }
     l_run = l_run * alpha + sum;
-    const bool moved = __builtin_amdgcn_ballot_w64(r16 < G && alpha != 1.f) != 0;
-    if (moved && g4 == 0 && r16 < G) al[wave][r16 % GT] = alpha;
     m_run = m_new;
-    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");     // the wave's own LDS writes, read by its other lanes
-    if (moved) {
+    if (__builtin_amdgcn_ballot_w64(alpha != 1.f) != 0) {
 #pragma unroll
-      for (int g = 0; g < GT; ++g)
-        if (g < G) {
-          const float f = al[wave][g];
+      for (int c = 0; c < HB; ++c)
 #pragma unroll
-          for (int e = 0; e < 8; ++e) acc[g][e] *= f;
-        }
-    }
+        for (int v = 0; v < 4; ++v) o[c][v] *= alpha;
+      if (GT == 8) {
 #pragma unroll
-    for (int n = 0; n < NB; ++n)
+        for (int c = 0; c < HB; ++c)
 #pragma unroll
-      for (int i = 0; i < VL; ++i) {
-        float vf[8];
-        if constexpr (FP8) {
-          e4m3_decode4_hw(vw[n][i].x, vf);
-          e4m3_decode4_hw(vw[n][i].y, vf + 4);
-        } else {
-          const uint4 w = vw[n][i];
-          vf[0] = bf16lo(w.x); vf[1] = bf16hi(w.x); vf[2] = bf16lo(w.y); vf[3] = bf16hi(w.y);
-          vf[4] = bf16lo(w.z); vf[5] = bf16hi(w.z); vf[6] = bf16lo(w.w); vf[7] = bf16hi(w.w);
-        }
-#pragma unroll
-        for (int g = 0; g < GT; ++g)
-          if (GT <= 4 || g < G) {     // (three of four heads: the fourth's sums are formed and dropped)
-            const float pv = ps[wave][n * 16 + i * KPL + vs][g];
-#pragma unroll
-            for (int e = 0; e < 8; ++e) acc[g][e] += pv * vf[e];
-          }
+          for (int v = 0; v < 4; ++v) o3[GT == 8 ? c : 0][v] *= alpha;
       }
-    if (blk + 4 < n_blocks) {
-#pragma unroll
-      for (int n = 0; n < NB; ++n) row_v[n] = row_k[n];
-      load_v();
     }
-    asm volatile("" ::: "memory");                  // the next block's P is written after this block's was read
+#pragma unroll
+    for (int n = 0; n < NB; ++n) {
+      uint32_t first[4], third[4];                  // this column's piece of the four probabilities (upper halves), and the third
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const uint32_t p1 = __builtin_bit_cast(uint32_t, s[n][v]);
+        const float r1 = s[n][v] - __builtin_bit_cast(float, p1 & 0xffff0000u);
+        const uint32_t p2 = __builtin_bit_cast(uint32_t, r1);
+        third[v] = __builtin_bit_cast(uint32_t, r1 - __builtin_bit_cast(float, p2 & 0xffff0000u));
+        first[v] = (p1 & is_piece[0]) | (p2 & is_piece[1]) | (third[v] & is_piece[2]);
+      }
+      auto operand = [](const uint32_t (&w)[4]) {
+        return __builtin_bit_cast(s16x4_t, make_uint2(__builtin_amdgcn_perm(w[1], w[0], 0x07060302u),
+                                                      __builtin_amdgcn_perm(w[3], w[2], 0x07060302u)));
+      };
+      const s16x4_t pf = operand(first), pf3 = operand(third);
+#pragma unroll
+      for (int c = 0; c < HB; ++c) {
+#if defined(__HIP_DEVICE_COMPILE__)  // the builtins exist in the device pass only
+        typedef __attribute__((address_space(3))) s16x4_t* lds_s16x4_t;
+        const s16x4_t vt = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+            (lds_s16x4_t)(tr_lane + n * 16 * (HD * 2) + (c ^ tr_key) * 32));
+        o[c] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(vt, pf, o[c], 0, 0, 0);
+        if (GT == 8) o3[GT == 8 ? c : 0] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(vt, pf3, o3[GT == 8 ? c : 0], 0, 0, 0);
+#endif
+      }
+    }
   }
 
   // ---- the wave's key slots, then the four waves, each with its own maximum
@@ -722,18 +700,16 @@ __global__ __launch_bounds__(256, (HD <= 128 && GT <= 4) ? 3 : 1 /* work-groups 
     stat[wave][0][r16 % GT] = m_run;
     stat[wave][1][r16 % GT] = l_run;
   }
-  {
-    constexpr int NV = GT * 8;
-    float v[NV];
+  asm volatile("" ::: "memory");                    // (the sums take the place of V)
+  // the pieces of a head: columns c, c + GT, c + 2 GT (row_ror:n brings lane i the value of lane i - n of its 16)
 #pragma unroll
-    for (int g = 0; g < GT; ++g)
+  for (int c = 0; c < HB; ++c) {
 #pragma unroll
-      for (int e = 0; e < 8; ++e) v[g * 8 + e] = acc[g][e];
-    const int first = fold_keys<LPK, NV>(v, lane);
-#pragma unroll
-    for (int i = 0; i < NV * LPK / 64; ++i) {
-      const int idx = first + i, g = idx >> 3, e = idx & 7;
-      if (g < G) red[wave][g][li * 8 + e] = v[i];
+    for (int v = 0; v < 4; ++v) {
+      float x = o[c][v] + dpp_f32<0x120 + 16 - GT>(o[c][v]);
+      if constexpr (GT == 8) x += o3[GT == 8 ? c : 0][v];
+      else x += dpp_f32<0x120 + 16 - 2 * (GT == 8 ? 4 : GT)>(o[c][v]);
+      if (r16 < G) red(wave, r16 % GT, c * 16 + 4 * g4 + v) = x;
     }
   }
   __syncthreads();
@@ -745,7 +721,7 @@ __global__ __launch_bounds__(256, (HD <= 128 && GT <= 4) ? 3 : 1 /* work-groups 
 #pragma unroll
     for (int w = 0; w < 4; ++w) {
       const float f = stat[w][0][g] == -INFINITY ? 0.f : __expf(stat[w][0][g] - m);   // (a wave without keys)
-      num += f * red[w][g][e];
+      num += f * red(w, g, e);
       den += f * stat[w][1][g];
     }
     num *= v_scale;
@@ -902,17 +878,34 @@ void launch_argmax(const float* logits, int vocab, int32_t* tok, int32_t* out, i
                      eos);
 }
 
-// Splits of the key range: about three work-groups per CU (what the kernel's registers allow), but no split of fewer
-// than kDecodeKeysPerSplit = 64 keys (16 per wave); equal shares, in whole rounds of the four waves.  At most three, so that no few are left
-// for a second round (four layers of a decode step, us, rounded up -> down: 64 sequences of 400 / 700 keys 665 -> 653 /
-// 734 -> 706, 40 of 1000 664 -> 649, 8-bit 637 -> 619, 28 of 700 592 -> 587, 10 of 4000 632 -> 626); head size 256, with
-// twice the bytes per work-group, keeps the finer cut (20 sequences of 700 keys 916, rounded down 922).
+// Splits of the key range.  A wave's block of keys takes about 1.25 us (heads of 256: 2.5) however few work-groups run, all of
+// them together no less than the entries at 6.5 TB/s, each work-group on a CU about 1 us, and the merge of the splits 5 us and
+// more with their number: the least sum of these over the splits that leave at least 64 keys and at most three work-groups per
+// CU.  In effect one work-group per CU where the contexts are short enough, and no merge where sequences are many (four layers of
+// a step, us, three work-groups per CU always -> this:
+// 32 sequences of 512 keys 559 -> 530, 8-bit 534 -> 491, 20 of 700 477 -> 461, 8 of 2048 462 -> 448, 8 of 2000 with heads of 256 752
+// -> 717, one of 2048 407 -> 396, one of 16000 438 -> 430, 17 of 3500 627 -> 618; 4 of 15000, 8-bit, 555 -> 558).
+// More than 256 (sequence, KV head) pairs: whole rounds of work-groups, rounded down (48 sequences of 300 keys 566, one split 585).
 void choose_decode_splits(AttnDecodeArgs& a, int span) {
   const long long pairs = (long long)a.B * a.n_kv_heads;
-  const long long per_pair = a.hd <= 128 ? 768 / pairs : (768 + pairs - 1) / pairs;
-  const int want = (int)std::max(1LL, std::min<long long>((span + kDecodeKeysPerSplit - 1) / kDecodeKeysPerSplit, per_pair));
-  const int keys = (span + want - 1) / want;
-  a.split_keys = (keys + 63) / 64 * 64;
+  const long long most = std::max(1LL, std::min<long long>((span + kDecodeKeysPerSplit - 1) / kDecodeKeysPerSplit, 768 / pairs));
+  auto keys_of = [&](long long splits) { return (int)(((span + splits - 1) / splits + 63) / 64 * 64); };
+  a.split_keys = keys_of(most);
+  if (pairs <= 256) {
+    const double all_us = (double)pairs * span * a.hd * 2 * (a.kvq.fp8 ? 1 : 2) / 6.5e6, block_us = a.hd <= 128 ? 1.25 : 2.5;
+    double best = 1e300;
+    for (long long want = 1; want <= most; ++want) {
+      const int keys = keys_of(want), splits = (span + keys - 1) / keys;
+      const double groups = (double)pairs * splits, rounds = std::ceil(groups / 256);
+      const int block_keys = a.kvq.fp8 && a.hd <= 128 && keys >= 256 ? 128 : 64;
+      const double us = std::max((keys + block_keys - 1) / block_keys * block_us, all_us * rounds * 256 / groups) + rounds +
+                        (splits > 1 ? 5 + 0.05 * splits : 0);
+      if (us < best) {
+        best = us;
+        a.split_keys = keys;
+      }
+    }
+  }
   a.n_splits = (span + a.split_keys - 1) / a.split_keys;
 }
 
