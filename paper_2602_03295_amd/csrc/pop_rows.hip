@@ -513,14 +513,16 @@ hipError_t launch_cfg(const RowsArgs& a, hipStream_t st) {
 
 template <int EPI>
 hipError_t launch_epi(const RowsArgs& a, hipStream_t st) {
-  // 16 columns per work-group: up to 256 work-groups (one per CU) with a ring as deep as LDS allows, more with one that lets two
-  // share a CU.  From 17 rows on the activations, which every work-group reads, outweigh its weights, and where there are more
-  // than 256 work-groups 32 columns are faster (QKV of 6144 columns, 32 rows: 24.5 -> 16.9 us; O of 4096: 11.0 -> 12.9).
+  // 16 columns per work-group; from 17 rows on, whose activations outweigh such a work-group's weights, 32 where there would be
+  // more than 256 work-groups (QKV of 6144 columns, 32 rows: 24.5 -> 16.9 us; O of 4096: 11.0 -> 12.9).
+  // Two to four stages: 32 to 48 KB are requested per CU, and its L1 has no room for more; deeper rings, as deep as LDS
+  // allows, were slower (O and down of 8 rows, mean of both, by stages: 12 15.5 us, 8 15.0, 6 14.7, 5 14.4, 4 14.35, 3 14.7, 2 17.4;
+  // QKV 6 12.9, 3 12.4, 2 12.1; 14 rows 9 16.4, 4 16.1, 3 15.8, 2 17.5; O of 32 rows 6 12.3, 4 12.3, 3 11.7, 2 12.2).
   const bool one = a.N / 16 <= 256;
-  if (a.M <= 8) return one ? launch_cfg<1, 1, 12, EPI>(a, st) : launch_cfg<1, 1, 6, EPI>(a, st);
-  if (a.M <= 16) return one ? launch_cfg<2, 1, 9, EPI>(a, st) : launch_cfg<2, 1, 4, EPI>(a, st);
-  if (a.M <= 24) return one ? launch_cfg<3, 1, 7, EPI>(a, st) : launch_cfg<3, 2, 5, EPI>(a, st);
-  return one ? launch_cfg<4, 1, 6, EPI>(a, st) : launch_cfg<4, 2, 4, EPI>(a, st);
+  if (a.M <= 8) return one ? launch_cfg<1, 1, 4, EPI>(a, st) : launch_cfg<1, 1, 2, EPI>(a, st);
+  if (a.M <= 16) return one ? launch_cfg<2, 1, 3, EPI>(a, st) : launch_cfg<2, 1, 2, EPI>(a, st);
+  if (a.M <= 24) return one ? launch_cfg<3, 1, 3, EPI>(a, st) : launch_cfg<3, 2, 3, EPI>(a, st);
+  return one ? launch_cfg<4, 1, 3, EPI>(a, st) : launch_cfg<4, 2, 3, EPI>(a, st);
 }
 
 }  // namespace rows_impl
