@@ -460,7 +460,7 @@ __global__ __launch_bounds__(NT) void attention_kernel(AttnF32 a) {
 }
 
 // The same for packed prompt rows: a work-group takes 16 consecutive rows of one query head, its waves the blocks of 16
-// keys in turn (four waves up to 64 keys; eight beyond, where a second block per wave is a second chain of dependent loads: 128
+// keys in turn (four waves; eight with heads of 64 and more than 64 keys, where a second block per wave is a second chain of dependent loads: 128
 // rows of 4 heads 7.0 -> 6.7 us, pages found by shifts instead of divisions included).  S^T = K Q^T and O^T += V^T P^T on the MFMA with a running maximum and sum per wave; a
 // lane then holds 4 keys of one row, which are the operand of the second product as they are (MFMA j takes key
 // 4 g + j from lane group g).  The waves' results meet in LDS.  Rows of different sequences in one tile are taken
@@ -699,7 +699,9 @@ hipError_t launch_attention_tile(const AttnF32& a, hipStream_t st) {
 template <int HD>
 hipError_t launch_attention_hd(const AttnF32& a, bool packed, int max_len, hipStream_t st) {
   if (packed) {
-    if (HD <= 128 && max_len > 64) return launch_attention_tile<HD, 8>(a, st);
+    if constexpr (HD == 64) {       // (wider heads spill with eight waves)
+      if (max_len > 64) return launch_attention_tile<HD, 8>(a, st);
+    }
     return launch_attention_tile<HD, 4>(a, st);
   } else {
     const dim3 grid(a.rows, a.n_q_heads);
