@@ -639,9 +639,10 @@ pop_status residual_few_rows_projection(const LayerCtx& x, const bf16_t* in, con
   float* xb = at<float>(x.ws, x.w->o_xb);
   x.ab_gamma = nullptr;
   x.ab_sums = 0;
-  // (from 17 rows on a long K, all of whose activations every work-group reads, is faster split over the chip: down of 32 rows
-  // 29.8 us here, 24.1 and a second kernel there; O 11.0 and 9.7)
-  if (rows_path(x.m->cfg, B) && (B <= 16 || K <= 8192)) {
+  // (with many rows a long K, all of whose activations every work-group reads, is faster split over the chip.  A step of four
+  // layers, us, split and here: K = 14336, 17 rows 439 and 423, 20 466 and 457, 24 475 and 475, 28 488 and 501; K = 12288, 20 rows
+  // 444 and 430, 24 450 and 445, 32 502 and 528; K = 15360, six layers, 18 rows 759 and 773, 24 771 and 805)
+  if (rows_path(x.m->cfg, B) && (B <= 16 || K <= 8192 || (B <= 24 && K <= 14336))) {
     pop::RowsArgs r{};
     r.x = in; r.W = (const bf16_t*)W; r.M = B; r.N = N; r.K = K; r.epilogue = pop::ROWS_ADD;
     r.out = xb; r.ldo = N; r.scale = scale;

@@ -73,9 +73,16 @@ def test_cache_types_and_key_norms(rows, kv_dtype, qk_norm):
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("rows,d_ffn", [(24, 14336), (25, 14336), (24, 14400)])
+def test_longest_k_of_the_down_projection_with_its_epilogue(rows, d_ffn):
+    """Both sides of where a split GEMM takes over."""
+    check(rows, head_dim=64, n_q_heads=4, n_kv_heads=2, d_ffn=d_ffn)
+
+
+@pytest.mark.gpu
 @pytest.mark.parametrize("rows", [16, 17, 32])
 def test_long_k_of_the_down_projection(rows):
-    """K above 8192: from 17 rows on down is a split GEMM between projections of this path, and gate|up takes 128-column tiles."""
+    """K above 8192: beyond 24 rows down is a split GEMM between projections of this path."""
     check(rows, head_dim=64, n_q_heads=4, n_kv_heads=2, d_ffn=8256)
 
 
