@@ -32,8 +32,9 @@ pop_status pop_op_gemm(const void* A, int64_t lda, const void* W, int64_t ldw, v
  * columns are W rows: with epilogue 2, half of them gate and half up.  Errors: POP_EINVAL, POP_ESHAPE. */
 pop_status pop_op_gemm_plan(int32_t M, int32_t N, int32_t K, int32_t epilogue, size_t scratch_bytes, int32_t* plan);
 
-/* Columns (W rows) of a tile with which a decode step of 3 to 32 sequences runs its gate|up projection (epilogue 2) or LM head
- * (epilogue 3), whose rows are scaled by 1 / rms behind the product: 64 or 128, 0 for arguments out of range.  Nothing is launched. */
+/* Columns (W rows) of a tile with which the tiled GEMM of a decode step of 3 to 32 sequences runs a gate|up projection (epilogue
+ * 2) or LM head (epilogue 3), whose rows are scaled by 1 / rms behind the product: 64 or 128, 0 for arguments out of range.
+ * (Those of 12289 to 32768 W rows, with K and N as the row projections need them, take one of these instead.)  Nothing is launched. */
 int32_t pop_op_gemm_row_scaled_tile_cols(int32_t M, int32_t N, int32_t K, int32_t epilogue);
 
 /* The same projection (Sec. 2.1, Attn / FFN blocks; the short prompts of Sec. 4.3, where a projection is

@@ -787,7 +787,8 @@ hipError_t launch_shape(int id, const GemmArgs& g, hipStream_t st, int n0, int n
   }
 }
 
-// Row-scaled forms: one row tile, of 64 or of 128 columns, whichever the cost model has as the faster one.  In effect 64 until
+// Row-scaled forms (where rows_wide_kernel does not take the projection): one row tile, of 64 or of 128 columns, whichever the cost
+// model has as the faster one.  In effect 64 until
 // those tiles fill the chip once (LM head of 16032 rows of 4096, 8 rows: 26 us, with 128 columns a third of the chip idles and it is 33),
 // then 128: a second round of 64-column tiles costs more than CUs that idle (four layers of a decode step of 32 sequences,
 // gate|up of 2 x 8448 to 2 x 10240 rows of 4096: 503 to 530 us with 64 columns, 473 to 495 with 128; 8 sequences 401 to 423 and 384 to 395).
